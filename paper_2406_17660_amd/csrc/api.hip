@@ -22,6 +22,11 @@ bool small(int64_t v) { return v < (int64_t{1} << 31); }
 bool dtype_ok(grass_dtype d) { return d == GRASS_F32 || d == GRASS_BF16; }
 bool layout_ok(grass_dy_layout l) { return l == GRASS_DY_TxM || l == GRASS_DY_MxT; }
 hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
+// The partial tiles of an fp32 product are an optimisation: with less workspace than the query
+// asks for (or none) its launcher plans fewer K slices.
+bool workspace_ok(grass_dtype dt, size_t need, const void* ws, size_t ws_bytes) {
+    return need == 0 || dt == GRASS_F32 || (ws && ws_bytes >= need);
+}
 
 grass_status check_products(const void* dY, grass_dy_layout layout, int64_t ldy, const void* X,
                             int64_t ldx, grass_dtype dt, int64_t T, int64_t m, int64_t n) {
@@ -166,10 +171,10 @@ grass_status grass_compressed_grad_timed(const void* dY, grass_dy_layout layout,
     if (st != GRASS_OK) return st;
     if (r < 0 || r > kMaxGridRows || ldgc < n || (r > 0 && m == 0)) return GRASS_ERR_SHAPE;
     if (!present(idx, r) || !present(rho, r) || !present(GC, r * n)) return GRASS_ERR_NULL;
-    const size_t need = gemm_workspace_bytes(T, r, n, dt, layout, true);
-    if (need > 0 && (!ws || ws_bytes < need)) return GRASS_ERR_WORKSPACE;
+    if (!workspace_ok(dt, gemm_workspace_bytes(T, r, n, dt, layout, true), ws, ws_bytes))
+        return GRASS_ERR_WORKSPACE;
     return launch_tn_gemm(dY, layout, ldy, X, ldx, dt, T, r, n, idx, rho, GC, GRASS_F32, ldgc, ws,
-                          as_stream(stream), m, static_cast<hipEvent_t>(ev_gemm_start),
+                          ws_bytes, as_stream(stream), m, static_cast<hipEvent_t>(ev_gemm_start),
                           static_cast<hipEvent_t>(ev_gemm_stop));
 }
 
@@ -179,7 +184,7 @@ size_t grass_cgrad_group_workspace(int64_t T, int64_t n, int count, const int64_
         return 0;
     for (int i = 0; i < count; ++i)
         if (r[i] < 0 || r[i] > kMaxGridRows) return 0;
-    return gemm_group_workspace_bytes(T, r, count, n, dt, layout);
+    return gemm_group_workspace_bytes(T, r, count, n, dt, layout, false);
 }
 
 grass_status grass_compressed_grad_group(int count, const void* const* dY, grass_dy_layout layout,
@@ -201,9 +206,9 @@ grass_status grass_compressed_grad_group(int count, const void* const* dY, grass
             return GRASS_ERR_NULL;
         seg[i] = GemmSegment{dY[i], ldy[i], idx[i], rho[i], GC[i], ldgc[i], r[i], m[i]};
     }
-    const size_t need = gemm_group_workspace_bytes(T, r, count, n, dt, layout);
-    if (need > 0 && (!ws || ws_bytes < need)) return GRASS_ERR_WORKSPACE;
-    return launch_tn_gemm_segments(seg, count, layout, X, ldx, dt, T, n, GRASS_F32, ws,
+    if (!workspace_ok(dt, gemm_group_workspace_bytes(T, r, count, n, dt, layout, false), ws, ws_bytes))
+        return GRASS_ERR_WORKSPACE;
+    return launch_tn_gemm_segments(seg, count, layout, X, ldx, dt, T, n, GRASS_F32, ws, ws_bytes,
                                    as_stream(stream));
 }
 
@@ -279,7 +284,7 @@ size_t grass_step_group_workspace(int64_t T, int64_t n, int count, const int64_t
         if (r[i] < 0 || r[i] > kMaxGridRows) return 0;
         extra += scratch_gc_bytes(r[i], n);
     }
-    return gemm_group_workspace_bytes(T, r, count, n, dt, layout) + extra;
+    return gemm_group_workspace_bytes(T, r, count, n, dt, layout, true) + extra;
 }
 
 grass_status grass_step_group(int count, const grass_step_layer* layers, grass_dy_layout layout,
@@ -318,10 +323,12 @@ grass_status grass_step_group_timed(int count, const grass_step_layer* layers,
         if (st != GRASS_OK) return st;
         rows[i] = L.r;
     }
-    const size_t gemm_bytes = gemm_group_workspace_bytes(T, rows, count, n, dt, layout);
-    size_t need = gemm_bytes + 256;
-    for (int i = 0; i < count; ++i) need += scratch_gc_bytes(rows[i], n);
-    if (!ws || ws_bytes < need) return GRASS_ERR_WORKSPACE;
+    size_t gemm_bytes = gemm_group_workspace_bytes(T, rows, count, n, dt, layout, true);
+    size_t gc_bytes = 256;
+    for (int i = 0; i < count; ++i) gc_bytes += scratch_gc_bytes(rows[i], n);
+    if (!ws || ws_bytes < gc_bytes) return GRASS_ERR_WORKSPACE;
+    if (!workspace_ok(dt, gemm_bytes, ws, ws_bytes - gc_bytes)) return GRASS_ERR_WORKSPACE;
+    if (gemm_bytes > ws_bytes - gc_bytes) gemm_bytes = (ws_bytes - gc_bytes) / 256 * 256;
     char* scratch = static_cast<char*>(ws) + gemm_bytes;
     scratch += (256 - reinterpret_cast<uintptr_t>(scratch) % 256) % 256;
     for (int i = 0; i < count; ++i) {
@@ -332,18 +339,23 @@ grass_status grass_step_group_timed(int count, const grass_step_layer* layers,
                              L.GC ? L.ldgc : n, L.r, L.m, &tail[i], L.GC != nullptr};
         if (!L.GC) scratch += scratch_gc_bytes(L.r, n);
     }
-    return launch_tn_gemm_segments(seg, count, layout, X, ldx, dt, T, n, GRASS_F32, ws,
+    return launch_tn_gemm_segments(seg, count, layout, X, ldx, dt, T, n, GRASS_F32, ws, gemm_bytes,
                                    as_stream(stream), static_cast<hipEvent_t>(ev_gemm_start),
                                    static_cast<hipEvent_t>(ev_gemm_stop),
                                    static_cast<hipEvent_t>(ev_tail_start),
                                    static_cast<hipEvent_t>(ev_tail_stop));
 }
 
+static size_t cols_gemm_bytes(int64_t T, int64_t m, int64_t r, grass_dtype dt) {
+    return dt == GRASS_F32 ? gemm_group_workspace_bytes(T, &r, 1, m, dt, GRASS_DY_TxM, true)
+                           : gemm_workspace_bytes(T, r, m, dt, GRASS_DY_TxM, true);
+}
+
 size_t grass_step_cols_workspace(int64_t T, int64_t m, int64_t n, int64_t r, grass_dtype dt) {
     if (T < 0 || m < 0 || n < 0 || r < 0 || !small(T) || !small(m) || !small(n) || r > kMaxGridRows)
         return 0;
     // the transposed problem: r selected rows of an n x m gradient, plus room for an unnamed G_C
-    return gemm_workspace_bytes(T, r, m, dt, GRASS_DY_TxM, true) + 256 + scratch_gc_bytes(r, m);
+    return cols_gemm_bytes(T, m, r, dt) + 256 + scratch_gc_bytes(r, m);
 }
 
 grass_status grass_step_cols(const void* dY, int64_t ldy, const void* X, int64_t ldx,
@@ -364,8 +376,11 @@ grass_status grass_step_cols(const void* dY, int64_t ldy, const void* X, int64_t
         return GRASS_ERR_NULL;
     if (!dtype_ok(wdt)) return GRASS_ERR_DTYPE;
     if (!aligned_to(U, 16)) return GRASS_ERR_SHAPE;
-    const size_t gemm_bytes = gemm_workspace_bytes(T, r, m, dt, GRASS_DY_TxM, true);
-    if (!ws || ws_bytes < gemm_bytes + 256 + scratch_gc_bytes(r, m)) return GRASS_ERR_WORKSPACE;
+    size_t gemm_bytes = cols_gemm_bytes(T, m, r, dt);
+    const size_t gc_bytes = 256 + scratch_gc_bytes(r, m);
+    if (!ws || ws_bytes < gc_bytes) return GRASS_ERR_WORKSPACE;
+    if (!workspace_ok(dt, gemm_bytes, ws, ws_bytes - gc_bytes)) return GRASS_ERR_WORKSPACE;
+    if (gemm_bytes > ws_bytes - gc_bytes) gemm_bytes = (ws_bytes - gc_bytes) / 256 * 256;
     char* scratch = static_cast<char*>(ws) + gemm_bytes;
     scratch += (256 - reinterpret_cast<uintptr_t>(scratch) % 256) % 256;
     StepTail tail{M, V, sdt, lr, beta1, beta2, eps, t, nullptr, W, wdt, ldw, alpha};
@@ -375,7 +390,7 @@ grass_status grass_step_cols(const void* dY, int64_t ldy, const void* X, int64_t
     // dense operand
     const GemmSegment seg{X, ldx, idx, rho, GC ? static_cast<void*>(GC) : scratch, GC ? ldgc : m,
                           r, n, &tail, GC != nullptr};
-    return launch_tn_gemm_segments(&seg, 1, GRASS_DY_TxM, dY, ldy, dt, T, m, GRASS_F32, ws,
+    return launch_tn_gemm_segments(&seg, 1, GRASS_DY_TxM, dY, ldy, dt, T, m, GRASS_F32, ws, gemm_bytes,
                                    as_stream(stream), static_cast<hipEvent_t>(ev_gemm_start),
                                    static_cast<hipEvent_t>(ev_gemm_stop));
 }
@@ -419,10 +434,10 @@ grass_status grass_dense_grad(const void* dY, grass_dy_layout layout, int64_t ld
     if (ldg < n || m > kMaxGridRows) return GRASS_ERR_SHAPE;
     if (!present(G, m * n)) return GRASS_ERR_NULL;
     if (!dtype_ok(gdt)) return GRASS_ERR_DTYPE;
-    const size_t need = gemm_workspace_bytes(T, m, n, dt, layout, false);
-    if (need > 0 && (!ws || ws_bytes < need)) return GRASS_ERR_WORKSPACE;
+    if (!workspace_ok(dt, gemm_workspace_bytes(T, m, n, dt, layout, false), ws, ws_bytes))
+        return GRASS_ERR_WORKSPACE;
     return launch_tn_gemm(dY, layout, ldy, X, ldx, dt, T, m, n, nullptr, nullptr, G, gdt, ldg, ws,
-                          as_stream(stream), m);
+                          ws_bytes, as_stream(stream), m);
 }
 
 size_t grass_grad_row_stats_workspace(int64_t T, int64_t m, int64_t n, grass_dtype dt,

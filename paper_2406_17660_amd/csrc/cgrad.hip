@@ -21,7 +21,7 @@
 //   3. reduce: sums the split-K partials in a fixed order (deterministic), applies rho and
 //              converts to the output dtype; in a regular step this, Adam and the update of
 //              the rows of W are one kernel that reads the partial tiles directly.
-// fp32 path: a plain LDS-tiled FMA kernel (small reference-precision configurations).
+// fp32 path: the same three stages on the fp32 matrix instruction, without the pack (gemm_f32.hpp).
 #include <atomic>
 
 #include "common.hpp"
@@ -31,6 +31,7 @@
 #include "gemm_small.hpp"
 #include "gemm_large.hpp"
 #include "gemm_gather_narrow.hpp"
+#include "gemm_f32.hpp"
 #include "reduce_kernels.hpp"
 
 namespace grass {
@@ -171,6 +172,75 @@ NarrowPlan narrow_plan(int64_t T, int64_t n, int tiles_m, int64_t panel_rows, in
     return p;
 }
 
+// ---- fp32 inputs (gemm_f32.hpp)
+struct F32Plan {
+    int bm;  // tile edge
+    int64_t Mp, Np;
+    int tiles_m, tiles_n, splits, ktiles_per_split;
+};
+constexpr int64_t kF32SplitMinT = 1024;
+// `rows`: the sets' row counts.  K is split where that pays: with W = tiles x slices workgroups
+// the product takes 2 T rows n / 150 TFLOP/s over the filled share of the machine's rounds, and a
+// slice of partial tiles costs 8 bytes per output element at 4 TB/s.  Each slice keeps at least
+// four K tiles.  The 128 tile from 256 workgroups of 256 tokens on (1024 x 1024, r = 256, T = 8192:
+// 62 against 68 us; 512 x 1376, r = 128, T = 4096: 36 against 35; 2048 x 2048, r = 256, T = 1024:
+// 35 against 27), unless it wastes more than a quarter of itself on padding.  A call without a fused tail (`step` false) of fewer than 1024 tokens is not split,
+// so that it needs no workspace: its K loop is short.
+F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, bool step, size_t cap_bytes) {
+    F32Plan p;
+    int64_t total = 0, t128 = 0, t64 = 0;
+    for (int i = 0; i < count; ++i) {
+        total += (rows[i] + 7) / 8 * 8;
+        t128 += (rows[i] + 127) / 128;
+        t64 += (rows[i] + 63) / 64;
+    }
+    const int64_t n128 = (n + 127) / 128, n64 = (n + 63) / 64;
+    const int forced = test_option(GRASS_TEST_GEMM_TILE);
+    p.bm = forced ? (forced == 64 ? 64 : 128) : (t128 * n128 * 4 <= t64 * n64 * 1.25 && t128 * n128 * (T / 256) >= 256 ? 128 : 64);
+    const int64_t tm = p.bm == 128 ? t128 : t64, tn = p.bm == 128 ? n128 : n64;
+    p.tiles_m = static_cast<int>(tm);
+    p.tiles_n = static_cast<int>(tn);
+    p.Mp = total;
+    p.Np = tn * p.bm;
+    const int64_t ktiles = (T + kF32BK - 1) / kF32BK, tiles = tm * tn;
+    const int64_t slice_bytes = p.Mp * p.Np * 4;
+    int64_t smax = ktiles / 4;
+    if (slice_bytes > 0 && static_cast<int64_t>(cap_bytes) / slice_bytes < smax) smax = static_cast<int64_t>(cap_bytes) / slice_bytes;
+    if (smax > 128) smax = 128;
+    if (!step && T < kF32SplitMinT) smax = 1;
+    if (const int cap = test_option(GRASS_TEST_MAX_K_SLICES)) smax = cap > 0 && cap < smax ? cap : smax;
+    const double flop_us = 2.0 * static_cast<double>(T) * tiles * p.bm * p.bm / 150e6;
+    const double slice_us = static_cast<double>(slice_bytes) * 2 / 4e6;
+    int64_t s = 1;
+    double best = 1e300;
+    for (int64_t c = 1; c <= smax && tiles > 0; ++c) {
+        const int64_t wgs = tiles * c, rounds = (wgs + 255) / 256;
+        const double cost = flop_us * static_cast<double>(rounds * 256) / static_cast<double>(wgs) + slice_us * c;
+        if (cost < best * (1 - 1e-9)) { best = cost; s = c; }
+    }
+    p.ktiles_per_split = static_cast<int>((ktiles + s - 1) / s);
+    if (p.ktiles_per_split < 1) p.ktiles_per_split = 1;
+    p.splits = static_cast<int>((ktiles + p.ktiles_per_split - 1) / p.ktiles_per_split);
+    if (p.splits < 1) p.splits = 1;
+    return p;
+}
+// Workspace for the partial tiles of a product that is planned without a limit.
+size_t f32_partial_bytes(int64_t T, const int64_t* rows, int count, int64_t n, bool step) {
+    const F32Plan p = f32_plan(T, rows, count, n, step, ~size_t{0} >> 1);
+    if (p.splits == 1 && !step) return 0;
+    return static_cast<size_t>(p.splits) * p.Mp * p.Np * 4 + 256;
+}
+
+template <int BM>
+void launch_f32_kernel(const F32Args& a, bool vec_a, bool vec_b, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const int64_t items = static_cast<int64_t>(a.tiles_m) * a.tiles_n * a.splits;
+    const dim3 grid(static_cast<unsigned>((items + kNumXcd - 1) / kNumXcd * kNumXcd)), block(256);
+    if (vec_a && vec_b) launch_stamped(tn_gemm_f32_mfma_kernel<BM, true, true>, grid, block, 0, s, e0, e1, a);
+    else if (vec_a) launch_stamped(tn_gemm_f32_mfma_kernel<BM, true, false>, grid, block, 0, s, e0, e1, a);
+    else if (vec_b) launch_stamped(tn_gemm_f32_mfma_kernel<BM, false, true>, grid, block, 0, s, e0, e1, a);
+    else launch_stamped(tn_gemm_f32_mfma_kernel<BM, false, false>, grid, block, 0, s, e0, e1, a);
+}
+
 template <typename Cfg, bool kDense>
 hipError_t launch_gemm_kernel(const GemmArgs& g, unsigned grid, hipStream_t s) {
     auto kernel = tn_gemm_bf16_kernel<Cfg, kDense>;
@@ -257,14 +327,14 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
     if (m > 65535) return GRASS_ERR_SHAPE;
     float* G = reinterpret_cast<float*>(base);
     const grass_status st = launch_tn_gemm(dY, layout, ldy, X, ldx, dt, T, m, n, nullptr, nullptr, G,
-                                           GRASS_F32, n, base + g_bytes, s, m);
+                                           GRASS_F32, n, base + g_bytes, need - g_bytes, s, m);
     if (st != GRASS_OK) return st;
     return launch_row_stats(G, GRASS_F32, m, n, n, sumsq, s);
 }
 
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
                             grass_dy_layout layout, bool gathered) {
-    if (dt == GRASS_F32) return 0;
+    if (dt == GRASS_F32) return f32_partial_bytes(T, &mrows, 1, n, false);
     // the launcher may fall back to the small tile when alignment rules out the large one
     const bool pack = needs_pack(layout, gathered, mrows);
     const Plan a = plan_for(kTile128, T, mrows, n, pack), b = plan_for(kTile256, T, mrows, n, pack);
@@ -274,9 +344,12 @@ size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
 
 void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n, grass_dtype dt,
                        grass_dy_layout layout, int* tile, int* k_slices) {
-    if (dt == GRASS_F32) {  // the fp32 kernel: 64 x 64 tiles, K not split
-        *tile = 64;
-        *k_slices = 1;
+    if (dt == GRASS_F32) {
+        int64_t each[GRASS_MAX_GROUP];  // the sets taken to be of equal size
+        for (int i = 0; i < count; ++i) each[i] = rows / count;
+        const F32Plan p = f32_plan(T, each, count, n, false, ~size_t{0} >> 1);
+        *tile = p.bm;
+        *k_slices = p.splits;
         return;
     }
     if (m > 0 && count >= 1 && narrow_shape_ok(T, n, dt, layout) &&
@@ -301,7 +374,8 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
 }
 
 size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int64_t n,
-                                  grass_dtype dt, grass_dy_layout layout) {
+                                  grass_dtype dt, grass_dy_layout layout, bool step) {
+    if (dt == GRASS_F32) return f32_partial_bytes(T, rows, count, n, step);
     int64_t total = 0;
     size_t need = 0;  // the sets may also be run one at a time
     for (int i = 0; i < count; ++i) {
@@ -396,8 +470,8 @@ grass_status finish_segments(const GemmSegment* seg, int count, const float* par
 // and the partial tiles are reduced into each set's own output.
 grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy_layout layout,
                                      const void* X, int64_t ldx, grass_dtype dt, int64_t T,
-                                     int64_t n, grass_dtype odt, void* ws, hipStream_t s,
-                                     hipEvent_t ev_start, hipEvent_t ev_stop,
+                                     int64_t n, grass_dtype odt, void* ws, size_t ws_bytes,
+                                     hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop,
                                      hipEvent_t ev_tail_start, hipEvent_t ev_tail_stop) {
     int64_t total = 0;  // panel columns in use
     for (int i = 0; i < count; ++i) {
@@ -406,21 +480,45 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     }
     if (total == 0 || n == 0) return GRASS_OK;
     if (dt == GRASS_F32) {
-        if (ev_start) (void)hipEventRecord(ev_start, s);
+        int64_t rows[GRASS_MAX_GROUP];
+        bool tails = false;
         for (int i = 0; i < count; ++i) {
-            const GemmSegment& g = seg[i];
-            if (g.rows == 0) continue;
-            const dim3 grid(static_cast<unsigned>((n + 63) / 64), static_cast<unsigned>((g.rows + 63) / 64));
-            if (odt == GRASS_F32)
-                tn_gemm_f32_kernel<float><<<grid, 256, 0, s>>>(
-                    static_cast<const float*>(g.dY), layout, g.ldy, static_cast<const float*>(X),
-                    ldx, T, g.rows, n, g.idx, g.rho, static_cast<float*>(g.C), g.ldc);
-            else
-                tn_gemm_f32_kernel<uint16_t><<<grid, 256, 0, s>>>(
-                    static_cast<const float*>(g.dY), layout, g.ldy, static_cast<const float*>(X),
-                    ldx, T, g.rows, n, g.idx, g.rho, static_cast<uint16_t*>(g.C), g.ldc);
+            rows[i] = seg[i].rows;
+            tails = tails || seg[i].tail != nullptr;
         }
-        if (ev_stop) (void)hipEventRecord(ev_stop, s);
+        char* base = static_cast<char*>(ws);
+        const size_t skip = base ? (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256 : 0;
+        const size_t cap = base && ws_bytes > skip ? ws_bytes - skip : 0;
+        const F32Plan p = f32_plan(T, rows, count, n, tails, cap);
+        // partial tiles whenever something reads them: several slices, or a fused tail (which takes
+        // the sums from there); a workspace that cannot hold even one slice leaves the direct form
+        const bool partial = (p.splits > 1 || tails) &&
+                             static_cast<size_t>(p.splits) * p.Mp * p.Np * 4 <= cap;
+        F32Args a;
+        bool vec_a = layout == GRASS_DY_TxM;
+        int64_t off = 0;
+        int tile0 = 0;
+        for (int i = 0; i < count; ++i) {
+            const GemmSegment& q = seg[i];
+            a.set[i] = F32Set{static_cast<const float*>(q.dY), q.ldy, q.idx, q.rho, q.C, q.ldc, q.rows, off, tile0};
+            vec_a = vec_a && !q.idx && aligned_to(q.dY, 16) && q.ldy % 4 == 0 && q.rows % 4 == 0;
+            off += (q.rows + 7) / 8 * 8;
+            tile0 += static_cast<int>((q.rows + p.bm - 1) / p.bm);
+        }
+        a.count = count;
+        a.X = static_cast<const float*>(X);
+        a.ldx = ldx; a.n = n; a.T = T;
+        a.P = partial ? reinterpret_cast<float*>(base + skip) : nullptr;
+        a.Mp = p.Mp; a.Np = p.Np;
+        a.mxt = layout == GRASS_DY_MxT;
+        a.c_bf16 = odt == GRASS_BF16;
+        a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
+        a.splits = p.splits; a.ktiles_per_split = p.ktiles_per_split;
+        const bool vec_b = aligned_to(X, 16) && ldx % 4 == 0 && n % 4 == 0;
+        if (p.bm == 128) launch_f32_kernel<128>(a, vec_a, vec_b, s, ev_start, ev_stop);
+        else launch_f32_kernel<64>(a, vec_a, vec_b, s, ev_start, ev_stop);
+        if (partial)
+            return finish_segments(seg, count, a.P, p.splits, p.Mp, p.Np, n, odt, s, ev_tail_start, ev_tail_stop);
         if (ev_tail_start) (void)hipEventRecord(ev_tail_start, s);
         for (int i = 0; i < count; ++i) {
             const grass_status st = run_tail_unfused(seg[i], n, s);
@@ -442,7 +540,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
                 // (timing hooks: the first set's GEMM and the last set's tail)
                 const bool first = i == 0, last = i + 1 == count;
                 const grass_status st = launch_tn_gemm_segments(
-                    seg + i, 1, layout, X, ldx, dt, T, n, odt, ws, s, first ? ev_start : nullptr,
+                    seg + i, 1, layout, X, ldx, dt, T, n, odt, ws, ws_bytes, s, first ? ev_start : nullptr,
                     first ? ev_stop : nullptr, last ? ev_tail_start : nullptr,
                     last ? ev_tail_stop : nullptr);
                 if (st != GRASS_OK) return st;
@@ -715,10 +813,10 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
 grass_status launch_tn_gemm(const void* dY, grass_dy_layout layout, int64_t ldy, const void* X,
                             int64_t ldx, grass_dtype dt, int64_t T, int64_t mrows, int64_t n,
                             const int32_t* idx, const float* rho, void* C, grass_dtype odt,
-                            int64_t ldc, void* ws, hipStream_t s, int64_t src_rows,
-                            hipEvent_t ev_start, hipEvent_t ev_stop) {
+                            int64_t ldc, void* ws, size_t ws_bytes, hipStream_t s,
+                            int64_t src_rows, hipEvent_t ev_start, hipEvent_t ev_stop) {
     const GemmSegment one{dY, ldy, idx, rho, C, ldc, mrows, src_rows};
-    return launch_tn_gemm_segments(&one, 1, layout, X, ldx, dt, T, n, odt, ws, s, ev_start, ev_stop);
+    return launch_tn_gemm_segments(&one, 1, layout, X, ldx, dt, T, n, odt, ws, ws_bytes, s, ev_start, ev_stop);
 }
 
 }  // namespace grass

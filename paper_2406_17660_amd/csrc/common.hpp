@@ -120,7 +120,7 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
 grass_status launch_tn_gemm(const void* dY, grass_dy_layout layout, int64_t ldy, const void* X,
                             int64_t ldx, grass_dtype dt, int64_t T, int64_t mrows, int64_t n,
                             const int32_t* idx, const float* rho, void* C, grass_dtype odt,
-                            int64_t ldc, void* ws, hipStream_t s, int64_t src_rows,
+                            int64_t ldc, void* ws, size_t ws_bytes, hipStream_t s, int64_t src_rows,
                             hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
 // What follows the compressed gradient in a regular step (Adam on r x n, update of the rows of
@@ -201,14 +201,14 @@ struct GemmSegment {
     bool c_wanted = true;
 };
 size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int64_t n,
-                                  grass_dtype dt, grass_dy_layout layout);
+                                  grass_dtype dt, grass_dy_layout layout, bool step);
 // ev_start / ev_stop: stamped with the start and the end of the matrix-multiply kernel (the
 // large-tile kernel's own dispatch; for the other kernels, recorded before and after the
 // launches); ev_tail_start / ev_tail_stop: the same for the fused tail of a regular step.
 grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy_layout layout,
                                      const void* X, int64_t ldx, grass_dtype dt, int64_t T,
-                                     int64_t n, grass_dtype odt, void* ws, hipStream_t s,
-                                     hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
+                                     int64_t n, grass_dtype odt, void* ws, size_t ws_bytes,
+                                     hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
                                      hipEvent_t ev_tail_start = nullptr,
                                      hipEvent_t ev_tail_stop = nullptr);
 

@@ -1,4 +1,4 @@
-// Split-K and row-statistic reductions; the fp32 FMA GEMM of the reference-precision path.
+// Split-K and row-statistic reductions.
 // Included by cgrad.hip only (device code shares one translation unit with its launchers).
 #pragma once
 #include "common.hpp"
@@ -72,60 +72,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_many_kernel(
     for (int e = 0; e < 4; ++e)
         if (i + e < cols) store_from_f32(out + j * ldo + i + e, r[e] * sc);
 }
-
-
-// ------------------------------------------------------------------------------ fp32 path
-// 64 x 64 output tile, 256 threads, each a 4 x 4 block; BK = 16.
-template <typename OT>
-__global__ __launch_bounds__(256) void tn_gemm_f32_kernel(
-    const float* __restrict__ dY, int layout, int64_t ldy, const float* __restrict__ X, int64_t ldx,
-    int64_t T, int64_t rows, int64_t n, const int32_t* __restrict__ idx,
-    const float* __restrict__ scale, OT* __restrict__ C, int64_t ldc) {
-    __shared__ float As[16][64 + 1];
-    __shared__ float Bs[16][64 + 1];
-    const int tid = threadIdx.x;
-    const int64_t j0 = static_cast<int64_t>(blockIdx.y) * 64, i0 = static_cast<int64_t>(blockIdx.x) * 64;
-    const int ty = tid / 16, tx = tid % 16;
-    float acc[4][4] = {};
-    for (int64_t k0 = 0; k0 < T; k0 += 16) {
-        for (int e = tid; e < 16 * 64; e += 256) {
-            const int kk = e / 64, c = e % 64;
-            const int64_t t = k0 + kk;
-            float a = 0.f, b = 0.f;
-            if (t < T) {
-                if (j0 + c < rows) {
-                    const int64_t col = idx ? idx[j0 + c] : j0 + c;
-                    a = layout == GRASS_DY_TxM ? dY[t * ldy + col] : dY[col * ldy + t];
-                }
-                if (i0 + c < n) b = X[t * ldx + i0 + c];
-            }
-            As[kk][c] = a;
-            Bs[kk][c] = b;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { a[u] = As[kk][ty * 4 + u]; b[u] = Bs[kk][tx * 4 + u]; }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] += a[u] * b[v];
-        }
-        __syncthreads();
-    }
-    for (int u = 0; u < 4; ++u) {
-        const int64_t j = j0 + ty * 4 + u;
-        if (j >= rows) continue;
-        const float s = scale ? scale[j] : 1.0f;
-        for (int v = 0; v < 4; ++v) {
-            const int64_t i = i0 + tx * 4 + v;
-            if (i < n) store_from_f32(C + j * ldc + i, s * acc[u][v]);
-        }
-    }
-}
-
 
 }  // namespace
 }  // namespace grass
