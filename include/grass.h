@@ -184,8 +184,9 @@ grass_status grass_compressed_grad(const void* dY, grass_dy_layout layout, int64
  * partial products are what the split-K reduction, or the fused tail of grass_step_group /
  * grass_step_cols, adds up; above 8 slices those kernels spread the slices over the wavefronts
  * of a workgroup).  A pure host function, for callers that want to know what a shape costs and
- * for tests that must reach every kernel.  Operands whose base or leading dimension is not
- * 16-byte aligned take the packed route with the 128 tile at launch whatever this reports.
+ * for tests that must reach every kernel.  Narrow layers whose operands' bases or
+ * leading dimensions are not 16-byte aligned take the packed route at launch whatever this
+ * reports.
  * Errors: NULL, SHAPE, DTYPE. */
 grass_status grass_cgrad_plan(int64_t T, int64_t m, int64_t n, int64_t rows, int count,
                               grass_dtype dt, grass_dy_layout layout, int* tile, int* k_slices);

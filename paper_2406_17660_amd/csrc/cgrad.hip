@@ -30,6 +30,7 @@
 #include "pack_kernels.hpp"
 #include "gemm_small.hpp"
 #include "gemm_large.hpp"
+#include "gemm_unaligned.hpp"
 #include "gemm_gather_narrow.hpp"
 #include "gemm_f32.hpp"
 #include "reduce_kernels.hpp"
@@ -42,7 +43,6 @@ using Cfg128 = TileCfg<128, 128, 64, 2, 2>;
 enum TileId { kTile128 = 0, kTile256 = 1 };
 struct Shape256 {
     static constexpr int BM = kFastBM, BN = kFastBN, BK = kFastBK, kWgPerCu = 1;
-    static constexpr bool kWholeKTilesOnly = true;  // a ragged tail of T is a separate slice
 };
 
 struct Plan {
@@ -65,7 +65,7 @@ Plan make_plan(int64_t T, int64_t rows, int64_t n, bool needs_pack) {
     p.Mp = static_cast<int64_t>(p.tiles_m) * Cfg::BM;
     p.Np = static_cast<int64_t>(p.tiles_n) * Cfg::BN;
     p.rp = p.Mp;
-    const int64_t ktiles = Cfg::kWholeKTilesOnly ? T / Cfg::BK : (T + Cfg::BK - 1) / Cfg::BK;
+    const int64_t ktiles = (T + Cfg::BK - 1) / Cfg::BK;
     const int64_t tiles = static_cast<int64_t>(p.tiles_m) * p.tiles_n;
     // Split K so that the workgroups fill whole rounds of the machine (256 CUs x workgroups
     // per CU) without paying too much for the partial tiles every slice adds.  In units of
@@ -96,20 +96,39 @@ Plan make_plan(int64_t T, int64_t rows, int64_t n, bool needs_pack) {
     p.splits = static_cast<int>((ktiles + p.ktiles_per_split - 1) / p.ktiles_per_split);
     if (p.splits < 1) p.splits = 1;
     p.pack_bytes = needs_pack ? round_up(static_cast<size_t>(T) * p.rp * 2, 256) : 0;
-    // one spare slice: the large-tile path gives the ragged tail of T to the small-tile kernel
-    p.partial_bytes = static_cast<size_t>(p.splits + 1) * p.Mp * p.Np * 4;
+    p.partial_bytes = static_cast<size_t>(p.splits) * p.Mp * p.Np * 4;
     return p;
 }
 
-// The GEMM kernels read the left operand as T x rows with 16-byte chunks along the rows: a
-// gather, the m x T storage, or a row count that breaks the chunks needs the packing pass.
-bool needs_pack(grass_dy_layout layout, bool gathered, int64_t rows) {
-    return gathered || layout == GRASS_DY_MxT || rows % 8 != 0;
+// The GEMM kernels read the left operand as T x rows: a gather or the m x T storage needs the
+// packing pass.
+bool needs_pack(grass_dy_layout layout, bool gathered) {
+    return gathered || layout == GRASS_DY_MxT;
 }
 
-// X with n not a multiple of 8 is first copied to rows of round_up(n, 8) elements.
+// An operand whose width is not a multiple of 8 has rows that start on 2-byte boundaries.  Either
+// the any-alignment form of the GEMM reads it where it is, or it is first copied into aligned rows
+// (the left operand through the packing pass) for the faster aligned form.
+struct Copies { bool a, b; };
+// Measured: the any-alignment forms take 10 - 20 % longer than the aligned ones (1.3 PFLOP/s with
+// the large tile, 0.45 with the small one), a copy moves 4 bytes per value at 5.2 TB/s and costs a
+// launch; in the large tile the register route takes 5 us more to fill and drain (2746 x 1509,
+// r = 686, T = 448: 38.6 us in place, 35.1 with the copy).  2048 x 5461, r = 512, T = 65536:
+// 429 us per step in place, 617 with the copy; full gradient of 2807 x 6144, T = 5248: 224 us in
+// place, 209 with the copy.  dY stored m x T is read row-wise by the aligned large tile without
+// any pack, which the copy keeps possible.
+Copies choose_copies(TileId tile, int64_t T, int64_t rows, int64_t n, grass_dy_layout layout, bool gathered) {
+    const bool b_odd = n % 8 != 0, a_odd = !needs_pack(layout, gathered) && rows % 8 != 0;
+    if (T < 1 || !(a_odd || b_odd)) return Copies{false, false};
+    if (layout == GRASS_DY_MxT && tile == kTile256 && T % kFastBK == 0) return Copies{false, b_odd};
+    const double t = static_cast<double>(T);
+    const double in_place = tile == kTile256 ? 5e-6 + 0.15 * 2.0 * t * rows * n / 1.3e15
+                                             : 0.15 * 2.0 * t * rows * n / 0.45e15;
+    const double copied = (a_odd ? 4.0 * t * rows / 5.2e12 + 3e-6 : 0.0) + (b_odd ? 4.0 * t * n / 5.2e12 + 3e-6 : 0.0);
+    return copied < in_place ? Copies{a_odd, b_odd} : Copies{false, false};
+}
 size_t aligned_x_bytes(int64_t T, int64_t n) {
-    return n % 8 != 0 ? round_up(static_cast<size_t>(T) * ((n + 7) / 8 * 8) * 2, 256) : 0;
+    return round_up(static_cast<size_t>(T) * ((n + 7) / 8 * 8) * 2, 256);
 }
 
 // The 256 x 256 tile halves the LDS traffic per flop and is the faster kernel whenever it
@@ -241,9 +260,9 @@ void launch_f32_kernel(const F32Args& a, bool vec_a, bool vec_b, hipStream_t s, 
     else launch_stamped(tn_gemm_f32_mfma_kernel<BM, false, false>, grid, block, 0, s, e0, e1, a);
 }
 
-template <typename Cfg, bool kDense>
+template <typename Cfg, bool kDense, bool kAnyAlign>
 hipError_t launch_gemm_kernel(const GemmArgs& g, unsigned grid, hipStream_t s) {
-    auto kernel = tn_gemm_bf16_kernel<Cfg, kDense>;
+    auto kernel = tn_gemm_bf16_kernel<Cfg, kDense, kAnyAlign>;
     if (Cfg::kLdsBytes > 64 * 1024) {
         // per instantiation and device; the attribute sticks for the life of the process, so it
         // is set once (the only state the library keeps: a flag per device, set with release
@@ -311,7 +330,6 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
         g.Np = static_cast<int64_t>(g.tiles_n) * kFastBN;
         g.splits = 1;
         g.ktiles_per_split = static_cast<int>(T / kFastBK);
-        g.a_fast = g.b_fast = 1;
         g.a_rows = nullptr;
         const int64_t items = static_cast<int64_t>(g.tiles_m) * g.tiles_n;
         const int64_t chunk = (items + kNumXcd - 1) / kNumXcd;
@@ -335,11 +353,15 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
                             grass_dy_layout layout, bool gathered) {
     if (dt == GRASS_F32) return f32_partial_bytes(T, &mrows, 1, n, false);
-    // the launcher may fall back to the small tile when alignment rules out the large one
-    const bool pack = needs_pack(layout, gathered, mrows);
-    const Plan a = plan_for(kTile128, T, mrows, n, pack), b = plan_for(kTile256, T, mrows, n, pack);
-    const size_t wa = a.pack_bytes + a.partial_bytes, wb = b.pack_bytes + b.partial_bytes;
-    return (wa > wb ? wa : wb) + aligned_x_bytes(T, n) + 256;
+    // the launcher may fall back to the small tile when the large one cannot be used
+    size_t need = 0;
+    for (const TileId id : {kTile128, kTile256}) {
+        const Copies copy = choose_copies(id, T, mrows, n, layout, gathered);
+        const Plan p = plan_for(id, T, mrows, n, needs_pack(layout, gathered) || copy.a);
+        const size_t bytes = p.pack_bytes + round_up(p.partial_bytes, 256) + (copy.b ? aligned_x_bytes(T, n) : 0);
+        need = bytes > need ? bytes : need;
+    }
+    return need + 256;
 }
 
 void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n, grass_dtype dt,
@@ -361,7 +383,7 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
         return;
     }
     const TileId id = T >= kFastBK && rows >= 8 && n >= 8 ? choose_tile(T, rows, n) : kTile128;
-    Plan p = plan_for(id, T, rows, n, needs_pack(layout, true, rows));
+    Plan p = plan_for(id, T, rows, n, needs_pack(layout, true));
     if (id == kTile256 && layout == GRASS_DY_MxT && T % (2 * kFastBK) == 0 &&
         test_option(GRASS_TEST_PACK_MXT) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0 &&
         p.ktiles_per_split % 2 != 0) {  // the row-gathering kernel takes K tiles in pairs
@@ -369,8 +391,7 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
         p.splits = static_cast<int>((T / kFastBK + p.ktiles_per_split - 1) / p.ktiles_per_split);
     }
     *tile = id == kTile256 ? 256 : 128;
-    // the large tile takes whole K tiles; a ragged tail of T is one more slice
-    *k_slices = p.splits + (id == kTile256 && T % kFastBK != 0 ? 1 : 0);
+    *k_slices = p.splits;
 }
 
 size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int64_t n,
@@ -529,7 +550,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     }
 
     const bool gathered = count > 1 || seg[0].idx != nullptr;
-    bool pack = needs_pack(layout, gathered, total);
+    bool pack = needs_pack(layout, gathered);
     if (count > 1) {
         // One panel pays off while a slice of partial tiles of the joint problem still fits
         // the caches (fewer, fuller launches).  Beyond that every set fills the machine on its
@@ -605,23 +626,23 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     const void* dY0 = seg[0].dY;  // read directly by the GEMM only when nothing is packed
     const int64_t ldy0 = seg[0].ldy;
     TileId tile = choose_tile(T, total, n);
-    // X whose width breaks the 16-byte chunks is copied to padded rows first (T > 0: nothing
-    // to copy otherwise); the GEMM then sees a matrix of round_up(n, 8) columns
-    const bool copy_x = n % 8 != 0 && aligned_to(X, 4) && T > 0;
-    const int64_t nb = copy_x ? (n + 7) / 8 * 8 : n;
-    {   // the large-tile kernel moves whole aligned 16-byte chunks only
-        const bool a_ok = pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0);
-        const bool b_ok = copy_x || (aligned_to(X, 16) && ldx % 8 == 0 && n % 8 == 0);
-        // per-lane byte offsets inside one K tile are kept in 32 bits
+    {   // per-lane byte offsets inside one K tile are kept in 32 bits
         const int64_t lda_eff = pack ? (total + kFastBM - 1) / kFastBM * kFastBM : ldy0;
         const bool off_ok = (kFastBK + 1) * lda_eff * 2 < (int64_t{1} << 32) &&
-                            (kFastBK + 1) * (copy_x ? nb : ldx) * 2 < (int64_t{1} << 32);
-        if (!(a_ok && b_ok && off_ok && T >= kFastBK && total >= 8 && n >= 8)) tile = kTile128;
+                            (kFastBK + 1) * ldx * 2 < (int64_t{1} << 32);
+        if (!(off_ok && T >= kFastBK && total >= 8 && n >= 8)) tile = kTile128;
     }
+    Copies copy = choose_copies(tile, T, total, n, layout, gathered);
+    if (copy.b && !aligned_to(X, 4)) copy = Copies{false, false};  // what the copy kernel asks for
+    pack = pack || copy.a;
+    const int64_t nb = copy.b ? (n + 7) / 8 * 8 : n;  // columns the GEMM sees
+    // whole aligned 16-byte chunks: what the load-to-LDS kernel and the aligned small tile move
+    const bool aligned = (pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0)) &&
+                         (copy.b || (aligned_to(X, 16) && ldx % 8 == 0 && n % 8 == 0));
     // dY stored m x T: the selected rows are contiguous, so the large-tile kernel gathers them
     // itself (no packing pass) when K is whole tiles and its 32-bit row offsets reach every row
     bool a_rows_form = false;
-    if (tile == kTile256 && layout == GRASS_DY_MxT && count == 1 && T % kFastBK == 0 &&
+    if (tile == kTile256 && layout == GRASS_DY_MxT && count == 1 && aligned && T % kFastBK == 0 &&
         aligned_to(dY0, 16) && ldy0 % 8 == 0 && test_option(GRASS_TEST_PACK_MXT) == 0) {
         const int64_t src_rows = seg[0].idx ? seg[0].src_rows : total;
         a_rows_form = src_rows > 0 && src_rows * ldy0 * 2 + 128 < (int64_t{1} << 32);
@@ -629,9 +650,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     if (a_rows_form) pack = false;
     // whole cache lines per row (64 values of k per load) when the K tiles pair up
     const bool a_pairs = a_rows_form && T % (2 * kFastBK) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0;
-    // the large-tile kernel takes whole K tiles; a ragged tail goes to the small-tile kernel
-    const int64_t T_main = tile == kTile256 ? T / kFastBK * kFastBK : T;
-    Plan p = plan_for(tile, T, total, n, pack);  // sized for all T rows; K tiling per tile kind
+    Plan p = plan_for(tile, T, total, n, pack);
     if (a_pairs && p.ktiles_per_split % 2 != 0) {  // every workgroup gets whole pairs of K tiles
         ++p.ktiles_per_split;
         const int64_t ktiles = T / kFastBK;
@@ -645,7 +664,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     const int64_t items = static_cast<int64_t>(p.tiles_m) * p.tiles_n * p.splits;
     const int64_t chunk = (items + kNumXcd - 1) / kNumXcd;
     const int x_chunks = static_cast<int>((nb / 8 + 255) / 256);  // workgroups per row of the aligning copy
-    if (chunk * kNumXcd > 0x7FFFFFFF || (copy_x && T * x_chunks > 0x7FFFFFFF)) return GRASS_ERR_SHAPE;
+    if (chunk * kNumXcd > 0x7FFFFFFF || (copy.b && T * x_chunks > 0x7FFFFFFF)) return GRASS_ERR_SHAPE;
 
     GemmArgs g;
     if (pack) {
@@ -735,30 +754,24 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         g.A = panel;
         g.lda = p.rp;
         g.Mcols = p.rp;
-        g.a_fast = 1;
     } else {
         g.A = static_cast<const uint16_t*>(dY0);
         g.lda = ldy0;
         g.Mcols = total;
-        g.a_fast = aligned_to(dY0, 16) && ldy0 % 8 == 0;
     }
     g.a_rows = a_rows_form ? seg[0].idx : nullptr;
-    if (copy_x) {
+    g.B = static_cast<const uint16_t*>(X);
+    g.ldb = ldx;
+    g.Ncols = nb;
+    if (copy.b) {
         uint16_t* xa = reinterpret_cast<uint16_t*>(base + p.pack_bytes + round_up(p.partial_bytes, 256));
         align_rows_kernel<<<static_cast<unsigned>(T * x_chunks), 256, 0, s>>>(
             static_cast<const uint16_t*>(X), ldx, T, n, nb, x_chunks, xa);
         g.B = xa;
         g.ldb = nb;
-        g.Ncols = nb;
-        g.b_fast = 1;
-    } else {
-        g.B = static_cast<const uint16_t*>(X);
-        g.ldb = ldx;
-        g.Ncols = n;
-        g.b_fast = aligned_to(X, 16) && ldx % 8 == 0;
     }
     g.P = partial;
-    g.K = T_main;
+    g.K = T;
     g.Mp = p.Mp;
     g.Np = p.Np;
     g.tiles_m = p.tiles_m;
@@ -775,6 +788,10 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         else if (a_rows_form)
             launch_stamped(tn_gemm_bf16_direct_kernel<false, false, true>, dim3(grid), dim3(256), 0, s,
                            ev_start, ev_stop, g);
+        else if (!aligned && gathered)
+            launch_stamped(tn_gemm_bf16_unaligned_kernel<false>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
+        else if (!aligned)
+            launch_stamped(tn_gemm_bf16_unaligned_kernel<true>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else if (gathered)
             launch_stamped(tn_gemm_bf16_direct_kernel<false>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else
@@ -782,32 +799,16 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         le = hipSuccess;
     } else {
         if (ev_start) (void)hipEventRecord(ev_start, s);
-        le = gathered ? launch_gemm_kernel<Cfg128, false>(g, grid, s)
-                      : launch_gemm_kernel<Cfg128, true>(g, grid, s);
+        if (aligned)
+            le = gathered ? launch_gemm_kernel<Cfg128, false, false>(g, grid, s)
+                          : launch_gemm_kernel<Cfg128, true, false>(g, grid, s);
+        else
+            le = gathered ? launch_gemm_kernel<Cfg128, false, true>(g, grid, s)
+                          : launch_gemm_kernel<Cfg128, true, true>(g, grid, s);
         if (le == hipSuccess && ev_stop) (void)hipEventRecord(ev_stop, s);
     }
     if (le != hipSuccess) return GRASS_ERR_DEVICE;
-    int slices = p.splits;
-    if (T_main < T) {  // rows [T_main, T) as one more slice, computed with 128 x 128 tiles
-        GemmArgs t = g;
-        t.A = g.A + T_main * g.lda;
-        t.B = g.B + T_main * g.ldb;
-        t.K = T - T_main;
-        t.P = partial + static_cast<int64_t>(p.splits) * p.Mp * p.Np;
-        t.tiles_m = static_cast<int>(p.Mp / Cfg128::BM);
-        t.tiles_n = static_cast<int>(p.Np / Cfg128::BN);
-        t.splits = 1;
-        t.ktiles_per_split = 1;
-        t.a_fast = t.b_fast = 1;
-        const int64_t titems = static_cast<int64_t>(t.tiles_m) * t.tiles_n;
-        const unsigned tgrid = static_cast<unsigned>((titems + kNumXcd - 1) / kNumXcd * kNumXcd);
-        le = gathered ? launch_gemm_kernel<Cfg128, false>(t, tgrid, s)
-                      : launch_gemm_kernel<Cfg128, true>(t, tgrid, s);
-        if (le != hipSuccess) return GRASS_ERR_DEVICE;
-        ++slices;
-    }
-
-    return finish_segments(seg, count, partial, slices, p.Mp, p.Np, n, odt, s, ev_tail_start, ev_tail_stop);
+    return finish_segments(seg, count, partial, p.splits, p.Mp, p.Np, n, odt, s, ev_tail_start, ev_tail_stop);
 }
 
 grass_status launch_tn_gemm(const void* dY, grass_dy_layout layout, int64_t ldy, const void* X,

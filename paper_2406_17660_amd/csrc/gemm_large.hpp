@@ -28,9 +28,10 @@ namespace {
 // banks exactly once.
 //
 // Edges.  Columns past the matrix edge are redirected to column 0 of the same row: they
-// only feed output rows / columns that are never read back.  Only whole K tiles are
-// processed (g.K is a multiple of kFastBK here; the launcher hands a ragged tail of T to
-// the small-tile kernel as one more split-K slice).
+// only feed output rows / columns that are never read back.  A ragged last K tile (T x m form) is
+// loaded during the drain with the tokens past T redirected to the last one, and their LDS rows
+// are cleared once it has landed: no extra slice or launch (the 4096 x 4096 layer at r = 1024,
+// T = 2047: 63 -> 57 us per step, against 56 at T = 2048).
 // Requirements (checked by the launcher): bases 16-byte aligned, leading dimensions and
 // column counts multiples of 8.
 constexpr int kFastBM = 256, kFastBN = 256, kFastBK = 32, kFastStages = 4;
@@ -109,10 +110,15 @@ void tn_gemm_bf16_direct_kernel(GemmArgs g) {
     tile_coords(tile, g.tiles_m, g.tiles_n, tm, tn);
     const int64_t m0 = static_cast<int64_t>(tm) * kFastBM, n0 = static_cast<int64_t>(tn) * kFastBN;
     const int64_t kt_begin = static_cast<int64_t>(split) * g.ktiles_per_split;
-    const int64_t ktiles_all = g.K / kFastBK;
+    constexpr bool kRagged = !kARows && !kRowStats;  // these forms are only given whole K tiles
+    const int64_t ktiles_all = kRagged ? (g.K + kFastBK - 1) / kFastBK : g.K / kFastBK;
     int64_t kt_end = kt_begin + g.ktiles_per_split;
     if (kt_end > ktiles_all) kt_end = ktiles_all;
     const int ntiles = kt_end > kt_begin ? static_cast<int>(kt_end - kt_begin) : 0;
+    // rows of this workgroup's last tile, and how many of its tiles are whole
+    const int last_rows = kRagged && ntiles > 0 && kt_end * kFastBK > g.K
+                              ? static_cast<int>(g.K - (kt_end - 1) * kFastBK) : kFastBK;
+    const int whole = last_rows == kFastBK ? ntiles : ntiles - 1;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -195,9 +201,32 @@ void tn_gemm_bf16_direct_kernel(GemmArgs g) {
     };
     auto advance_tile = [&]() { gA += tileA; gB += tileB; };
     auto issue = [&](int i) {
+        if (kRagged && i >= whole) {  // the ragged last tile
+            const uint32_t d = ring_base + ((i % kFastStages) * kFastStageElems + ldsrow * 256) * 2;
 #pragma unroll
-        for (int part = 0; part < kFastLoadsPerTile; ++part) issue_part(i, part);
+            for (int p = 0; p < kFastBK / 8; ++p) {
+                const int row = p * 8 + lrow, src = row < last_rows ? row : last_rows - 1;
+                load16_to_lds(gA, static_cast<uint32_t>((src * g.lda + colA) * 2), d + p * 8 * 256 * 2);
+                load16_to_lds(gB, static_cast<uint32_t>((src * g.ldb + colB) * 2),
+                              d + kFastOperandElems * 2 + p * 8 * 256 * 2);
+            }
+        } else {
+#pragma unroll
+            for (int part = 0; part < kFastLoadsPerTile; ++part) issue_part(i, part);
+        }
         advance_tile();
+    };
+    // clears the rows of the ragged last tile that lie past K (after it has landed; ends in a barrier)
+    auto clear_rows = [&](int i) {
+        if (kRagged && last_rows < kFastBK && i == ntiles - 1) {
+            uint16_t* st = ring + (i % kFastStages) * kFastStageElems;
+            const uint4 zero = make_uint4(0, 0, 0, 0);
+            for (int c = last_rows * 32 + tid; c < kFastBK * 32; c += 256) {
+                *reinterpret_cast<uint4*>(st + c * 8) = zero;
+                *reinterpret_cast<uint4*>(st + kFastOperandElems + c * 8) = zero;
+            }
+            __syncthreads();
+        }
     };
 
     // ---- LDS -> MFMA operand addressing (element offsets inside an operand block)
@@ -388,6 +417,7 @@ void tn_gemm_bf16_direct_kernel(GemmArgs g) {
         // tile 0: nothing to overlap with yet
         if (ntiles > kAhead - 1) wait_vmcnt<(kAhead - 1) * kFastLoadsPerTile>(); else wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
+        clear_rows(0);
         read_frags(F, 0, 0);
         if (kAhead < ntiles) issue(kAhead);
         read_frags(G, 0, 16);
@@ -396,7 +426,7 @@ void tn_gemm_bf16_direct_kernel(GemmArgs g) {
         __builtin_amdgcn_sched_barrier(0);
         // steady state: tiles i+1, i+2 are in flight behind tile i; tile i+kAhead is issued here
         int i = 1;
-        for (; i + kAhead < ntiles; ++i) {
+        for (; i + kAhead < whole; ++i) {
             wait_vmcnt<(kAhead - 1) * kFastLoadsPerTile>();
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): own LDS reads of tile i-1 done
             __builtin_amdgcn_s_barrier();
@@ -405,12 +435,14 @@ void tn_gemm_bf16_direct_kernel(GemmArgs g) {
             slice(F, G, i, 16, i + kAhead, 4, true);
             advance_tile();
         }
-        // drain: nothing left to issue; wait for everything that is still in flight
+        // drain: at most the ragged last tile is left to issue; wait for everything in flight
         for (; i < ntiles; ++i) {
             wait_vmcnt<0>();
             __builtin_amdgcn_s_waitcnt(0xC07F);
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
+            if (kRagged && i + kAhead < ntiles) issue(i + kAhead);
+            clear_rows(i);
             slice(G, F, i, 0, 0, 0, false);
             slice(F, G, i, 16, 0, 0, false);
         }

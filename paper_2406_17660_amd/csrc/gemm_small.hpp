@@ -1,4 +1,4 @@
-// bf16 MFMA GEMM with 128 x 128 tiles, register-staged: small and unaligned problems, K tails.
+// bf16 MFMA GEMM with 128 x 128 tiles, register-staged: small problems.
 // Included by cgrad.hip only (device code shares one translation unit with its launchers).
 #pragma once
 #include "common.hpp"
@@ -8,23 +8,29 @@ namespace grass {
 namespace {
 
 // ------------------------------------------------------------------------------ bf16 MFMA GEMM
-// One 16-byte chunk (8 bf16) of row `krow` starting at column `col` of a [K x ncols] matrix,
-// zero outside the matrix.
+// 16 bytes from any element of a matrix (rows may start on 2-byte boundaries).
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+struct __attribute__((packed, aligned(2))) Chunk16 { u32x4_t v; };
+
+// One aligned 16-byte chunk (8 bf16) of row `krow` starting at column `col` of a [K x ncols] matrix
+// (ncols a multiple of 8), zero outside the matrix.
 __device__ __forceinline__ uint4 load_chunk(const uint16_t* __restrict__ base, int64_t ld,
-                                            int64_t krow, int64_t col, int64_t K, int64_t ncols,
-                                            bool fast) {
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (krow >= K || col >= ncols) return v;
-    const uint16_t* p = base + krow * ld + col;
-    if (fast && col + 8 <= ncols) return *reinterpret_cast<const uint4*>(p);
-    uint16_t e[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) e[i] = col + i < ncols ? p[i] : static_cast<uint16_t>(0);
-    v.x = e[0] | (static_cast<uint32_t>(e[1]) << 16);
-    v.y = e[2] | (static_cast<uint32_t>(e[3]) << 16);
-    v.z = e[4] | (static_cast<uint32_t>(e[5]) << 16);
-    v.w = e[6] | (static_cast<uint32_t>(e[7]) << 16);
-    return v;
+                                            int64_t krow, int64_t col, int64_t K, int64_t ncols) {
+    if (krow >= K || col >= ncols) return make_uint4(0, 0, 0, 0);
+    return *reinterpret_cast<const uint4*>(base + krow * ld + col);
+}
+
+// v without its first `drop` (0..8) bf16 values, zeros moved in behind them.
+__device__ __forceinline__ uint4 drop_elems(u32x4_t v, int drop) {
+    unsigned long long lo = v[0] | (static_cast<unsigned long long>(v[1]) << 32);
+    unsigned long long hi = v[2] | (static_cast<unsigned long long>(v[3]) << 32);
+    if (drop & 4) { lo = hi; hi = 0; }
+    const int bits = (drop & 3) * 16;
+    lo = (lo >> bits) | ((hi << 1) << (63 - bits));
+    hi >>= bits;
+    if (drop & 8) { lo = 0; hi = 0; }
+    return make_uint4(static_cast<uint32_t>(lo), static_cast<uint32_t>(lo >> 32),
+                      static_cast<uint32_t>(hi), static_cast<uint32_t>(hi >> 32));
 }
 
 template <int BM_, int BN_, int BK_, int WR_, int WC_>
@@ -39,7 +45,6 @@ struct TileCfg {
     static constexpr int B_CHUNKS = BK * BN / 8 / kThreads;
     static constexpr size_t kLdsBytes = static_cast<size_t>(BK) * (LDA + LDB) * 2;
     static constexpr int kWgPerCu = 2;
-    static constexpr bool kWholeKTilesOnly = false;
     static_assert(BK % 16 == 0 && WM % 32 == 0 && WN % 32 == 0, "tile shape");
     static_assert((BK * BM / 8) % kThreads == 0 && (BK * BN / 8) % kThreads == 0, "chunking");
 };
@@ -67,7 +72,6 @@ struct GemmArgs {
     float* P;           // partials [S][Mp][Np]
     int64_t lda, ldb, K, Mcols, Ncols, Mp, Np;
     int tiles_m, tiles_n, splits, ktiles_per_split;
-    int a_fast, b_fast;
     // row form of the left operand (large-tile kernel only): A is [rows of length K], row j of
     // the product is A + a_rows[j] * lda (a_rows == nullptr: row j itself)
     const int32_t* a_rows;
@@ -75,7 +79,9 @@ struct GemmArgs {
 
 // kDense only tags the instantiation (dense full gradient vs compressed gradient) so that a
 // profiler lists the two uses separately; the code is identical.
-template <typename Cfg, bool kDense>
+// kAnyAlign: operands whose rows, widths or bases break the aligned 16-byte chunks (about 10 %
+// slower than the aligned form, which costs less than a copy of a wide operand).
+template <typename Cfg, bool kDense, bool kAnyAlign>
 __global__ __launch_bounds__(Cfg::kThreads) void tn_gemm_bf16_kernel(GemmArgs g) {
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
     uint16_t* As = lds;
@@ -110,40 +116,79 @@ __global__ __launch_bounds__(Cfg::kThreads) void tn_gemm_bf16_kernel(GemmArgs g)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    uint4 ra[Cfg::A_CHUNKS], rb[Cfg::B_CHUNKS];
+    // Global -> registers.  kAnyAlign: a thread fetches 16 bytes of the same columns in every row it
+    // serves, from any element on; a chunk across the right edge is read from the last 8 columns and
+    // one past it from the first (never outside a row), tokens past K from the last token; what
+    // does not belong to the tile is dropped or zeroed on the way to LDS, in edge tiles only.
+    u32x4_t ra[Cfg::A_CHUNKS], rb[Cfg::B_CHUNKS];
     constexpr int ACPR = Cfg::BM / 8, BCPR = Cfg::BN / 8;  // chunks per tile row
-
+    static_assert(Cfg::kThreads % ACPR == 0 && Cfg::kThreads % BCPR == 0, "one column per thread");
+    struct Side {
+        const uint16_t* p;  // this thread's chunk in row 0
+        int drop;           // leading values of the chunk that belong to the one before (8: all)
+    };
+    auto side = [&](const uint16_t* base, int64_t col, int64_t ncols) {
+        Side q;
+        q.drop = col >= ncols ? 8 : (col + 8 > ncols ? static_cast<int>(col + 8 - ncols) : 0);
+        q.p = base + (q.drop == 0 ? col : (q.drop == 8 || ncols < 8 ? 0 : ncols - 8));
+        return q;
+    };
+    const Side qa = side(g.A, m0 + (tid % ACPR) * 8, g.Mcols), qb = side(g.B, n0 + (tid % BCPR) * 8, g.Ncols);
+    const bool edge = m0 + Cfg::BM > g.Mcols || n0 + Cfg::BN > g.Ncols;
+    auto fetch_side = [&](u32x4_t& v, const uint16_t* base, const Side& q, int64_t ld, int64_t ncols,
+                          int64_t row, int64_t col) {
+        if (!kAnyAlign) {
+            const uint4 w = load_chunk(base, ld, row, col, g.K, ncols);
+            v = u32x4_t{w.x, w.y, w.z, w.w};
+            return;
+        }
+        const uint16_t* p = q.p + (row < g.K ? row : g.K - 1) * ld;
+        if (ncols >= 8) {
+            v = reinterpret_cast<const Chunk16*>(p)->v;
+        } else {  // fewer than 8 columns in all: element by element, from column 0
+            uint16_t e[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) e[i] = i < ncols ? p[i] : static_cast<uint16_t>(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = e[2 * i] | (static_cast<uint32_t>(e[2 * i + 1]) << 16);
+        }
+    };
     auto fetch = [&](int64_t kt) {
         const int64_t k0 = kt * Cfg::BK;
 #pragma unroll
-        for (int c = 0; c < Cfg::A_CHUNKS; ++c) {
-            const int id = tid + c * Cfg::kThreads;
-            ra[c] = load_chunk(g.A, g.lda, k0 + id / ACPR, m0 + (id % ACPR) * 8, g.K, g.Mcols,
-                               g.a_fast);
-        }
+        for (int c = 0; c < Cfg::A_CHUNKS; ++c)
+            fetch_side(ra[c], g.A, qa, g.lda, g.Mcols, k0 + (tid + c * Cfg::kThreads) / ACPR,
+                       m0 + ((tid + c * Cfg::kThreads) % ACPR) * 8);
 #pragma unroll
-        for (int c = 0; c < Cfg::B_CHUNKS; ++c) {
-            const int id = tid + c * Cfg::kThreads;
-            rb[c] = load_chunk(g.B, g.ldb, k0 + id / BCPR, n0 + (id % BCPR) * 8, g.K, g.Ncols,
-                               g.b_fast);
-        }
+        for (int c = 0; c < Cfg::B_CHUNKS; ++c)
+            fetch_side(rb[c], g.B, qb, g.ldb, g.Ncols, k0 + (tid + c * Cfg::kThreads) / BCPR,
+                       n0 + ((tid + c * Cfg::kThreads) % BCPR) * 8);
     };
-    auto stash = [&]() {
+    auto fixed = [&](const u32x4_t& v, const Side& q, int64_t ncols, bool live) {
+        return drop_elems(v, !live ? 8 : (ncols < 8 && q.drop < 8 ? 0 : q.drop));
+    };
+    auto stash = [&](int64_t kt) {
+        const int64_t k0 = kt * Cfg::BK;
+        const bool as_is = !kAnyAlign || (!edge && k0 + Cfg::BK <= g.K);
 #pragma unroll
         for (int c = 0; c < Cfg::A_CHUNKS; ++c) {
             const int id = tid + c * Cfg::kThreads;
-            *reinterpret_cast<uint4*>(As + (id / ACPR) * Cfg::LDA + (id % ACPR) * 8) = ra[c];
+            uint4 v = make_uint4(ra[c][0], ra[c][1], ra[c][2], ra[c][3]);
+            if (!as_is) v = fixed(ra[c], qa, g.Mcols, k0 + id / ACPR < g.K);
+            *reinterpret_cast<uint4*>(As + (id / ACPR) * Cfg::LDA + (id % ACPR) * 8) = v;
         }
 #pragma unroll
         for (int c = 0; c < Cfg::B_CHUNKS; ++c) {
             const int id = tid + c * Cfg::kThreads;
-            *reinterpret_cast<uint4*>(Bs + (id / BCPR) * Cfg::LDB + (id % BCPR) * 8) = rb[c];
+            uint4 v = make_uint4(rb[c][0], rb[c][1], rb[c][2], rb[c][3]);
+            if (!as_is) v = fixed(rb[c], qb, g.Ncols, k0 + id / BCPR < g.K);
+            *reinterpret_cast<uint4*>(Bs + (id / BCPR) * Cfg::LDB + (id % BCPR) * 8) = v;
         }
     };
 
     if (kt_begin < kt_end) {
         fetch(kt_begin);
-        stash();
+        stash(kt_begin);
         __syncthreads();
         for (int64_t kt = kt_begin; kt < kt_end; ++kt) {
             const bool more = kt + 1 < kt_end;
@@ -166,7 +211,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void tn_gemm_bf16_kernel(GemmArgs g)
             }
             __syncthreads();
             if (more) {
-                stash();
+                stash(kt + 1);
                 __syncthreads();
             }
         }

@@ -1,0 +1,83 @@
+"""GPU parity of the bf16 products on operands in any position (odd widths, sliced tensors, bases off
+16 bytes) and with any number of tokens, against the fp64 oracle.
+
+Everything around the operands holds Inf: a value read from outside a row, or a token past the end
+that is not cleared, turns an output into Inf or NaN.  Bound: products of bf16 values are exact
+in fp32, a sum of T of them is off by about sqrt(T) * 2^-24 relatively, 3e-6 at the largest T
+here; TOL_F32 (1e-5) covers it."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from paper_2406_17660_amd import grass
+from gpu_util import DEV, TOL_F32, rel_fro, to_f64, to_np
+
+pytestmark = pytest.mark.gpu
+BF = torch.bfloat16
+
+
+def _framed(rows, cols, ld, first, gen):
+    """A rows x cols bf16 matrix with leading dimension ld that starts `first` elements into a buffer
+    of Inf (16-byte aligned when first is 8)."""
+    flat = torch.full((first + rows * ld + 64,), float("inf"), dtype=BF, device=DEV)
+    view = flat[first:first + rows * ld].view(rows, ld)[:, :cols]
+    view.copy_(torch.randn(rows, cols, generator=gen, device=DEV))
+    return view
+
+
+def _check(T, m, n, r, layout, ldy_pad, ldx_pad, first, seed=0):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    X = _framed(T, n, n + ldx_pad, first, gen)
+    dY = _framed(m, T, T + ldy_pad, first, gen) if layout == grass.DY_MxT else \
+        _framed(T, m, m + ldy_pad, first, gen)
+    idx = torch.randint(0, m, (r,), generator=gen, device=DEV).sort()[0].to(torch.int32)
+    rho = torch.rand(r, generator=gen, device=DEV) + 0.5
+    d = to_f64(dY)
+    d = np.ascontiguousarray(d.T) if layout == grass.DY_MxT else d
+    want = ref.compressed_grad(d, to_f64(X), to_np(idx), to_np(rho))
+    GC = torch.full((r, n), float("nan"), device=DEV)
+    grass.compressed_grad(dY, X, idx, rho, GC,
+                          grass.workspace(grass.cgrad_workspace(T, m, n, r, grass.BF16, layout)), layout)
+    assert rel_fro(to_np(GC), want) <= TOL_F32
+    G = torch.full((m, n), float("nan"), device=DEV)
+    grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(T, m, n, grass.BF16, layout)), layout)
+    assert rel_fro(to_np(G), d.T @ to_f64(X)) <= TOL_F32
+
+
+# tokens around the K tiles of both kernels (32 and 64) and around the six whole tiles from which the
+# large tile's steady loop runs; widths around a chunk (8), a wavefront's block (128) and a tile
+@pytest.mark.parametrize("tile", [128, 256])
+@pytest.mark.parametrize("T", [1, 31, 32, 33, 63, 64, 95, 129, 192, 200, 257, 1000])
+@pytest.mark.parametrize("m,n,first,pad", [(9, 9, 8, 0), (257, 135, 9, 0), (263, 250, 8, 3), (120, 391, 15, 2)])
+def test_any_position(tile, T, m, n, first, pad):
+    grass.set_test_option(grass.TEST_GEMM_TILE, tile)
+    _check(T, m, n, min(m, 140), grass.DY_TxM, pad, pad, first)
+
+
+@pytest.mark.parametrize("tile", [128, 256])
+@pytest.mark.parametrize("T", [33, 64, 320, 2501])
+@pytest.mark.parametrize("m,n", [(264, 248), (3, 5), (256, 7), (6, 256)])
+def test_ragged_tokens_of_aligned_and_tiny_operands(tile, T, m, n):
+    grass.set_test_option(grass.TEST_GEMM_TILE, tile)
+    _check(T, m, n, min(m, 136), grass.DY_TxM, -m % 8, -n % 8, 8)
+
+
+@pytest.mark.parametrize("T,n,first", [(320, 261, 8), (321, 261, 8), (320, 264, 9), (45, 300, 11)])
+def test_mxt_storage(T, n, first):
+    grass.set_test_option(grass.TEST_GEMM_TILE, 256)
+    _check(T, 270, n, 260, grass.DY_MxT, -T % 8, 0, first)
+
+
+@pytest.mark.parametrize("slices", [1, 3, 5])
+def test_slices_end_in_a_ragged_tile(slices):
+    grass.set_test_option(grass.TEST_GEMM_TILE, 256)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, slices)
+    _check(2477, 300, 515, 260, grass.DY_TxM, 0, 0, 8)
+    _check(2477, 304, 520, 260, grass.DY_TxM, 0, 0, 8)
+
+
+@pytest.mark.parametrize("T,m,n", [(96, 5000, 2051), (96, 2051, 5000)])
+def test_full_gradient_whose_odd_operand_is_copied(T, m, n):
+    _check(T, m, n, 8, grass.DY_TxM, 0, 0, 8)
