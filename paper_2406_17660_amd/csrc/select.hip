@@ -10,14 +10,16 @@
 //   with repl.      fixed-point weights -> 64-bit inclusive prefix sums in the workspace;
 //                   the r draws are independent: Philox word, 64x64 high multiply, binary
 //                   search; a per-row hit counter plus a scan emits idx sorted.
-//   without repl.   draws are sequential by definition.  A radix-64 sum tree over the
-//                   weights (in LDS when it fits in 144 KiB, else in the workspace) lets
-//                   one wavefront do a draw in log64(m) steps: 64 children per load, a
-//                   wavefront scan and a ballot pick the child; the path is then
-//                   decremented.  Chosen leaves have weight 0; a scan compacts them.
+//   without repl.   draws are sequential by definition.  Up to 16384 rows, prefix sums over
+//                   groups of 64 rows sit in one wavefront's registers and those of the rows
+//                   in LDS (a draw is two compares and one LDS read).  Beyond, a radix-64 sum
+//                   tree over the weights (in LDS when it fits in 144 KiB, else in the
+//                   workspace) lets the wavefront do a draw in log64(m) steps: 64 children per
+//                   load, a wavefront scan and a ballot pick the child; the path is then
+//                   decremented.  A scan compacts the chosen rows.
 //
-// Selection arithmetic is integer (or correctly rounded IEEE double sqrt / divide) so
-// that the indices are reproducible bit for bit.
+// Selection arithmetic is integer, or IEEE double where that gives the same integers (or the
+// correctly rounded sqrt / divide), so that the indices are reproducible bit for bit.
 #include <atomic>
 
 #include "common.hpp"
@@ -44,7 +46,6 @@ struct Shared {
     unsigned long long bcast64;
     uint32_t prefix;
     uint32_t need;
-    int bad;
 };
 
 __device__ __forceinline__ uint32_t key_of(float s) { return s == 0.0f ? 0u : __float_as_uint(s); }
@@ -110,17 +111,10 @@ __device__ __forceinline__ double block_max(double v, Shared* sh) {
     return r;
 }
 
-// Common prologue: reject NaN / Inf / negative statistics.  Returns true (for every
-// thread) when the input is bad, after writing the placeholder selection.
-__device__ bool reject_nonfinite(const float* sumsq, int64_t m, int64_t r, int32_t* idx,
-                                 float* rho, int32_t* status, Shared* sh) {
-    if (threadIdx.x == 0) sh->bad = 0;
-    __syncthreads();
-    bool bad = false;
-    for (int64_t k = threadIdx.x; k < m; k += kThreads) bad |= is_bad(sumsq[k]);
-    if (bad) sh->bad = 1;
-    __syncthreads();
-    if (!sh->bad) {
+// Common prologue: reject NaN / Inf / negative statistics.  `bad`: this thread has seen one.  Returns
+// true (for every thread) when any has, after writing the placeholder selection.
+__device__ bool report_nonfinite(bool bad, int64_t m, int64_t r, int32_t* idx, float* rho, int32_t* status) {
+    if (!__syncthreads_or(bad)) {
         if (threadIdx.x == 0) *status = GRASS_OK;
         return false;
     }
@@ -131,13 +125,127 @@ __device__ bool reject_nonfinite(const float* sumsq, int64_t m, int64_t r, int32
     }
     return true;
 }
+__device__ bool reject_nonfinite(const float* sumsq, int64_t m, int64_t r, int32_t* idx,
+                                 float* rho, int32_t* status) {
+    bool bad = false;
+    for (int64_t k = threadIdx.x; k < m; k += kThreads) bad |= is_bad(sumsq[k]);
+    return report_nonfinite(bad, m, r, idx, rho, status);
+}
+
+// Up to 16384 rows (every layer's row count in practice) each thread keeps PER consecutive rows in
+// registers: the statistic is read once, with all loads in flight, and a compaction needs a single
+// block scan, where the kernels for any size read it in up to six passes of m / 1024 dependent
+// rounds and scan once per round.  Those rounds are what the small selections spend their time on
+// (13824 rows: Top-r 36 -> 29 us, with replacement 65 -> 31 us; 4096 rows: 12.6 -> 11.3
+// and 25 -> 16 us).
+constexpr int kRegRows = 16;
+constexpr int64_t kRegMaxRows = int64_t{kRegRows} * kThreads;
+template <int PER>
+__device__ __forceinline__ bool load_rows(const float* sumsq, int m, int first, int count, float (&s)[PER]) {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) s[i] = i < count && first + i < m ? sumsq[first + i] : 0.f;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) bad |= is_bad(s[i]);
+    return bad;
+}
 
 // ------------------------------------------------------------------------------ Top-r
+// One pass of the radix select, by one wavefront: the digit at which the count of rows with a larger
+// digit first reaches `need`.  Lane L owns digits 255-4L .. 252-4L (descending).
+__device__ __forceinline__ void find_digit(Shared* sh, uint32_t prefix, uint32_t need, int shift) {
+    const int lane = threadIdx.x;
+    uint32_t h[4], s = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { h[e] = sh->hist[255 - 4 * lane - e]; s += h[e]; }
+    const uint32_t incl = wave_inclusive_scan(s);
+    uint32_t above = incl - s;
+    if (above < need && need <= incl) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (need <= above + h[e]) {
+                sh->prefix = prefix | (static_cast<uint32_t>(255 - 4 * lane - e) << shift);
+                sh->need = need - above;
+                break;
+            }
+            above += h[e];
+        }
+    }
+}
+
+// The rows in registers (see load_rows); otherwise the kernel below.
+template <int PER>
+__global__ __launch_bounds__(kThreads) void select_topr_reg_kernel(
+    const float* __restrict__ sumsq, int m, int r, int32_t* __restrict__ idx, float* __restrict__ rho,
+    int32_t* __restrict__ status) {
+    __shared__ Shared sh;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int per = (m + kThreads - 1) / kThreads, first = tid * per;
+    float s[PER];
+    const bool bad = load_rows(sumsq, m, first, per, s);
+    if (report_nonfinite(bad, m, r, idx, rho, status)) return;
+    if (r == 0) return;  // nothing to select: only the status word is written
+    const int mine = first >= m ? 0 : (m - first < per ? m - first : per);  // rows of this thread
+
+    uint32_t prefix = 0, need = static_cast<uint32_t>(r);
+    for (int pass = 3; pass >= 0; --pass) {
+        const int shift = pass * 8;
+        if (tid < 256) sh.hist[tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (i >= per) continue;
+            const uint32_t key = key_of(s[i]), digit = (key >> shift) & 255u;
+            bool count = i < mine && (pass == 3 || (key >> (shift + 8)) == (prefix >> (shift + 8)));
+            // the leading digits are nearly all alike (sign and exponent): one add per value and
+            // wavefront instead of 64 that would queue for one LDS word
+            for (int round = 0; pass == 3 && round < 4; ++round) {
+                const unsigned long long left = __ballot(count);
+                if (!left) break;
+                const int leader = __ffsll(static_cast<long long>(left)) - 1;
+                const bool same = count && digit == static_cast<uint32_t>(__builtin_amdgcn_readlane(digit, leader));
+                const int n = __popcll(__ballot(same));
+                if (lane == leader) atomicAdd(&sh.hist[digit], static_cast<uint32_t>(n));
+                count = count && !same;
+            }
+            if (count) atomicAdd(&sh.hist[digit], 1u);
+        }
+        __syncthreads();
+        if (tid < kWave) find_digit(&sh, prefix, need, shift);
+        __syncthreads();
+        prefix = sh.prefix;
+        need = sh.need;
+    }
+
+    // every key above the threshold, and the first `need` rows that equal it (ties go to the
+    // lower index), in row order; low 32 bits: rows above, high: rows equal
+    unsigned long long counts = 0, total;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const uint32_t key = key_of(s[i]);
+        if (i < mine) counts += (key > prefix ? 1ull : 0ull) | (key == prefix ? (1ull << 32) : 0ull);
+    }
+    const unsigned long long before = block_exclusive_scan(counts, &sh, total);
+    uint32_t gt = static_cast<uint32_t>(before), eq = static_cast<uint32_t>(before >> 32);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (i >= mine) continue;
+        const uint32_t key = key_of(s[i]);
+        if (key > prefix || (key == prefix && eq < need)) {
+            const uint32_t pos = gt + (eq < need ? eq : need);
+            idx[pos] = first + i;
+            rho[pos] = 1.0f;
+        }
+        gt += key > prefix;
+        eq += key == prefix;
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void select_topr_kernel(
     const float* __restrict__ sumsq, int64_t m, int64_t r, int32_t* __restrict__ idx,
     float* __restrict__ rho, int32_t* __restrict__ status) {
     __shared__ Shared sh;
-    if (reject_nonfinite(sumsq, m, r, idx, rho, status, &sh)) return;
+    if (reject_nonfinite(sumsq, m, r, idx, rho, status)) return;
     if (r == 0) return;  // nothing to select: only the status word is written
     const int tid = threadIdx.x;
 
@@ -154,26 +262,7 @@ __global__ __launch_bounds__(kThreads) void select_topr_kernel(
             if (match) atomicAdd(&sh.hist[(key >> shift) & 255u], 1u);
         }
         __syncthreads();
-        if (tid < kWave) {
-            // lane L owns digits 255-4L .. 252-4L (descending); find the digit at which the
-            // count of rows with a larger digit first reaches `need`
-            uint32_t h[4], s = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { h[e] = sh.hist[255 - 4 * tid - e]; s += h[e]; }
-            const uint32_t incl = wave_inclusive_scan(s);
-            uint32_t above = incl - s;
-            if (above < need && need <= incl) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (need <= above + h[e]) {
-                        sh.prefix = prefix | (static_cast<uint32_t>(255 - 4 * tid - e) << shift);
-                        sh.need = need - above;
-                        break;
-                    }
-                    above += h[e];
-                }
-            }
-        }
+        if (tid < kWave) find_digit(&sh, prefix, need, shift);
         __syncthreads();
         prefix = sh.prefix;
         need = sh.need;
@@ -211,7 +300,7 @@ __global__ __launch_bounds__(kThreads) void select_repl_kernel(
     float* __restrict__ rho, int32_t* __restrict__ status, unsigned long long* __restrict__ csum,
     uint32_t* __restrict__ hits) {
     __shared__ Shared sh;
-    if (reject_nonfinite(sumsq, m, r, idx, rho, status, &sh)) return;
+    if (reject_nonfinite(sumsq, m, r, idx, rho, status)) return;
     if (r == 0) return;  // nothing to select: only the status word is written
     const int tid = threadIdx.x;
 
@@ -272,6 +361,84 @@ __global__ __launch_bounds__(kThreads) void select_repl_kernel(
             }
         }
         out_carry += total;
+    }
+}
+
+// The rows in registers (see load_rows) and the prefix sums in LDS, where the draws' binary searches
+// run; otherwise the kernel above.
+template <int PER>
+__global__ __launch_bounds__(kThreads) void select_repl_reg_kernel(
+    const float* __restrict__ sumsq, int m, int64_t r, int method, int rescale, unsigned long long seed,
+    unsigned long long refresh, int32_t* __restrict__ idx, float* __restrict__ rho,
+    int32_t* __restrict__ status, uint32_t* __restrict__ ws_hits) {
+    __shared__ Shared sh;
+    // m inclusive prefix sums of the integer weights, then, while both fit in 48 KB, the m hit counters
+    extern __shared__ unsigned long long lds_csum[];
+    uint32_t* hits = PER < kRegRows ? reinterpret_cast<uint32_t*>(lds_csum + m) : ws_hits;
+    const int tid = threadIdx.x;
+    const int per = (m + kThreads - 1) / kThreads, first = tid * per;
+    float s[PER], smax = 0.f;
+    const bool bad = load_rows(sumsq, m, first, per, s);
+    if (report_nonfinite(bad, m, r, idx, rho, status)) return;
+    if (r == 0) return;  // nothing to select: only the status word is written
+    const int mine = first >= m ? 0 : (m - first < per ? m - first : per);  // rows of this thread
+    // the weights are monotone in the statistic: the largest weight is that of the largest one
+#pragma unroll
+    for (int i = 0; i < PER; ++i) smax = s[i] > smax ? s[i] : smax;
+    const double wmax = weight_of(static_cast<float>(block_max(static_cast<double>(smax), &sh)), method);
+    unsigned long long wq[PER], sum = 0, total_w;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        wq[i] = 0;
+        if (i < mine) {
+            wq[i] = quantise(weight_of(s[i], method), wmax);
+            hits[first + i] = 0;
+        }
+        sum += wq[i];
+    }
+    unsigned long long run = block_exclusive_scan(sum, &sh, total_w);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        run += wq[i];
+        if (i < mine) lds_csum[first + i] = run;
+    }
+    __threadfence_block();
+    __syncthreads();
+
+    // independent draws: first k with csum[k] > target
+    for (int64_t j = tid; j < r; j += kThreads) {
+        const unsigned long long target = __umul64hi(draw_word(seed, refresh, j), total_w);
+        int lo = 0, hi = m - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (lds_csum[mid] > target) hi = mid; else lo = mid + 1;
+        }
+        atomicAdd(&hits[lo], 1u);
+    }
+    __threadfence_block();
+    __syncthreads();
+
+    // emit rows in ascending order, each as often as it was hit
+    uint32_t h[PER], count = 0, all;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        h[i] = i < mine ? hits[first + i] : 0u;
+        count += h[i];
+    }
+    uint32_t pos = block_exclusive_scan(count, &sh, all);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (h[i] == 0) continue;
+        float rk = 1.0f;
+        if (rescale) {
+            const double q = static_cast<double>(wq[i]) / static_cast<double>(total_w);
+            rk = static_cast<float>(1.0 / sqrt(static_cast<double>(r) * q));
+        }
+        for (uint32_t e = 0; e < h[i]; ++e) {
+            idx[pos + e] = first + i;
+            rho[pos + e] = rk;
+        }
+        pos += h[i];
     }
 }
 
@@ -359,7 +526,7 @@ __global__ __launch_bounds__(kThreads) void select_norepl_kernel(
     TreeShape shape) {
     __shared__ Shared sh;
     extern __shared__ unsigned long long lds_tree[];
-    if (reject_nonfinite(sumsq, m, r, idx, rho, status, &sh)) return;
+    if (reject_nonfinite(sumsq, m, r, idx, rho, status)) return;
     if (r == 0) return;  // nothing to select: only the status word is written
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     unsigned long long* tree = kTreeInLds ? lds_tree : ws_tree;
@@ -423,6 +590,215 @@ __global__ __launch_bounds__(kThreads) void select_norepl_kernel(
     }
 }
 
+// The same draws for up to 16384 rows with fewer instructions from one draw to the next.  What
+// bounds sampling without replacement is that chain: draw j needs the weight that draw j - 1 took
+// out, one wavefront runs it, and a lone wavefront issues an instruction about every five clocks.
+// The tree above spends an LDS round trip, a ballot and an update per level (three levels at
+// m = 13824: 0.40 us per draw).  Here the weights of 64 rows form a group whose inclusive prefix sums
+// lie in LDS, and the EXCLUSIVE prefix sums over the groups (at most 256) stay in E registers per lane:
+//   group   g = (number of groups whose prefix is <= target) - 1: E compares and bit counts
+//   row     f = number of rows of the group whose prefix is <= target - prefix(g): one compare
+//   weight  difference of neighbouring prefixes, formed by a lane shift
+//   update  the lanes that failed a compare are the ones that lose the weight
+// and the drawn rows are collected in a register and put into a bit map 64 at a time.
+//
+// While the total weight is below 2^53 (always for fewer than 8192 rows, and for more unless most
+// weigh as much as the heaviest) every prefix and difference is an integer that a double holds
+// exactly, and 64-bit integer steps (two instructions and a carry each, fifteen for the high
+// product) become single double ones.  Only the target x S / 2^64 is rounded: the double product
+// is within 2 of it, so unless a prefix lies within 4 (checked against every prefix compared) each
+// comparison falls as with the exact target floor(x S / 2^64); otherwise that is computed and used.
+// The rows drawn are those of the sequential integer definition in every case.
+// (Guessing the next draw's group a draw ahead, to hide the one LDS read, costs more instructions
+// than the read takes: 324 against 207 us at 4096 rows.)
+// Measured, 1024 draws from 13824 rows: 420 -> 263 us; 1024 from 4096: 286 -> 165 us.
+constexpr int kFlatMaxE = 4;
+constexpr int64_t kFlatMaxRows = 64 * kWave * kFlatMaxE;
+
+// v of the lane below, 0 in lane 0
+__device__ __forceinline__ unsigned long long from_lane_below(unsigned long long v) {
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x138, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(v >> 32), 0x138, 0xf, 0xf, true);
+    return (static_cast<unsigned long long>(hi) << 32) | lo;
+}
+
+__device__ __forceinline__ double from_lane_below(double v) {
+    return __longlong_as_double(static_cast<long long>(from_lane_below(static_cast<unsigned long long>(__double_as_longlong(v)))));
+}
+__device__ __forceinline__ unsigned long long read_lane(unsigned long long v, int l) { return read_lane64(v, l); }
+__device__ __forceinline__ double read_lane(double v, int l) {
+    return __longlong_as_double(static_cast<long long>(read_lane64(static_cast<unsigned long long>(__double_as_longlong(v)), l)));
+}
+
+// Where a draw's target falls.  V is the type the prefixes are held in; gpre: a copy of pex in LDS
+// (with four registers per lane, picking the group's prefix out of them takes longer than
+// reading it beside the rows; with two it does not).  near: some boundary of the group lies within 4 of the target, the
+// only ones a target off by 2 could be on the wrong side of (a target put into the wrong group is
+// next to that group's edge).
+template <typename V, int E>
+struct Located {
+    int g, f;
+    V cur;
+    bool upto[E], below, near;
+};
+template <int E, typename V>
+__device__ __forceinline__ Located<V, E> locate(const V (&pex)[E], const V* gpre, const V* leaf, V target,
+                                                int groups, int lane) {
+    Located<V, E> q;
+    int n = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        q.upto[e] = pex[e] <= target;
+        n += __popcll(__ballot(q.upto[e]));
+    }
+    q.g = n < groups ? n - 1 : groups - 1;  // n >= 1: the first group's prefix is 0
+    q.cur = leaf[q.g * kWave + lane];
+    V before;
+    if (E > 2) {
+        before = gpre[q.g];
+    } else {
+        before = pex[0];
+        if (E > 1 && q.g >= kWave) before = pex[E - 1];
+        before = read_lane(before, q.g & (kWave - 1));
+    }
+    const V t = target - before;
+    q.below = q.cur <= t;
+    if constexpr (static_cast<V>(0.5) != static_cast<V>(0)) q.near = fmin(fabs(q.cur - t), t) < 4.0;
+    else q.near = false;
+    q.f = __popcll(__ballot(q.below));
+    return q;
+}
+// Takes the drawn row's weight out of its group, the groups after it and the total.
+template <int E, typename V>
+__device__ __forceinline__ void take_out(const Located<V, E>& q, V (&pex)[E], V* gpre, V* leaf, V& left, int lane) {
+    const V w = read_lane(q.cur - from_lane_below(q.cur), q.f);
+    leaf[q.g * kWave + lane] = q.cur - (q.below ? V(0) : w);  // the drawn row and those after it
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        pex[e] -= q.upto[e] ? V(0) : w;
+        if (E > 2) gpre[e * kWave + lane] = pex[e];
+    }
+    left -= w;
+}
+
+template <int E>
+__global__ __launch_bounds__(kThreads) void select_norepl_flat_kernel(
+    const float* __restrict__ sumsq, int m, int r, int method, int rescale, unsigned long long seed,
+    unsigned long long refresh, int32_t* __restrict__ idx, float* __restrict__ rho,
+    int32_t* __restrict__ status) {
+    constexpr int kGroupsPerWave = E * kWave / kWaves;
+    __shared__ Shared sh;
+    __shared__ unsigned long long gsum[E * kWave];
+    __shared__ uint32_t chosen[E * kWave * 2];  // one bit per row
+    extern __shared__ unsigned long long leaf[];  // [groups][64] inclusive prefix sums, or their doubles
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int groups = (m + kWave - 1) / kWave;
+
+    float s[kGroupsPerWave], smax = 0.f;
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < kGroupsPerWave; ++i) {
+        const int k = (wave + i * kWaves) * kWave + lane;
+        s[i] = k < m ? sumsq[k] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < kGroupsPerWave; ++i) {
+        bad |= is_bad(s[i]);
+        smax = s[i] > smax ? s[i] : smax;
+    }
+    if (report_nonfinite(bad, m, r, idx, rho, status)) return;
+    if (r == 0) return;  // nothing to select: only the status word is written
+    // the weights are monotone in the statistic: the largest weight is that of the largest one
+    const double wmax = weight_of(static_cast<float>(block_max(static_cast<double>(smax), &sh)), method);
+    unsigned long long prefix[kGroupsPerWave];
+#pragma unroll
+    for (int i = 0; i < kGroupsPerWave; ++i) {
+        const int g = wave + i * kWaves, k = g * kWave + lane;
+        prefix[i] = 0ull;  // groups that do not exist weigh nothing
+        if (g < groups) prefix[i] = wave_inclusive_scan(k < m ? quantise(weight_of(s[i], method), wmax) : 0ull);
+        if (lane == kWave - 1) gsum[g] = prefix[i];
+    }
+    for (int e = tid; e < E * kWave * 2; e += kThreads) chosen[e] = 0;
+    __syncthreads();
+    unsigned long long pex[E], total_w = 0;  // pex: weight before group e * 64 + lane
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const unsigned long long own = gsum[e * kWave + lane], incl = wave_inclusive_scan(own);
+        pex[e] = total_w + incl - own;
+        total_w += read_lane64(incl, kWave - 1);
+    }
+    const bool in_doubles = total_w < (1ull << 53);
+#pragma unroll
+    for (int i = 0; i < kGroupsPerWave; ++i) {
+        const int g = wave + i * kWaves;
+        if (g < groups)
+            leaf[g * kWave + lane] = in_doubles
+                ? static_cast<unsigned long long>(__double_as_longlong(static_cast<double>(prefix[i]))) : prefix[i];
+    }
+    __syncthreads();
+
+    if (wave == 0) {
+        double* dleaf = reinterpret_cast<double*>(leaf);
+        double* dgpre = reinterpret_cast<double*>(gsum);  // the group sums have been used up
+        double dpex[E], dleft = static_cast<double>(total_w);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            dpex[e] = static_cast<double>(pex[e]);
+            if (in_doubles) dgpre[e * kWave + lane] = dpex[e];
+            else gsum[e * kWave + lane] = pex[e];
+        }
+        unsigned long long left = total_w;
+        for (int j0 = 0; j0 < r; j0 += kWave) {
+            const unsigned long long words = draw_word(seed, refresh, j0 + lane);
+            const double unit = static_cast<double>(words) * 0x1p-64;
+            const int count = __builtin_amdgcn_readfirstlane(r - j0 < kWave ? r - j0 : kWave);
+            int rows = 0;  // lane jj: the row of draw j0 + jj
+            if (in_doubles) {
+                for (int jj = 0; jj < count; ++jj) {
+                    auto q = locate<E>(dpex, dgpre, dleaf, dleft * read_lane(unit, jj), groups, lane);
+                    int row = q.g * kWave + q.f;
+                    if (!__ballot(q.near)) {
+                        take_out<E>(q, dpex, dgpre, dleaf, dleft, lane);
+                    } else {  // too close to a boundary to call: the exact target
+                        const unsigned long long exact =
+                            __umul64hi(read_lane64(words, jj), static_cast<unsigned long long>(dleft));
+                        auto z = locate<E>(dpex, dgpre, dleaf, static_cast<double>(exact), groups, lane);
+                        take_out<E>(z, dpex, dgpre, dleaf, dleft, lane);
+                        row = z.g * kWave + z.f;
+                    }
+                    rows = lane == jj ? row : rows;
+                }
+            } else {
+                for (int jj = 0; jj < count; ++jj) {
+                    auto q = locate<E>(pex, gsum, leaf, __umul64hi(read_lane64(words, jj), left), groups, lane);
+                    take_out<E>(q, pex, gsum, leaf, left, lane);
+                    rows = lane == jj ? q.g * kWave + q.f : rows;
+                }
+            }
+            if (lane < count) atomicOr(&chosen[rows >> 5], 1u << (rows & 31));
+        }
+    }
+    __syncthreads();
+
+    // emit the chosen rows in ascending order: every thread owns 32 consecutive rows
+    static_assert(E * kWave * 2 <= kThreads, "one word of the bit map per thread");
+    uint32_t bits = tid < E * kWave * 2 ? chosen[tid] : 0u, all;
+    uint32_t pos = block_exclusive_scan(static_cast<uint32_t>(__popc(bits)), &sh, all);
+    while (bits) {
+        const int k = tid * 32 + __ffs(bits) - 1;
+        bits &= bits - 1;
+        float rk = 1.0f;
+        if (rescale) {
+            const unsigned long long wq = quantise(weight_of(sumsq[k], method), wmax);
+            const double q = static_cast<double>(wq) / static_cast<double>(total_w);
+            rk = static_cast<float>(1.0 / sqrt(static_cast<double>(r) * q));
+        }
+        idx[pos] = k;
+        rho[pos] = rk;
+        ++pos;
+    }
+}
+
 TreeShape tree_shape(int64_t m) {
     TreeShape s;
     s.levels = 0;
@@ -453,12 +829,34 @@ size_t select_workspace_bytes(int64_t m, int64_t r, grass_method method, int rep
     return kHeaderBytes + tree_bytes(tree_shape(m));
 }
 
+template <int E>
+static grass_status launch_flat(const float* sumsq, int64_t m, int64_t r, grass_method method, int rescale,
+                                uint64_t seed, uint64_t refresh_id, int32_t* idx, float* rho,
+                                int32_t* status, hipStream_t s) {
+    const size_t bytes = static_cast<size_t>((m + kWave - 1) / kWave) * kWave * sizeof(unsigned long long);
+    if (bytes > 48 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void*>(select_norepl_flat_kernel<E>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(kFlatMaxRows * sizeof(unsigned long long))) != hipSuccess)
+        return GRASS_ERR_DEVICE;
+    select_norepl_flat_kernel<E><<<1, kThreads, bytes, s>>>(sumsq, static_cast<int>(m), static_cast<int>(r),
+                                                            method, rescale, seed, refresh_id, idx, rho, status);
+    return launch_status();
+}
+
 // `status`: the device status word; `body`: select_workspace_bytes(...) - kHeaderBytes bytes of
 // device scratch (prefix sums and hit counters, or the tree), 256-byte aligned.
 static grass_status launch_select_kernels(const float* sumsq, int64_t m, int64_t r,
                                           grass_method method, int replacement, grass_scale scale,
                                           uint64_t seed, uint64_t refresh_id, int32_t* idx,
                                           float* rho, int32_t* status, char* body, hipStream_t s) {
+    if (method == GRASS_SEL_TOPR && m <= kRegMaxRows) {
+        const int mi = static_cast<int>(m), ri = static_cast<int>(r);
+        if (m <= kThreads) select_topr_reg_kernel<1><<<1, kThreads, 0, s>>>(sumsq, mi, ri, idx, rho, status);
+        else if (m <= kRegMaxRows / 4) select_topr_reg_kernel<kRegRows / 4><<<1, kThreads, 0, s>>>(sumsq, mi, ri, idx, rho, status);
+        else select_topr_reg_kernel<kRegRows><<<1, kThreads, 0, s>>>(sumsq, mi, ri, idx, rho, status);
+        return launch_status();
+    }
     if (method == GRASS_SEL_TOPR) {
         select_topr_kernel<<<1, kThreads, 0, s>>>(sumsq, m, r, idx, rho, status);
         return launch_status();
@@ -468,9 +866,34 @@ static grass_status launch_select_kernels(const float* sumsq, int64_t m, int64_t
     if (replacement) {
         unsigned long long* csum = reinterpret_cast<unsigned long long*>(body);
         uint32_t* hits = reinterpret_cast<uint32_t*>(body + static_cast<size_t>(m) * 8);
+        if (m <= kRegMaxRows) {
+            const size_t bytes = static_cast<size_t>(m) * sizeof(unsigned long long);
+            if (m <= kThreads) {
+                select_repl_reg_kernel<1><<<1, kThreads, bytes + m * 4, s>>>(
+                    sumsq, static_cast<int>(m), r, method, rescale, seed, refresh_id, idx, rho, status, hits);
+                return launch_status();
+            }
+            if (m <= kRegMaxRows / 4) {  // at most 48 KB of LDS
+                select_repl_reg_kernel<kRegRows / 4><<<1, kThreads, bytes + m * 4, s>>>(
+                    sumsq, static_cast<int>(m), r, method, rescale, seed, refresh_id, idx, rho, status, hits);
+                return launch_status();
+            }
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(select_repl_reg_kernel<kRegRows>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    static_cast<int>(kRegMaxRows * sizeof(unsigned long long))) != hipSuccess)
+                return GRASS_ERR_DEVICE;
+            select_repl_reg_kernel<kRegRows><<<1, kThreads, bytes, s>>>(
+                sumsq, static_cast<int>(m), r, method, rescale, seed, refresh_id, idx, rho, status, hits);
+            return launch_status();
+        }
         select_repl_kernel<<<1, kThreads, 0, s>>>(sumsq, m, r, method, rescale, seed, refresh_id,
                                                   idx, rho, status, csum, hits);
         return launch_status();
+    }
+    if (m > 0 && m <= kFlatMaxRows) {
+        return m <= 64 * kWave ? launch_flat<1>(sumsq, m, r, method, rescale, seed, refresh_id, idx, rho, status, s)
+               : m <= 128 * kWave ? launch_flat<2>(sumsq, m, r, method, rescale, seed, refresh_id, idx, rho, status, s)
+                                  : launch_flat<4>(sumsq, m, r, method, rescale, seed, refresh_id, idx, rho, status, s);
     }
     const TreeShape shape = tree_shape(m);
     const size_t bytes = tree_bytes(shape);
