@@ -31,6 +31,7 @@
 #include "gemm_small.hpp"
 #include "gemm_large.hpp"
 #include "gemm_unaligned.hpp"
+#include "gemm_mid.hpp"
 #include "gemm_gather_narrow.hpp"
 #include "gemm_f32.hpp"
 #include "reduce_kernels.hpp"
@@ -40,14 +41,24 @@ namespace {
 
 // ------------------------------------------------------------------------------ host side
 using Cfg128 = TileCfg<128, 128, 64, 2, 2>;
-enum TileId { kTile128 = 0, kTile256 = 1 };
-struct Shape256 {
-    static constexpr int BM = kFastBM, BN = kFastBN, BK = kFastBK, kWgPerCu = 1;
-};
+enum TileId { kTile128 = 0, kTile256 = 1, kTileMid = 2 };  // mid: 128 x 256
+constexpr int rows_log2(TileId id) { return id == kTile256 ? 8 : 7; }
+constexpr int cols_log2(TileId id) { return id == kTile128 ? 7 : 8; }
+constexpr int tile_rows(TileId id) { return 1 << rows_log2(id); }
+constexpr int tile_k(TileId id) { return id == kTile128 ? Cfg128::BK : kFastBK; }
+static_assert(kFastBM == 256 && kFastBN == 256 && kMidBM == 128 && kMidBN == 256 && kMidBK == kFastBK, "tile shapes");
 
+// How the token dimension is divided: `splits` slices of `tokens` tokens (the last one shorter), and,
+// with `tail`, the tokens past the last whole K tile of 32 as one more slice.
+struct KSplit {
+    int splits;
+    int64_t tokens;
+    bool tail;
+    int slices() const { return splits + (tail ? 1 : 0); }
+};
 struct Plan {
     int64_t Mp, Np, rp;  // padded rows / cols of the partial buffer; packed panel width
-    int tiles_m, tiles_n, splits, ktiles_per_split;
+    int tiles_m, tiles_n;
     size_t pack_bytes, partial_bytes;
 };
 
@@ -57,16 +68,21 @@ size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 constexpr int64_t kCachedSliceBytes = int64_t{16} << 20;
 constexpr int kManySlices = 8;  // above this the reduction spreads the slices over wavefronts
 
-template <typename Cfg>
-Plan make_plan(int64_t T, int64_t rows, int64_t n, bool needs_pack) {
-    Plan p;
-    p.tiles_m = static_cast<int>((rows + Cfg::BM - 1) / Cfg::BM);
-    p.tiles_n = static_cast<int>((n + Cfg::BN - 1) / Cfg::BN);
-    p.Mp = static_cast<int64_t>(p.tiles_m) * Cfg::BM;
-    p.Np = static_cast<int64_t>(p.tiles_n) * Cfg::BN;
-    p.rp = p.Mp;
-    const int64_t ktiles = (T + Cfg::BK - 1) / Cfg::BK;
-    const int64_t tiles = static_cast<int64_t>(p.tiles_m) * p.tiles_n;
+// The square tile that a product's K slices are planned for: 256 x 256 unless it wastes much of
+// itself on padding.  (The kernel that runs may use another tile, see choose_tile: a slice's sums are
+// taken in the same order whatever the tile, so results depend on the slices alone.)
+TileId planned_tile(int64_t rows, int64_t n) {
+    if (const int forced = test_option(GRASS_TEST_GEMM_TILE)) return forced == 256 ? kTile256 : kTile128;
+    if (rows < 1 || n < 1) return kTile128;
+    const double padded = static_cast<double>((rows + 255) / 256 * 256) * ((n + 255) / 256 * 256);
+    return padded <= 1.35 * static_cast<double>(rows) * static_cast<double>(n) ? kTile256 : kTile128;
+}
+
+KSplit split_k(TileId planned, int64_t T, int64_t rows, int64_t n) {
+    const int edge = tile_rows(planned), bk = tile_k(planned);
+    const int64_t tm = (rows + edge - 1) >> rows_log2(planned), tn = (n + edge - 1) >> rows_log2(planned);
+    const int64_t tiles = tm * tn;
+    const int64_t ktiles = planned == kTile256 ? T / kFastBK : (T + Cfg128::BK - 1) / Cfg128::BK;
     // Split K so that the workgroups fill whole rounds of the machine (256 CUs x workgroups
     // per CU) without paying too much for the partial tiles every slice adds.  In units of
     // the GEMM's time at full occupancy, c slices cost about 1 / fill(c) + c * k / T.  For
@@ -78,25 +94,38 @@ Plan make_plan(int64_t T, int64_t rows, int64_t n, bool needs_pack) {
     // (T = 65536): 2400 for the large tile (1024 x 1024 at r = 256: 42 slices, 81 us per step,
     // against 64 slices, 92 us) and 800 for the small one (512 x 512 at r = 128: 94 slices).
     // Each slice keeps at least 8 K tiles.
-    const int64_t slots = 256 * Cfg::kWgPerCu;
+    const int slots_log2 = planned == kTile256 ? 8 : 9;
     int64_t smax = ktiles / 8 > 0 ? (ktiles / 8 < 128 ? ktiles / 8 : 128) : 1;
     if (const int cap = test_option(GRASS_TEST_MAX_K_SLICES)) smax = cap > 0 && cap < smax ? cap : smax;
-    const bool cached = p.Mp * p.Np * 4 <= kCachedSliceBytes;
-    const double k = cached ? (Cfg::BM == 256 ? 2400.0 : 800.0) : 1400.0;
+    const bool cached = tm * edge * tn * edge * 4 <= kCachedSliceBytes;
+    const double k = cached ? (planned == kTile256 ? 2400.0 : 800.0) : 1400.0;
     const double per_slice = k / static_cast<double>(T > 0 ? T : 1);
     int64_t s = 1;
     double best = 1e300;
     for (int64_t c = 1; c <= smax && tiles > 0; ++c) {
-        const int64_t wgs = tiles * c, rounds = (wgs + slots - 1) / slots;
-        const double cost = static_cast<double>(rounds * slots) / static_cast<double>(wgs) + per_slice * c;
+        const int64_t wgs = tiles * c, filled = ((wgs - 1) >> slots_log2) + 1;
+        const double cost = static_cast<double>(filled << slots_log2) / static_cast<double>(wgs) + per_slice * c;
         if (cost < best - 1e-12) { best = cost; s = c; }
     }
-    p.ktiles_per_split = static_cast<int>((ktiles + s - 1) / s);
-    if (p.ktiles_per_split < 1) p.ktiles_per_split = 1;
-    p.splits = static_cast<int>((ktiles + p.ktiles_per_split - 1) / p.ktiles_per_split);
-    if (p.splits < 1) p.splits = 1;
-    p.pack_bytes = needs_pack ? round_up(static_cast<size_t>(T) * p.rp * 2, 256) : 0;
-    p.partial_bytes = static_cast<size_t>(p.splits) * p.Mp * p.Np * 4;
+    int64_t per = (ktiles + s - 1) / s;
+    if (per < 1) per = 1;
+    KSplit q;
+    q.tokens = per * bk;
+    q.splits = static_cast<int>((ktiles + per - 1) / per);
+    if (q.splits < 1) q.splits = 1;
+    q.tail = planned == kTile256 && T % bk != 0;
+    return q;
+}
+
+Plan make_plan(TileId id, const KSplit& k, int64_t T, int64_t rows, int64_t n, bool pack) {
+    Plan p;
+    p.tiles_m = static_cast<int>((rows + tile_rows(id) - 1) >> rows_log2(id));
+    p.tiles_n = static_cast<int>((n + (1 << cols_log2(id)) - 1) >> cols_log2(id));
+    p.Mp = static_cast<int64_t>(p.tiles_m) << rows_log2(id);
+    p.Np = static_cast<int64_t>(p.tiles_n) << cols_log2(id);
+    p.rp = p.Mp;
+    p.pack_bytes = pack ? round_up(static_cast<size_t>(T) * p.rp * 2, 256) : 0;
+    p.partial_bytes = static_cast<size_t>(k.slices()) * p.Mp * p.Np * 4;
     return p;
 }
 
@@ -112,8 +141,9 @@ bool needs_pack(grass_dy_layout layout, bool gathered) {
 struct Copies { bool a, b; };
 // Measured: the any-alignment forms take 10 - 20 % longer than the aligned ones (1.3 PFLOP/s with
 // the large tile, 0.45 with the small one), a copy moves 4 bytes per value at 5.2 TB/s and costs a
-// launch; in the large tile the register route takes 5 us more to fill and drain (2746 x 1509,
-// r = 686, T = 448: 38.6 us in place, 35.1 with the copy).  2048 x 5461, r = 512, T = 65536:
+// launch; in the large tile the register route takes about 7 us more to fill and drain (2746 x 1509,
+// r = 686, T = 448: 38.6 us in place, 35.1 with the copy), in the small one 4 (9576 x 371, r = 1024,
+// T = 1472: 40.0 and 38.6).  2048 x 5461, r = 512, T = 65536:
 // 429 us per step in place, 617 with the copy; full gradient of 2807 x 6144, T = 5248: 224 us in
 // place, 209 with the copy.  dY stored m x T is read row-wise by the aligned large tile without
 // any pack, which the copy keeps possible.
@@ -122,8 +152,8 @@ Copies choose_copies(TileId tile, int64_t T, int64_t rows, int64_t n, grass_dy_l
     if (T < 1 || !(a_odd || b_odd)) return Copies{false, false};
     if (layout == GRASS_DY_MxT && tile == kTile256 && T % kFastBK == 0) return Copies{false, b_odd};
     const double t = static_cast<double>(T);
-    const double in_place = tile == kTile256 ? 5e-6 + 0.15 * 2.0 * t * rows * n / 1.3e15
-                                             : 0.15 * 2.0 * t * rows * n / 0.45e15;
+    const double in_place = tile == kTile256 ? 7e-6 + 0.15 * 2.0 * t * rows * n / 1.3e15
+                                             : 4e-6 + 0.15 * 2.0 * t * rows * n / 0.45e15;
     const double copied = (a_odd ? 4.0 * t * rows / 5.2e12 + 3e-6 : 0.0) + (b_odd ? 4.0 * t * n / 5.2e12 + 3e-6 : 0.0);
     return copied < in_place ? Copies{a_odd, b_odd} : Copies{false, false};
 }
@@ -131,18 +161,40 @@ size_t aligned_x_bytes(int64_t T, int64_t n) {
     return round_up(static_cast<size_t>(T) * ((n + 7) / 8 * 8) * 2, 256);
 }
 
-// The 256 x 256 tile halves the LDS traffic per flop and is the faster kernel whenever it
-// does not waste much of itself on padding; narrow problems (r = 128, say) keep 128 x 128.
-TileId choose_tile(int64_t T, int64_t rows, int64_t n) {
-    if (const int forced = test_option(GRASS_TEST_GEMM_TILE)) return forced == 256 ? kTile256 : kTile128;
-    (void)T;
-    if (rows < 1 || n < 1) return kTile128;
-    const double padded = static_cast<double>((rows + 255) / 256 * 256) * ((n + 255) / 256 * 256);
-    return padded <= 1.35 * static_cast<double>(rows) * static_cast<double>(n) ? kTile256 : kTile128;
-}
-
-Plan plan_for(TileId id, int64_t T, int64_t rows, int64_t n, bool pack) {
-    return id == kTile256 ? make_plan<Shape256>(T, rows, n, pack) : make_plan<Cfg128>(T, rows, n, pack);
+// The tile a product with these K slices runs with: the one whose estimated time is smallest.  Rates
+// are those reached with full tiles and a full machine (any-alignment forms: 13 % less); slices
+// of partial tiles cost 3e-12 s per output element (written, then read by the reduction), 2.2e-12
+// while they stay in the caches; two workgroups of the mid tile share a compute unit, which
+// gains 15 %; dY stored m x T has to be packed (transposed) for all but the large tile, which
+// gathers its rows itself.
+// Measured per step, planned square tile -> the one chosen here:
+//   2048 x 2048, r = 300, T = 8192    45 -> 37 us (mid)     4096 x 4096, r = 1024, T = 2048  54 -> 51 (mid)
+//   1024 x 2048, r = 128, T = 131072 191 -> 170 (mid)       1024 x 4096, r = 600, T = 4096   37 -> 31 (mid)
+//   1456 x 1800, r = 364, T = 128866 385 -> 335 (256)       1560 x 6416, r = 390, T = 75136 800 -> 723 (mid)
+TileId choose_tile(TileId planned, const KSplit& k, int64_t T, int64_t rows, int64_t n, bool rows_form,
+                   grass_dy_layout layout, bool aligned) {
+    if (const int forced = test_option(GRASS_TEST_GEMM_TILE))
+        return forced == 192 && aligned ? kTileMid : planned;
+    TileId best = planned;
+    double least = 1e300;
+    for (const TileId id : {kTile256, kTileMid, kTile128}) {
+        if (id == kTileMid && !aligned) continue;
+        if (id == kTile128 && planned == kTile256) continue;  // its K tiles are twice as long
+        const Plan p = make_plan(id, k, T, rows, n, false);
+        const double outputs = static_cast<double>(p.Mp) * static_cast<double>(p.Np);
+        const double wgs = static_cast<double>(p.tiles_m) * p.tiles_n * k.splits;
+        const double slots = id == kTile128 ? 512.0 : 256.0;
+        double rounds = ceil(wgs / slots);
+        if (id == kTileMid && rounds > 1) rounds *= 0.85;
+        double rate = id == kTile256 ? 1.4e15 : id == kTileMid ? 0.9e15 : 0.6e15;
+        if (!aligned) rate *= 0.87;
+        double t = 2.0 * static_cast<double>(T) * outputs / rate * (rounds * slots / wgs) +
+                   (outputs * 4 <= kCachedSliceBytes ? 2.2e-12 : 3e-12) * outputs * k.slices();
+        if (!aligned && id == kTile256) t += 7e-6;  // the register route takes longer to fill and drain
+        if (layout == GRASS_DY_MxT && !(rows_form && id == kTile256)) t += 4.0 * static_cast<double>(T) * p.Mp / 4e12 + 4e-6;
+        if (t < least) { least = t; best = id; }
+    }
+    return best;
 }
 
 // ---- narrow layers: the gather inside the GEMM (gemm_gather_narrow.hpp)
@@ -260,6 +312,20 @@ void launch_f32_kernel(const F32Args& a, bool vec_a, bool vec_b, hipStream_t s, 
     else launch_stamped(tn_gemm_f32_mfma_kernel<BM, false, false>, grid, block, 0, s, e0, e1, a);
 }
 
+// More than 64 KB of dynamic LDS has to be asked for, per kernel and device; the attribute sticks for
+// the life of the process, so it is set once (the only state the library keeps: a flag per device
+// and kernel, set with release order after the attribute call has returned; two first callers
+// both make the call).  `which`: a number per kernel.
+hipError_t raise_lds_limit(const void* kernel, int bytes, int which) {
+    static std::atomic<bool> raised[2][64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
+    if (dev >= 0 && dev < 64 && raised[which][dev].load(std::memory_order_acquire)) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess && dev >= 0 && dev < 64) raised[which][dev].store(true, std::memory_order_release);
+    return e;
+}
+
 template <typename Cfg, bool kDense, bool kAnyAlign>
 hipError_t launch_gemm_kernel(const GemmArgs& g, unsigned grid, hipStream_t s) {
     auto kernel = tn_gemm_bf16_kernel<Cfg, kDense, kAnyAlign>;
@@ -329,6 +395,7 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
         g.Mp = static_cast<int64_t>(g.tiles_m) * kFastBM;
         g.Np = static_cast<int64_t>(g.tiles_n) * kFastBN;
         g.splits = 1;
+        g.tail = 0;
         g.ktiles_per_split = static_cast<int>(T / kFastBK);
         g.a_rows = nullptr;
         const int64_t items = static_cast<int64_t>(g.tiles_m) * g.tiles_n;
@@ -353,15 +420,43 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
                             grass_dy_layout layout, bool gathered) {
     if (dt == GRASS_F32) return f32_partial_bytes(T, &mrows, 1, n, false);
-    // the launcher may fall back to the small tile when the large one cannot be used
-    size_t need = 0;
-    for (const TileId id : {kTile128, kTile256}) {
-        const Copies copy = choose_copies(id, T, mrows, n, layout, gathered);
-        const Plan p = plan_for(id, T, mrows, n, needs_pack(layout, gathered) || copy.a);
-        const size_t bytes = p.pack_bytes + round_up(p.partial_bytes, 256) + (copy.b ? aligned_x_bytes(T, n) : 0);
-        need = bytes > need ? bytes : need;
+    // The launcher may plan for the small tile where the large one cannot be used, and run either plan
+    // with any tile: room for the larger number of slices and the widest padding.
+    const KSplit k1 = split_k(kTile128, T, mrows, n), k2 = split_k(kTile256, T, mrows, n);
+    const int64_t slices = k1.slices() > k2.slices() ? k1.slices() : k2.slices();
+    const int64_t Mp = (mrows + 255) / 256 * 256, Np = (n + 255) / 256 * 256;
+    bool pack = needs_pack(layout, gathered), copy_x = false;
+    if (n % 8 != 0 || (!pack && mrows % 8 != 0)) {
+        for (const TileId id : {kTile128, kTile256, kTileMid}) {
+            const Copies copy = choose_copies(id, T, mrows, n, layout, gathered);
+            pack = pack || copy.a;
+            copy_x = copy_x || copy.b;
+        }
     }
-    return need + 256;
+    return (pack ? round_up(static_cast<size_t>(T) * Mp * 2, 256) : 0) + static_cast<size_t>(slices) * Mp * Np * 4 +
+           (copy_x ? aligned_x_bytes(T, n) : 0) + 256;
+}
+
+// Bytes the narrow kernel's partial tiles may take: what a packed product with either square tile
+// and one spare slice would (gemm_workspace_bytes asks for at least as much).
+size_t narrow_cap_bytes(int64_t T, int64_t rows, int64_t n) {
+    size_t cap = 0;
+    for (const TileId id : {kTile128, kTile256}) {
+        const KSplit k = split_k(id, T, rows, n);
+        const Plan p = make_plan(id, k, T, rows, n, true);
+        const size_t bytes = p.pack_bytes + static_cast<size_t>(k.splits + 1) * p.Mp * p.Np * 4;
+        cap = bytes > cap ? bytes : cap;
+    }
+    return cap;
+}
+
+// The row-gathering kernel takes K tiles in pairs: every workgroup gets whole pairs.
+static KSplit paired(KSplit k, int64_t T) {
+    if (k.tokens % (2 * kFastBK) != 0) {
+        k.tokens += kFastBK;
+        k.splits = static_cast<int>((T + k.tokens - 1) / k.tokens);
+    }
+    return k;
 }
 
 void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n, grass_dtype dt,
@@ -376,22 +471,19 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
     }
     if (m > 0 && count >= 1 && narrow_shape_ok(T, n, dt, layout) &&
         narrow_set_ok((rows / count + 7) / 8 * 8, m)) {  // the sets taken to be of equal size
-        const size_t cap = gemm_workspace_bytes(T, rows, n, dt, layout, true) - 256;
+        const size_t cap = narrow_cap_bytes(T, rows, n);
         const NarrowPlan p = narrow_plan(T, n, count, rows, m * count + n, cap);
         *tile = 0;
         *k_slices = p.splits;
         return;
     }
-    const TileId id = T >= kFastBK && rows >= 8 && n >= 8 ? choose_tile(T, rows, n) : kTile128;
-    Plan p = plan_for(id, T, rows, n, needs_pack(layout, true));
+    const TileId id = T >= kFastBK && rows >= 8 && n >= 8 ? planned_tile(rows, n) : kTile128;
+    KSplit k = split_k(id, T, rows, n);
     if (id == kTile256 && layout == GRASS_DY_MxT && T % (2 * kFastBK) == 0 &&
-        test_option(GRASS_TEST_PACK_MXT) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0 &&
-        p.ktiles_per_split % 2 != 0) {  // the row-gathering kernel takes K tiles in pairs
-        ++p.ktiles_per_split;
-        p.splits = static_cast<int>((T / kFastBK + p.ktiles_per_split - 1) / p.ktiles_per_split);
-    }
-    *tile = id == kTile256 ? 256 : 128;
-    *k_slices = p.splits;
+        test_option(GRASS_TEST_PACK_MXT) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0)
+        k = paired(k, T);
+    *tile = tile_rows(id);
+    *k_slices = k.slices();
 }
 
 size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int64_t n,
@@ -555,7 +647,8 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         // One panel pays off while a slice of partial tiles of the joint problem still fits
         // the caches (fewer, fuller launches).  Beyond that every set fills the machine on its
         // own and the joint partial tiles would only spill to HBM: run the sets one by one.
-        const Plan joint = plan_for(choose_tile(T, total, n), T, total, n, pack);
+        const TileId square = planned_tile(total, n);
+        const Plan joint = make_plan(square, split_k(square, T, total, n), T, total, n, pack);
         if (joint.Mp * joint.Np * 4 > kCachedSliceBytes) {
             for (int i = 0; i < count; ++i) {
                 // (timing hooks: the first set's GEMM and the last set's tail)
@@ -589,8 +682,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
             off += static_cast<int>((seg[i].rows + 7) / 8 * 8);
             in_cols += seg[i].src_rows;
         }
-        // the workspace every caller has been asked for holds at least this much (same formula)
-        const size_t cap = gemm_workspace_bytes(T, total, n, dt, layout, true) - 256;
+        const size_t cap = narrow_cap_bytes(T, total, n);
         const NarrowPlan np = narrow_plan(T, n, count, off, in_cols, cap);
         a.count = count;
         a.X = static_cast<const uint16_t*>(X);
@@ -625,46 +717,52 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     }
     const void* dY0 = seg[0].dY;  // read directly by the GEMM only when nothing is packed
     const int64_t ldy0 = seg[0].ldy;
-    TileId tile = choose_tile(T, total, n);
-    {   // per-lane byte offsets inside one K tile are kept in 32 bits
-        const int64_t lda_eff = pack ? (total + kFastBM - 1) / kFastBM * kFastBM : ldy0;
-        const bool off_ok = (kFastBK + 1) * lda_eff * 2 < (int64_t{1} << 32) &&
-                            (kFastBK + 1) * ldx * 2 < (int64_t{1} << 32);
-        if (!(off_ok && T >= kFastBK && total >= 8 && n >= 8)) tile = kTile128;
+    // K slices: planned for the large tile where it can be used at all
+    TileId planned = planned_tile(total, n);
+    bool sizes;  // what the 256-wide kernels ask for: per-lane byte offsets inside a K tile in 32 bits
+    {
+        const int64_t panel_ld = (total + kFastBM - 1) / kFastBM * kFastBM;
+        const int64_t lda_max = pack || panel_ld > ldy0 ? panel_ld : ldy0;
+        sizes = (kFastBK + 1) * lda_max * 2 < (int64_t{1} << 32) &&
+                (kFastBK + 1) * ldx * 2 < (int64_t{1} << 32) && T >= kFastBK && total >= 8 && n >= 8;
+        const bool a_ok = pack || total % 8 != 0 || (aligned_to(dY0, 16) && ldy0 % 8 == 0);
+        const bool b_ok = n % 8 != 0 ? aligned_to(X, 4) : aligned_to(X, 16) && ldx % 8 == 0;
+        if (!(a_ok && b_ok && sizes)) planned = kTile128;
     }
+    KSplit ks = split_k(planned, T, total, n);
+    // dY stored m x T: the selected rows are contiguous, so the large-tile kernel can gather them
+    // itself (no packing pass) when K is whole tiles and its 32-bit row offsets reach every row
+    const int64_t src_rows = seg[0].idx ? seg[0].src_rows : total;
+    const bool rows_ok = layout == GRASS_DY_MxT && count == 1 && sizes && T % kFastBK == 0 &&
+                         aligned_to(dY0, 16) && ldy0 % 8 == 0 && src_rows > 0 &&
+                         src_rows * ldy0 * 2 + 128 < (int64_t{1} << 32) && test_option(GRASS_TEST_PACK_MXT) == 0;
+    // whole cache lines per row (64 values of k per load) when the K tiles pair up
+    const bool pairs_ok = rows_ok && T % (2 * kFastBK) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0;
+    if (pairs_ok && planned == kTile256) ks = paired(ks, T);
+    const bool chunks = aligned_to(X, 16) && ldx % 8 == 0 && n % 8 == 0 &&
+                        (pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0));
+    const TileId tile = sizes ? choose_tile(planned, ks, T, total, n, rows_ok, layout, chunks) : kTile128;
     Copies copy = choose_copies(tile, T, total, n, layout, gathered);
     if (copy.b && !aligned_to(X, 4)) copy = Copies{false, false};  // what the copy kernel asks for
     pack = pack || copy.a;
     const int64_t nb = copy.b ? (n + 7) / 8 * 8 : n;  // columns the GEMM sees
-    // whole aligned 16-byte chunks: what the load-to-LDS kernel and the aligned small tile move
+    // whole aligned 16-byte chunks: what the load-to-LDS kernels and the aligned small tile move
     const bool aligned = (pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0)) &&
                          (copy.b || (aligned_to(X, 16) && ldx % 8 == 0 && n % 8 == 0));
-    // dY stored m x T: the selected rows are contiguous, so the large-tile kernel gathers them
-    // itself (no packing pass) when K is whole tiles and its 32-bit row offsets reach every row
-    bool a_rows_form = false;
-    if (tile == kTile256 && layout == GRASS_DY_MxT && count == 1 && aligned && T % kFastBK == 0 &&
-        aligned_to(dY0, 16) && ldy0 % 8 == 0 && test_option(GRASS_TEST_PACK_MXT) == 0) {
-        const int64_t src_rows = seg[0].idx ? seg[0].src_rows : total;
-        a_rows_form = src_rows > 0 && src_rows * ldy0 * 2 + 128 < (int64_t{1} << 32);
-    }
+    const bool a_rows_form = rows_ok && tile == kTile256 && aligned;
+    const bool a_pairs = a_rows_form && pairs_ok;
     if (a_rows_form) pack = false;
-    // whole cache lines per row (64 values of k per load) when the K tiles pair up
-    const bool a_pairs = a_rows_form && T % (2 * kFastBK) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0;
-    Plan p = plan_for(tile, T, total, n, pack);
-    if (a_pairs && p.ktiles_per_split % 2 != 0) {  // every workgroup gets whole pairs of K tiles
-        ++p.ktiles_per_split;
-        const int64_t ktiles = T / kFastBK;
-        p.splits = static_cast<int>((ktiles + p.ktiles_per_split - 1) / p.ktiles_per_split);
-    }
+    const Plan p = make_plan(tile, ks, T, total, n, pack);
     char* base = static_cast<char*>(ws);
     base += (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256;
     uint16_t* panel = reinterpret_cast<uint16_t*>(base);
     float* partial = reinterpret_cast<float*>(base + p.pack_bytes);
     // launch sizes are checked before the first launch: a refused call has done nothing
-    const int64_t items = static_cast<int64_t>(p.tiles_m) * p.tiles_n * p.splits;
-    const int64_t chunk = (items + kNumXcd - 1) / kNumXcd;
+    const int64_t tiles = static_cast<int64_t>(p.tiles_m) * p.tiles_n;
+    const int64_t chunk = (tiles * ks.splits + kNumXcd - 1) / kNumXcd;
+    const int64_t blocks = chunk * kNumXcd + (ks.tail ? tiles : 0);
     const int x_chunks = static_cast<int>((nb / 8 + 255) / 256);  // workgroups per row of the aligning copy
-    if (chunk * kNumXcd > 0x7FFFFFFF || (copy.b && T * x_chunks > 0x7FFFFFFF)) return GRASS_ERR_SHAPE;
+    if (blocks > 0x7FFFFFFF || (copy.b && T * x_chunks > 0x7FFFFFFF)) return GRASS_ERR_SHAPE;
 
     GemmArgs g;
     if (pack) {
@@ -776,10 +874,11 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     g.Np = p.Np;
     g.tiles_m = p.tiles_m;
     g.tiles_n = p.tiles_n;
-    g.splits = p.splits;
-    g.ktiles_per_split = p.ktiles_per_split;
+    g.splits = ks.slices();
+    g.tail = ks.tail ? 1 : 0;
+    g.ktiles_per_split = static_cast<int>(ks.tokens / tile_k(tile));
 
-    const unsigned grid = static_cast<unsigned>(chunk * kNumXcd);
+    const unsigned grid = static_cast<unsigned>(blocks);
     hipError_t le;
     if (tile == kTile256) {  // the events are stamped with this dispatch's own start and end
         if (a_pairs)
@@ -797,6 +896,16 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         else
             launch_stamped(tn_gemm_bf16_direct_kernel<true>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         le = hipSuccess;
+    } else if (tile == kTileMid) {
+        le = raise_lds_limit(reinterpret_cast<const void*>(gathered ? tn_gemm_bf16_mid_kernel<false>
+                                                                    : tn_gemm_bf16_mid_kernel<true>),
+                             kMidLdsBytes, gathered ? 0 : 1);
+        if (le == hipSuccess) {
+            if (gathered)
+                launch_stamped(tn_gemm_bf16_mid_kernel<false>, dim3(grid), dim3(256), kMidLdsBytes, s, ev_start, ev_stop, g);
+            else
+                launch_stamped(tn_gemm_bf16_mid_kernel<true>, dim3(grid), dim3(256), kMidLdsBytes, s, ev_start, ev_stop, g);
+        }
     } else {
         if (ev_start) (void)hipEventRecord(ev_start, s);
         if (aligned)
@@ -808,7 +917,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         if (le == hipSuccess && ev_stop) (void)hipEventRecord(ev_stop, s);
     }
     if (le != hipSuccess) return GRASS_ERR_DEVICE;
-    return finish_segments(seg, count, partial, p.splits, p.Mp, p.Np, n, odt, s, ev_tail_start, ev_tail_stop);
+    return finish_segments(seg, count, partial, ks.slices(), p.Mp, p.Np, n, odt, s, ev_tail_start, ev_tail_stop);
 }
 
 grass_status launch_tn_gemm(const void* dY, grass_dy_layout layout, int64_t ldy, const void* X,

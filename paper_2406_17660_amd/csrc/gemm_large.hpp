@@ -30,8 +30,9 @@ namespace {
 // Edges.  Columns past the matrix edge are redirected to column 0 of the same row: they
 // only feed output rows / columns that are never read back.  A ragged last K tile (T x m form) is
 // loaded during the drain with the tokens past T redirected to the last one, and their LDS rows
-// are cleared once it has landed: no extra slice or launch (the 4096 x 4096 layer at r = 1024,
-// T = 2047: 63 -> 57 us per step, against 56 at T = 2048).
+// are cleared once it has landed.  Where the ragged tile is a K slice of its own, that slice's
+// workgroups are part of the same launch (4096 x 4096, r = 1024, T = 2047: a separate launch cost
+// 7.4 us of a 63 us step).
 // Requirements (checked by the launcher): bases 16-byte aligned, leading dimensions and
 // column counts multiples of 8.
 constexpr int kFastBM = 256, kFastBN = 256, kFastBK = 32, kFastStages = 4;
@@ -98,26 +99,19 @@ void tn_gemm_bf16_direct_kernel(GemmArgs g) {
     static_assert(!kAPairs || kARows, "paired A stages are a form of the row-gathering kernel");
     __shared__ __attribute__((aligned(1024))) uint16_t ring[kFastStages * kFastStageElems];
 
-    const int64_t items = static_cast<int64_t>(g.tiles_m) * g.tiles_n * g.splits;
-    const int64_t chunk_items = (items + kNumXcd - 1) / kNumXcd;
-    const int64_t item =
-        static_cast<int64_t>(blockIdx.x % kNumXcd) * chunk_items + blockIdx.x / kNumXcd;
-    if (item >= items) return;
+    const int64_t item = work_item(g);
+    if (item < 0) return;
     const int tiles = g.tiles_m * g.tiles_n;
     const int split = static_cast<int>(item / tiles);
     const int tile = static_cast<int>(item % tiles);
     int tm, tn;
     tile_coords(tile, g.tiles_m, g.tiles_n, tm, tn);
     const int64_t m0 = static_cast<int64_t>(tm) * kFastBM, n0 = static_cast<int64_t>(tn) * kFastBN;
-    const int64_t kt_begin = static_cast<int64_t>(split) * g.ktiles_per_split;
     constexpr bool kRagged = !kARows && !kRowStats;  // these forms are only given whole K tiles
-    const int64_t ktiles_all = kRagged ? (g.K + kFastBK - 1) / kFastBK : g.K / kFastBK;
-    int64_t kt_end = kt_begin + g.ktiles_per_split;
-    if (kt_end > ktiles_all) kt_end = ktiles_all;
-    const int ntiles = kt_end > kt_begin ? static_cast<int>(kt_end - kt_begin) : 0;
-    // rows of this workgroup's last tile, and how many of its tiles are whole
-    const int last_rows = kRagged && ntiles > 0 && kt_end * kFastBK > g.K
-                              ? static_cast<int>(g.K - (kt_end - 1) * kFastBK) : kFastBK;
+    const KRange kr = k_range<kFastBK>(g, split);
+    const int64_t kt_begin = kr.begin;
+    const int ntiles = kr.end > kr.begin ? static_cast<int>(kr.end - kr.begin) : 0;
+    const int last_rows = kRagged ? kr.rows : kFastBK;
     const int whole = last_rows == kFastBK ? ntiles : ntiles - 1;
 
     const int tid = threadIdx.x, lane = tid & 63;

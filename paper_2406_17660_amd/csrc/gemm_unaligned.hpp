@@ -35,25 +35,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void tn_gemm_bf16_unaligned_kernel(GemmArgs g) {
     __shared__ __attribute__((aligned(1024))) uint16_t ring[2 * kFastStageElems];
 
-    const int64_t items = static_cast<int64_t>(g.tiles_m) * g.tiles_n * g.splits;
-    const int64_t chunk_items = (items + kNumXcd - 1) / kNumXcd;
-    const int64_t item =
-        static_cast<int64_t>(blockIdx.x % kNumXcd) * chunk_items + blockIdx.x / kNumXcd;
-    if (item >= items) return;
+    const int64_t item = work_item(g);
+    if (item < 0) return;
     const int tiles = g.tiles_m * g.tiles_n;
     const int split = __builtin_amdgcn_readfirstlane(static_cast<int>(item / tiles));
     const int tile = __builtin_amdgcn_readfirstlane(static_cast<int>(item % tiles));
     int tm, tn;
     tile_coords(tile, g.tiles_m, g.tiles_n, tm, tn);
     const int64_t m0 = static_cast<int64_t>(tm) * kFastBM, n0 = static_cast<int64_t>(tn) * kFastBN;
-    const int64_t kt_begin = static_cast<int64_t>(split) * g.ktiles_per_split;
-    const int64_t ktiles_all = (g.K + kFastBK - 1) / kFastBK;
-    int64_t kt_end = kt_begin + g.ktiles_per_split;
-    if (kt_end > ktiles_all) kt_end = ktiles_all;
-    const int ntiles = kt_end > kt_begin ? static_cast<int>(kt_end - kt_begin) : 0;
-    // rows of this workgroup's last tile (the others are whole)
-    const int last_rows = ntiles > 0 && kt_end * kFastBK > g.K
-                              ? static_cast<int>(g.K - (kt_end - 1) * kFastBK) : kFastBK;
+    const KRange kr = k_range<kFastBK>(g, split);
+    const int64_t kt_begin = kr.begin;
+    const int ntiles = kr.end > kr.begin ? static_cast<int>(kr.end - kr.begin) : 0, last_rows = kr.rows;
     const int whole = last_rows == kFastBK ? ntiles : ntiles - 1;
 
     const int tid = threadIdx.x, lane = tid & 63;
