@@ -429,6 +429,82 @@ __global__ __launch_bounds__(kThreads) void reduce_adam_scatter_few_kernel(
     wv.store_once(W + static_cast<int64_t>(row) * ldw + c);
 }
 
+// The same where rows do not start on 16-byte boundaries (n % 4 != 0, or an odd base or leading
+// dimension).  A thread owns kStrided columns, kThreads apart: every access is then one element per
+// lane and coalesced whatever the alignment, and as many bytes are in flight as with four columns
+// side by side.  The sum runs over the slices in order, as in splitk_reduce_kernel.  Bound by
+// memory: 512 x 5461 with two slices takes 22.8 us, 24 us in column form; the reduction and Adam as
+// two kernels with G_C between them took 16.3 + 19.6 us and 16.3 + 14.8 us.
+constexpr int kStrided = 4;
+template <typename WT, typename ST, bool kToU>
+__global__ __launch_bounds__(kThreads) void reduce_adam_scatter_strided_kernel(
+    TailSets sets, int slices, int64_t Mp, int64_t Np, int64_t n, AdamParams p_in, float alpha) {
+    const TailSet& q = sets.set[blockIdx.z];
+    const int64_t j = blockIdx.y, r = q.r;
+    if (j >= r) return;
+    const float* __restrict__ part = q.part;
+    ST* __restrict__ M = static_cast<ST*>(q.M);
+    ST* __restrict__ V = static_cast<ST*>(q.V);
+    const int64_t ldgc = q.ldgc;
+    const int32_t* __restrict__ idx = q.idx;
+    const float* __restrict__ rho = q.rho;
+    float* __restrict__ GC = q.GC;
+    float* __restrict__ U = q.U;
+    const AdamParams p = resolve(p_in);
+    const int32_t row = kToU ? 0 : idx[j];
+    if (!kToU && j > 0 && idx[j - 1] == row) return;
+    const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kThreads * kStrided + threadIdx.x;
+    if (c0 >= n) return;
+    WT* __restrict__ wrow = static_cast<WT*>(q.W) + (kToU ? 0 : static_cast<int64_t>(row) * q.ldw);
+    int64_t c[kStrided];
+    bool live[kStrided];
+#pragma unroll
+    for (int u = 0; u < kStrided; ++u) {
+        live[u] = c0 + u * kThreads < n;
+        c[u] = live[u] ? c0 + u * kThreads : c0;  // past the edge: this thread's first column again
+    }
+    const int64_t slice_stride = Mp * Np;
+    WVec<WT, 1> wv[kStrided];
+    float acc[kStrided] = {0.f, 0.f, 0.f, 0.f};
+    if (!kToU)
+#pragma unroll
+        for (int u = 0; u < kStrided; ++u) wv[u].load_once(wrow + c[u]);
+    for (int64_t jj = j; kToU ? jj == j : (jj < r && idx[jj] == row); ++jj) {
+        WVec<ST, 1> mv[kStrided], vv[kStrided];
+        float g[kStrided] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < kStrided; ++u) {
+            mv[u].load_once(M + jj * n + c[u]);
+            vv[u].load_once(V + jj * n + c[u]);
+        }
+        const float* src = part + jj * Np;
+#pragma unroll 4
+        for (int k = 0; k < slices; ++k, src += slice_stride)
+#pragma unroll
+            for (int u = 0; u < kStrided; ++u) g[u] += src[c[u]];
+        const float sc = rho[jj];
+#pragma unroll
+        for (int u = 0; u < kStrided; ++u) {
+            g[u] *= sc;
+            const float up = adam_elem<ST>(g[u], mv[u].x[0], vv[u].x[0], p);
+            acc[u] += sc * up;
+            if (live[u]) {
+                if (GC) GC[jj * ldgc + c[u]] = g[u];
+                if (kToU) U[jj * n + c[u]] = up;
+                mv[u].store_once(M + jj * n + c[u]);
+                vv[u].store_once(V + jj * n + c[u]);
+            }
+        }
+    }
+    if (kToU) return;
+#pragma unroll
+    for (int u = 0; u < kStrided; ++u)
+        if (live[u]) {
+            wv[u].x[0] += alpha * acc[u];
+            wv[u].store_once(wrow + c[u]);
+        }
+}
+
 template <typename GT, int VEC>
 __global__ __launch_bounds__(kThreads) void gather_rows_kernel(
     const GT* __restrict__ G, int64_t ldg, const int32_t* __restrict__ idx,
@@ -459,33 +535,54 @@ __global__ __launch_bounds__(kThreads) void gather_rows_kernel(
 // four-byte read-modify-writes fall into the few cache lines that hold 64 consecutive
 // selected columns of one row of W.  The first member of a run of equal idx sums the run
 // (members beyond this tile are read from global memory), so each W element is written by
-// one thread only.
+// one thread only.  A thread loads its 16 elements of W and its 16 of U before it uses any (with
+// one load and store after the other the kernel waited for memory 32 times in a row: 35.8 us
+// instead of 29.3 us for 512 columns of a 5461 x 2048 W).
 template <typename WT>
 __global__ __launch_bounds__(256) void scatter_cols_kernel(
     WT* __restrict__ W, int64_t ldw, int64_t mrows, const int32_t* __restrict__ idx,
     const float* __restrict__ rho, float alpha, const float* __restrict__ U, int64_t r) {
     __shared__ float tile[64][65];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr int kPer = 16;  // rows of the tile per wavefront
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 64, j0 = static_cast<int64_t>(blockIdx.y) * 64;
-    for (int jj = w; jj < 64; jj += 4) {
-        const int64_t j = j0 + jj, i = i0 + lane;
-        tile[jj][lane] = (j < r && i < mrows) ? rho[j] * U[j * mrows + i] : 0.f;
+    const int64_t j = j0 + lane;
+    const int32_t col = j < r ? idx[j] : 0;
+    const bool first = j < r && !(j > 0 && idx[j - 1] == col);  // not a later member of a run
+    const int64_t i_lane = i0 + lane < mrows ? i0 + lane : mrows - 1;
+    float u[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {  // past the edges: the last row or column, never used
+        const int64_t jr = j0 + w + 4 * q;
+        u[q] = U[(jr < r ? jr : r - 1) * mrows + i_lane];
+    }
+    WVec<WT, 1> wv[kPer];
+    if (first && i0 + w < mrows) {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {  // past the last row: this thread's first element again
+            const int64_t i = i0 + w + 4 * q;
+            wv[q].load(W + (i < mrows ? i : i0 + w) * ldw + col);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int64_t jr = j0 + w + 4 * q;
+        tile[w + 4 * q][lane] = jr < r ? rho[jr] * u[q] : 0.f;
     }
     __syncthreads();
-    const int64_t j = j0 + lane;
-    if (j >= r) return;
-    const int32_t col = idx[j];
-    if (j > 0 && idx[j - 1] == col) return;  // a later member of a run
+    if (!first) return;
     int64_t run_end = j + 1;
     while (run_end < r && idx[run_end] == col) ++run_end;
-    for (int ii = w; ii < 64; ii += 4) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int ii = w + 4 * q;
         const int64_t i = i0 + ii;
         if (i >= mrows) break;
         float acc = 0.f;
         for (int64_t jn = j; jn < run_end; ++jn)
             acc += jn < j0 + 64 ? tile[jn - j0][ii] : rho[jn] * U[jn * mrows + i];
-        WT* wp = W + i * ldw + col;
-        store_from_f32(wp, load_as_f32(wp) + alpha * acc);
+        wv[q].x[0] += alpha * acc;
+        wv[q].store(W + i * ldw + col);
     }
 }
 
@@ -657,17 +754,25 @@ grass_status launch_gather_rows(const void* G, grass_dtype gdt, int64_t n, int64
                             : gather_typed<uint16_t>(G, gdt, n, ldg, idx, rho, r, out, ldo, s);
 }
 
-bool reduce_adam_scatter_ok(const StepTail& t, int64_t n, const float* GC, int64_t ldgc) {
+bool reduce_adam_scatter_wide(const StepTail& t, int64_t n, const float* GC, int64_t ldgc) {
     return n % 4 == 0 && w_rows_vectorisable(t.M, t.sdt, n) && w_rows_vectorisable(t.V, t.sdt, n) &&
            (t.U ? f32_rows_vectorisable(t.U, n) : w_rows_vectorisable(t.W, t.wdt, t.ldw)) &&
            (!GC || f32_rows_vectorisable(GC, ldgc));
 }
 
 template <typename WT, typename ST, bool kToU = false>
-static void reduce_adam_scatter_typed(const TailSets& sets, int count, int64_t rmax, int slices,
-                                      int64_t Mp, int64_t Np, int64_t n, const AdamParams& p,
-                                      float alpha, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    if (slices <= 8) {
+static void reduce_adam_scatter_typed(const TailSets& sets, int count, bool wide, int64_t rmax,
+                                      int slices, int64_t Mp, int64_t Np, int64_t n,
+                                      const AdamParams& p, float alpha, hipStream_t s,
+                                      hipEvent_t e0, hipEvent_t e1) {
+    if (!wide && !reduce_many(slices, Np)) {
+        dim3 grid = grid_for(n, rmax, kStrided);
+        grid.z = static_cast<unsigned>(count);
+        launch_stamped(reduce_adam_scatter_strided_kernel<WT, ST, kToU>, grid, dim3(kThreads), 0, s, e0,
+                       e1, sets, slices, Mp, Np, n, p, alpha);
+        return;
+    }
+    if (wide && slices <= 8) {
         dim3 grid = grid_for(n, rmax, 4);
         grid.z = static_cast<unsigned>(count);
         launch_stamped(reduce_adam_scatter_few_kernel<WT, ST, kToU>, grid, dim3(kThreads), 0, s, e0, e1,
@@ -676,7 +781,10 @@ static void reduce_adam_scatter_typed(const TailSets& sets, int count, int64_t r
     }
     const dim3 grid(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(rmax),
                     static_cast<unsigned>(count));
-    if (slices <= 32)
+    // Not wide: always four shares, the order in which splitk_reduce_many_kernel adds the slices
+    // (the finishing phase takes one column per lane and the partial tiles are aligned, so the
+    // kernel itself asks nothing of the rows).
+    if (!wide || slices <= 32)
         launch_stamped(reduce_adam_scatter_kernel<WT, ST, kToU, 4>, grid, dim3(4 * 64), 0, s, e0, e1,
                        sets, slices, Mp, Np, n, p, alpha);
     else if (slices <= 64)
@@ -687,9 +795,9 @@ static void reduce_adam_scatter_typed(const TailSets& sets, int count, int64_t r
                        sets, slices, Mp, Np, n, p, alpha);
 }
 
-grass_status launch_reduce_adam_scatter(const TailSets& sets, int count, int slices, int64_t Mp,
-                                        int64_t Np, int64_t n, const StepTail& t, hipStream_t s,
-                                        hipEvent_t e0, hipEvent_t e1) {
+grass_status launch_reduce_adam_scatter(const TailSets& sets, int count, bool wide, int slices,
+                                        int64_t Mp, int64_t Np, int64_t n, const StepTail& t,
+                                        hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     int64_t rmax = 0;
     for (int i = 0; i < count; ++i) rmax = sets.set[i].r > rmax ? sets.set[i].r : rmax;
     if (count < 1 || rmax == 0 || n == 0) return GRASS_OK;
@@ -699,14 +807,14 @@ grass_status launch_reduce_adam_scatter(const TailSets& sets, int count, int sli
     if (sets.set[0].U) {  // column form: W is not touched here
         for (int i = 0; i < count; ++i)
             if (!sets.set[i].U) return GRASS_ERR_SHAPE;  // one form per launch
-        if (sf) reduce_adam_scatter_typed<uint16_t, float, true>(sets, count, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
-        else reduce_adam_scatter_typed<uint16_t, uint16_t, true>(sets, count, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
+        if (sf) reduce_adam_scatter_typed<uint16_t, float, true>(sets, count, wide, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
+        else reduce_adam_scatter_typed<uint16_t, uint16_t, true>(sets, count, wide, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
         return launch_status();
     }
-    if (wf && sf) reduce_adam_scatter_typed<float, float>(sets, count, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
-    else if (wf) reduce_adam_scatter_typed<float, uint16_t>(sets, count, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
-    else if (sf) reduce_adam_scatter_typed<uint16_t, float>(sets, count, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
-    else reduce_adam_scatter_typed<uint16_t, uint16_t>(sets, count, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
+    if (wf && sf) reduce_adam_scatter_typed<float, float>(sets, count, wide, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
+    else if (wf) reduce_adam_scatter_typed<float, uint16_t>(sets, count, wide, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
+    else if (sf) reduce_adam_scatter_typed<uint16_t, float>(sets, count, wide, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
+    else reduce_adam_scatter_typed<uint16_t, uint16_t>(sets, count, wide, rmax, slices, Mp, Np, n, p, t.alpha, s, e0, e1);
     return launch_status();
 }
 

@@ -66,7 +66,6 @@ size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // A slice of partial tiles up to this size is re-read from the caches by the reduction.
 constexpr int64_t kCachedSliceBytes = int64_t{16} << 20;
-constexpr int kManySlices = 8;  // above this the reduction spreads the slices over wavefronts
 
 // The square tile that a product's K slices are planned for: 256 x 256 unless it wastes much of
 // itself on padding.  (The kernel that runs may use another tile, see choose_tile: a slice's sums are
@@ -523,13 +522,16 @@ grass_status finish_segments(const GemmSegment* seg, int count, const float* par
                              int64_t Mp, int64_t Np, int64_t n, grass_dtype odt, hipStream_t s,
                              hipEvent_t ev_tail_start, hipEvent_t ev_tail_stop) {
     int64_t off = 0;
-    TailSets tails;  // sets whose reduction, Adam and row update run as one kernel (one launch)
-    int ntails = 0;
-    const StepTail* tail_common = nullptr;
+    // sets whose reduction, Adam and row update run as one kernel: a launch for those whose rows
+    // allow wide accesses ([1]) and a launch for the others ([0])
+    TailSets tails[2];
+    int ntails[2] = {0, 0};
+    const StepTail* tail_common[2] = {nullptr, nullptr};
     for (int i = 0; i < count; ++i) {
         const GemmSegment& q = seg[i];
-        if (q.rows > 0 && q.tail && odt == GRASS_F32 &&
-            reduce_adam_scatter_ok(*q.tail, n, q.c_wanted ? static_cast<float*>(q.C) : nullptr, q.ldc)) {
+        if (q.rows > 0 && q.tail) {
+            const bool wide =
+                reduce_adam_scatter_wide(*q.tail, n, q.c_wanted ? static_cast<float*>(q.C) : nullptr, q.ldc);
             // straight from the partial tiles; launched after the loop, together
             const TailSet one{partial + off * Np, q.rows, q.tail->M, q.tail->V, q.tail->W,
                               q.tail->ldw, q.idx, q.rho,
@@ -537,20 +539,21 @@ grass_status finish_segments(const GemmSegment* seg, int count, const float* par
             if (q.tail->U) {  // column form: its own launch, followed by the column update
                 TailSets single;
                 single.set[0] = one;
-                grass_status st = launch_reduce_adam_scatter(single, 1, slices, Mp, Np, n, *q.tail, s,
+                grass_status st = launch_reduce_adam_scatter(single, 1, wide, slices, Mp, Np, n, *q.tail, s,
                                                              ev_tail_start, ev_tail_stop);
                 if (st != GRASS_OK) return st;
                 st = launch_scatter_cols(q.tail->W, q.tail->wdt, q.tail->w_rows, q.tail->ldw, q.idx,
                                          q.rho, q.tail->alpha, q.tail->U, q.rows, s);
                 if (st != GRASS_OK) return st;
             } else {
-                tails.set[ntails++] = one;
-                tail_common = q.tail;
+                tails[wide].set[ntails[wide]++] = one;
+                tail_common[wide] = q.tail;
             }
         } else if (q.rows > 0) {
-            const dim3 rgrid(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(q.rows));
+            const int64_t span = reduce_many(slices, Np) ? 256 : 256 * kReduceCols;
+            const dim3 rgrid(static_cast<unsigned>((n + span - 1) / span), static_cast<unsigned>(q.rows));
             const float* part = partial + off * Np;
-            if (slices > kManySlices && Np % 128 == 0) {
+            if (reduce_many(slices, Np)) {
                 if (odt == GRASS_F32)
                     splitk_reduce_many_kernel<float><<<rgrid, 256, 0, s>>>(
                         part, slices, Mp, Np, q.rows, n, q.rho, static_cast<float*>(q.C), q.ldc);
@@ -563,16 +566,14 @@ grass_status finish_segments(const GemmSegment* seg, int count, const float* par
             else
                 splitk_reduce_kernel<uint16_t><<<rgrid, 256, 0, s>>>(
                     part, slices, Mp, Np, q.rows, n, q.rho, static_cast<uint16_t*>(q.C), q.ldc);
-            if (q.tail && ev_tail_start) (void)hipEventRecord(ev_tail_start, s);
-            const grass_status st = run_tail_unfused(q, n, s);
-            if (st != GRASS_OK) return st;
-            if (q.tail && ev_tail_stop) (void)hipEventRecord(ev_tail_stop, s);
         }
         off += (q.rows + 7) / 8 * 8;
     }
-    if (ntails > 0) {
-        const grass_status st = launch_reduce_adam_scatter(tails, ntails, slices, Mp, Np, n,
-                                                           *tail_common, s, ev_tail_start, ev_tail_stop);
+    for (int wide = 1; wide >= 0; --wide) {
+        if (ntails[wide] == 0) continue;
+        const grass_status st =
+            launch_reduce_adam_scatter(tails[wide], ntails[wide], wide != 0, slices, Mp, Np, n,
+                                       *tail_common[wide], s, ev_tail_start, ev_tail_stop);
         if (st != GRASS_OK) return st;
     }
     return launch_status();

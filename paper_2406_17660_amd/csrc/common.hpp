@@ -144,8 +144,12 @@ struct StepTail {
     float* U = nullptr;
     int64_t w_rows = 0;
 };
-// True when M, V, W or U (and GC, if given) allow the 16-byte accesses of the fused kernel.
-bool reduce_adam_scatter_ok(const StepTail& t, int64_t n, const float* GC, int64_t ldgc);
+// Above eight slices the reductions spread the slices over wavefronts (tiles of at least 128
+// columns; the narrower ones add them in order).
+inline bool reduce_many(int slices, int64_t Np) { return slices > 8 && Np % 128 == 0; }
+// True when M, V, W or U (and GC, if given) allow 16-byte accesses; otherwise the fused tail takes
+// its one-element-per-lane forms.
+bool reduce_adam_scatter_wide(const StepTail& t, int64_t n, const float* GC, int64_t ldgc);
 // One row set of the fused tail.  part: partial tiles [slices][Mp][Np], already offset to this
 // set's first row; GC: where to store the compressed gradient, or nullptr.
 struct TailSet {
@@ -166,10 +170,11 @@ struct TailSets {
 };
 // The fused tail for `count` row sets in one launch.  The sets share the partial-tile geometry,
 // n, the dtypes, the form (row or column) and Adam's scalars, which are taken from `t` (its M, V,
-// W, U are not read).  In column form the caller launches the column update afterwards.
+// W, U are not read) and are all wide or all not.  In column form the caller launches the column update afterwards.
 // ev_start / ev_stop: optional events that receive the kernel's own start and stop times.
-grass_status launch_reduce_adam_scatter(const TailSets& sets, int count, int slices, int64_t Mp,
-                                        int64_t Np, int64_t n, const StepTail& t, hipStream_t s,
+grass_status launch_reduce_adam_scatter(const TailSets& sets, int count, bool wide, int slices,
+                                        int64_t Mp, int64_t Np, int64_t n, const StepTail& t,
+                                        hipStream_t s,
                                         hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
 // A kernel launch that, given events, has the runtime stamp them with the start and the end of
