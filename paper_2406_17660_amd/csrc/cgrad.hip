@@ -892,6 +892,10 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
             launch_stamped(tn_gemm_bf16_unaligned_kernel<false>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else if (!aligned)
             launch_stamped(tn_gemm_bf16_unaligned_kernel<true>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
+        else if (T % kFastBK != 0 && gathered)
+            launch_stamped(tn_gemm_bf16_direct_ragged_kernel<false>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
+        else if (T % kFastBK != 0)
+            launch_stamped(tn_gemm_bf16_direct_ragged_kernel<true>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else if (gathered)
             launch_stamped(tn_gemm_bf16_direct_kernel<false>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else

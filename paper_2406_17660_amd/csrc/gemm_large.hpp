@@ -93,9 +93,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 // slot c of row j stored at slot c ^ ((j / 2) % 8)), each serving two consecutive K tiles: the
 // pair (i, i+1), i even, is loaded during K tile i-2, right after the pair (i-2, i-1) has been
 // used up.  B keeps its four single stages.  Needs an even number of K tiles per workgroup.
-template <bool kDense, bool kRowStats = false, bool kARows = false, bool kAPairs = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void tn_gemm_bf16_direct_kernel(GemmArgs g) {
+// kRagged: T is not a multiple of the K tile (kernels of their own, below: the extra branches of the
+// prologue and the drain cost a launch 0.5 us).
+template <bool kDense, bool kRowStats, bool kARows, bool kAPairs, bool kRagged>
+__device__ __forceinline__ void direct_gemm(const GemmArgs& g) {
+    static_assert(!kRagged || (!kARows && !kRowStats), "these forms are only given whole K tiles");
     static_assert(!kAPairs || kARows, "paired A stages are a form of the row-gathering kernel");
     __shared__ __attribute__((aligned(1024))) uint16_t ring[kFastStages * kFastStageElems];
 
@@ -107,11 +109,17 @@ void tn_gemm_bf16_direct_kernel(GemmArgs g) {
     int tm, tn;
     tile_coords(tile, g.tiles_m, g.tiles_n, tm, tn);
     const int64_t m0 = static_cast<int64_t>(tm) * kFastBM, n0 = static_cast<int64_t>(tn) * kFastBN;
-    constexpr bool kRagged = !kARows && !kRowStats;  // these forms are only given whole K tiles
-    const KRange kr = k_range<kFastBK>(g, split);
+    KRange kr;
+    if constexpr (kRagged) {
+        kr = k_range<kFastBK>(g, split);
+    } else {
+        kr.begin = static_cast<int64_t>(split) * g.ktiles_per_split;
+        kr.end = kr.begin + g.ktiles_per_split < g.K / kFastBK ? kr.begin + g.ktiles_per_split : g.K / kFastBK;
+        kr.rows = kFastBK;
+    }
     const int64_t kt_begin = kr.begin;
     const int ntiles = kr.end > kr.begin ? static_cast<int>(kr.end - kr.begin) : 0;
-    const int last_rows = kRagged ? kr.rows : kFastBK;
+    const int last_rows = kr.rows;
     const int whole = last_rows == kFastBK ? ntiles : ntiles - 1;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -476,6 +484,17 @@ void tn_gemm_bf16_direct_kernel(GemmArgs g) {
             }
 }
 
+template <bool kDense, bool kRowStats = false, bool kARows = false, bool kAPairs = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void tn_gemm_bf16_direct_kernel(GemmArgs g) {
+    direct_gemm<kDense, kRowStats, kARows, kAPairs, false>(g);
+}
+
+template <bool kDense>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void tn_gemm_bf16_direct_ragged_kernel(GemmArgs g) {
+    direct_gemm<kDense, false, false, false, true>(g);
+}
 
 }  // namespace
 }  // namespace grass
