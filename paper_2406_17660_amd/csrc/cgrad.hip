@@ -143,7 +143,8 @@ struct Copies { bool a, b; };
 // launch; in the large tile the register route takes about 7 us more to fill and drain (2746 x 1509,
 // r = 686, T = 448: 38.6 us in place, 35.1 with the copy), in the small one 4 (9576 x 371, r = 1024,
 // T = 1472: 40.0 and 38.6).  2048 x 5461, r = 512, T = 65536:
-// 429 us per step in place, 617 with the copy; full gradient of 2807 x 6144, T = 5248: 224 us in
+// 429 us per step in place, 617 with the copy (split-K sum and Adam as two kernels in both; fused,
+// the step in place takes 407); full gradient of 2807 x 6144, T = 5248: 224 us in
 // place, 209 with the copy.  dY stored m x T is read row-wise by the aligned large tile without
 // any pack, which the copy keeps possible.
 Copies choose_copies(TileId tile, int64_t T, int64_t rows, int64_t n, grass_dy_layout layout, bool gathered) {
