@@ -417,6 +417,19 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
     return launch_row_stats(G, GRASS_F32, m, n, n, sumsq, s);
 }
 
+// Bytes the narrow kernel's partial tiles may take: what a packed product with either square tile
+// and one spare slice would.  gemm_workspace_bytes asks for as much wherever this kernel can run.
+size_t narrow_cap_bytes(int64_t T, int64_t rows, int64_t n) {
+    size_t cap = 0;
+    for (const TileId id : {kTile128, kTile256}) {
+        const KSplit k = split_k(id, T, rows, n);
+        const Plan p = make_plan(id, k, T, rows, n, true);
+        const size_t bytes = p.pack_bytes + static_cast<size_t>(k.splits + 1) * p.Mp * p.Np * 4;
+        cap = bytes > cap ? bytes : cap;
+    }
+    return cap;
+}
+
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
                             grass_dy_layout layout, bool gathered) {
     if (dt == GRASS_F32) return f32_partial_bytes(T, &mrows, 1, n, false);
@@ -433,21 +446,12 @@ size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
             copy_x = copy_x || copy.b;
         }
     }
-    return (pack ? round_up(static_cast<size_t>(T) * Mp * 2, 256) : 0) + static_cast<size_t>(slices) * Mp * Np * 4 +
-           (copy_x ? aligned_x_bytes(T, n) : 0) + 256;
-}
-
-// Bytes the narrow kernel's partial tiles may take: what a packed product with either square tile
-// and one spare slice would (gemm_workspace_bytes asks for at least as much).
-size_t narrow_cap_bytes(int64_t T, int64_t rows, int64_t n) {
-    size_t cap = 0;
-    for (const TileId id : {kTile128, kTile256}) {
-        const KSplit k = split_k(id, T, rows, n);
-        const Plan p = make_plan(id, k, T, rows, n, true);
-        const size_t bytes = p.pack_bytes + static_cast<size_t>(k.splits + 1) * p.Mp * p.Np * 4;
-        cap = bytes > cap ? bytes : cap;
-    }
-    return cap;
+    const size_t tiled = (pack ? round_up(static_cast<size_t>(T) * Mp * 2, 256) : 0) +
+                         static_cast<size_t>(slices) * Mp * Np * 4 + (copy_x ? aligned_x_bytes(T, n) : 0);
+    // the narrow kernel's slices are bounded by a cap of their own
+    const bool narrow = gathered && narrow_shape_ok(T, n, dt, layout) && mrows <= GRASS_MAX_GROUP * kNarrowBM;
+    const size_t cap = narrow ? narrow_cap_bytes(T, mrows, n) : 0;
+    return (cap > tiled ? cap : tiled) + 256;
 }
 
 // The row-gathering kernel takes K tiles in pairs: every workgroup gets whole pairs.
@@ -674,7 +678,9 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
                  (kNarrowBK + 1) * seg[i].ldy * 2 < (int64_t{1} << 32);
     if (narrow) {
         char* base = static_cast<char*>(ws);
-        base += (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256;
+        const size_t skip = (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256;
+        base += skip;
+        const size_t room = ws_bytes > skip ? ws_bytes - skip : 0;
         NarrowArgs a;
         int64_t in_cols = n;
         int off = 0;
@@ -686,6 +692,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         }
         const size_t cap = narrow_cap_bytes(T, total, n);
         const NarrowPlan np = narrow_plan(T, n, count, off, in_cols, cap);
+        if (static_cast<size_t>(np.splits) * np.Mp * np.Np * 4 > room) return GRASS_ERR_WORKSPACE;
         a.count = count;
         a.X = static_cast<const uint16_t*>(X);
         a.ldx = ldx;

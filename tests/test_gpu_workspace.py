@@ -1,0 +1,54 @@
+"""A call writes nothing outside the workspace its query asked for: the bytes behind it (and before
+it) keep their pattern."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from paper_2406_17660_amd import grass
+from gpu_util import DEV, rel_fro, to_f64, to_np
+from test_gpu_parity import make_idx, randn
+
+pytestmark = pytest.mark.gpu
+BF = torch.bfloat16
+GUARD = 1 << 20
+
+
+def guarded(nbytes, shift=0):
+    """(workspace of nbytes that starts `shift` bytes after a 256-byte boundary, guard check)."""
+    buf = torch.full((GUARD + nbytes + shift + GUARD,), 0x5A, dtype=torch.uint8, device=DEV)
+    lo, hi = GUARD + shift, GUARD + shift + nbytes
+
+    def untouched():
+        return bool((buf[:lo] == 0x5A).all()) and bool((buf[hi:] == 0x5A).all())
+    return buf[lo:hi], untouched
+
+
+@pytest.mark.parametrize("shift", [0, 252])
+@pytest.mark.parametrize("T,n,m,rs", [
+    (480, 256, 512, (64,) * 4), (1024, 64, 512, (32,) * 8), (2048, 256, 512, (32,) * 8),
+    (8192, 512, 512, (32,) * 8), (2048, 264, 384, (9, 17, 33, 64, 65, 127, 128, 1))])
+def test_narrow_groups_stay_inside_the_queried_workspace(T, n, m, rs, shift):
+    X = randn((T, n), BF, 1)
+    dYs = [randn((T, m), BF, 2 + i, scale=0.1) for i in range(len(rs))]
+    host = [make_idx(m, r, 20 + i, duplicates=False) for i, r in enumerate(rs)]
+    idxs = [torch.from_numpy(i).to(DEV) for i, _ in host]
+    rhos = [torch.from_numpy(p).to(DEV) for _, p in host]
+    want = [ref.compressed_grad(to_np(dY), to_np(X), i, p) for dY, (i, p) in zip(dYs, host)]
+    total = sum((r + 7) // 8 * 8 for r in rs)
+    assert grass.cgrad_plan(T, n, total, grass.BF16, m=m, count=len(rs))[0] == 0
+
+    GCs = [torch.full((r, n), float("nan"), device=DEV) for r in rs]
+    ws, untouched = guarded(grass.cgrad_group_workspace(T, n, rs, grass.BF16), shift)
+    grass.compressed_grad_group(dYs, X, idxs, rhos, GCs, ws)
+    assert untouched()
+    for got, w in zip(GCs, want):
+        assert np.isfinite(to_np(got)).all() and rel_fro(to_f64(got), w) <= 2e-5
+
+    Ms, Vs = ([torch.zeros((r, n), device=DEV) for r in rs] for _ in range(2))
+    Ws = [torch.zeros((m, n), dtype=BF, device=DEV) for _ in rs]
+    ws, untouched = guarded(grass.step_group_workspace(T, n, rs, grass.BF16), shift)
+    grass.step_group(dYs, X, idxs, rhos, Ms, Vs, Ws, 1e-3, 0.9, 0.999, 1e-8, 1, 0.5, ws)
+    assert untouched()
+    for M, w in zip(Ms, want):
+        assert rel_fro(to_f64(M), 0.1 * w) <= 2e-5

@@ -1,0 +1,49 @@
+"""What the workspace queries promise, from the library's host functions alone: the partial tiles a
+planned product writes fit into the workspace its query asks for."""
+import numpy as np
+import pytest
+
+from paper_2406_17660_amd import grass
+
+
+def narrow_partial_bytes(T, n, rs, m):
+    """Bytes of partial tiles of the kernel that gathers by itself (the tiles are 256 columns wide and
+    the rows of all sets lie in one panel, each set rounded up to 8 rows), or None where another
+    kernel is planned."""
+    panel = sum((r + 7) // 8 * 8 for r in rs)
+    tile, slices = grass.cgrad_plan(T, n, panel if len(rs) > 1 else rs[0], grass.BF16, m=m, count=len(rs))
+    return slices * panel * ((n + 255) // 256 * 256) * 4 if tile == 0 else None
+
+
+def narrow_workspace(T, n, rs, m):
+    return (grass.cgrad_workspace(T, m, n, rs[0], grass.BF16) if len(rs) == 1
+            else grass.cgrad_group_workspace(T, n, rs, grass.BF16))
+
+
+@pytest.mark.parametrize("sets", range(1, 9))
+def test_partial_tiles_of_narrow_groups_fit_the_queried_workspace(sets):
+    """One to eight sets, equal and unequal ranks, over the kernel's whole range.  255 bytes of the
+    workspace may go into aligning its start."""
+    rng = np.random.default_rng(sets)
+    narrow = 0
+    for k in range(400):
+        T = int(2 ** rng.uniform(4, 17)) // 16 * 16
+        n, m = int(rng.integers(1, 65)) * 8, int(rng.integers(1, 65)) * 8
+        rs = [int(rng.integers(1, 129))] * sets if k % 2 else [int(r) for r in rng.integers(1, 129, sets)]
+        used = narrow_partial_bytes(T, n, rs, m)
+        if used is None:
+            continue
+        narrow += 1
+        assert used + 255 <= narrow_workspace(T, n, rs, m), (T, n, m, rs)
+        step = grass.step_group_workspace(T, n, rs, grass.BF16)
+        # a step keeps an unnamed G_C of each set behind the partial tiles
+        assert used + 255 + sum(r * n * 4 for r in rs) <= step, (T, n, m, rs)
+    assert narrow > 300
+
+
+@pytest.mark.parametrize("T,n,m,rs", [(8192, 512, 512, [32] * 8), (2048, 256, 512, [32] * 8),
+                                      (480, 256, 512, [64] * 4), (1024, 64, 512, [32] * 8)])
+def test_narrow_groups_of_many_slices_fit(T, n, m, rs):
+    """Groups whose slice count is bounded by the room for the partial tiles."""
+    used = narrow_partial_bytes(T, n, rs, m)
+    assert used is not None and used + 255 <= narrow_workspace(T, n, rs, m)
