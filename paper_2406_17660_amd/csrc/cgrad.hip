@@ -406,13 +406,14 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
             g.P, 2 * g.tiles_n, g.Mp, m, sumsq);
         return launch_status();
     }
-    const size_t g_bytes = static_cast<size_t>(m) * n * 4 + 256;
-    const size_t need = g_bytes + gemm_workspace_bytes(T, m, n, dt, layout, false);
-    if (ws_bytes < need) return GRASS_ERR_WORKSPACE;
+    // G, then the product's own workspace (which starts at the next multiple of 256 bytes)
+    const size_t g_bytes = static_cast<size_t>(m) * n * 4;
+    if (ws_bytes < g_bytes + 256 + gemm_workspace_bytes(T, m, n, dt, layout, false)) return GRASS_ERR_WORKSPACE;
     if (m > 65535) return GRASS_ERR_SHAPE;
     float* G = reinterpret_cast<float*>(base);
+    const size_t rest = ws_bytes - static_cast<size_t>(base - static_cast<char*>(ws)) - g_bytes;
     const grass_status st = launch_tn_gemm(dY, layout, ldy, X, ldx, dt, T, m, n, nullptr, nullptr, G,
-                                           GRASS_F32, n, base + g_bytes, need - g_bytes, s, m);
+                                           GRASS_F32, n, base + g_bytes, rest, s, m);
     if (st != GRASS_OK) return st;
     return launch_row_stats(G, GRASS_F32, m, n, n, sumsq, s);
 }

@@ -52,3 +52,17 @@ def test_narrow_groups_stay_inside_the_queried_workspace(T, n, m, rs, shift):
     assert untouched()
     for M, w in zip(Ms, want):
         assert rel_fro(to_f64(M), 0.1 * w) <= 2e-5
+
+
+@pytest.mark.parametrize("shift", [0, 255])
+@pytest.mark.parametrize("T,m,n", [(16071, 216, 507), (4096, 248, 255), (513, 127, 131)])
+def test_row_statistic_stays_inside_the_queried_workspace(T, m, n, shift):
+    """G and the product's partial tiles one after the other, from a start that is not aligned and
+    with an m x n whose bytes are not a multiple of 256."""
+    X, dY = randn((T, n), BF, 5), randn((T, m), BF, 6, scale=0.1)
+    ss = torch.full((m,), float("nan"), device=DEV)
+    ws, untouched = guarded(grass.grad_row_stats_workspace(T, m, n, grass.BF16, grass.DY_TxM, m, n), shift)
+    grass.grad_row_stats(dY, X, ss, ws)
+    assert untouched()
+    # squares of sums that are off by about sqrt(T) * 2^-24 each: twice that
+    assert rel_fro(to_np(ss), ref.row_stats(ref.full_grad(to_np(dY), to_np(X)))) <= 2e-5
