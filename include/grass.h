@@ -162,9 +162,14 @@ grass_status grass_select_rows_static(const float* sumsq, int64_t m, int64_t r,
  * are multiplied on the matrix cores with fp32 accumulation); GC is fp32, r x n,
  * leading dimension ldgc.  idx values must lie in [0, m) (not checked on the
  * device: idx comes from grass_select_rows); duplicates are allowed.
- * T = 0 writes zeros.  `ws` must hold grass_cgrad_workspace(...) bytes; for fp32 inputs, here
- * and in the calls below, it may be smaller or NULL (less of the product then runs in parallel:
- * the sums are split over fewer slices of T).
+ * T = 0 writes zeros.  `ws` must hold grass_cgrad_workspace(...) bytes.
+ *
+ * fp32 inputs: the partial tiles of the product are an aid, and a workspace that is smaller than
+ * the query says is accepted as follows.  grass_compressed_grad, grass_compressed_grad_group
+ * and grass_dense_grad: any size, or NULL.  grass_grad_row_stats: from m*n*4 + 256 bytes on.
+ * grass_step_group and grass_step_cols: from 256 bytes plus 4*r*n (column form: 4*r*m), rounded
+ * up to a multiple of 256 per layer, on.  The sums over T are then split over fewer slices, which
+ * changes them within fp32 rounding and takes longer.
  * Errors: NULL, SHAPE, DTYPE, WORKSPACE. */
 size_t grass_cgrad_workspace(int64_t T, int64_t m, int64_t n, int64_t r, grass_dtype dt,
                              grass_dy_layout layout);

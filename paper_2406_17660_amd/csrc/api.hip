@@ -454,7 +454,7 @@ grass_status grass_grad_row_stats(const void* dY, grass_dy_layout layout, int64_
     if (st != GRASS_OK) return st;
     if (!present(sumsq, m)) return GRASS_ERR_NULL;
     if (m > kMaxGridRows) return GRASS_ERR_SHAPE;
-    if (!ws || ws_bytes < grad_row_stats_workspace_bytes(T, m, n, dt, layout, ldy, ldx))
+    if (!ws || ws_bytes < grad_row_stats_least_bytes(T, m, n, dt, layout, ldy, ldx))
         return GRASS_ERR_WORKSPACE;
     return launch_grad_row_stats(dY, layout, ldy, X, ldx, dt, T, m, n, sumsq, ws, ws_bytes,
                                  as_stream(stream));

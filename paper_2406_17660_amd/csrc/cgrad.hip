@@ -374,6 +374,12 @@ size_t grad_row_stats_workspace_bytes(int64_t T, int64_t m, int64_t n, grass_dty
     return static_cast<size_t>(m) * n * 4 + 256 + gemm_workspace_bytes(T, m, n, dt, layout, false);
 }
 
+size_t grad_row_stats_least_bytes(int64_t T, int64_t m, int64_t n, grass_dtype dt,
+                                  grass_dy_layout layout, int64_t ldy, int64_t ldx) {
+    return dt == GRASS_F32 ? static_cast<size_t>(m) * n * 4 + 256
+                           : grad_row_stats_workspace_bytes(T, m, n, dt, layout, ldy, ldx);
+}
+
 grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64_t ldy,
                                    const void* X, int64_t ldx, grass_dtype dt, int64_t T, int64_t m,
                                    int64_t n, float* sumsq, void* ws, size_t ws_bytes,
@@ -408,7 +414,8 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
     }
     // G, then the product's own workspace (which starts at the next multiple of 256 bytes)
     const size_t g_bytes = static_cast<size_t>(m) * n * 4;
-    if (ws_bytes < g_bytes + 256 + gemm_workspace_bytes(T, m, n, dt, layout, false)) return GRASS_ERR_WORKSPACE;
+    if (ws_bytes < g_bytes + 256 + (dt == GRASS_F32 ? 0 : gemm_workspace_bytes(T, m, n, dt, layout, false)))
+        return GRASS_ERR_WORKSPACE;
     if (m > 65535) return GRASS_ERR_SHAPE;
     float* G = reinterpret_cast<float*>(base);
     const size_t rest = ws_bytes - static_cast<size_t>(base - static_cast<char*>(ws)) - g_bytes;

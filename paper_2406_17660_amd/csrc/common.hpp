@@ -220,6 +220,9 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
 // Row statistic of G = dY^T X without storing G (fused into the GEMM when the shape allows).
 size_t grad_row_stats_workspace_bytes(int64_t T, int64_t m, int64_t n, grass_dtype dt,
                                       grass_dy_layout layout, int64_t ldy, int64_t ldx);
+// What a call cannot do without: for fp32 inputs G alone (the product then runs without K slices).
+size_t grad_row_stats_least_bytes(int64_t T, int64_t m, int64_t n, grass_dtype dt,
+                                  grass_dy_layout layout, int64_t ldy, int64_t ldx);
 grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64_t ldy,
                                    const void* X, int64_t ldx, grass_dtype dt, int64_t T, int64_t m,
                                    int64_t n, float* sumsq, void* ws, size_t ws_bytes,

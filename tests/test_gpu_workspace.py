@@ -66,3 +66,20 @@ def test_row_statistic_stays_inside_the_queried_workspace(T, m, n, shift):
     assert untouched()
     # squares of sums that are off by about sqrt(T) * 2^-24 each: twice that
     assert rel_fro(to_np(ss), ref.row_stats(ref.full_grad(to_np(dY), to_np(X)))) <= 2e-5
+
+
+@pytest.mark.parametrize("room", ["least", "half", "query"])
+@pytest.mark.parametrize("T,m,n", [(8192, 200, 96), (2047, 259, 261)])
+def test_row_statistic_of_fp32_inputs_takes_a_short_workspace(T, m, n, room):
+    """Room for G alone is enough: the partial tiles of the product are an aid."""
+    X, dY = randn((T, n), torch.float32, 7), randn((T, m), torch.float32, 8, scale=0.1)
+    least = m * n * 4 + 256
+    query = grass.grad_row_stats_workspace(T, m, n, grass.F32)
+    assert least < query
+    ss = torch.full((m,), float("nan"), device=DEV)
+    ws, untouched = guarded({"least": least, "half": (least + query) // 2, "query": query}[room], 0)
+    grass.grad_row_stats(dY, X, ss, ws)
+    assert untouched()
+    assert rel_fro(to_np(ss), ref.row_stats(ref.full_grad(to_np(dY), to_np(X)))) <= 2e-5
+    with pytest.raises(grass.GrassError):
+        grass.grad_row_stats(dY, X, ss, guarded(least - 1)[0])
