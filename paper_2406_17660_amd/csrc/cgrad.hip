@@ -275,8 +275,8 @@ F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, bool step
     p.Np = tn * p.bm;
     const int64_t ktiles = (T + kF32BK - 1) / kF32BK, tiles = tm * tn;
     const int64_t slice_bytes = p.Mp * p.Np * 4;
+    const int64_t room = slice_bytes > 0 ? static_cast<int64_t>(cap_bytes) / slice_bytes : 1;
     int64_t smax = ktiles / 4;
-    if (slice_bytes > 0 && static_cast<int64_t>(cap_bytes) / slice_bytes < smax) smax = static_cast<int64_t>(cap_bytes) / slice_bytes;
     if (smax > 128) smax = 128;
     if (!step && T < kF32SplitMinT) smax = 1;
     if (const int cap = test_option(GRASS_TEST_MAX_K_SLICES)) smax = cap > 0 && cap < smax ? cap : smax;
@@ -285,6 +285,10 @@ F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, bool step
     int64_t s = 1;
     double best = 1e300;
     for (int64_t c = 1; c <= smax && tiles > 0; ++c) {
+        // slices of whole K tiles: the room must hold those that remain (a workspace of the size that
+        // the unlimited plan asks for then gives that plan again)
+        const int64_t per = (ktiles + c - 1) / c;
+        if ((ktiles + per - 1) / per > room) break;
         const int64_t wgs = tiles * c, rounds = (wgs + 255) / 256;
         const double cost = flop_us * static_cast<double>(rounds * 256) / static_cast<double>(wgs) + slice_us * c;
         if (cost < best * (1 - 1e-9)) { best = cost; s = c; }

@@ -83,3 +83,19 @@ def test_row_statistic_of_fp32_inputs_takes_a_short_workspace(T, m, n, room):
     assert rel_fro(to_np(ss), ref.row_stats(ref.full_grad(to_np(dY), to_np(X)))) <= 2e-5
     with pytest.raises(grass.GrassError):
         grass.grad_row_stats(dY, X, ss, guarded(least - 1)[0])
+
+
+@pytest.mark.parametrize("T,m,n,r", [(6672, 40, 1394, 5), (2513, 300, 257, 130), (4096, 128, 128, 128), (1500, 64, 1030, 9)])
+def test_fp32_results_do_not_depend_on_room_beyond_the_query(T, m, n, r):
+    """A workspace of the queried size gives the slices that an unlimited one gives: the same bits."""
+    X, dY = randn((T, n), torch.float32, 9), randn((T, m), torch.float32, 10)
+    idx, rho = (torch.from_numpy(a).to(DEV) for a in make_idx(m, r, 11, False))
+    need = grass.cgrad_workspace(T, m, n, r, grass.F32)
+    outs = []
+    for nbytes in (need, 4 * need):
+        GC = torch.full((r, n), float("nan"), device=DEV)
+        ws, untouched = guarded(nbytes)
+        grass.compressed_grad(dY, X, idx, rho, GC, ws)
+        assert untouched()
+        outs.append(GC)
+    assert torch.equal(*outs)
