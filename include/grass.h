@@ -386,8 +386,9 @@ grass_status grass_step_group(int count, const grass_step_layer* layers, grass_d
 /* grass_step_group with a second pair of timing hooks: ev_tail_start / ev_tail_stop (hipEvent_t
  * as void*, either may be NULL) receive the start and the end of the kernel that follows the
  * matrix multiply (split-K reduction + Adam + row update; with several layers, the launch that
- * serves them together, or the last layer's when the layers run one after the other), stamped
- * with that dispatch's own times.  For a benchmark that wants the step's tail as it runs inside
+ * serves them together, or two launches where the rows of some layers start on 16-byte boundaries
+ * and those of others do not; the last layer's when the layers run one after the other), stamped
+ * with the dispatches' own times.  For a benchmark that wants the step's tail as it runs inside
  * the step sequence.  Everything else is grass_step_group. */
 grass_status grass_step_group_timed(int count, const grass_step_layer* layers,
                                     grass_dy_layout layout, const void* X, int64_t ldx,

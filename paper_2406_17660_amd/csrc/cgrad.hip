@@ -588,9 +588,10 @@ grass_status finish_segments(const GemmSegment* seg, int count, const float* par
     }
     for (int wide = 1; wide >= 0; --wide) {
         if (ntails[wide] == 0) continue;
-        const grass_status st =
-            launch_reduce_adam_scatter(tails[wide], ntails[wide], wide != 0, slices, Mp, Np, n,
-                                       *tail_common[wide], s, ev_tail_start, ev_tail_stop);
+        const bool first = wide == 1 || ntails[1] == 0, last = wide == 0 || ntails[0] == 0;
+        const grass_status st = launch_reduce_adam_scatter(
+            tails[wide], ntails[wide], wide != 0, slices, Mp, Np, n, *tail_common[wide], s,
+            first ? ev_tail_start : nullptr, last ? ev_tail_stop : nullptr);
         if (st != GRASS_OK) return st;
     }
     return launch_status();

@@ -180,6 +180,7 @@ grass_status launch_reduce_adam_scatter(const TailSets& sets, int count, bool wi
 // A kernel launch that, given events, has the runtime stamp them with the start and the end of
 // this very dispatch (what a profiler's kernel trace reports), instead of events recorded as
 // separate commands before and after it, which add the gaps between commands to the interval.
+// Either event may be absent.
 template <typename Kernel, typename... Args>
 inline void launch_stamped(Kernel kernel, dim3 grid, dim3 block, unsigned lds_bytes, hipStream_t s,
                            hipEvent_t ev_start, hipEvent_t ev_stop, Args... args) {
