@@ -7,7 +7,7 @@ import torch
 from oracle import ref
 from paper_2406_17660_amd import grass
 from gpu_util import DEV, rel_fro, to_f64, to_np
-from test_gpu_parity import make_idx, randn
+from test_gpu_parity import make_idx, randn, run_step_cols, run_step_group
 
 pytestmark = pytest.mark.gpu
 BF = torch.bfloat16
@@ -99,3 +99,52 @@ def test_fp32_results_do_not_depend_on_room_beyond_the_query(T, m, n, r):
         assert untouched()
         outs.append(GC)
     assert torch.equal(*outs)
+
+
+def rounded(nbytes):
+    return (nbytes + 255) // 256 * 256
+
+
+@pytest.mark.parametrize("T,n,ms,rs,want_gc", [
+    (2048, 256, (256,), (16,), False), (1500, 50, (70, 64, 9), (33, 64, 1), True),
+    (512, 260, (40, 64), (40, 0), False)])
+def test_fp32_step_with_room_for_the_gradient_alone(monkeypatch, T, n, ms, rs, want_gc):
+    """Not one slice of partial tiles fits: the product is stored directly, Adam and the row update
+    follow as a kernel of their own.  Duplicate rows, an empty set."""
+    least = 256 + sum(rounded(4 * r * n) for r in rs)
+    assert least < grass.step_group_workspace(T, n, rs, grass.F32)
+    monkeypatch.setattr(grass, "step_group_workspace", lambda *a: least)
+    run_step_group(torch.float32, torch.float32, torch.float32, T, n, ms, rs, want_gc, None)
+    monkeypatch.setattr(grass, "step_group_workspace", lambda *a: least - 1)
+    with pytest.raises(grass.GrassError):
+        run_step_group(torch.float32, torch.float32, torch.float32, T, n, ms, rs, want_gc, None)
+
+
+@pytest.mark.parametrize("T,m,n,r,want_gc", [(2048, 256, 64, 16, False), (300, 130, 50, 17, True)])
+def test_fp32_column_step_with_room_for_the_gradient_alone(monkeypatch, T, m, n, r, want_gc):
+    least = 256 + rounded(4 * r * m)
+    assert least < grass.step_cols_workspace(T, m, n, r, grass.F32)
+    monkeypatch.setattr(grass, "step_cols_workspace", lambda *a: least)
+    run_step_cols(torch.float32, torch.float32, T, m, n, r, True, want_gc, None)
+
+
+@pytest.mark.parametrize("T", [512, 1000, 1536])
+def test_fp32_step_and_separate_call_differ_in_summation_order_alone(T):
+    """Below 1024 tokens a step splits K where the separate call does not: equal within the rounding
+    of their sums (sqrt(T) * 2^-24 each), and bit for bit with one slice in both."""
+    m, n, r = 256, 256, 16
+    X, dY = randn((T, n), torch.float32, 12), randn((T, m), torch.float32, 13, scale=0.1)
+    idx, rho = (torch.from_numpy(a).to(DEV) for a in make_idx(m, r, 14, False))
+
+    def both():
+        outs = [torch.full((r, n), float("nan"), device=DEV) for _ in range(2)]
+        grass.compressed_grad(dY, X, idx, rho, outs[0],
+                              grass.workspace(max(grass.cgrad_workspace(T, m, n, r, grass.F32), 16)))
+        M, V, W = (torch.zeros((k, n), device=DEV) for k in (r, r, m))
+        grass.step_group([dY], X, [idx], [rho], [M], [V], [W], 1e-3, 0.9, 0.999, 1e-8, 1, 0.5,
+                         grass.workspace(grass.step_group_workspace(T, n, [r], grass.F32)), GCs=[outs[1]])
+        return outs
+    call, step = both()
+    assert rel_fro(to_f64(step), to_f64(call)) <= 4 * T ** 0.5 * 2.0 ** -24
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 1)
+    assert torch.equal(*both())
