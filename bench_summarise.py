@@ -128,7 +128,7 @@ def hbm_traffic(folder, line, key, argv):
     fc = max(v for k, vals in f.items() if "copyBuffer" in k for v in vals)
     wc = max(v for k, vals in w.items() if "copyBuffer" in k for v in vals)
     fu, wu = copy_bytes / fc, copy_bytes / wc
-    slices = (line.get("step_tail") or {}).get("k_slices", 1)
+    slices = (line.get("step_tail") or {}).get("k_slices") or 1
     out = [f"# HBM traffic of the kernels of bench.py {argv} (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE)".replace("  ", " "), "",
            f"Workload: {c['workload']}", "", "Commands (two runs, one counter each):", "",
            f"    rocprofv3 --pmc FETCH_SIZE --kernel-trace --output-format csv -d DIR/fetch -o bench -- python3 bench.py {argv} --steps 10 --warmup 2 --settle-launches 20 --no-cpu-baseline --no-extras".replace("  ", " "),

@@ -184,15 +184,17 @@ grass_status grass_compressed_grad(const void* dY, grass_dy_layout layout, int64
  * rounded up to a multiple of 8; the sets are taken to be of equal size), m the row length of
  * dY (0: not given).  `*tile` receives the edge of the output tile that the slices are
  * planned for (256 or 128; for fp32 inputs 128 or 64; the kernel may run with another tile where
- * that is faster, with the same sums), or 0 for narrow layers (bf16, T x m storage, m <= 512, r <= 128 per set, n <= 512, T
- * a multiple of 16), whose gather runs inside the matrix-multiply kernel (128 x 256 tiles, no
+ * that is faster, with the same sums), or 0 for narrow layers (bf16, T x m storage, m <= 512,
+ * r <= 128 per set, n <= 512, T a multiple of 16), whose gather runs inside the matrix-multiply kernel (128 x 256 tiles, no
  * packed panel); `*k_slices` the number of slices the token dimension is split into (their
  * partial products are what the split-K reduction, or the fused tail of grass_step_group /
  * grass_step_cols, adds up; above 8 slices those kernels spread the slices over the wavefronts
- * of a workgroup).  A pure host function, for callers that want to know what a shape costs and
- * for tests that must reach every kernel.  Narrow layers whose operands' bases or
- * leading dimensions are not 16-byte aligned take the packed route at launch whatever this
- * reports.
+ * of a workgroup).  For fp32 inputs it is the plan of grass_compressed_grad: steps of fewer than
+ * 1024 tokens split K where that call does not.  A pure host function, for callers that want to
+ * know what a shape costs.  It does not name the kernel that runs, the narrow one apart: to reach
+ * a kernel for certain, force its tile (grass_set_test_option).  Narrow layers whose operands'
+ * bases or leading dimensions are not 16-byte aligned take the packed route at launch whatever
+ * this reports.
  * Errors: NULL, SHAPE, DTYPE. */
 grass_status grass_cgrad_plan(int64_t T, int64_t m, int64_t n, int64_t rows, int count,
                               grass_dtype dt, grass_dy_layout layout, int* tile, int* k_slices);
@@ -217,9 +219,10 @@ grass_status grass_compressed_grad_timed(const void* dY, grass_dy_layout layout,
  * projections of an MLP: Section 4 trains all linear layers of a block).  For set
  * i < count:
  *   GC[i][j, c] = rho[i][j] * sum_t dY[i][t, idx[i][j]] * X[t, c],  j < r[i], c < n,
- * exactly what grass_compressed_grad returns for (dY[i], idx[i], rho[i]) alone; the
- * selected rows of all sets are gathered into one panel and multiplied with X in a
- * single pass over X.
+ * what grass_compressed_grad returns for (dY[i], idx[i], rho[i]) alone, up to the order of
+ * the fp32 sums over t (the token dimension is split for all sets together); the selected
+ * rows of all sets are gathered into one panel and multiplied with X in a single pass
+ * over X.
  * dY, ldy, m, r, idx, rho, GC, ldgc are HOST arrays of `count` entries (1 <= count
  * <= GRASS_MAX_GROUP); the entries of dY, idx, rho and GC are device pointers.  All
  * sets share T, n, dt, layout, X and the stream.  Each GC[i] is fp32, r[i] x n,
@@ -346,8 +349,8 @@ grass_status grass_gather_rows(const void* G, grass_dtype gdt, int64_t m, int64_
 /* ---------------------------------------------------------------------------
  * The regular step of Algorithm 1 in one call ("G_C <- P^T grad; Delta <- opt.update(G_C);
  * W <- W + alpha P Delta"), for `count` weight matrices that read the same activations X
- * (count = 1: one layer).  Per layer it computes exactly what grass_compressed_grad followed
- * by grass_adam_scatter_state computes; the split-K reduction of the matrix product, Adam and
+ * (count = 1: one layer).  Per layer it computes what grass_compressed_grad followed by
+ * grass_adam_scatter_state computes, up to the order of the fp32 sums over t; the split-K reduction of the matrix product, Adam and
  * the row update run as one kernel that reads the product's partial tiles directly, so G_C
  * is not written unless the layer asks for it (GC != NULL), and one launch and one pass over
  * r x n are saved per layer.
@@ -404,9 +407,9 @@ grass_status grass_step_group_timed(int count, const grass_step_layer* layers,
  *   G_C = rho ((B X^T) dY)            r x m   (= (G P)^T, P the n x r projection),
  *   Adam on r x m moments M, V        (U = its output, r x m fp32),
  *   W[:, idx[j]] += alpha * rho[j] * U[j, :]^T.
- * Exactly what grass_compressed_grad (X in the place of dY and dY in the place of X),
- * grass_adam_rows_state and grass_scatter_update_cols compute one after the other; the
- * split-K reduction of the product and Adam run as one kernel that reads the product's
+ * What grass_compressed_grad (X in the place of dY and dY in the place of X),
+ * grass_adam_rows_state and grass_scatter_update_cols compute one after the other, up to the
+ * order of the fp32 sums over t; the split-K reduction of the product and Adam run as one kernel that reads the product's
  * partial tiles.  idx: r column indices in [0, n), ascending; GC: NULL, or r x m fp32 (leading
  * dimension ldgc) to receive G_C; U: r x m fp32, contiguous, 16-byte aligned (scratch the
  * caller owns; holds Adam's output afterwards); W: m x n of dtype wdt, leading dimension ldw;

@@ -316,7 +316,8 @@ __global__ __launch_bounds__(kManyWaves * 64) void reduce_adam_scatter_kernel(
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int32_t row = kToU ? 0 : idx[j];
     if (!kToU && j > 0 && idx[j - 1] == row) return;  // whole workgroup: no barrier is skipped by part of it
-    // summing phase: this lane's four columns; n % 4 == 0, so a live lane owns four whole columns
+    // summing phase: this lane's four columns of the partial tiles, whose rows are whole tiles (where
+    // n % 4 != 0 the last lane also adds padding columns, which no finishing lane reads)
     const int64_t c4 = static_cast<int64_t>(blockIdx.x) * 256 + lane * 4;
     const bool live4 = c4 < n;
     const int per = (slices + kManyWaves - 1) / kManyWaves;

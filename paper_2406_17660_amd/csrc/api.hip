@@ -271,6 +271,9 @@ grass_status grass_adam_scatter_state(const float* GC, int64_t ldgc, void* M, vo
                                idx, rho, alpha, as_stream(stream));
 }
 
+// Room for a G_C that the caller does not name.  Only fp32 steps whose workspace holds no partial tiles
+// store one (the fused tail reads the partial tiles); every query counts it all the same, so that
+// a step never needs more than its query for want of partial tiles.
 static size_t scratch_gc_bytes(int64_t r, int64_t n) {
     return (static_cast<size_t>(r) * n * 4 + 255) / 256 * 256;
 }
@@ -279,7 +282,7 @@ size_t grass_step_group_workspace(int64_t T, int64_t n, int count, const int64_t
                                   grass_dtype dt, grass_dy_layout layout) {
     if (T < 0 || n < 0 || !small(T) || !small(n) || count < 1 || count > GRASS_MAX_GROUP || !r)
         return 0;
-    size_t extra = 256;  // a G_C for every layer that does not name one (the two-kernel route)
+    size_t extra = 256;  // a G_C for every layer that does not name one
     for (int i = 0; i < count; ++i) {
         if (r[i] < 0 || r[i] > kMaxGridRows) return 0;
         extra += scratch_gc_bytes(r[i], n);

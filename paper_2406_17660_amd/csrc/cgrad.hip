@@ -162,10 +162,12 @@ size_t aligned_x_bytes(int64_t T, int64_t n) {
 }
 
 // The tile a product with these K slices runs with: the one whose estimated time is smallest.  Rates
-// are those reached with full tiles and a full machine (any-alignment forms: 13 % less); slices
+// are those reached with full tiles on all compute units (any-alignment forms: 13 % less): 1.4 and
+// 0.6 PFLOP/s for the square tiles, for the mid tile 0.9 with one workgroup per compute unit and,
+// with two that share it, 15 % less time per round: 1.06 (measured over whole products: 1.28 - 1.39
+// and 0.60 - 0.66 against 1.05 - 1.16 at 5120 x 5120 and 4096 x 4096, r = 1024).  Slices
 // of partial tiles cost 3e-12 s per output element (written, then read by the reduction), 2.2e-12
-// while they stay in the caches; two workgroups of the mid tile share a compute unit, which
-// gains 15 %; dY stored m x T has to be packed (transposed) for all but the large tile, which
+// while they stay in the caches; dY stored m x T has to be packed (transposed) for all but the large tile, which
 // gathers its rows itself.
 // Measured per step, planned square tile -> the one chosen here:
 //   2048 x 2048, r = 300, T = 8192    45 -> 37 us (mid)     4096 x 4096, r = 1024, T = 2048  54 -> 51 (mid)
@@ -317,9 +319,9 @@ void launch_f32_kernel(const F32Args& a, bool vec_a, bool vec_b, hipStream_t s, 
 }
 
 // More than 64 KB of dynamic LDS has to be asked for, per kernel and device; the attribute sticks for
-// the life of the process, so it is set once (the only state the library keeps: a flag per device
-// and kernel, set with release order after the attribute call has returned; two first callers
-// both make the call).  `which`: a number per kernel.
+// the life of the process, so it is set once: a flag per device and kernel, set with release order
+// after the attribute call has returned; two first callers both make the call.  `which`: a number
+// per kernel.
 hipError_t raise_lds_limit(const void* kernel, int bytes, int which) {
     static std::atomic<bool> raised[2][64];
     int dev = 0;
@@ -334,9 +336,7 @@ template <typename Cfg, bool kDense, bool kAnyAlign>
 hipError_t launch_gemm_kernel(const GemmArgs& g, unsigned grid, hipStream_t s) {
     auto kernel = tn_gemm_bf16_kernel<Cfg, kDense, kAnyAlign>;
     if (Cfg::kLdsBytes > 64 * 1024) {
-        // per instantiation and device; the attribute sticks for the life of the process, so it
-        // is set once (the only state the library keeps: a flag per device, set with release
-        // order after the attribute call has returned; two first callers both make the call)
+        // set once per instantiation and device, as in raise_lds_limit
         static std::atomic<bool> raised[64];
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
@@ -516,7 +516,8 @@ size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int
     return joint > need ? joint : need;
 }
 
-// Adam and the row update from a G_C that has been written to seg.C (two-kernel route).
+// Adam and the row update from a G_C that has been written to seg.C: fp32 steps whose workspace holds
+// not one slice of partial tiles.
 grass_status run_tail_unfused(const GemmSegment& q, int64_t n, hipStream_t s) {
     if (!q.tail || q.rows == 0) return GRASS_OK;
     const StepTail& t = *q.tail;
@@ -720,7 +721,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         a.ktiles_per_split = np.ktiles_per_split;
         const int64_t items = static_cast<int64_t>(count) * np.tiles_n * np.splits;
         const unsigned grid = static_cast<unsigned>((items + kNumXcd - 1) / kNumXcd * kNumXcd);
-        {   // more than 64 KB of LDS: the attribute is set once per device (see launch_gemm_kernel)
+        {   // more than 64 KB of LDS: the attribute is set once per device (see raise_lds_limit)
             static std::atomic<bool> raised[64];
             int dev = 0;
             if (hipGetDevice(&dev) != hipSuccess) return GRASS_ERR_DEVICE;

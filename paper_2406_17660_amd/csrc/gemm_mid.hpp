@@ -11,9 +11,11 @@ namespace {
 // reads, hand-placed waits and fragment double-buffering) on a tile of 128 rows x 256 columns: four
 // wavefronts of 64 x 128 (128 accumulator registers), K tiles of 32 in a ring of three 24 KB
 // stages, so that two workgroups share a compute unit and fill each other's barriers.  Per flop it
-// reads a third more from LDS and half as much again from L2 as the 256 x 256 tile, which bounds it
-// at about 0.85 of that kernel's rate; the register-staged 128 x 128 kernel it replaces where both
-// apply has one K tile in flight and is LDS-bound at half of that.
+// reads half as much again from LDS and from L2 as the 256 x 256 tile.  With two workgroups on every
+// compute unit it reaches 0.82 - 0.87 of that kernel's rate (4096 x 4096, r = 1024, T = 131072: 1.16
+// against 1.39 PFLOP/s; 2048 x 2048, r = 512, T = 65536: 1.01 against 1.16); the register-staged
+// 128 x 128 kernel it replaces where both apply has one K tile in flight and reaches 0.60 - 0.66
+// PFLOP/s there.
 // Measured (whole steps, same K slices): 2048 x 2048, r = 300, T = 8192: 37 us, 45 with 128 x 128
 // tiles; 488 x 8200, r = 122, T = 12224: 65 against 72; 4096 x 4096, r = 1024, T = 2048: 50
 // against 54 with 256 x 256 tiles (256 workgroups instead of 128).

@@ -52,7 +52,7 @@ def test_product_at_tile_edges(tile, layout, T, m, n, r, shift):
     assert rel_fro(to_np(G), (d if layout == grass.DY_MxT else d.T) @ to_f64(X)) <= TOL_F32
 
 
-@pytest.mark.parametrize("n", [48, 50])  # fused tail, and the two-kernel route
+@pytest.mark.parametrize("n", [48, 50])  # fused tail on 16-byte accesses, and on single elements
 def test_group_step_equals_separate_calls(n):
     T, ms, rs = 1500, (70, 64, 9), (33, 64, 1)
     X = torch.randn(T, n, device=DEV)

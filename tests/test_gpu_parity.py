@@ -808,7 +808,7 @@ def test_select_rows_random_sizes_bit_exact(case):
     (512, 256, (256,), (16,), True, None),                   # one layer, G_C requested
     (4096, 512, (300, 520, 64), (130, 129, 0), False, None), # group, several K slices, an empty set
     (1056, 264, (300, 520), (130, 129), True, "256"),        # large tile, K tail
-    (777, 334, (130, 90), (40, 9), False, None),             # n % 4 != 0: the two-kernel route
+    (777, 334, (130, 90), (40, 9), False, None),             # n % 4 != 0: the tail on single elements
     (640, 1024, (400,), (256,), False, "256"),               # duplicates walk runs across the tile
 ])
 def test_step_group_equals_the_separate_calls_and_the_oracle(dtype, wdtype, sdtype, T, n,
@@ -953,7 +953,7 @@ def test_step_cols_with_more_than_eight_k_slices(sdtype, T, m, n, r, dup, want_g
 @pytest.mark.parametrize("sdtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("T,m,n,r,dup,want_gc,tile", [
     (512, 688, 256, 64, True, True, None),      # gate/up-shaped, duplicates
-    (300, 130, 50, 17, False, False, None),     # nothing divides anything (m % 4 != 0: separate kernels)
+    (300, 130, 50, 17, False, False, None),     # nothing divides anything (m % 4 != 0: the tail on single elements)
     (1056, 520, 264, 260, True, False, "256"),  # large tile
     (4096, 64, 32, 8, False, True, None),       # several K slices for a small output
 ])
