@@ -158,8 +158,8 @@ def test_config3_llama350m_layers_at_65536_tokens(layer, slices):
                                                  (2, "multi_norm", (2, 16))])
 def test_config4_llama1b_layers_at_65536_tokens(layer, method, slices):
     """2048 x 2048, 5461 x 2048, 2048 x 5461 at r = 512, draws with replacement from a log-normal
-    spread of the row norms (long runs of repeated rows); the 5461-wide activations are copied to
-    16-byte-aligned rows first, and rows of the 5461-long dY start at every byte offset."""
+    spread of the row norms (long runs of repeated rows); the 5461-wide activations are
+    read in place, and rows of the 5461-long dY start at every byte offset."""
     st, idx = run_layer(workloads.CONFIGS[4], layer, method, True, "lognormal", *slices)
     if method == "multi_norm":
         assert len(np.unique(idx)) < 0.9 * len(idx)  # the heavy rows are drawn over and over
