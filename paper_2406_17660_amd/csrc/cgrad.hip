@@ -289,8 +289,10 @@ F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, bool step
     for (int64_t c = 1; c <= smax && tiles > 0; ++c) {
         // slices of whole K tiles: the room must hold those that remain (a workspace of the size that
         // the unlimited plan asks for then gives that plan again)
-        const int64_t per = (ktiles + c - 1) / c;
-        if ((ktiles + per - 1) / per > room) break;
+        if (c > room) {
+            const int64_t per = (ktiles + c - 1) / c;
+            if ((ktiles + per - 1) / per > room) break;
+        }
         const int64_t wgs = tiles * c, rounds = (wgs + 255) / 256;
         const double cost = flop_us * static_cast<double>(rounds * 256) / static_cast<double>(wgs) + slice_us * c;
         if (cost < best * (1 - 1e-9)) { best = cost; s = c; }
