@@ -450,7 +450,8 @@ grass_status grass_adam_scatter_replayable(const float* GC, int64_t ldgc, void* 
  * while no other thread is inside the library, and query workspaces after setting them.
  *   GRASS_TEST_GEMM_TILE     128, 256 or 192 (128 rows x 256 columns): the matrix-multiply tile
  *                            (the larger ones still fall back to 128 where alignment or size
- *                            rules them out); fp32 inputs: 64, or 128 for any other value
+ *                            rules them out); fp32 inputs: 64 or 128 (operands split into bf16
+ *                            parts; 128 for any other value), 16 (the fp32 matrix instruction)
  *   GRASS_TEST_FUSED_STATS   1: grass_grad_row_stats takes the squares in the GEMM epilogue
  *                            whenever the shape allows, not only when the tiles fill the machine
  *   GRASS_TEST_PACK_MXT      1: dY stored m x T goes through the packing pass instead of the

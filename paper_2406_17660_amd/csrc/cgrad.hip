@@ -21,7 +21,8 @@
 //   3. reduce: sums the split-K partials in a fixed order (deterministic), applies rho and
 //              converts to the output dtype; in a regular step this, Adam and the update of
 //              the rows of W are one kernel that reads the partial tiles directly.
-// fp32 path: the same three stages on the fp32 matrix instruction, without the pack (gemm_f32.hpp).
+// fp32 path: the same three stages without the pack, on operands split into bf16 parts or, for small
+// products, on the fp32 matrix instruction (gemm_f32_split.hpp, gemm_f32.hpp).
 #include <atomic>
 
 #include "common.hpp"
@@ -34,6 +35,7 @@
 #include "gemm_mid.hpp"
 #include "gemm_gather_narrow.hpp"
 #include "gemm_f32.hpp"
+#include "gemm_f32_split.hpp"
 #include "reduce_kernels.hpp"
 
 namespace grass {
@@ -245,79 +247,94 @@ NarrowPlan narrow_plan(int64_t T, int64_t n, int tiles_m, int64_t panel_rows, in
     return p;
 }
 
-// ---- fp32 inputs (gemm_f32.hpp)
+// ---- fp32 inputs (gemm_f32_split.hpp, gemm_f32.hpp)
+enum class F32Kernel { kSplit, kMfma };
 struct F32Plan {
+    F32Kernel kernel;
     int bm;  // tile edge
     int64_t Mp, Np;
     int tiles_m, tiles_n, splits, ktiles_per_split;
 };
 constexpr int64_t kF32SplitMinT = 1024;
-// `rows`: the sets' row counts.  K is split where that pays: with W = tiles x slices workgroups
-// the product takes 2 T rows n / 150 TFLOP/s over the filled share of the machine's rounds, and a
-// slice of partial tiles costs 8 bytes per output element at 4 TB/s.  Each slice keeps at least
-// four K tiles.  The 128 tile from 256 workgroups of 256 tokens on (1024 x 1024, r = 256, T = 8192:
-// 62 against 68 us; 512 x 1376, r = 128, T = 4096: 36 against 35; 2048 x 2048, r = 256, T = 1024:
-// 35 against 27), unless it wastes more than a quarter of itself on padding.  A call without a fused tail (`step` false) of fewer than 1024 tokens is not split,
-// so that it needs no workspace: its K loop is short.
-F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, bool step, size_t cap_bytes) {
-    F32Plan p;
-    int64_t total = 0, t128 = 0, t64 = 0;
-    for (int i = 0; i < count; ++i) {
-        total += (rows[i] + 7) / 8 * 8;
-        t128 += (rows[i] + 127) / 128;
-        t64 += (rows[i] + 63) / 64;
+// Which kernel: the fp32 instruction below 0.3 Gflop, where starting up is what costs (680 x 288, r = 42,
+// T = 1856: 12.8 against 16.7 us with split operands, 959 x 1928, r = 119, T = 448, 0.2 Gflop: 15.9 and 17.4,
+// 1112 x 1056, r = 278, T = 432, 0.25 Gflop: 16.5 both; 1800 x 1356, r = 450, T = 320, 0.39 Gflop: 22.5 and
+// 20.9); split operands beyond.
+F32Kernel f32_kernel(int64_t T, const int64_t* rows, int count, int64_t n) {
+    switch (test_option(GRASS_TEST_GEMM_TILE)) {
+        case 0: break;
+        case 16: return F32Kernel::kMfma;
+        default: return F32Kernel::kSplit;
     }
-    const int64_t n128 = (n + 127) / 128, n64 = (n + 63) / 64;
-    const int forced = test_option(GRASS_TEST_GEMM_TILE);
-    p.bm = forced ? (forced == 64 ? 64 : 128) : (t128 * n128 * 4 <= t64 * n64 * 1.25 && t128 * n128 * (T / 256) >= 256 ? 128 : 64);
-    const int64_t tm = p.bm == 128 ? t128 : t64, tn = p.bm == 128 ? n128 : n64;
-    p.tiles_m = static_cast<int>(tm);
-    p.tiles_n = static_cast<int>(tn);
-    p.Mp = total;
-    p.Np = tn * p.bm;
-    const int64_t ktiles = (T + kF32BK - 1) / kF32BK, tiles = tm * tn;
-    const int64_t slice_bytes = p.Mp * p.Np * 4;
-    const int64_t room = slice_bytes > 0 ? static_cast<int64_t>(cap_bytes) / slice_bytes : 1;
-    int64_t smax = ktiles / 4;
-    if (smax > 128) smax = 128;
-    if (!step && T < kF32SplitMinT) smax = 1;
-    if (const int cap = test_option(GRASS_TEST_MAX_K_SLICES)) smax = cap > 0 && cap < smax ? cap : smax;
-    const double flop_us = 2.0 * static_cast<double>(T) * tiles * p.bm * p.bm / 150e6;
-    const double slice_us = static_cast<double>(slice_bytes) * 2 / 4e6;
-    int64_t s = 1;
+    int64_t total = 0;
+    for (int i = 0; i < count; ++i) total += rows[i];
+    return 2.0 * static_cast<double>(T) * static_cast<double>(total) * static_cast<double>(n) < 0.3e9 ? F32Kernel::kMfma
+                                                                                                     : F32Kernel::kSplit;
+}
+// `rows`: the sets' row counts.  Tile and K slices are those of least estimated time.  Split operands: a
+// workgroup (one per compute unit) takes its slice in turns of two K tiles, and a turn takes so long.
+// Columns gathered one by one cost the 64 tile more than its arithmetic does.  Measured per step, 128 / 64
+// tile at the best slice count of each: 1024 x 1024, r = 256, T = 8192: 42 / 56 us (39 / 45 with dY stored
+// m x T); 2048 x 2048, r = 256, T = 1024: 26 / 29 (22 / 20); 2048 x 512, r = 512, T = 512: 19 / 16 (18 /
+// 15); 768 x 2000, r = 48, T = 8192: 40 / 44 (35 / 27).  The fp32 instruction: 150 TFLOP/s over the filled
+// share of the machine's rounds.  A slice of partial tiles costs 8 bytes per output element at 4 TB/s, and
+// every slice keeps at least four K tiles.  A call without a fused tail (`step` false) of fewer than 1024
+// tokens is not split, so that it needs no workspace: its K loop is short.
+constexpr double f32_turn_us(int bm, bool mxt) { return bm == 128 ? (mxt ? 1.2 : 1.4) : (mxt ? 1.1 : 1.6); }
+F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_layout layout, bool step,
+                 size_t cap_bytes) {
+    const F32Kernel kernel = f32_kernel(T, rows, count, n);
+    F32Plan best_plan{kernel, 64, 0, 0, 0, 0, 1, 1};  // an empty product
     double best = 1e300;
-    for (int64_t c = 1; c <= smax && tiles > 0; ++c) {
-        // slices of whole K tiles: the room must hold those that remain (a workspace of the size that
-        // the unlimited plan asks for then gives that plan again)
-        if (c > room) {
-            const int64_t per = (ktiles + c - 1) / c;
-            if ((ktiles + per - 1) / per > room) break;
+    const int forced = test_option(GRASS_TEST_GEMM_TILE);
+    for (const int bm : {128, 64}) {
+        if (kernel == F32Kernel::kMfma ? bm != kF32Tile : forced && bm != (forced == 64 ? 64 : 128)) continue;
+        int64_t total = 0, tm = 0;
+        for (int i = 0; i < count; ++i) {
+            total += (rows[i] + 7) / 8 * 8;
+            tm += (rows[i] + bm - 1) / bm;
         }
-        const int64_t wgs = tiles * c, rounds = (wgs + 255) / 256;
-        const double cost = flop_us * static_cast<double>(rounds * 256) / static_cast<double>(wgs) + slice_us * c;
-        if (cost < best * (1 - 1e-9)) { best = cost; s = c; }
+        const int64_t tn = (n + bm - 1) / bm;
+        F32Plan p;
+        p.kernel = kernel;
+        p.bm = bm;
+        p.tiles_m = static_cast<int>(tm);
+        p.tiles_n = static_cast<int>(tn);
+        p.Mp = total;
+        p.Np = tn * bm;
+        const int64_t bk = kernel == F32Kernel::kSplit ? f32_bk(bm) : kF32BK, ktiles = (T + bk - 1) / bk, tiles = tm * tn;
+        const int64_t slice_bytes = p.Mp * p.Np * 4;
+        const int64_t room = slice_bytes > 0 ? static_cast<int64_t>(cap_bytes) / slice_bytes : 1;
+        int64_t smax = ktiles / 4;
+        if (smax > 128) smax = 128;
+        if (smax < 1 || (!step && T < kF32SplitMinT)) smax = 1;
+        if (const int cap = test_option(GRASS_TEST_MAX_K_SLICES)) smax = cap > 0 && cap < smax ? cap : smax;
+        const double slice_us = static_cast<double>(slice_bytes) * 2 / 4e6;
+        const double tile_us = 2.0 * static_cast<double>(T) * bm * bm / 150e6;  // on the whole machine
+        for (int64_t c = 1; c <= smax && tiles > 0; ++c) {
+            // slices of whole K tiles: the room must hold those that remain (a workspace of the size that
+            // the unlimited plan asks for then gives that plan again)
+            const int64_t per = (ktiles + c - 1) / c > 0 ? (ktiles + c - 1) / c : 1, slices = (ktiles + per - 1) / per;
+            if (c > 1 && c > room && slices > room) break;
+            const double rounds = static_cast<double>((tiles * c + 255) / 256);
+            double cost = slice_us * static_cast<double>(c);
+            if (kernel == F32Kernel::kMfma) cost += tile_us * rounds * 256 / static_cast<double>(c);
+            else cost += rounds * static_cast<double>((per + 1) / 2) * f32_turn_us(bm, layout == GRASS_DY_MxT) + (bm == 128 ? 3 : 0);
+            if (cost < best * (1 - 1e-9)) {
+                best = cost;
+                p.ktiles_per_split = static_cast<int>(per);
+                p.splits = slices > 0 ? static_cast<int>(slices) : 1;
+                best_plan = p;
+            }
+        }
     }
-    p.ktiles_per_split = static_cast<int>((ktiles + s - 1) / s);
-    if (p.ktiles_per_split < 1) p.ktiles_per_split = 1;
-    p.splits = static_cast<int>((ktiles + p.ktiles_per_split - 1) / p.ktiles_per_split);
-    if (p.splits < 1) p.splits = 1;
-    return p;
+    return best_plan;
 }
 // Workspace for the partial tiles of a product that is planned without a limit.
-size_t f32_partial_bytes(int64_t T, const int64_t* rows, int count, int64_t n, bool step) {
-    const F32Plan p = f32_plan(T, rows, count, n, step, ~size_t{0} >> 1);
+size_t f32_partial_bytes(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_layout layout, bool step) {
+    const F32Plan p = f32_plan(T, rows, count, n, layout, step, ~size_t{0} >> 1);
     if (p.splits == 1 && !step) return 0;
     return static_cast<size_t>(p.splits) * p.Mp * p.Np * 4 + 256;
-}
-
-template <int BM>
-void launch_f32_kernel(const F32Args& a, bool vec_a, bool vec_b, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    const int64_t items = static_cast<int64_t>(a.tiles_m) * a.tiles_n * a.splits;
-    const dim3 grid(static_cast<unsigned>((items + kNumXcd - 1) / kNumXcd * kNumXcd)), block(256);
-    if (vec_a && vec_b) launch_stamped(tn_gemm_f32_mfma_kernel<BM, true, true>, grid, block, 0, s, e0, e1, a);
-    else if (vec_a) launch_stamped(tn_gemm_f32_mfma_kernel<BM, true, false>, grid, block, 0, s, e0, e1, a);
-    else if (vec_b) launch_stamped(tn_gemm_f32_mfma_kernel<BM, false, true>, grid, block, 0, s, e0, e1, a);
-    else launch_stamped(tn_gemm_f32_mfma_kernel<BM, false, false>, grid, block, 0, s, e0, e1, a);
 }
 
 // More than 64 KB of dynamic LDS has to be asked for, per kernel and device; the attribute sticks for
@@ -325,13 +342,33 @@ void launch_f32_kernel(const F32Args& a, bool vec_a, bool vec_b, hipStream_t s, 
 // after the attribute call has returned; two first callers both make the call.  `which`: a number
 // per kernel.
 hipError_t raise_lds_limit(const void* kernel, int bytes, int which) {
-    static std::atomic<bool> raised[2][64];
+    static std::atomic<bool> raised[6][64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
     if (dev >= 0 && dev < 64 && raised[which][dev].load(std::memory_order_acquire)) return hipSuccess;
     const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e == hipSuccess && dev >= 0 && dev < 64) raised[which][dev].store(true, std::memory_order_release);
     return e;
+}
+
+void launch_f32_mfma(const F32Args& a, bool vec_a, bool vec_b, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const int64_t items = static_cast<int64_t>(a.tiles_m) * a.tiles_n * a.splits;
+    const dim3 grid(static_cast<unsigned>((items + kNumXcd - 1) / kNumXcd * kNumXcd)), block(256);
+    if (vec_a && vec_b) launch_stamped(tn_gemm_f32_mfma_kernel<true, true>, grid, block, 0, s, e0, e1, a);
+    else if (vec_a) launch_stamped(tn_gemm_f32_mfma_kernel<true, false>, grid, block, 0, s, e0, e1, a);
+    else if (vec_b) launch_stamped(tn_gemm_f32_mfma_kernel<false, true>, grid, block, 0, s, e0, e1, a);
+    else launch_stamped(tn_gemm_f32_mfma_kernel<false, false>, grid, block, 0, s, e0, e1, a);
+}
+
+template <int BM, bool kMxT>
+hipError_t launch_f32_split(const F32Args& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(tn_gemm_f32_split_kernel<BM, kMxT>),
+                                         kF32LdsBytes, 2 + (BM == 128 ? 2 : 0) + (kMxT ? 1 : 0));
+    if (e != hipSuccess) return e;
+    const int64_t items = static_cast<int64_t>(a.tiles_m) * a.tiles_n * a.splits;
+    const dim3 grid(static_cast<unsigned>((items + kNumXcd - 1) / kNumXcd * kNumXcd)), block(kF32Threads);
+    launch_stamped(tn_gemm_f32_split_kernel<BM, kMxT>, grid, block, kF32LdsBytes, s, e0, e1, a);
+    return hipSuccess;
 }
 
 template <typename Cfg, bool kDense, bool kAnyAlign>
@@ -446,7 +483,7 @@ size_t narrow_cap_bytes(int64_t T, int64_t rows, int64_t n) {
 
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
                             grass_dy_layout layout, bool gathered) {
-    if (dt == GRASS_F32) return f32_partial_bytes(T, &mrows, 1, n, false);
+    if (dt == GRASS_F32) return f32_partial_bytes(T, &mrows, 1, n, layout, false);
     // The launcher may plan for the small tile where the large one cannot be used, and run either plan
     // with any tile: room for the larger number of slices and the widest padding.
     const KSplit k1 = split_k(kTile128, T, mrows, n), k2 = split_k(kTile256, T, mrows, n);
@@ -482,7 +519,7 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
     if (dt == GRASS_F32) {
         int64_t each[GRASS_MAX_GROUP];  // the sets taken to be of equal size
         for (int i = 0; i < count; ++i) each[i] = rows / count;
-        const F32Plan p = f32_plan(T, each, count, n, false, ~size_t{0} >> 1);
+        const F32Plan p = f32_plan(T, each, count, n, layout, false, ~size_t{0} >> 1);
         *tile = p.bm;
         *k_slices = p.splits;
         return;
@@ -506,7 +543,7 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
 
 size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int64_t n,
                                   grass_dtype dt, grass_dy_layout layout, bool step) {
-    if (dt == GRASS_F32) return f32_partial_bytes(T, rows, count, n, step);
+    if (dt == GRASS_F32) return f32_partial_bytes(T, rows, count, n, layout, step);
     int64_t total = 0;
     size_t need = 0;  // the sets may also be run one at a time
     for (int i = 0; i < count; ++i) {
@@ -624,12 +661,13 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         char* base = static_cast<char*>(ws);
         const size_t skip = base ? (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256 : 0;
         const size_t cap = base && ws_bytes > skip ? ws_bytes - skip : 0;
-        const F32Plan p = f32_plan(T, rows, count, n, tails, cap);
+        const F32Plan p = f32_plan(T, rows, count, n, layout, tails, cap);
         // partial tiles whenever something reads them: several slices, or a fused tail (which takes
         // the sums from there); a workspace that cannot hold even one slice leaves the direct form
         const bool partial = (p.splits > 1 || tails) &&
                              static_cast<size_t>(p.splits) * p.Mp * p.Np * 4 <= cap;
         F32Args a;
+        a.exact = ldx >= kF32MaxStride;
         bool vec_a = layout == GRASS_DY_TxM;
         int64_t off = 0;
         int tile0 = 0;
@@ -637,6 +675,8 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
             const GemmSegment& q = seg[i];
             a.set[i] = F32Set{static_cast<const float*>(q.dY), q.ldy, q.idx, q.rho, q.C, q.ldc, q.rows, off, tile0};
             vec_a = vec_a && !q.idx && aligned_to(q.dY, 16) && q.ldy % 4 == 0 && q.rows % 4 == 0;
+            a.exact |= layout == GRASS_DY_TxM ? q.ldy >= kF32MaxStride
+                                              : (q.idx ? q.src_rows : q.rows) * q.ldy >= (int64_t{1} << 30) - 64;
             off += (q.rows + 7) / 8 * 8;
             tile0 += static_cast<int>((q.rows + p.bm - 1) / p.bm);
         }
@@ -649,9 +689,15 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         a.c_bf16 = odt == GRASS_BF16;
         a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
         a.splits = p.splits; a.ktiles_per_split = p.ktiles_per_split;
-        const bool vec_b = aligned_to(X, 16) && ldx % 4 == 0 && n % 4 == 0;
-        if (p.bm == 128) launch_f32_kernel<128>(a, vec_a, vec_b, s, ev_start, ev_stop);
-        else launch_f32_kernel<64>(a, vec_a, vec_b, s, ev_start, ev_stop);
+        hipError_t le = hipSuccess;
+        if (p.kernel == F32Kernel::kMfma)
+            launch_f32_mfma(a, vec_a, aligned_to(X, 16) && ldx % 4 == 0 && n % 4 == 0, s, ev_start, ev_stop);
+        else if (p.kernel == F32Kernel::kSplit)
+            le = p.bm == 128 ? (a.mxt ? launch_f32_split<128, true>(a, s, ev_start, ev_stop)
+                                      : launch_f32_split<128, false>(a, s, ev_start, ev_stop))
+                             : (a.mxt ? launch_f32_split<64, true>(a, s, ev_start, ev_stop)
+                                      : launch_f32_split<64, false>(a, s, ev_start, ev_stop));
+        if (le != hipSuccess) return GRASS_ERR_DEVICE;
         if (partial)
             return finish_segments(seg, count, a.P, p.splits, p.Mp, p.Np, n, odt, s, ev_tail_start, ev_tail_stop);
         if (ev_tail_start) (void)hipEventRecord(ev_tail_start, s);

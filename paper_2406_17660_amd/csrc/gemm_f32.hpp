@@ -18,14 +18,10 @@ namespace {
 // reads them once more from L2), which costs less than a packing pass would.  dY stored m x T is
 // read the same way, lane = row: 16 consecutive t share a cache line through L1.
 //
-// BM = BN = 64: four wavefronts of 32 x 32; BM = BN = 128: four of 64 x 64 (half the operand
-// traffic per flop, for products with enough tiles).
-//
-// Measured (MI355X): 2048 x 2048, T = 8192: 115 TFLOP/s dense, 90 with 2048 of 8192 columns
-// gathered (the gather's address processing is what is left).  Steps of whole layers, against the
-// vector-ALU kernel this one replaced: 1024 x 1024, r = 256, T = 8192 1535 -> 62 us (64-wide tile
-// 68); 256 x 256, r = 16, T = 512 77 -> 16 us, of which the kernels are less than half.
-constexpr int kF32BK = 16, kF32Stages = 4;
+// Four wavefronts of 32 x 32 on a 64 x 64 tile.  Small products only: it starts 3 - 4 us sooner than the
+// kernel with split operands (gemm_f32_split.hpp), which is up to 1.75 times as fast on large ones; the
+// line between them is in f32_kernel().
+constexpr int kF32Tile = 64, kF32BK = 16, kF32Stages = 4;
 
 struct F32Set {
     const float* dY;
@@ -47,6 +43,7 @@ struct F32Args {
     int64_t Mp, Np;
     int mxt;             // dY stored m x T
     int c_bf16;          // direct output in bf16
+    int exact;           // 1: the fp32 instruction from the start (row strides past 32-bit offsets)
     int tiles_m, tiles_n, splits, ktiles_per_split;
 };
 
@@ -59,9 +56,9 @@ __device__ __forceinline__ void load4_to_lds(const void* lane_addr, uint32_t lds
 }
 
 // kVecA: dense left operand (no idx, T x m), 16-byte loads; kVecB: 16-byte loads of X.
-template <int BM, bool kVecA, bool kVecB>
-__global__ __launch_bounds__(256, BM == 64 ? 4 : 2) void tn_gemm_f32_mfma_kernel(F32Args g) {
-    constexpr int BN = BM, BK = kF32BK, F = BM / 64;  // F x F fragments of 32 x 32 per wavefront
+template <bool kVecA, bool kVecB>
+__global__ __launch_bounds__(256, 4) void tn_gemm_f32_mfma_kernel(F32Args g) {
+    constexpr int BM = kF32Tile, BN = kF32Tile, BK = kF32BK, F = BM / 64;  // F x F fragments of 32 x 32 per wavefront
     constexpr int kOperand = BK * BM;                 // floats of one operand of one stage
     constexpr int kLoadsA = kVecA ? F : 4 * F, kLoadsB = kVecB ? F : 4 * F, kLoads = kLoadsA + kLoadsB;
     __shared__ __attribute__((aligned(1024))) float ring[kF32Stages * 2 * kOperand];

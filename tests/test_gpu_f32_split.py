@@ -1,0 +1,74 @@
+"""GPU parity of the two fp32 products: operands split into bf16 parts (tiles 64 and 128) and the fp32 matrix
+instruction (forced as 16), each against the fp64 oracle or a wider sum.
+
+Bound for normal inputs: see test_gpu_f32.py (TOL_F32)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_17660_amd import grass
+from gpu_util import DEV, TOL_F32, rel_fro, to_f64, to_np
+from test_gpu_f32 import _inputs, _want
+
+pytestmark = pytest.mark.gpu
+KERNELS = [16, 64, 128]
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
+@pytest.mark.parametrize("layout", [grass.DY_TxM, grass.DY_MxT])
+@pytest.mark.parametrize("T,m,n,r", [
+    (1, 3, 2, 2), (31, 40, 33, 32), (33, 64, 31, 33), (257, 70, 65, 5), (511, 90, 97, 65), (1055, 130, 129, 40)])
+def test_every_kernel_at_edges(kernel, layout, T, m, n, r):
+    """Ragged tokens, rows and columns, odd numbers of K tiles (one half of a slice then has a turn less),
+    with as many slices as the workspace allows and with one."""
+    dY, X, idx, rho = _inputs(T, m, n, r, layout, seed=T)
+    want = _want(dY, X, idx, rho, layout)
+    grass.set_test_option(grass.TEST_GEMM_TILE, kernel)
+    for cap in (0, 1, 3):
+        grass.set_test_option(grass.TEST_MAX_K_SLICES, cap)
+        GC = torch.full((r, n), float("nan"), device=DEV)
+        need = grass.cgrad_workspace(T, m, n, r, grass.F32, layout)
+        grass.compressed_grad(dY, X, idx, rho, GC, grass.workspace(need) if need else None, layout)
+        assert rel_fro(to_np(GC), want) <= TOL_F32
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
+@pytest.mark.parametrize("low,high", [(-149, -130), (-140, -100), (-102, -98), (-130, 20), (100, 127)])
+def test_magnitudes_that_bf16_parts_do_not_hold(kernel, low, high):
+    """Values between 2^low and 2^high.  A sum of T products is off by at most T * 2^-24 of the sum of
+    their magnitudes, and by half a subnormal step per addition."""
+    T, m, n = 200, 40, 36
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    e = torch.rand((T, m), generator=g, device=DEV, dtype=torch.float64) * (high - low) + low
+    sign = torch.randint(0, 2, (T, m), generator=g, device=DEV) * 2 - 1
+    dY = (sign * 2.0 ** e).float()
+    X = (torch.randn((T, n), generator=g, device=DEV) * 2.0 ** (10 - (high if high > 0 else low) / 2)).float()
+    grass.set_test_option(grass.TEST_GEMM_TILE, kernel)
+    G = torch.full((m, n), float("nan"), device=DEV)
+    grass.dense_grad(dY, X, G, grass.workspace(max(16, grass.dense_workspace(T, m, n, grass.F32))))
+    want = dY.double().t() @ X.double()
+    bound = T * 2.0 ** -24 * (dY.double().abs().t() @ X.double().abs()) + T * 2.0 ** -149
+    assert bool(((G.double() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
+def test_infinities_and_nan_stay_where_they_belong(kernel):
+    """An output is not finite exactly where the product of its own column and row is not; the largest
+    finite values (which round to an infinite bf16) stay finite."""
+    T, m, n = 70, 40, 37
+    g = torch.Generator(device=DEV)
+    g.manual_seed(2)
+    dY, X = torch.rand((T, m), generator=g, device=DEV) + 0.5, torch.rand((T, n), generator=g, device=DEV) * 1e-3 + 1e-3
+    big = torch.finfo(torch.float32).max
+    dY[3, 1], dY[69, 2], dY[5, 3], dY[7, 4], dY[:, 5] = float("inf"), -float("inf"), float("nan"), big, 0.0
+    X[4, 6], X[3, 7] = float("inf"), 0.0
+    grass.set_test_option(grass.TEST_GEMM_TILE, kernel)
+    G = torch.empty((m, n), device=DEV)
+    grass.dense_grad(dY, X, G, grass.workspace(max(16, grass.dense_workspace(T, m, n, grass.F32))))
+    want = (dY.double().cpu().t() @ X.double().cpu()).numpy()
+    got = to_f64(G)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    fine = np.isfinite(want)
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    assert np.abs(got[fine] / np.where(want[fine] == 0, 1, want[fine]) - (want[fine] != 0)).max() <= T * 2.0 ** -24
