@@ -183,7 +183,7 @@ grass_status grass_compressed_grad(const void* dY, grass_dy_layout layout, int64
  * one matrix), `rows` rows in all (r for one matrix; for a group call the sum of its r[i], each
  * rounded up to a multiple of 8; the sets are taken to be of equal size), m the row length of
  * dY (0: not given).  `*tile` receives the edge of the output tile that the slices are
- * planned for (256 or 128; for fp32 inputs 128 or 64; the kernel may run with another tile where
+ * planned for (256 or 128; for fp32 inputs 128 or 64, or 64 for the smaller tile of short products; the kernel may run with another tile where
  * that is faster, with the same sums), or 0 for narrow layers (bf16, T x m storage, m <= 512,
  * r <= 128 per set, n <= 512, T a multiple of 16), whose gather runs inside the matrix-multiply kernel (128 x 256 tiles, no
  * packed panel); `*k_slices` the number of slices the token dimension is split into (their
@@ -451,7 +451,8 @@ grass_status grass_adam_scatter_replayable(const float* GC, int64_t ldgc, void* 
  *   GRASS_TEST_GEMM_TILE     128, 256 or 192 (128 rows x 256 columns): the matrix-multiply tile
  *                            (the larger ones still fall back to 128 where alignment or size
  *                            rules them out); fp32 inputs: 64 or 128 (operands split into bf16
- *                            parts; 128 for any other value), 16 (the fp32 matrix instruction)
+ *                            parts; 128 for any other value), 16 (the fp32 matrix instruction),
+ *                            32 (short products)
  *   GRASS_TEST_FUSED_STATS   1: grass_grad_row_stats takes the squares in the GEMM epilogue
  *                            whenever the shape allows, not only when the tiles fill the machine
  *   GRASS_TEST_PACK_MXT      1: dY stored m x T goes through the packing pass instead of the

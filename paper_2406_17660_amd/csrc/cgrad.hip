@@ -36,6 +36,7 @@
 #include "gemm_gather_narrow.hpp"
 #include "gemm_f32.hpp"
 #include "gemm_f32_split.hpp"
+#include "gemm_f32_short.hpp"
 #include "reduce_kernels.hpp"
 
 namespace grass {
@@ -247,8 +248,8 @@ NarrowPlan narrow_plan(int64_t T, int64_t n, int tiles_m, int64_t panel_rows, in
     return p;
 }
 
-// ---- fp32 inputs (gemm_f32_split.hpp, gemm_f32.hpp)
-enum class F32Kernel { kSplit, kMfma };
+// ---- fp32 inputs (gemm_f32_split.hpp, gemm_f32.hpp, gemm_f32_short.hpp)
+enum class F32Kernel { kSplit, kMfma, kShort };
 struct F32Plan {
     F32Kernel kernel;
     int bm;  // tile edge
@@ -256,18 +257,25 @@ struct F32Plan {
     int tiles_m, tiles_n, splits, ktiles_per_split;
 };
 constexpr int64_t kF32SplitMinT = 1024;
-// Which kernel: the fp32 instruction below 0.3 Gflop, where starting up is what costs (680 x 288, r = 42,
-// T = 1856: 12.8 against 16.7 us with split operands, 959 x 1928, r = 119, T = 448, 0.2 Gflop: 15.9 and 17.4,
-// 1112 x 1056, r = 278, T = 432, 0.25 Gflop: 16.5 both; 1800 x 1356, r = 450, T = 320, 0.39 Gflop: 22.5 and
-// 20.9); split operands beyond.
+// Which kernel: the one of short products where all sets are single row tiles and K is short enough for
+// one workgroup per tile (256 x 256, r = 16, T = 512: 9.0 us in one launch; 6.4 + 3.8 us and the gap between
+// them with the fp32 instruction; at T = 4096 47 us against 13); the fp32
+// instruction below 0.3 Gflop, where starting up is what costs (680 x 288, r = 42, T = 1856: 12.8 against
+// 16.7 us with split operands, 959 x 1928, r = 119, T = 448, 0.2 Gflop: 15.9 and 17.4, 1112 x 1056, r = 278,
+// T = 432, 0.25 Gflop: 16.5 both; 1800 x 1356, r = 450, T = 320, 0.39 Gflop: 22.5 and 20.9); split operands beyond.
 F32Kernel f32_kernel(int64_t T, const int64_t* rows, int count, int64_t n) {
     switch (test_option(GRASS_TEST_GEMM_TILE)) {
         case 0: break;
         case 16: return F32Kernel::kMfma;
+        case kShortTile: return F32Kernel::kShort;
         default: return F32Kernel::kSplit;
     }
-    int64_t total = 0;
-    for (int i = 0; i < count; ++i) total += rows[i];
+    int64_t total = 0, most = 0;
+    for (int i = 0; i < count; ++i) {
+        total += rows[i];
+        most = rows[i] > most ? rows[i] : most;
+    }
+    if (most <= kShortTile && T <= 512) return F32Kernel::kShort;
     return 2.0 * static_cast<double>(T) * static_cast<double>(total) * static_cast<double>(n) < 0.3e9 ? F32Kernel::kMfma
                                                                                                      : F32Kernel::kSplit;
 }
@@ -287,8 +295,11 @@ F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_
     F32Plan best_plan{kernel, 64, 0, 0, 0, 0, 1, 1};  // an empty product
     double best = 1e300;
     const int forced = test_option(GRASS_TEST_GEMM_TILE);
-    for (const int bm : {128, 64}) {
-        if (kernel == F32Kernel::kMfma ? bm != kF32Tile : forced && bm != (forced == 64 ? 64 : 128)) continue;
+    for (const int bm : {128, 64, kShortTile}) {
+        if (kernel == F32Kernel::kShort ? bm != kShortTile
+            : kernel == F32Kernel::kMfma ? bm != kF32Tile
+                                         : bm == kShortTile || (forced && bm != (forced == 64 ? 64 : 128)))
+            continue;
         int64_t total = 0, tm = 0;
         for (int i = 0; i < count; ++i) {
             total += (rows[i] + 7) / 8 * 8;
@@ -307,7 +318,7 @@ F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_
         const int64_t room = slice_bytes > 0 ? static_cast<int64_t>(cap_bytes) / slice_bytes : 1;
         int64_t smax = ktiles / 4;
         if (smax > 128) smax = 128;
-        if (smax < 1 || (!step && T < kF32SplitMinT)) smax = 1;
+        if (smax < 1 || (!step && T < kF32SplitMinT) || kernel == F32Kernel::kShort) smax = 1;
         if (const int cap = test_option(GRASS_TEST_MAX_K_SLICES)) smax = cap > 0 && cap < smax ? cap : smax;
         const double slice_us = static_cast<double>(slice_bytes) * 2 / 4e6;
         const double tile_us = 2.0 * static_cast<double>(T) * bm * bm / 150e6;  // on the whole machine
@@ -333,7 +344,7 @@ F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_
 // Workspace for the partial tiles of a product that is planned without a limit.
 size_t f32_partial_bytes(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_layout layout, bool step) {
     const F32Plan p = f32_plan(T, rows, count, n, layout, step, ~size_t{0} >> 1);
-    if (p.splits == 1 && !step) return 0;
+    if (p.splits == 1 && !step && T < kF32SplitMinT) return 0;
     return static_cast<size_t>(p.splits) * p.Mp * p.Np * 4 + 256;
 }
 
@@ -520,7 +531,7 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
         int64_t each[GRASS_MAX_GROUP];  // the sets taken to be of equal size
         for (int i = 0; i < count; ++i) each[i] = rows / count;
         const F32Plan p = f32_plan(T, each, count, n, layout, false, ~size_t{0} >> 1);
-        *tile = p.bm;
+        *tile = p.bm == 128 ? 128 : 64;
         *k_slices = p.splits;
         return;
     }
@@ -689,6 +700,33 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         a.c_bf16 = odt == GRASS_BF16;
         a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
         a.splits = p.splits; a.ktiles_per_split = p.ktiles_per_split;
+        if (p.kernel == F32Kernel::kShort) {
+            F32StepArgs q{};
+            // one row tile per set, and nobody asks for the product's and the tail's own times
+            bool fused = tails && !ev_start && !ev_stop && !ev_tail_start && !ev_tail_stop;
+            for (int i = 0; i < count && fused; ++i) fused = seg[i].tail && !seg[i].tail->U && seg[i].rows <= kShortTile;
+            if (fused) {
+                for (int i = 0; i < count; ++i) {
+                    const StepTail& t = *seg[i].tail;
+                    q.set[i] = F32StepSet{t.M, t.V, t.W, t.ldw, seg[i].c_wanted ? static_cast<float*>(seg[i].C) : nullptr, seg[i].ldc};
+                }
+                const StepTail& t = *seg[0].tail;
+                q.adam = make_params(t.lr, t.beta1, t.beta2, t.eps, t.t, t.step_scalars);
+                q.alpha = t.alpha;
+                q.s_bf16 = t.sdt == GRASS_BF16;
+                q.w_bf16 = t.wdt == GRASS_BF16;
+            }
+            const int64_t tiles = static_cast<int64_t>(p.tiles_m) * p.tiles_n;
+            if (tiles > 0x7FFFFFFF) return GRASS_ERR_SHAPE;
+            const dim3 grid(static_cast<unsigned>(tiles)), block(kShortWaves * 64);
+            if (fused) {
+                if (a.mxt) tn_gemm_f32_short_kernel<true, true><<<grid, block, 0, s>>>(a, q);
+                else tn_gemm_f32_short_kernel<false, true><<<grid, block, 0, s>>>(a, q);
+                return launch_status();
+            }
+            if (a.mxt) launch_stamped(tn_gemm_f32_short_kernel<true, false>, grid, block, 0, s, ev_start, ev_stop, a, q);
+            else launch_stamped(tn_gemm_f32_short_kernel<false, false>, grid, block, 0, s, ev_start, ev_stop, a, q);
+        }
         hipError_t le = hipSuccess;
         if (p.kernel == F32Kernel::kMfma)
             launch_f32_mfma(a, vec_a, aligned_to(X, 16) && ldx % 4 == 0 && n % 4 == 0, s, ev_start, ev_stop);

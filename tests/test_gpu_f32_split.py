@@ -1,5 +1,5 @@
-"""GPU parity of the two fp32 products: operands split into bf16 parts (tiles 64 and 128) and the fp32 matrix
-instruction (forced as 16), each against the fp64 oracle or a wider sum.
+"""GPU parity of the three fp32 products: operands split into bf16 parts (tiles 64 and 128), the fp32 matrix
+instruction (forced as 16) and the short product (32), each against the fp64 oracle or a wider sum.
 
 Bound for normal inputs: see test_gpu_f32.py (TOL_F32)."""
 import numpy as np
@@ -11,7 +11,7 @@ from gpu_util import DEV, TOL_F32, rel_fro, to_f64, to_np
 from test_gpu_f32 import _inputs, _want
 
 pytestmark = pytest.mark.gpu
-KERNELS = [16, 64, 128]
+KERNELS = [16, 32, 64, 128]
 
 
 @pytest.mark.parametrize("kernel", KERNELS)
@@ -72,3 +72,32 @@ def test_infinities_and_nan_stay_where_they_belong(kernel):
     fine = np.isfinite(want)
     assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
     assert np.abs(got[fine] / np.where(want[fine] == 0, 1, want[fine]) - (want[fine] != 0)).max() <= T * 2.0 ** -24
+
+
+@pytest.mark.parametrize("sdt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("wdt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,n,rs,layout", [(512, 256, (16,), grass.DY_TxM), (100, 33, (32, 1, 7), grass.DY_TxM),
+                                           (17, 40, (31, 32), grass.DY_MxT)])
+def test_step_in_one_launch_equals_the_one_in_two(sdt, wdt, T, n, rs, layout):
+    """Adam and the row update inside the short product (runs of repeated rows, groups, G_C stored or not)
+    against the same step with events on its kernels, which runs them as two: bit for bit."""
+    m = 20
+    X = torch.randn(T, n, device=DEV)
+    sets = []
+    for k, r in enumerate(rs):
+        dY, _, idx, rho = _inputs(T, m, n, r, layout, seed=k)
+        sets.append((dY, idx, rho, torch.randn(r, n, device=DEV).to(sdt), torch.rand(r, n, device=DEV).to(sdt),
+                     torch.randn(m, n, device=DEV).to(wdt)))
+    ws = grass.workspace(grass.step_group_workspace(T, n, rs, grass.F32, layout))
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in events:
+        e.record()
+    results = []
+    for gemm_events in (None, events):
+        dYs, idxs, rhos, Ms, Vs, Ws = (list(t) for t in zip(*[(s[0], s[1], s[2], *(x.clone() for x in s[3:])) for s in sets]))
+        GCs = [torch.full((r, n), float("nan"), device=DEV) if k != 1 else None for k, r in enumerate(rs)]
+        grass.step_group(dYs, X, idxs, rhos, Ms, Vs, Ws, 1e-2, 0.9, 0.999, 1e-8, 3, 0.5, ws, layout, GCs=GCs,
+                         gemm_events=gemm_events)
+        results.append([*Ms, *Vs, *Ws, *(G for G in GCs if G is not None)])
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
