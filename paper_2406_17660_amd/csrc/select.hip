@@ -11,7 +11,7 @@
 //                   the r draws are independent: Philox word, 64x64 high multiply, binary
 //                   search; a per-row hit counter plus a scan emits idx sorted.
 //   without repl.   draws are sequential by definition.  Up to 16384 rows, prefix sums over
-//                   groups of 64 rows sit in one wavefront's registers and those of the rows
+//                   groups of 64 or 128 rows sit in one wavefront's registers and those of the rows
 //                   in LDS (a draw is two compares and one LDS read).  Beyond, a radix-64 sum
 //                   tree over the weights (in LDS when it fits in 144 KiB, else in the
 //                   workspace) lets the wavefront do a draw in log64(m) steps: 64 children per
@@ -592,12 +592,13 @@ __global__ __launch_bounds__(kThreads) void select_norepl_kernel(
 
 // The same draws for up to 16384 rows with fewer instructions from one draw to the next.  What
 // bounds sampling without replacement is that chain: draw j needs the weight that draw j - 1 took
-// out, one wavefront runs it, and a lone wavefront issues an instruction about every five clocks.
+// out, one wavefront runs it, and a lone wavefront issues an instruction every five to eight clocks.
 // The tree above spends an LDS round trip, a ballot and an update per level (three levels at
-// m = 13824: 0.40 us per draw).  Here the weights of 64 rows form a group whose inclusive prefix sums
-// lie in LDS, and the EXCLUSIVE prefix sums over the groups (at most 256) stay in E registers per lane:
+// m = 13824: 0.40 us per draw).  Here the weights of 64 R rows form a group whose inclusive prefix sums
+// lie in LDS (R consecutive rows per lane), and the EXCLUSIVE prefix sums over the groups (at most 64 E)
+// stay in E registers per lane:
 //   group   g = (number of groups whose prefix is <= target) - 1: E compares and bit counts
-//   row     f = number of rows of the group whose prefix is <= target - prefix(g): one compare
+//   row     f = number of rows of the group whose prefix is <= target - prefix(g): R of each
 //   weight  difference of neighbouring prefixes, formed by a lane shift
 //   update  the lanes that failed a compare are the ones that lose the weight
 // and the drawn rows are collected in a register and put into a bit map 64 at a time.
@@ -609,11 +610,14 @@ __global__ __launch_bounds__(kThreads) void select_norepl_kernel(
 // is within 2 of it, so unless a prefix lies within 4 (checked against every prefix compared) each
 // comparison falls as with the exact target floor(x S / 2^64); otherwise that is computed and used.
 // The rows drawn are those of the sequential integer definition in every case.
-// (Guessing the next draw's group a draw ahead, to hide the one LDS read, costs more instructions
-// than the read takes: 324 against 207 us at 4096 rows.)
-// Measured, 1024 draws from 13824 rows: 420 -> 263 us; 1024 from 4096: 286 -> 165 us.
-constexpr int kFlatMaxE = 4;
-constexpr int64_t kFlatMaxRows = 64 * kWave * kFlatMaxE;
+// E, R = 1, 1 up to 4096 rows, 1, 2 up to 8192 and 2, 2 up to 16384.  1024 draws take 128 us of 4096 rows,
+// 153 of 8192 and 177 of 13824; before the masks went into EXEC, four draws into a turn of the loop, the
+// weight ahead of the updates and two rows into a lane: 166, 188 and 264 (E, R = 1, 1; 2, 1; 4, 1), with the
+// three-level tree 286 of 4096 and 420 of 13824.  E, R = 2, 1 of 8192 rows and 4, 1 of 13824 in the present
+// form: 153 and 204.  (Guessing the next draw's group a draw ahead, to hide the one LDS read, costs more
+// instructions than the read takes; forming the next target in every lane before the drawn one is known
+// saves a multiplication and costs two reads of a lane: 160 against 153.)
+constexpr int64_t kFlatMaxRows = int64_t{4} * kWave * kWave;
 
 // v of the lane below, 0 in lane 0
 __device__ __forceinline__ unsigned long long from_lane_below(unsigned long long v) {
@@ -625,63 +629,122 @@ __device__ __forceinline__ unsigned long long from_lane_below(unsigned long long
 __device__ __forceinline__ double from_lane_below(double v) {
     return __longlong_as_double(static_cast<long long>(from_lane_below(static_cast<unsigned long long>(__double_as_longlong(v)))));
 }
-__device__ __forceinline__ unsigned long long read_lane(unsigned long long v, int l) { return read_lane64(v, l); }
 __device__ __forceinline__ double read_lane(double v, int l) {
     return __longlong_as_double(static_cast<long long>(read_lane64(static_cast<unsigned long long>(__double_as_longlong(v)), l)));
 }
 
-// Where a draw's target falls.  V is the type the prefixes are held in; gpre: a copy of pex in LDS
-// (with four registers per lane, picking the group's prefix out of them takes longer than
-// reading it beside the rows; with two it does not).  near: some boundary of the group lies within 4 of the target, the
-// only ones a target off by 2 could be on the wrong side of (a target put into the wrong group is
-// next to that group's edge).
-template <typename V, int E>
-struct Located {
-    int g, f;
-    V cur;
-    bool upto[E], below, near;
-};
-template <int E, typename V>
-__device__ __forceinline__ Located<V, E> locate(const V (&pex)[E], const V* gpre, const V* leaf, V target,
-                                                int groups, int lane) {
-    Located<V, E> q;
-    int n = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        q.upto[e] = pex[e] <= target;
-        n += __popcll(__ballot(q.upto[e]));
-    }
-    q.g = n < groups ? n - 1 : groups - 1;  // n >= 1: the first group's prefix is 0
-    q.cur = leaf[q.g * kWave + lane];
-    V before;
-    if (E > 2) {
-        before = gpre[q.g];
-    } else {
-        before = pex[0];
-        if (E > 1 && q.g >= kWave) before = pex[E - 1];
-        before = read_lane(before, q.g & (kWave - 1));
-    }
-    const V t = target - before;
-    q.below = q.cur <= t;
-    if constexpr (static_cast<V>(0.5) != static_cast<V>(0)) q.near = fmin(fabs(q.cur - t), t) < 4.0;
-    else q.near = false;
-    q.f = __popcll(__ballot(q.below));
-    return q;
-}
-// Takes the drawn row's weight out of its group, the groups after it and the total.
-template <int E, typename V>
-__device__ __forceinline__ void take_out(const Located<V, E>& q, V (&pex)[E], V* gpre, V* leaf, V& left, int lane) {
-    const V w = read_lane(q.cur - from_lane_below(q.cur), q.f);
-    leaf[q.g * kWave + lane] = q.cur - (q.below ? V(0) : w);  // the drawn row and those after it
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        pex[e] -= q.upto[e] ? V(0) : w;
-        if (E > 2) gpre[e * kWave + lane] = pex[e];
-    }
-    left -= w;
+// lane l of v becomes x (both the same for the whole wavefront)
+__device__ __forceinline__ void write_lane(int& v, int x, int l) {
+    asm("s_mov_b32 m0, %2\n\tv_writelane_b32 %0, %1, m0" : "+v"(v) : "s"(x), "s"(l) : "m0");
 }
 
-template <int E>
+// A draw in doubles.  pex[e]: the weight before group E * lane + e (infinite for groups that do not exist).
+// near: some boundary of the group lies within 4 of the target, the only ones a target off by 2 could be on
+// the wrong side of (a target put into the wrong group is next to that group's edge).
+template <int E, int R>
+struct Draw {
+    int n, f;  // group n - 1, row f of it
+    double cur[R], w;
+    unsigned long long upto[E], below[R];  // the lanes outside these masks lose the drawn weight
+    bool near;
+};
+template <int E, int R>
+__device__ __forceinline__ Draw<E, R> locate(const double (&pex)[E], const double* leaf, double target, int lane) {
+    Draw<E, R> q;
+    q.n = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        q.upto[e] = __ballot(pex[e] <= target);
+        q.n += __popcll(q.upto[e]);  // at least 1: the first group's prefix is 0
+    }
+    const double* src = leaf + (lane - kWave) * R + q.n * (kWave * R);
+#pragma unroll
+    for (int i = 0; i < R; ++i) q.cur[i] = src[i];
+    double before = pex[0];  // of the last of this lane's groups that starts at or before the target
+#pragma unroll
+    for (int e = 1; e < E; ++e) before = pex[e] <= target ? pex[e] : before;
+    before = read_lane(before, (__popcll(q.upto[0]) - 1) & (kWave - 1));
+    __builtin_amdgcn_sched_barrier(0);  // while the read is under way: nothing that waits for it moves up
+    double own = q.cur[0] - from_lane_below(q.cur[R - 1]);
+    const double t = target - before;
+    double least = t;
+    q.f = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        q.below[i] = __ballot(q.cur[i] <= t);
+        q.f += __popcll(q.below[i]);
+        if (i > 0) own = q.cur[i - 1] <= t ? q.cur[i] - q.cur[i - 1] : own;
+        least = fmin(fabs(q.cur[i] - t), least);
+    }
+    q.near = __ballot(least < 4.0) != 0;
+    q.w = read_lane(own, __popcll(q.below[R - 1]) & (kWave - 1));  // the first lane with a row past the target
+    return q;
+}
+// Takes w out of the drawn row's group (the row and those after it) and of the groups after its own.  All
+// 64 lanes are active before and after: with a mask in EXEC a subtraction is one vector instruction
+// instead of three (two selects and an addition).  The s_nop: w may come from the instruction just before,
+// a v_readlane, and a vector instruction may read a scalar register two wait states after one wrote it.
+template <int E, int R>
+__device__ __forceinline__ void take_out(Draw<E, R>& q, double (&pex)[E], double* leaf, int lane) {
+    static_assert(E <= R && R <= 2, "the forms below");
+    if constexpr (R == 1)
+        asm("s_not_b64 exec, %3\n\ts_nop 0\n\tv_add_f64 %0, %0, -%2\n\ts_not_b64 exec, %4\n\tv_add_f64 %1, %1, -%2\n\t"
+            "s_mov_b64 exec, -1"
+            : "+v"(pex[0]), "+v"(q.cur[0]) : "s"(q.w), "s"(q.upto[0]), "s"(q.below[0]) : "scc");
+    else if constexpr (E == 1)
+        asm("s_not_b64 exec, %4\n\ts_nop 0\n\tv_add_f64 %0, %0, -%3\n\ts_not_b64 exec, %5\n\tv_add_f64 %1, %1, -%3\n\t"
+            "s_not_b64 exec, %6\n\tv_add_f64 %2, %2, -%3\n\ts_mov_b64 exec, -1"
+            : "+v"(pex[0]), "+v"(q.cur[0]), "+v"(q.cur[1])
+            : "s"(q.w), "s"(q.upto[0]), "s"(q.below[0]), "s"(q.below[1]) : "scc");
+    else
+        asm("s_not_b64 exec, %5\n\ts_nop 0\n\tv_add_f64 %0, %0, -%4\n\ts_not_b64 exec, %6\n\tv_add_f64 %1, %1, -%4\n\t"
+            "s_not_b64 exec, %7\n\tv_add_f64 %2, %2, -%4\n\ts_not_b64 exec, %8\n\tv_add_f64 %3, %3, -%4\n\t"
+            "s_mov_b64 exec, -1"
+            : "+v"(pex[0]), "+v"(pex[1]), "+v"(q.cur[0]), "+v"(q.cur[1])
+            : "s"(q.w), "s"(q.upto[0]), "s"(q.upto[1]), "s"(q.below[0]), "s"(q.below[1]) : "scc");
+    double* dst = leaf + (lane - kWave) * R + q.n * (kWave * R);
+#pragma unroll
+    for (int i = 0; i < R; ++i) dst[i] = q.cur[i];
+}
+
+// The same draw in 64-bit integers; returns the row.
+template <int E, int R>
+__device__ __forceinline__ int draw_in_integers(unsigned long long (&pex)[E], unsigned long long* leaf,
+                                                unsigned long long& left, unsigned long long word, int groups, int lane) {
+    unsigned long long target = __umul64hi(word, left);
+    int n = 0, f = 0;
+    unsigned long long before = 0, cur[R];
+    bool upto[E], below[R];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        upto[e] = pex[e] <= target;
+        n += __popcll(__ballot(upto[e]));
+    }
+    const int g = n < groups ? n - 1 : groups - 1;  // groups that do not exist have the total as their prefix
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (g % E == e) before = read_lane64(pex[e], g / E);
+    target -= before;
+    unsigned long long* at = leaf + (g * kWave + lane) * R;
+#pragma unroll
+    for (int i = 0; i < R; ++i) cur[i] = at[i];
+    unsigned long long own = cur[0] - from_lane_below(cur[R - 1]);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        below[i] = cur[i] <= target;
+        f += __popcll(__ballot(below[i]));
+        if (i > 0) own = below[i - 1] ? cur[i] - cur[i - 1] : own;
+    }
+    const unsigned long long w = read_lane64(own, __popcll(__ballot(below[R - 1])));
+#pragma unroll
+    for (int i = 0; i < R; ++i) at[i] = cur[i] - (below[i] ? 0ull : w);
+#pragma unroll
+    for (int e = 0; e < E; ++e) pex[e] -= upto[e] ? 0ull : w;
+    left -= w;
+    return g * kWave * R + f;
+}
+
+template <int E, int R>
 __global__ __launch_bounds__(kThreads) void select_norepl_flat_kernel(
     const float* __restrict__ sumsq, int m, int r, int method, int rescale, unsigned long long seed,
     unsigned long long refresh, int32_t* __restrict__ idx, float* __restrict__ rho,
@@ -689,64 +752,86 @@ __global__ __launch_bounds__(kThreads) void select_norepl_flat_kernel(
     constexpr int kGroupsPerWave = E * kWave / kWaves;
     __shared__ Shared sh;
     __shared__ unsigned long long gsum[E * kWave];
-    __shared__ uint32_t chosen[E * kWave * 2];  // one bit per row
-    extern __shared__ unsigned long long leaf[];  // [groups][64] inclusive prefix sums, or their doubles
+    constexpr int kWords = E * R * kWave * 2;
+    __shared__ uint32_t chosen[kWords];  // one bit per row
+    extern __shared__ __attribute__((aligned(16))) unsigned long long leaf[];  // [groups][64 R] inclusive prefix sums, or their doubles
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int groups = (m + kWave - 1) / kWave;
+    const int groups = (m + kWave * R - 1) / (kWave * R);
 
-    float s[kGroupsPerWave], smax = 0.f;
+    float s[kGroupsPerWave][R], smax = 0.f;
     bool bad = false;
 #pragma unroll
-    for (int i = 0; i < kGroupsPerWave; ++i) {
-        const int k = (wave + i * kWaves) * kWave + lane;
-        s[i] = k < m ? sumsq[k] : 0.f;
-    }
+    for (int i = 0; i < kGroupsPerWave; ++i)
 #pragma unroll
-    for (int i = 0; i < kGroupsPerWave; ++i) {
-        bad |= is_bad(s[i]);
-        smax = s[i] > smax ? s[i] : smax;
-    }
+        for (int u = 0; u < R; ++u) {
+            const int k = ((wave + i * kWaves) * kWave + lane) * R + u;
+            s[i][u] = k < m ? sumsq[k] : 0.f;
+        }
+#pragma unroll
+    for (int i = 0; i < kGroupsPerWave; ++i)
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            bad |= is_bad(s[i][u]);
+            smax = s[i][u] > smax ? s[i][u] : smax;
+        }
     if (report_nonfinite(bad, m, r, idx, rho, status)) return;
     if (r == 0) return;  // nothing to select: only the status word is written
     // the weights are monotone in the statistic: the largest weight is that of the largest one
     const double wmax = weight_of(static_cast<float>(block_max(static_cast<double>(smax), &sh)), method);
-    unsigned long long prefix[kGroupsPerWave];
+    unsigned long long prefix[kGroupsPerWave][R];
 #pragma unroll
     for (int i = 0; i < kGroupsPerWave; ++i) {
-        const int g = wave + i * kWaves, k = g * kWave + lane;
-        prefix[i] = 0ull;  // groups that do not exist weigh nothing
-        if (g < groups) prefix[i] = wave_inclusive_scan(k < m ? quantise(weight_of(s[i], method), wmax) : 0ull);
-        if (lane == kWave - 1) gsum[g] = prefix[i];
-    }
-    for (int e = tid; e < E * kWave * 2; e += kThreads) chosen[e] = 0;
-    __syncthreads();
-    unsigned long long pex[E], total_w = 0;  // pex: weight before group e * 64 + lane
+        const int g = wave + i * kWaves;
+        if (g < groups) {  // (the same for the whole wavefront)
+            unsigned long long sum = 0;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const unsigned long long own = gsum[e * kWave + lane], incl = wave_inclusive_scan(own);
-        pex[e] = total_w + incl - own;
-        total_w += read_lane64(incl, kWave - 1);
+            for (int u = 0; u < R; ++u) {
+                const int k = (g * kWave + lane) * R + u;
+                sum += k < m ? quantise(weight_of(s[i][u], method), wmax) : 0ull;
+                prefix[i][u] = sum;
+            }
+            const unsigned long long before = wave_inclusive_scan(sum) - sum;
+#pragma unroll
+            for (int u = 0; u < R; ++u) prefix[i][u] += before;
+        } else {  // groups that do not exist weigh nothing
+#pragma unroll
+            for (int u = 0; u < R; ++u) prefix[i][u] = 0ull;
+        }
+        if (lane == kWave - 1) gsum[g] = prefix[i][R - 1];
+    }
+    for (int e = tid; e < kWords; e += kThreads) chosen[e] = 0;
+    __syncthreads();
+    unsigned long long pex[E], total_w;  // pex[e]: weight before group E * lane + e
+    {
+        unsigned long long own[E], lane_sum = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            own[e] = gsum[E * lane + e];
+            lane_sum += own[e];
+        }
+        const unsigned long long incl = wave_inclusive_scan(lane_sum);
+        total_w = read_lane64(incl, kWave - 1);
+        pex[0] = incl - lane_sum;
+#pragma unroll
+        for (int e = 1; e < E; ++e) pex[e] = pex[e - 1] + own[e - 1];
     }
     const bool in_doubles = total_w < (1ull << 53);
 #pragma unroll
     for (int i = 0; i < kGroupsPerWave; ++i) {
         const int g = wave + i * kWaves;
         if (g < groups)
-            leaf[g * kWave + lane] = in_doubles
-                ? static_cast<unsigned long long>(__double_as_longlong(static_cast<double>(prefix[i]))) : prefix[i];
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                leaf[(g * kWave + lane) * R + u] = in_doubles
+                    ? static_cast<unsigned long long>(__double_as_longlong(static_cast<double>(prefix[i][u]))) : prefix[i][u];
     }
     __syncthreads();
 
     if (wave == 0) {
         double* dleaf = reinterpret_cast<double*>(leaf);
-        double* dgpre = reinterpret_cast<double*>(gsum);  // the group sums have been used up
         double dpex[E], dleft = static_cast<double>(total_w);
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            dpex[e] = static_cast<double>(pex[e]);
-            if (in_doubles) dgpre[e * kWave + lane] = dpex[e];
-            else gsum[e * kWave + lane] = pex[e];
-        }
+        for (int e = 0; e < E; ++e) dpex[e] = E * lane + e < groups ? static_cast<double>(pex[e]) : __builtin_inf();
         unsigned long long left = total_w;
         for (int j0 = 0; j0 < r; j0 += kWave) {
             const unsigned long long words = draw_word(seed, refresh, j0 + lane);
@@ -754,26 +839,32 @@ __global__ __launch_bounds__(kThreads) void select_norepl_flat_kernel(
             const int count = __builtin_amdgcn_readfirstlane(r - j0 < kWave ? r - j0 : kWave);
             int rows = 0;  // lane jj: the row of draw j0 + jj
             if (in_doubles) {
-                for (int jj = 0; jj < count; ++jj) {
-                    auto q = locate<E>(dpex, dgpre, dleaf, dleft * read_lane(unit, jj), groups, lane);
-                    int row = q.g * kWave + q.f;
-                    if (!__ballot(q.near)) {
-                        take_out<E>(q, dpex, dgpre, dleaf, dleft, lane);
-                    } else {  // too close to a boundary to call: the exact target
+                double target = dleft * read_lane(unit, 0);
+                auto draw = [&](int jj) {
+                    const double next_unit = read_lane(unit, (jj + 1) & (kWave - 1));
+                    auto q = locate<E, R>(dpex, dleaf, target, lane);
+                    if (__builtin_expect(q.near, 0)) {  // too close to a boundary to call: the exact target
                         const unsigned long long exact =
                             __umul64hi(read_lane64(words, jj), static_cast<unsigned long long>(dleft));
-                        auto z = locate<E>(dpex, dgpre, dleaf, static_cast<double>(exact), groups, lane);
-                        take_out<E>(z, dpex, dgpre, dleaf, dleft, lane);
-                        row = z.g * kWave + z.f;
+                        q = locate<E, R>(dpex, dleaf, static_cast<double>(exact), lane);
                     }
-                    rows = lane == jj ? row : rows;
+                    // the next draw's target first: it is what the next draw begins with
+                    dleft -= q.w;
+                    target = dleft * next_unit;
+                    take_out<E, R>(q, dpex, dleaf, lane);
+                    write_lane(rows, (q.n - 1) * (kWave * R) + q.f, jj);
+                };
+                int jj = 0;
+                for (; jj + 4 <= count; jj += 4) {  // a taken branch costs a lone wavefront tens of clocks
+                    draw(jj);
+                    draw(jj + 1);
+                    draw(jj + 2);
+                    draw(jj + 3);
                 }
+                for (; jj < count; ++jj) draw(jj);
             } else {
-                for (int jj = 0; jj < count; ++jj) {
-                    auto q = locate<E>(pex, gsum, leaf, __umul64hi(read_lane64(words, jj), left), groups, lane);
-                    take_out<E>(q, pex, gsum, leaf, left, lane);
-                    rows = lane == jj ? q.g * kWave + q.f : rows;
-                }
+                for (int jj = 0; jj < count; ++jj)
+                    write_lane(rows, draw_in_integers<E, R>(pex, leaf, left, read_lane64(words, jj), groups, lane), jj);
             }
             if (lane < count) atomicOr(&chosen[rows >> 5], 1u << (rows & 31));
         }
@@ -781,8 +872,8 @@ __global__ __launch_bounds__(kThreads) void select_norepl_flat_kernel(
     __syncthreads();
 
     // emit the chosen rows in ascending order: every thread owns 32 consecutive rows
-    static_assert(E * kWave * 2 <= kThreads, "one word of the bit map per thread");
-    uint32_t bits = tid < E * kWave * 2 ? chosen[tid] : 0u, all;
+    static_assert(kWords <= kThreads, "one word of the bit map per thread");
+    uint32_t bits = tid < kWords ? chosen[tid] : 0u, all;
     uint32_t pos = block_exclusive_scan(static_cast<uint32_t>(__popc(bits)), &sh, all);
     while (bits) {
         const int k = tid * 32 + __ffs(bits) - 1;
@@ -829,17 +920,17 @@ size_t select_workspace_bytes(int64_t m, int64_t r, grass_method method, int rep
     return kHeaderBytes + tree_bytes(tree_shape(m));
 }
 
-template <int E>
+template <int E, int R>
 static grass_status launch_flat(const float* sumsq, int64_t m, int64_t r, grass_method method, int rescale,
                                 uint64_t seed, uint64_t refresh_id, int32_t* idx, float* rho,
                                 int32_t* status, hipStream_t s) {
-    const size_t bytes = static_cast<size_t>((m + kWave - 1) / kWave) * kWave * sizeof(unsigned long long);
+    const size_t bytes = static_cast<size_t>((m + kWave * R - 1) / (kWave * R)) * kWave * R * sizeof(unsigned long long);
     if (bytes > 48 * 1024 &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(select_norepl_flat_kernel<E>),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(select_norepl_flat_kernel<E, R>),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
                             static_cast<int>(kFlatMaxRows * sizeof(unsigned long long))) != hipSuccess)
         return GRASS_ERR_DEVICE;
-    select_norepl_flat_kernel<E><<<1, kThreads, bytes, s>>>(sumsq, static_cast<int>(m), static_cast<int>(r),
+    select_norepl_flat_kernel<E, R><<<1, kThreads, bytes, s>>>(sumsq, static_cast<int>(m), static_cast<int>(r),
                                                             method, rescale, seed, refresh_id, idx, rho, status);
     return launch_status();
 }
@@ -891,9 +982,10 @@ static grass_status launch_select_kernels(const float* sumsq, int64_t m, int64_t
         return launch_status();
     }
     if (m > 0 && m <= kFlatMaxRows) {
-        return m <= 64 * kWave ? launch_flat<1>(sumsq, m, r, method, rescale, seed, refresh_id, idx, rho, status, s)
-               : m <= 128 * kWave ? launch_flat<2>(sumsq, m, r, method, rescale, seed, refresh_id, idx, rho, status, s)
-                                  : launch_flat<4>(sumsq, m, r, method, rescale, seed, refresh_id, idx, rho, status, s);
+        return m <= kWave * kWave ? launch_flat<1, 1>(sumsq, m, r, method, rescale, seed, refresh_id, idx, rho, status, s)
+               : m <= 2 * kWave * kWave
+                   ? launch_flat<1, 2>(sumsq, m, r, method, rescale, seed, refresh_id, idx, rho, status, s)
+                   : launch_flat<2, 2>(sumsq, m, r, method, rescale, seed, refresh_id, idx, rho, status, s);
     }
     const TreeShape shape = tree_shape(m);
     const size_t bytes = tree_bytes(shape);

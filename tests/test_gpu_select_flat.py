@@ -42,3 +42,22 @@ def test_draws_match_the_oracle(m, method, law):
 def test_every_row_is_drawn_when_r_is_m(m):
     idx, rho, _ = gpu_select(torch.from_numpy(_statistic(m, "spread", 1)).to(DEV), m, grass.SEL_MULTI_NORM, False)
     assert np.array_equal(to_np(idx), np.arange(m)) and (to_np(rho) == 1).all()
+
+
+@pytest.mark.parametrize("m", [4097, 4224, 4225, 8191, 8319, 16257])
+@pytest.mark.parametrize("law", ["spread", "zeros", "equal"])
+def test_two_rows_per_lane_match_the_oracle(m, law):
+    """Groups of 128 rows: their edges, draws too close to a boundary for the rounded target (weights of 1)
+    and, with equal weights in 16257 rows, the total past 2^53."""
+    s = _statistic(m, law, m + 1)
+    r = min(m, 2500)
+    idx, rho, status = gpu_select(torch.from_numpy(s).to(DEV), r, grass.SEL_MULTI_NORM, False, grass.SCALE_INV_SQRT_RQ, seed=m)
+    want_idx, want_rho, _ = ref.select_rows(s, r, ref.MULTI_NORM, False, grass.SCALE_INV_SQRT_RQ, m, 0)
+    assert status == grass.OK and np.array_equal(to_np(idx), want_idx)
+    assert np.array_equal(to_np(rho), np.asarray(want_rho, np.float32))
+
+
+def test_every_row_of_groups_of_128_is_drawn():
+    for m in (4500, 8400):
+        idx, _, _ = gpu_select(torch.from_numpy(_statistic(m, "zeros", 2)).to(DEV), m, grass.SEL_MULTI_NORM2, False)
+        assert np.array_equal(to_np(idx), np.arange(m))
