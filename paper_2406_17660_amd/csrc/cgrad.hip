@@ -49,7 +49,7 @@ constexpr int rows_log2(TileId id) { return id == kTile256 ? 8 : 7; }
 constexpr int cols_log2(TileId id) { return id == kTile128 ? 7 : 8; }
 constexpr int tile_rows(TileId id) { return 1 << rows_log2(id); }
 constexpr int tile_k(TileId id) { return id == kTile128 ? Cfg128::BK : kFastBK; }
-static_assert(kFastBM == 256 && kFastBN == 256 && kMidBM == 128 && kMidBN == 256 && kMidBK == kFastBK, "tile shapes");
+static_assert(kFastBM == 256 && kFastBN == 256 && kMidBM == 128 && kMidBK == kFastBK, "tile shapes");
 
 // How the token dimension is divided: `splits` slices of `tokens` tokens (the last one shorter), and,
 // with `tail`, the tokens past the last whole K tile of 32 as one more slice.
@@ -164,18 +164,32 @@ size_t aligned_x_bytes(int64_t T, int64_t n) {
     return round_up(static_cast<size_t>(T) * ((n + 7) / 8 * 8) * 2, 256);
 }
 
-// The tile a product with these K slices runs with: the one whose estimated time is smallest.  Rates
-// are those reached with full tiles on all compute units (any-alignment forms: 13 % less): 1.4 and
-// 0.6 PFLOP/s for the square tiles, for the mid tile 0.9 with one workgroup per compute unit and,
-// with two that share it, 15 % less time per round: 1.06 (measured over whole products: 1.28 - 1.39
-// and 0.60 - 0.66 against 1.05 - 1.16 at 5120 x 5120 and 4096 x 4096, r = 1024).  Slices
-// of partial tiles cost 3e-12 s per output element (written, then read by the reduction), 2.2e-12
+// The tile a product with these K slices runs with: the one whose estimated time is smallest.
+// Load-to-LDS kernels (aligned operands): a workgroup takes `start` us and, per K tile of 32, a time that
+// depends on how many share a compute unit, u = workgroups / 256 (fitted to the kernel times of 44 layers over
+// the range, all three tiles each):
+//   256 x 256   10 us, 0.45 + 0.3 u up to one per unit (the clock falls as the chip fills), then 0.78 a round
+//   128 x 256    8.3, 0.33 + 0.17 u up to one, 0.95 with two, then 0.5 u
+//   128 x 128    6,   0.345 with one, 0.69 with two, 1.0 with three, then 0.35 u
+// Measured products, 256 / 128 x 256 / 128 tile: 4096 x 4096, r = 1024, T = 2047: 30.7 / 24.8 / 26.8 us; 10016 x 3864,
+// r = 1024, T = 640: 19.4 / 15.0 / 12.9; 2176 x 480, r = 272, T = 4461: 18.8 / 13.8 / 11.2; 1408 x 608, r = 352,
+// T = 109824: 89 / 101 / 79; 512 x 1376, r = 128, T = 65536: 90 / 68 / 50; 10860 x 3616, r = 1024, T = 9280: 65 / 77 / 94;
+// 1024 x 2048, r = 128, T = 131072: 123 / 103 / 118.
+// Operands in any position: 1.2 and 0.5 PFLOP/s with full tiles on all compute units, and the register route of
+// the 256 tile takes 7 us longer to fill and drain.
+// Slices of partial tiles cost 3e-12 s per output element (written, then read by the reduction), 2.2e-12
 // while they stay in the caches; dY stored m x T has to be packed (transposed) for all but the large tile, which
-// gathers its rows itself.
-// Measured per step, planned square tile -> the one chosen here:
-//   2048 x 2048, r = 300, T = 8192    45 -> 37 us (mid)     4096 x 4096, r = 1024, T = 2048  54 -> 51 (mid)
-//   1024 x 2048, r = 128, T = 131072 191 -> 170 (mid)       1024 x 4096, r = 600, T = 4096   37 -> 31 (mid)
-//   1456 x 1800, r = 364, T = 128866 385 -> 335 (256)       1560 x 6416, r = 390, T = 75136 800 -> 723 (mid)
+// gathers its rows itself: one more launch, 8 us with its gap (1888 x 1072, r = 472, T = 2944: 25.5 us so, 26.3 with
+// the pack and 128 tiles).
+// Whole steps against a rule that knew full-chip rates only (1.4, 0.9 and 0.6 PFLOP/s): 400 x 744, r = 50, T = 1280:
+// 19.5 -> 17.2 us; 776 x 456, r = 97, T = 3136: 20.2 -> 18.1; 1648 x 1896, r = 474 (columns), T = 448: 34.5 -> 32.5; 4640 x
+// 1064, r = 1024, T = 896: 28.7 -> 26.5; 1672 x 288, r = 209, T = 12404: 32.0 -> 29.8; long products unchanged.
+double direct_us(TileId id, double wgs, double ktiles) {
+    const double u = wgs / 256.0;
+    if (id == kTile256) return 10.0 + ktiles * (u <= 1 ? 0.45 + 0.3 * u : 0.78 * ceil(u));
+    if (id == kTileMid) return 8.3 + ktiles * (u <= 1 ? 0.33 + 0.17 * u : u <= 2 ? 0.95 : 0.5 * u);
+    return 6.0 + ktiles * (u <= 1 ? 0.345 : u <= 2 ? 0.69 : u <= 3 ? 1.0 : 0.35 * u);
+}
 TileId choose_tile(TileId planned, const KSplit& k, int64_t T, int64_t rows, int64_t n, bool rows_form,
                    grass_dy_layout layout, bool aligned) {
     if (const int forced = test_option(GRASS_TEST_GEMM_TILE))
@@ -184,19 +198,20 @@ TileId choose_tile(TileId planned, const KSplit& k, int64_t T, int64_t rows, int
     double least = 1e300;
     for (const TileId id : {kTile256, kTileMid, kTile128}) {
         if (id == kTileMid && !aligned) continue;
-        if (id == kTile128 && planned == kTile256) continue;  // its K tiles are twice as long
+        if (id == kTile128 && planned == kTile256 && !aligned) continue;  // its K tiles are twice as long
         const Plan p = make_plan(id, k, T, rows, n, false);
         const double outputs = static_cast<double>(p.Mp) * static_cast<double>(p.Np);
         const double wgs = static_cast<double>(p.tiles_m) * p.tiles_n * k.splits;
-        const double slots = id == kTile128 ? 512.0 : 256.0;
-        double rounds = ceil(wgs / slots);
-        if (id == kTileMid && rounds > 1) rounds *= 0.85;
-        double rate = id == kTile256 ? 1.4e15 : id == kTileMid ? 0.9e15 : 0.6e15;
-        if (!aligned) rate *= 0.87;
-        double t = 2.0 * static_cast<double>(T) * outputs / rate * (rounds * slots / wgs) +
-                   (outputs * 4 <= kCachedSliceBytes ? 2.2e-12 : 3e-12) * outputs * k.slices();
-        if (!aligned && id == kTile256) t += 7e-6;  // the register route takes longer to fill and drain
-        if (layout == GRASS_DY_MxT && !(rows_form && id == kTile256)) t += 4.0 * static_cast<double>(T) * p.Mp / 4e12 + 4e-6;
+        double t;
+        if (aligned) {
+            t = 1e-6 * direct_us(id, wgs, static_cast<double>(k.tokens) / kFastBK);
+        } else {
+            const double slots = id == kTile128 ? 512.0 : 256.0;
+            t = 2.0 * static_cast<double>(T) * outputs / (id == kTile256 ? 1.22e15 : 0.52e15) * (ceil(wgs / slots) * slots / wgs);
+            if (id == kTile256) t += 7e-6;
+        }
+        t += (outputs * 4 <= kCachedSliceBytes ? 2.2e-12 : 3e-12) * outputs * k.slices();
+        if (layout == GRASS_DY_MxT && !(rows_form && id == kTile256)) t += 4.0 * static_cast<double>(T) * p.Mp / 4e12 + 8e-6;
         if (t < least) { least = t; best = id; }
     }
     return best;
@@ -985,7 +1000,9 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     g.tiles_n = p.tiles_n;
     g.splits = ks.slices();
     g.tail = ks.tail ? 1 : 0;
-    g.ktiles_per_split = static_cast<int>(ks.tokens / tile_k(tile));
+    // the 128 tile by load-to-LDS where that can fetch the operands (its K tiles are shorter, its sums the same)
+    const bool small_direct = tile == kTile128 && aligned && sizes;
+    g.ktiles_per_split = static_cast<int>(ks.tokens / (small_direct ? kMidBK : tile_k(tile)));
 
     const unsigned grid = static_cast<unsigned>(blocks);
     hipError_t le;
@@ -1010,15 +1027,21 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
             launch_stamped(tn_gemm_bf16_direct_kernel<true>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         le = hipSuccess;
     } else if (tile == kTileMid) {
-        le = raise_lds_limit(reinterpret_cast<const void*>(gathered ? tn_gemm_bf16_mid_kernel<false>
-                                                                    : tn_gemm_bf16_mid_kernel<true>),
-                             kMidLdsBytes, gathered ? 0 : 1);
+        le = raise_lds_limit(reinterpret_cast<const void*>(gathered ? tn_gemm_bf16_mid_kernel<false, 256>
+                                                                    : tn_gemm_bf16_mid_kernel<true, 256>),
+                             mid_lds_bytes(256), gathered ? 0 : 1);
         if (le == hipSuccess) {
             if (gathered)
-                launch_stamped(tn_gemm_bf16_mid_kernel<false>, dim3(grid), dim3(256), kMidLdsBytes, s, ev_start, ev_stop, g);
+                launch_stamped(tn_gemm_bf16_mid_kernel<false, 256>, dim3(grid), dim3(256), mid_lds_bytes(256), s, ev_start, ev_stop, g);
             else
-                launch_stamped(tn_gemm_bf16_mid_kernel<true>, dim3(grid), dim3(256), kMidLdsBytes, s, ev_start, ev_stop, g);
+                launch_stamped(tn_gemm_bf16_mid_kernel<true, 256>, dim3(grid), dim3(256), mid_lds_bytes(256), s, ev_start, ev_stop, g);
         }
+    } else if (small_direct) {
+        if (gathered)
+            launch_stamped(tn_gemm_bf16_mid_kernel<false, 128>, dim3(grid), dim3(256), mid_lds_bytes(128), s, ev_start, ev_stop, g);
+        else
+            launch_stamped(tn_gemm_bf16_mid_kernel<true, 128>, dim3(grid), dim3(256), mid_lds_bytes(128), s, ev_start, ev_stop, g);
+        le = hipSuccess;
     } else {
         if (ev_start) (void)hipEventRecord(ev_start, s);
         if (aligned)

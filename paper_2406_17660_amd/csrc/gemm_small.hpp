@@ -1,4 +1,5 @@
-// bf16 MFMA GEMM with 128 x 128 tiles, register-staged: small problems.
+// bf16 MFMA GEMM with 128 x 128 tiles, register-staged: operands that load-to-LDS cannot fetch (rows on 2-byte
+// boundaries, fewer than 32 tokens or 8 columns, 32-bit offsets that do not reach).
 // Included by cgrad.hip only (device code shares one translation unit with its launchers).
 #pragma once
 #include "common.hpp"

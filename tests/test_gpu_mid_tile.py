@@ -12,7 +12,7 @@ from gpu_util import DEV, TOL_F32, rel_fro, to_f64, to_np
 pytestmark = pytest.mark.gpu
 
 
-def _run(T, m, n, r, slices=0, seed=0):
+def _run(T, m, n, r, slices=0, seed=0, tile=192):
     gen = torch.Generator(device=DEV)
     gen.manual_seed(seed)
     # Inf behind the last token and behind the last column: must not be multiplied in
@@ -22,7 +22,7 @@ def _run(T, m, n, r, slices=0, seed=0):
     dY = torch.randn(T, m, generator=gen, device=DEV).to(torch.bfloat16)
     idx = torch.randint(0, m, (r,), generator=gen, device=DEV).sort()[0].to(torch.int32)
     rho = torch.rand(r, generator=gen, device=DEV) + 0.5
-    grass.set_test_option(grass.TEST_GEMM_TILE, 192)
+    grass.set_test_option(grass.TEST_GEMM_TILE, tile)
     grass.set_test_option(grass.TEST_MAX_K_SLICES, slices)
     GC = torch.full((r, n), float("nan"), device=DEV)
     grass.compressed_grad(dY, X, idx, rho, GC, grass.workspace(grass.cgrad_workspace(T, m, n, r, grass.BF16)))
@@ -41,3 +41,15 @@ def test_tiles_and_ring(T, m, n, r):
 @pytest.mark.parametrize("slices", [1, 2, 5, 9, 40])
 def test_slices_end_in_a_ragged_tile(slices):
     _run(2477, 304, 520, 260, slices)
+
+
+@pytest.mark.parametrize("T", [32, 33, 64, 95, 96, 97, 128, 193, 1001])
+@pytest.mark.parametrize("m,n,r", [(8, 8, 1), (128, 128, 127), (136, 136, 130), (264, 392, 257)])
+def test_128_columns(T, m, n, r):
+    _run(T, m, n, r, tile=128)
+    _run(T, m, n, r, 1, tile=128)
+
+
+@pytest.mark.parametrize("slices", [2, 5, 40])
+def test_128_columns_slices_end_in_a_ragged_tile(slices):
+    _run(2477, 304, 520, 260, slices, tile=128)
