@@ -170,7 +170,7 @@ size_t aligned_x_bytes(int64_t T, int64_t n) {
 // the range, all three tiles each):
 //   256 x 256   10 us, 0.45 + 0.3 u up to one per unit (the clock falls as the chip fills), then 0.78 a round
 //   128 x 256    8.3, 0.33 + 0.17 u up to one, 0.95 with two, then 0.5 u
-//   128 x 128    6,   0.345 with one, 0.69 with two, 1.0 with three, then 0.35 u
+//   128 x 128    6 or, beyond one, 8; 0.345 with one, 0.69 with two, 1.0 with three, then 0.35 u
 // Measured products, 256 / 128 x 256 / 128 tile: 4096 x 4096, r = 1024, T = 2047: 30.7 / 24.8 / 26.8 us; 10016 x 3864,
 // r = 1024, T = 640: 19.4 / 15.0 / 12.9; 2176 x 480, r = 272, T = 4461: 18.8 / 13.8 / 11.2; 1408 x 608, r = 352,
 // T = 109824: 89 / 101 / 79; 512 x 1376, r = 128, T = 65536: 90 / 68 / 50; 10860 x 3616, r = 1024, T = 9280: 65 / 77 / 94;
@@ -188,7 +188,7 @@ double direct_us(TileId id, double wgs, double ktiles) {
     const double u = wgs / 256.0;
     if (id == kTile256) return 10.0 + ktiles * (u <= 1 ? 0.45 + 0.3 * u : 0.78 * ceil(u));
     if (id == kTileMid) return 8.3 + ktiles * (u <= 1 ? 0.33 + 0.17 * u : u <= 2 ? 0.95 : 0.5 * u);
-    return 6.0 + ktiles * (u <= 1 ? 0.345 : u <= 2 ? 0.69 : u <= 3 ? 1.0 : 0.35 * u);
+    return (u <= 1 ? 6.0 : 8.0) + ktiles * (u <= 1 ? 0.345 : u <= 2 ? 0.69 : u <= 3 ? 1.0 : 0.35 * u);
 }
 TileId choose_tile(TileId planned, const KSplit& k, int64_t T, int64_t rows, int64_t n, bool rows_form,
                    grass_dy_layout layout, bool aligned) {
@@ -871,7 +871,8 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     pack = pack || copy.a;
     const int64_t nb = copy.b ? (n + 7) / 8 * 8 : n;  // columns the GEMM sees
     // whole aligned 16-byte chunks: what the load-to-LDS kernels and the aligned small tile move
-    const bool aligned = (pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0)) &&
+    const bool a_chunks = pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0);
+    const bool aligned = a_chunks &&
                          (copy.b || (aligned_to(X, 16) && ldx % 8 == 0 && n % 8 == 0));
     const bool a_rows_form = rows_ok && tile == kTile256 && aligned;
     const bool a_pairs = a_rows_form && pairs_ok;
@@ -1004,6 +1005,8 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     const bool small_direct = tile == kTile128 && aligned && sizes;
     g.ktiles_per_split = static_cast<int>(ks.tokens / (small_direct ? kMidBK : tile_k(tile)));
 
+    const bool a_direct = a_chunks && p.tiles_m > 1 && g.ktiles_per_split >= kUnalignedXMin;
+
     const unsigned grid = static_cast<unsigned>(blocks);
     hipError_t le;
     if (tile == kTile256) {  // the events are stamped with this dispatch's own start and end
@@ -1013,6 +1016,10 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         else if (a_rows_form)
             launch_stamped(tn_gemm_bf16_direct_kernel<false, false, true>, dim3(grid), dim3(256), 0, s,
                            ev_start, ev_stop, g);
+        else if (!aligned && a_direct && gathered)
+            launch_stamped(tn_gemm_bf16_unaligned_x_kernel<false>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
+        else if (!aligned && a_direct)
+            launch_stamped(tn_gemm_bf16_unaligned_x_kernel<true>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else if (!aligned && gathered)
             launch_stamped(tn_gemm_bf16_unaligned_kernel<false>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else if (!aligned)

@@ -81,3 +81,13 @@ def test_slices_end_in_a_ragged_tile(slices):
 @pytest.mark.parametrize("T,m,n", [(96, 5000, 2051), (96, 2051, 5000)])
 def test_full_gradient_whose_odd_operand_is_copied(T, m, n):
     _check(T, m, n, 8, grass.DY_TxM, 0, 0, 8)
+
+
+# aligned left operand, odd X: every length of the ring's start (nine whole tiles), of its steady loop
+# (four tiles a turn) and of its end
+@pytest.mark.parametrize("rest", [0, 5])
+@pytest.mark.parametrize("tiles", [*range(1, 19), 21, 22])
+def test_left_operand_by_load_to_lds(tiles, rest):
+    grass.set_test_option(grass.TEST_GEMM_TILE, 256)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 1)
+    _check(32 * tiles + rest, 264, 261, 140, grass.DY_TxM, 0, 0, 8)
