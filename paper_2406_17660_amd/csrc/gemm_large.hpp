@@ -282,41 +282,47 @@ __device__ __forceinline__ void direct_gemm(const GemmArgs& g) {
 #pragma unroll
         for (int part = 0; part < 4; ++part) read_quarter(f, i, k16, part);
     };
-    // Row `a` of the 4 x 4 fragment products of a slice.  Odd rows run through the columns
-    // backwards, so that only one operand changes from the last instruction of a row to the
-    // first of the next (fewer operand switches: measured 0.5 % faster; the kernel is bound
+    // Two products (half `hf`) of row `a` of the 4 x 4 fragment products of a slice.  Odd rows run
+    // through the columns backwards, so that only one operand changes from the last instruction of a
+    // row to the first of the next (fewer operand switches: measured 0.5 % faster; the kernel is bound
     // by power).
-    auto mfma_row = [&](const Frags& f, int a) {
+    auto mfma_half = [&](const Frags& f, int a, int hf) {
 #pragma unroll
-        for (int bb = 0; bb < 4; ++bb) {
+        for (int bb = 2 * hf; bb < 2 * hf + 2; ++bb) {
             const int b = (a & 1) ? 3 - bb : bb;
             acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[a], f.b[b], acc[a][b], 0, 0, 0);
         }
     };
     auto mfma16 = [&](const Frags& f) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) mfma_row(f, a);
+        for (int a = 0; a < 4; ++a) {
+            mfma_half(f, a, 0);
+            mfma_half(f, a, 1);
+        }
     };
-    // "one MFMA, one LDS read" four times: the reads issue in the shadow of the MFMAs
-    auto interleave_hint4 = [&]() {
+    // "one MFMA, two LDS reads" twice: the reads issue in the shadow of the MFMAs
+    auto interleave_hint2 = [&]() {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < 2; ++k) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // DS read
         }
     };
     // One slice of work: the 16 MFMAs of `cur` in four groups of four, each group overlapped
-    // with a quarter of the LDS reads of the following slice (`next`) and followed by one
-    // global->LDS load of tile `load_tile` (if any).
+    // with a quarter of the LDS reads of the following slice (`next`) and with one global->LDS load
+    // of tile `load_tile` (if any) in its middle (behind the group instead: 781 against 773 us at
+    // 4096 x 4096, r = 1024, T = 131072; 332 against 326 at 2048 x 5464, r = 512, T = 65536).
     auto slice = [&](const Frags& cur, Frags& next, int next_tile, int next_k16, int load_tile,
                      int load_part0, bool do_load) {
 #pragma unroll
         for (int part = 0; part < 4; ++part) {
             read_quarter(next, next_tile, next_k16, part);
-            mfma_row(cur, part);
-            interleave_hint4();
+            mfma_half(cur, part, 0);
+            interleave_hint2();
             __builtin_amdgcn_sched_barrier(0);
             if (do_load) issue_part(load_tile, load_part0 + part);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_half(cur, part, 1);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -346,15 +352,15 @@ __device__ __forceinline__ void direct_gemm(const GemmArgs& g) {
 #pragma unroll
             for (int part = 0; part < 4; ++part) {
                 read_quarter(next, next_tile, next_k16, part);
-                mfma_row(cur, part);
-                interleave_hint4();
+                mfma_half(cur, part, 0);
+                interleave_hint2();
                 __builtin_amdgcn_sched_barrier(0);
-                if (kind == 1) {
-                    issue_pair_part(load_tile, 2 * part);
-                    issue_pair_part(load_tile, 2 * part + 1);
-                } else if (kind == 2) {
-                    issue_b_part(load_tile, part);
-                }
+                if (kind == 1) issue_pair_part(load_tile, 2 * part);
+                else if (kind == 2) issue_b_part(load_tile, part);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_half(cur, part, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (kind == 1) issue_pair_part(load_tile, 2 * part + 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
