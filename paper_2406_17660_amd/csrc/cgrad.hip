@@ -272,6 +272,12 @@ struct F32Plan {
     int tiles_m, tiles_n, splits, ktiles_per_split;
 };
 constexpr int64_t kF32SplitMinT = 1024;
+// Below this many tokens the fp32 instruction, whose products are exact: split operands leave up to 2^-24 of a
+// product out, which shows until the roundings of a longer sum outweigh it.  Error against 64 bits at 256 x 256, norm
+// (and largest, over the sum of magnitudes), fp32 instruction / 64 tile / short kernel: T = 1: 2.5e-8 / 3.5e-8 / 4.2e-8
+// (0.6e-7 / 1.4e-7 / 1.9e-7), T = 4: 4.0e-8 / 3.2e-8 / 4.1e-8 (1.7e-7 / 1.3e-7 / 1.7e-7), T = 8: 5.4e-8 / 3.1e-8 / 4.0e-8
+// (2.2e-7 / 1.0e-7 / 1.3e-7).  A step of 32 rows takes 13.5 us so, 11 with the short kernel.
+constexpr int64_t kF32PartsMinT = 8;
 // Which kernel: the one of short products where all sets are single row tiles and K is short enough for
 // one workgroup per tile (256 x 256, r = 16, T = 512: 9.0 us in one launch; 6.4 + 3.8 us and the gap between
 // them with the fp32 instruction; at T = 4096 47 us against 13); the fp32
@@ -285,6 +291,7 @@ F32Kernel f32_kernel(int64_t T, const int64_t* rows, int count, int64_t n) {
         case kShortTile: return F32Kernel::kShort;
         default: return F32Kernel::kSplit;
     }
+    if (T < kF32PartsMinT) return F32Kernel::kMfma;
     int64_t total = 0, most = 0;
     for (int i = 0; i < count; ++i) {
         total += rows[i];

@@ -8,10 +8,11 @@ namespace {
 
 // The fp32 matrix instruction does 256 flop per clock and compute unit, the bf16 one 4096.  A value is
 // the exact sum of three bf16 parts (24 significant bits as 8 + 8 + 8, each the nearest bf16 of what the
-// ones before leave), so a product of two values is nine exact products of parts; the three least, below
-// 2^-26 of it, are left out, and six bf16 instructions of 16 tokens stand for eight fp32 ones of two.
-// The error against 64 bits is smaller than with the fp32 instruction (drawn layers: 4e-8 - 9e-8 on the
-// first moment against 6e-8 - 2e-7): products are exact and sums are rounded once per 16 tokens and part.
+// ones before leave), so a product of two values is nine exact products of parts; the three least, together
+// up to 2^-24 of it (2^-28 is typical), are left out, and six bf16 instructions of 16 tokens stand for eight fp32
+// ones of two.  From 8 tokens on the error against 64 bits is smaller than with the fp32 instruction (drawn layers:
+// 4e-8 - 9e-8 on the first moment against 6e-8 - 2e-7), because sums are rounded once per 16 tokens and part; below,
+// where it would be larger, the fp32 instruction is used (f32_kernel()).
 // What the parts cannot hold is found and done again with the fp32 instruction, one whole slice of a tile
 // at a time: a magnitude below 2^-100 but not 0 (the last part would be subnormal or lost), and any sum
 // that is not finite (an input that is not, or that rounds to an infinite part).

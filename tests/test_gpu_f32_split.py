@@ -101,3 +101,31 @@ def test_step_in_one_launch_equals_the_one_in_two(sdt, wdt, T, n, rs, layout):
         results.append([*Ms, *Vs, *Ws, *(G for G in GCs if G is not None)])
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 5, 7])
+def test_few_tokens_take_exact_products(T):
+    """Below 8 tokens the products are those of the fp32 instruction, whatever the shape, in separate calls and in
+    steps: one token gives the correctly rounded product of the two values."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T)
+    for m, n, r in ((40, 96, 32), (6400, 6400, 6400)):  # a single row tile; more than 0.3 Gflop from T = 4 on
+        # mantissas whose parts are as large as they get, and random ones
+        dY = torch.where(torch.rand((T, m), generator=g, device=DEV) < 0.5, float.fromhex("0x1.00ff8p+0"), 0.0)
+        dY += torch.randn((T, m), generator=g, device=DEV) * (dY == 0)
+        X = torch.where(torch.rand((T, n), generator=g, device=DEV) < 0.5, float.fromhex("0x1.00ff8p+0"), 0.0)
+        X += torch.randn((T, n), generator=g, device=DEV) * (X == 0)
+        idx, rho = torch.arange(r, dtype=torch.int32, device=DEV), torch.ones(r, device=DEV)
+        results = []
+        for kernel in (0, 16):
+            grass.set_test_option(grass.TEST_GEMM_TILE, kernel)
+            GC, G = (torch.full((r, n), float("nan"), device=DEV) for _ in range(2))
+            grass.compressed_grad(dY, X, idx, rho, GC, None)
+            M, V, W = (torch.zeros(s, n, device=DEV) for s in (r, r, m))
+            grass.step_group([dY], X, [idx], [rho], [M], [V], [W], 1e-2, 0.9, 0.999, 1e-8, 1, 0.5,
+                             grass.workspace(grass.step_group_workspace(T, n, [r], grass.F32)), GCs=[G])
+            results.append((GC, G))
+        for a, b in zip(*results):
+            assert torch.equal(a, b)
+        if T == 1:
+            assert torch.equal(results[0][0], dY.t()[:r] * X)
