@@ -363,10 +363,11 @@ F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_
     }
     return best_plan;
 }
-// Workspace for the partial tiles of a product that is planned without a limit.
+// Workspace for the partial tiles of a product that is planned without a limit: a single slice without a fused
+// tail has none (and is what the plan gives for no workspace too).
 size_t f32_partial_bytes(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_layout layout, bool step) {
     const F32Plan p = f32_plan(T, rows, count, n, layout, step, ~size_t{0} >> 1);
-    if (p.splits == 1 && !step && T < kF32SplitMinT) return 0;
+    if (p.splits == 1 && !step) return 0;
     return static_cast<size_t>(p.splits) * p.Mp * p.Np * 4 + 256;
 }
 

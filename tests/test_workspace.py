@@ -47,3 +47,15 @@ def test_narrow_groups_of_many_slices_fit(T, n, m, rs):
     """Groups whose slice count is bounded by the room for the partial tiles."""
     used = narrow_partial_bytes(T, n, rs, m)
     assert used is not None and used + 255 <= narrow_workspace(T, n, rs, m)
+
+
+@pytest.mark.parametrize("layout", [grass.DY_TxM, grass.DY_MxT])
+@pytest.mark.parametrize("T,n,r", [(1, 64, 16), (512, 256, 16), (1023, 300, 200), (1024, 4096, 4096), (2048, 11008, 4096),
+                                   (4096, 4096, 4096), (8192, 2048, 2048), (8192, 1024, 256), (8192, 64, 33)])
+def test_fp32_products_of_one_slice_ask_for_no_workspace(T, n, r, layout):
+    """Partial tiles are written for several slices, or for the tail of a step; the sums of one slice go to the
+    output."""
+    _, slices = grass.cgrad_plan(T, n, r, grass.F32, layout)
+    sizes = [grass.cgrad_workspace(T, r, n, r, grass.F32, layout), grass.dense_workspace(T, r, n, grass.F32, layout),
+             grass.cgrad_group_workspace(T, n, [r], grass.F32, layout)]
+    assert all((size == 0) == (slices == 1) for size in sizes), (slices, sizes)
