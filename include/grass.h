@@ -169,7 +169,9 @@ grass_status grass_select_rows_static(const float* sumsq, int64_t m, int64_t r,
  * and grass_dense_grad: any size, or NULL.  grass_grad_row_stats: from m*n*4 + 256 bytes on.
  * grass_step_group and grass_step_cols: from 256 bytes plus 4*r*n (column form: 4*r*m), rounded
  * up to a multiple of 256 per layer, on.  The sums over T are then split over fewer slices, which
- * changes them within fp32 rounding and takes longer.
+ * changes them within fp32 rounding and takes longer.  The time does not depend on the values as
+ * long as they stay below 2^104 and sums below 2^80; infinities, NaN and what exceeds that are handled, at
+ * up to about three times the time of the call.
  * Errors: NULL, SHAPE, DTYPE, WORKSPACE. */
 size_t grass_cgrad_workspace(int64_t T, int64_t m, int64_t n, int64_t r, grass_dtype dt,
                              grass_dy_layout layout);

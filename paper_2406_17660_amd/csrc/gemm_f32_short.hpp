@@ -103,7 +103,6 @@ __global__ __launch_bounds__(kShortWaves * 64) void tn_gemm_f32_short_kernel(F32
             r.b[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, offB, e * bytesB, 0));
         }
     };
-    uint32_t least = 0xFFFFFFFFu;
     uint32_t low_bits = 0x0000BF80u, high_bits = 0xBF800000u;  // see gemm_f32_split.hpp
     asm("" : "+s"(low_bits), "+s"(high_bits));
     const bf16x2 kLow = __builtin_bit_cast(bf16x2, low_bits), kHigh = __builtin_bit_cast(bf16x2, high_bits);
@@ -112,8 +111,8 @@ __global__ __launch_bounds__(kShortWaves * 64) void tn_gemm_f32_short_kernel(F32
     for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = 0.f;
     auto multiply = [&](const Raw& r) {
         SplitParts a, b;
-        split_parts(r.a, a, least, kLow, kHigh);
-        split_parts(r.b, b, least, kLow, kHigh);
+        split_parts(r.a, a, kLow, kHigh);
+        split_parts(r.b, b, kLow, kHigh);
         auto product = [&](int i, int j, int k) {
             acc[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a.p[i]), __builtin_bit_cast(bf16x8, b.p[j]), acc[k], 0, 0, 0);
         };
@@ -133,10 +132,16 @@ __global__ __launch_bounds__(kShortWaves * 64) void tn_gemm_f32_short_kernel(F32
             }
         }
         if (T % 16 != 0 && wave == whole % kShortWaves) {  // the last chunk: tokens past T count as 0
+            const int first = whole * 16 + half * 8;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {  // the last token in place of those: no load waits for the one before it
+                const int t = first + e < T ? first + e : T - 1;
+                r0.a[e] = pa[t * strideA];
+                r0.b[e] = pb[t * g.ldx];
+            }
+#pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int t = whole * 16 + half * 8 + e;
-                r0.a[e] = t < T ? pa[t * strideA] : 0.f;
-                r0.b[e] = t < T ? pb[t * g.ldx] : 0.f;
+                if (first + e >= T) r0.a[e] = r0.b[e] = 0.f;
             }
             multiply(r0);
         }
@@ -147,7 +152,10 @@ __global__ __launch_bounds__(kShortWaves * 64) void tn_gemm_f32_short_kernel(F32
         acc[0][e] += acc[1][e];
         finite = __builtin_fmaf(acc[0][e], 0.f, finite);
     }
-    if (__syncthreads_or(least < 2 * kF32Least - 1 || finite != 0.f) || g.exact) {  // see gemm_f32_split.hpp
+    if (!__any(finite != 0.f) && !g.exact) {  // see gemm_f32_split.hpp
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[0][e] *= kF32Unscale;
+    } else {
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[0][e] = 0.f;
         for (int c = wave; c < chunks; c += kShortWaves) {

@@ -13,9 +13,12 @@ namespace {
 // ones of two.  From 8 tokens on the error against 64 bits is smaller than with the fp32 instruction (drawn layers:
 // 4e-8 - 9e-8 on the first moment against 6e-8 - 2e-7), because sums are rounded once per 16 tokens and part; below,
 // where it would be larger, the fp32 instruction is used (f32_kernel()).
-// What the parts cannot hold is found and done again with the fp32 instruction, one whole slice of a tile
-// at a time: a magnitude below 2^-100 but not 0 (the last part would be subnormal or lost), and any sum
-// that is not finite (an input that is not, or that rounds to an infinite part).
+// Operands are multiplied by 2^24 before the split and sums by 2^-48 after the last one: the parts of every
+// finite value, subnormal ones included, are then multiples of 2^-125, none of them subnormal or lost.  What is
+// too large for that, values from 2^104 and sums from 2^80 on, gives a sum that is not finite, as infinities and NaN
+// do; a wavefront that has one does its half of the slice again with the fp32 instruction.  That takes longer than
+// the first time (the step of 1024 x 1024, r = 256, T = 8192: 44 us, 108 with one infinity in dY; 4096 x 4096,
+// r = 1024, T = 2048: 139 and 439), which a step that is lost anyway may.
 //
 // A workgroup has eight wavefronts in two groups of four; each group multiplies its half of the slice's
 // tokens, and their sums meet in LDS, so that two wavefronts per SIMD hide each other's waits without a
@@ -35,7 +38,7 @@ constexpr int f32_bk(int bm) { return bm == 128 ? 16 : 32; }  // tokens per K ti
 constexpr int64_t kF32MaxStride = int64_t{1} << 24;
 
 constexpr int kF32Threads = 512, kF32LdsBytes = 96 * 1024;
-constexpr uint32_t kF32Least = 27u << 23;  // 2^-100
+constexpr float kF32Scale = 0x1p24f, kF32Unscale = 0x1p-48f;  // of each operand; of the sums
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -56,21 +59,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t f32_buffer(const float* base, 
                                              kBufferFlags);
 }
 
-// Eight values as the sums of three bf16 each; `least` takes twice the bits of the least magnitude, less
-// 1 (0 is then the largest value).  kLow, kHigh: (-1, 0) and (0, -1).
+// Eight values, times kF32Scale, as the sums of three bf16 each.  kLow, kHigh: (-1, 0) and (0, -1).
 struct SplitParts { u32x4_t p[3]; };
-__device__ __forceinline__ void split_parts(const float (&x)[8], SplitParts& o, uint32_t& least, bf16x2 kLow, bf16x2 kHigh) {
+__device__ __forceinline__ void split_parts(const float (&x)[8], SplitParts& o, bf16x2 kLow, bf16x2 kHigh) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const bf16x2 hi = bf16_pair(x[2 * e], x[2 * e + 1]);
-        const float r0 = __builtin_amdgcn_fdot2_f32_bf16(hi, kLow, x[2 * e], false);
-        const float r1 = __builtin_amdgcn_fdot2_f32_bf16(hi, kHigh, x[2 * e + 1], false);
+        const float x0 = x[2 * e] * kF32Scale, x1 = x[2 * e + 1] * kF32Scale;
+        const bf16x2 hi = bf16_pair(x0, x1);
+        const float r0 = __builtin_amdgcn_fdot2_f32_bf16(hi, kLow, x0, false);
+        const float r1 = __builtin_amdgcn_fdot2_f32_bf16(hi, kHigh, x1, false);
         const bf16x2 mid = bf16_pair(r0, r1);
         const float s0 = __builtin_amdgcn_fdot2_f32_bf16(mid, kLow, r0, false);
         const float s1 = __builtin_amdgcn_fdot2_f32_bf16(mid, kHigh, r1, false);
-        const uint32_t m0 = 2 * __float_as_uint(x[2 * e]) - 1, m1 = 2 * __float_as_uint(x[2 * e + 1]) - 1;
-        const uint32_t m = m0 < m1 ? m0 : m1;
-        least = m < least ? m : least;
         o.p[0][e] = __builtin_bit_cast(uint32_t, hi);
         o.p[1][e] = __builtin_bit_cast(uint32_t, mid);
         o.p[2][e] = __builtin_bit_cast(uint32_t, bf16_pair(s0, s1));
@@ -154,31 +154,31 @@ __global__ __launch_bounds__(kF32Threads, 2) void tn_gemm_f32_split_kernel(F32Ar
 #pragma unroll
         for (int e = 0; e < 8; ++e) r.b[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, offB, e * bytesB, 0));
     };
-    // the ragged last tile, by itself: tokens past T count as 0
+    // the ragged last tile, by itself: tokens past T count as 0 (the last token is fetched in their place, so that
+    // no load waits for the one before it)
     auto load_ragged = [&](Raw& r, int i) {
         const int t0 = t_begin + i * BK + krow;
         if (t_begin + (i + 1) * BK <= t_end) return;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            r.a[e] = r.b[e] = 0.f;
-            if (t0 + e < t_end) {
-                const int64_t t = t0 + e;
-                r.a[e] = sg.dY[kMxT ? colA * sg.ldy + t : t * sg.ldy + colA];
-                r.b[e] = g.X[t * g.ldx + colB];
-            }
+            const int64_t t = t0 + e < t_end ? t0 + e : t_end - 1;
+            r.a[e] = sg.dY[kMxT ? colA * sg.ldy + t : t * sg.ldy + colA];
+            r.b[e] = g.X[t * g.ldx + colB];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (t0 + e >= t_end) r.a[e] = r.b[e] = 0.f;
         }
     };
 
-    // ---- registers -> LDS, split.  `least`: the least magnitude but 0 (twice its bits - 1, so that 0 is
-    // the largest value; see below).
-    uint32_t least = 0xFFFFFFFFu;
+    // ---- registers -> LDS, split.
     // (-1, 0) and (0, -1) in bf16, kept in registers: an inline -1.0 is not the first to the instruction
     uint32_t low_bits = 0x0000BF80u, high_bits = 0xBF800000u;
     asm("" : "+s"(low_bits), "+s"(high_bits));
     const bf16x2 kLow = __builtin_bit_cast(bf16x2, low_bits), kHigh = __builtin_bit_cast(bf16x2, high_bits);
     auto split8 = [&](const float (&x)[8], uint16_t* dst) {
         SplitParts o;
-        split_parts(x, o, least, kLow, kHigh);
+        split_parts(x, o, kLow, kHigh);
 #pragma unroll
         for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4_t*>(dst + q * kUnit) = o.p[q];
     };
@@ -282,8 +282,8 @@ __global__ __launch_bounds__(kF32Threads, 2) void tn_gemm_f32_split_kernel(F32Ar
                 for (int v = 0; v < 16; ++v) acc[0][a][b][v] += acc[K16 - 1][a][b][v];
     }
 
-    // Three parts hold every value from 2^-100 on, and 0.  A smaller one, or a sum that is not finite (an
-    // input that is not, or that rounds to an infinite part): the slice again, with the fp32 instruction.
+    // A sum that is not finite (an input that is not, or that is too large for its parts): this wavefront's block
+    // again, with the fp32 instruction.
     float finite = 0.f;  // stays 0
 #pragma unroll
     for (int a = 0; a < F; ++a)
@@ -291,7 +291,14 @@ __global__ __launch_bounds__(kF32Threads, 2) void tn_gemm_f32_split_kernel(F32Ar
         for (int b = 0; b < F; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) finite = __builtin_fmaf(acc[0][a][b][v], 0.f, finite);
-    if (__syncthreads_or(least < 2 * kF32Least - 1 || finite != 0.f) || g.exact) {
+    if (!__any(finite != 0.f) && !g.exact) {
+#pragma unroll
+        for (int a = 0; a < F; ++a)
+#pragma unroll
+            for (int b = 0; b < F; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[0][a][b][v] *= kF32Unscale;
+    } else {
         clear();
         const int64_t strideA = kMxT ? 1 : sg.ldy;
         const float *pa[F], *pb[F];

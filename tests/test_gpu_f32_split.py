@@ -53,6 +53,45 @@ def test_magnitudes_that_bf16_parts_do_not_hold(kernel, low, high):
 
 
 @pytest.mark.parametrize("kernel", KERNELS)
+@pytest.mark.parametrize("low,high", [(-75, -50), (-149, -60), (40, 44), (52, 56)])
+def test_small_and_large_products(kernel, low, high):
+    """Both operands between 2^low and 2^high: products below the smallest normal value, and sums around 2^80.
+    The bound of the test above."""
+    T, m, n = 200, 40, 36
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    dY, X = (((torch.randint(0, 2, (T, w), generator=g, device=DEV) * 2 - 1) * 2.0 ** (
+        torch.rand((T, w), generator=g, device=DEV, dtype=torch.float64) * (high - low) + low)).float() for w in (m, n))
+    grass.set_test_option(grass.TEST_GEMM_TILE, kernel)
+    G = torch.full((m, n), float("nan"), device=DEV)
+    grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(T, m, n, grass.F32)))
+    want = dY.double().t() @ X.double()
+    bound = T * 2.0 ** -24 * (dY.double().abs().t() @ X.double().abs()) + T * 2.0 ** -149
+    assert bool(((G.double() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
+@pytest.mark.parametrize("T", [40, 1100])
+def test_tiny_values_leave_other_outputs_as_they_are(kernel, T):
+    """The bits of an output depend on its own column and row alone: values of 2^-110 and subnormal ones elsewhere
+    in the tile are multiplied like all others, and cost nothing more."""
+    m, n = 140, 136
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    dY, X = torch.randn((T, m), generator=g, device=DEV), torch.randn((T, n), generator=g, device=DEV)
+    grass.set_test_option(grass.TEST_GEMM_TILE, kernel)
+    ws = grass.workspace(grass.dense_workspace(T, m, n, grass.F32))
+    G, H = (torch.full((m, n), float("nan"), device=DEV) for _ in range(2))
+    grass.dense_grad(dY, X, G, ws)
+    dY[T // 2, 3], dY[T - 1, 70], X[0, 100] = 2.0 ** -110, 2.0 ** -149, -2.0 ** -127
+    grass.dense_grad(dY, X, H, ws)
+    assert bool(torch.isfinite(H).all())
+    same = torch.ones((m, n), dtype=torch.bool, device=DEV)
+    same[[3, 70]], same[:, 100] = False, False
+    assert torch.equal(G[same], H[same])
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
 def test_infinities_and_nan_stay_where_they_belong(kernel):
     """An output is not finite exactly where the product of its own column and row is not; the largest
     finite values (which round to an infinite bf16) stay finite."""
