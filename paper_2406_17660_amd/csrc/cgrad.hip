@@ -284,7 +284,9 @@ constexpr int64_t kF32PartsMinT = 8;
 // instruction below 0.3 Gflop, where starting up is what costs (680 x 288, r = 42, T = 1856: 12.8 against
 // 16.7 us with split operands, 959 x 1928, r = 119, T = 448, 0.2 Gflop: 15.9 and 17.4, 1112 x 1056, r = 278,
 // T = 432, 0.25 Gflop: 16.5 both; 1800 x 1356, r = 450, T = 320, 0.39 Gflop: 22.5 and 20.9); split operands beyond.
-F32Kernel f32_kernel(int64_t T, const int64_t* rows, int count, int64_t n) {
+// `far`: rows of T x m or T x n storage further apart than the offsets of the kernels with split operands reach.
+F32Kernel f32_kernel(int64_t T, const int64_t* rows, int count, int64_t n, bool far) {
+    if (far) return F32Kernel::kMfma;
     switch (test_option(GRASS_TEST_GEMM_TILE)) {
         case 0: break;
         case 16: return F32Kernel::kMfma;
@@ -312,8 +314,8 @@ F32Kernel f32_kernel(int64_t T, const int64_t* rows, int count, int64_t n) {
 // tokens is not split, so that it needs no workspace: its K loop is short.
 constexpr double f32_turn_us(int bm, bool mxt) { return bm == 128 ? (mxt ? 1.2 : 1.4) : (mxt ? 1.1 : 1.6); }
 F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_layout layout, bool step,
-                 size_t cap_bytes) {
-    const F32Kernel kernel = f32_kernel(T, rows, count, n);
+                 size_t cap_bytes, bool far = false) {
+    const F32Kernel kernel = f32_kernel(T, rows, count, n, far);
     F32Plan best_plan{kernel, 64, 0, 0, 0, 0, 1, 1};  // an empty product
     double best = 1e300;
     const int forced = test_option(GRASS_TEST_GEMM_TILE);
@@ -334,7 +336,7 @@ F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_
         p.tiles_m = static_cast<int>(tm);
         p.tiles_n = static_cast<int>(tn);
         p.Mp = total;
-        p.Np = tn * bm;
+        p.Np = (tn * bm + kF32Tile - 1) / kF32Tile * kF32Tile;  // a slice of any plan holds one of the fp32 instruction's
         const int64_t bk = kernel == F32Kernel::kSplit ? f32_bk(bm) : kF32BK, ktiles = (T + bk - 1) / bk, tiles = tm * tn;
         const int64_t slice_bytes = p.Mp * p.Np * 4;
         const int64_t room = slice_bytes > 0 ? static_cast<int64_t>(cap_bytes) / slice_bytes : 1;
@@ -695,13 +697,14 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         char* base = static_cast<char*>(ws);
         const size_t skip = base ? (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256 : 0;
         const size_t cap = base && ws_bytes > skip ? ws_bytes - skip : 0;
-        const F32Plan p = f32_plan(T, rows, count, n, layout, tails, cap);
+        bool far = ldx >= kF32MaxStride;
+        for (int i = 0; i < count; ++i) far = far || (layout == GRASS_DY_TxM && seg[i].ldy >= kF32MaxStride);
+        const F32Plan p = f32_plan(T, rows, count, n, layout, tails, cap, far);
         // partial tiles whenever something reads them: several slices, or a fused tail (which takes
         // the sums from there); a workspace that cannot hold even one slice leaves the direct form
         const bool partial = (p.splits > 1 || tails) &&
                              static_cast<size_t>(p.splits) * p.Mp * p.Np * 4 <= cap;
         F32Args a;
-        a.exact = ldx >= kF32MaxStride;
         bool vec_a = layout == GRASS_DY_TxM;
         int64_t off = 0;
         int tile0 = 0;
@@ -709,8 +712,6 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
             const GemmSegment& q = seg[i];
             a.set[i] = F32Set{static_cast<const float*>(q.dY), q.ldy, q.idx, q.rho, q.C, q.ldc, q.rows, off, tile0};
             vec_a = vec_a && !q.idx && aligned_to(q.dY, 16) && q.ldy % 4 == 0 && q.rows % 4 == 0;
-            a.exact |= layout == GRASS_DY_TxM ? q.ldy >= kF32MaxStride
-                                              : (q.idx ? q.src_rows : q.rows) * q.ldy >= (int64_t{1} << 30) - 64;
             off += (q.rows + 7) / 8 * 8;
             tile0 += static_cast<int>((q.rows + p.bm - 1) / p.bm);
         }

@@ -43,7 +43,6 @@ struct F32Args {
     int64_t Mp, Np;
     int mxt;             // dY stored m x T
     int c_bf16;          // direct output in bf16
-    int exact;           // 1: the fp32 instruction from the start (row strides past 32-bit offsets)
     int tiles_m, tiles_n, splits, ktiles_per_split;
 };
 

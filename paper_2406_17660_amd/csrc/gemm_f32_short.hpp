@@ -89,9 +89,9 @@ __global__ __launch_bounds__(kShortWaves * 64) void tn_gemm_f32_short_kernel(F32
     const float* const pb = g.X + colB;
     struct Raw { float a[8], b[8]; };
     const int chunks = (T + 15) / 16;
-    const uint32_t offA = static_cast<uint32_t>((kMxT ? colA * sg.ldy + half * 8 : half * 8 * sg.ldy + colA) * 4);
+    const uint32_t offA = static_cast<uint32_t>((half * 8 * sg.ldy + colA) * 4);  // T x m
     const uint32_t offB = static_cast<uint32_t>((half * 8 * g.ldx + colB) * 4);
-    const uint32_t bytesA = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(kMxT ? 4 : sg.ldy * 4));
+    const uint32_t bytesA = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(sg.ldy * 4));
     const uint32_t bytesB = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(g.ldx * 4));
     const int whole = __builtin_amdgcn_readfirstlane(T / 16);
     auto load = [&](Raw& r, int c) {  // past the last whole chunk: that one again, unused
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kShortWaves * 64) void tn_gemm_f32_short_kernel(F32
         const auto ra = f32_buffer(sg.dY, t, bytesA), rb = f32_buffer(g.X, t, bytesB);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            r.a[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, offA, e * bytesA, 0));
+            r.a[e] = kMxT ? pa[t + half * 8 + e] : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, offA, e * bytesA, 0));
             r.b[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, offB, e * bytesB, 0));
         }
     };
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kShortWaves * 64) void tn_gemm_f32_short_kernel(F32
         };
         product(2, 0, 0); product(0, 2, 1); product(1, 1, 0); product(1, 0, 1); product(0, 1, 0); product(0, 0, 1);
     };
-    if (!g.exact) {
+    {
         Raw r0, r1;
         if (wave < whole) {
             load(r0, wave);
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(kShortWaves * 64) void tn_gemm_f32_short_kernel(F32
         acc[0][e] += acc[1][e];
         finite = __builtin_fmaf(acc[0][e], 0.f, finite);
     }
-    if (!__any(finite != 0.f) && !g.exact) {  // see gemm_f32_split.hpp
+    if (!__any(finite != 0.f)) {  // see gemm_f32_split.hpp
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[0][e] *= kF32Unscale;
     } else {

@@ -34,7 +34,8 @@ namespace {
 // 55 -> 35); 1868 x 1864, r = 467,
 // T = 7191: 176 -> 109; 472 x 1480, r = 118, T = 7488, dY stored m x T: 56 -> 32.
 constexpr int f32_bk(int bm) { return bm == 128 ? 16 : 32; }  // tokens per K tile
-// row strides (in elements) below this keep a lane's byte offset inside a K tile in 32 bits
+// Row strides (in elements) below this keep a lane's byte offset inside a K tile in 32 bits.  (Rows of a dY stored
+// m x T may lie anywhere: they are addressed in 64 bits.)
 constexpr int64_t kF32MaxStride = int64_t{1} << 24;
 
 constexpr int kF32Threads = 512, kF32LdsBytes = 96 * 1024;
@@ -49,6 +50,9 @@ __device__ __forceinline__ bf16x2 bf16_pair(float a, float b) {
     const f32x2_t v = {a, b};
     return __builtin_convertvector(v, bf16x2);
 }
+
+// 16 bytes from an address on a 4-byte boundary
+struct __attribute__((packed, aligned(4))) F32Chunk { u32x4_t v; };
 
 // A buffer of the whole address range from token t of a matrix on (rows `bytes` apart).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t f32_buffer(const float* base, uint32_t t, uint32_t bytes) {
@@ -131,23 +135,25 @@ __global__ __launch_bounds__(kF32Threads, 2) void tn_gemm_f32_split_kernel(F32Ar
     const int64_t ja = row0 + own_f * 32 + l32 < sg.rows ? row0 + own_f * 32 + l32 : 0;
     const int64_t colA = sg.idx ? sg.idx[ja] : ja;
     const int64_t colB = n0 + own_f * 32 + l32 < g.n ? n0 + own_f * 32 + l32 : 0;
-    const uint32_t offA = static_cast<uint32_t>((kMxT ? colA * sg.ldy + krow : krow * sg.ldy + colA) * 4);
+    const uint32_t offA = static_cast<uint32_t>((krow * sg.ldy + colA) * 4);  // T x m
+    const float* const rowA = sg.dY + colA * sg.ldy + krow;                   // m x T
     const uint32_t offB = static_cast<uint32_t>((krow * g.ldx + colB) * 4);
     struct Raw { float a[8], b[8]; };
-    const uint32_t bytesA = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(kMxT ? 4 : sg.ldy * 4));
+    const uint32_t bytesA = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(sg.ldy * 4));
     const uint32_t bytesB = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(g.ldx * 4));
     const int t_whole = __builtin_amdgcn_readfirstlane(
         ntiles > 0 ? t_begin + (t_end - t_begin) / BK * BK - BK : t_begin - BK);  // last whole tile
     auto load = [&](Raw& r, int i) {
         const int at = t_begin + i * BK;
         const uint32_t t0 = __builtin_amdgcn_readfirstlane(at < t_whole ? at : t_whole);
-        const auto ra = f32_buffer(sg.dY, t0, bytesA), rb = f32_buffer(g.X, t0, bytesB);
+        const auto rb = f32_buffer(g.X, t0, bytesB);
         if (kMxT) {
-            const u32x4_t lo = __builtin_amdgcn_raw_buffer_load_b128(ra, offA, 0, 0);
-            const u32x4_t hi = __builtin_amdgcn_raw_buffer_load_b128(ra, offA + 16, 0, 0);
+            const F32Chunk* const src = reinterpret_cast<const F32Chunk*>(rowA + t0);
+            const u32x4_t lo = src[0].v, hi = src[1].v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) { r.a[e] = __uint_as_float(lo[e]); r.a[4 + e] = __uint_as_float(hi[e]); }
         } else {
+            const auto ra = f32_buffer(sg.dY, t0, bytesA);
 #pragma unroll
             for (int e = 0; e < 8; ++e) r.a[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, offA, e * bytesA, 0));
         }
@@ -236,7 +242,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void tn_gemm_f32_split_kernel(F32Ar
 
     // Tile i is multiplied from LDS stage i % 2 while tile i + 1 is split into the other one and three
     // more are in flight.  Both groups take the same number of turns (the barrier is the workgroup's).
-    if (turns > 0 && !g.exact) {
+    if (turns > 0) {
         Raw R0 = {}, R1 = {}, R2 = {};
         if (t_whole >= t_begin) {
             load(R0, 0);
@@ -291,7 +297,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void tn_gemm_f32_split_kernel(F32Ar
         for (int b = 0; b < F; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) finite = __builtin_fmaf(acc[0][a][b][v], 0.f, finite);
-    if (!__any(finite != 0.f) && !g.exact) {
+    if (!__any(finite != 0.f)) {
 #pragma unroll
         for (int a = 0; a < F; ++a)
 #pragma unroll

@@ -168,3 +168,52 @@ def test_few_tokens_take_exact_products(T):
             assert torch.equal(a, b)
         if T == 1:
             assert torch.equal(results[0][0], dY.t()[:r] * X)
+
+
+def _spread(t, ld):
+    """`t` with rows ld elements apart, the gaps left as they are."""
+    buf = torch.empty((t.shape[0] - 1) * ld + t.shape[1], device=DEV)
+    view = buf.as_strided(t.shape, (ld, 1))
+    view.copy_(t)
+    return view
+
+
+def _products_and_step(dY, X, idx, rho, layout, kernel):
+    (T, n), r = X.shape, idx.shape[0]
+    m = dY.shape[1] if layout == grass.DY_TxM else dY.shape[0]
+    grass.set_test_option(grass.TEST_GEMM_TILE, kernel)
+    ws = grass.workspace(max(grass.step_group_workspace(T, n, [r], grass.F32, layout),
+                             grass.dense_workspace(T, m, n, grass.F32, layout)))
+    GC, G, M, V, W = (torch.zeros(k, n, device=DEV) for k in (r, m, r, r, m))
+    grass.compressed_grad(dY, X, idx, rho, GC, ws, layout)
+    grass.dense_grad(dY, X, G, ws, layout)
+    grass.step_group([dY], X, [idx], [rho], [M], [V], [W], 1e-2, 0.9, 0.999, 1e-8, 1, 0.5, ws, layout)
+    return GC, G, M, V, W
+
+
+@pytest.mark.parametrize("kernel", [32, 64, 128])
+@pytest.mark.parametrize("T,ld,m", [(50, 1 << 24, 63), (50, 1 << 24, 64), (43, (1 << 24) + 3, 90), (70, 1 << 27, 10)])
+def test_rows_of_mxt_storage_may_lie_anywhere(kernel, T, ld, m):
+    """A dY stored m x T whose rows reach past 2^30 elements (and one just below): the same kernel, the same bits as
+    with rows next to each other."""
+    n, r = 70, min(m, 40)
+    dY, X, _, rho = _inputs(T, m, n, r, grass.DY_MxT, seed=ld % 97)
+    idx = torch.arange(m - r, m, dtype=torch.int32, device=DEV)
+    want = _products_and_step(dY, X, idx, rho, grass.DY_MxT, kernel)
+    assert rel_fro(to_np(want[0]), _want(dY, X, idx, rho, grass.DY_MxT)) <= TOL_F32
+    for a, b in zip(_products_and_step(_spread(dY, ld), X, idx, rho, grass.DY_MxT, kernel), want):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kernel", [0, 32, 64, 128])
+@pytest.mark.parametrize("ldy,ldx", [((1 << 24) - 1, 64), (48, (1 << 24) - 1), (1 << 24, 64), (48, (1 << 24) + 1)])
+def test_row_strides_around_32_bit_offsets(kernel, ldy, ldx):
+    """From row strides of 2^24 on the kernel that addresses in 64 bits runs, whatever the size; below, the chosen
+    one.  Same bits as with rows next to each other."""
+    T, m, n, r = 41, 48, 64, 30
+    dY, X, idx, rho = _inputs(T, m, n, r, grass.DY_TxM, seed=7)
+    want = _products_and_step(dY, X, idx, rho, grass.DY_TxM, 16 if max(ldy, ldx) >= 1 << 24 else kernel)
+    got = _products_and_step(_spread(dY, ldy) if ldy > m else dY, _spread(X, ldx) if ldx > n else X, idx, rho,
+                             grass.DY_TxM, kernel)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
