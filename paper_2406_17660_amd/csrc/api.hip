@@ -136,9 +136,8 @@ grass_status grass_select_rows_static(const float* sumsq, int64_t m, int64_t r,
 
 size_t grass_cgrad_workspace(int64_t T, int64_t m, int64_t n, int64_t r, grass_dtype dt,
                              grass_dy_layout layout) {
-    (void)m;
     if (T < 0 || n < 0 || r < 0 || !small(T) || !small(n) || !small(r)) return 0;
-    return gemm_workspace_bytes(T, r, n, dt, layout, true);
+    return gemm_workspace_bytes(T, r, n, dt, layout, true, m);
 }
 
 grass_status grass_cgrad_plan(int64_t T, int64_t m, int64_t n, int64_t rows, int count,
@@ -171,7 +170,7 @@ grass_status grass_compressed_grad_timed(const void* dY, grass_dy_layout layout,
     if (st != GRASS_OK) return st;
     if (r < 0 || r > kMaxGridRows || ldgc < n || (r > 0 && m == 0)) return GRASS_ERR_SHAPE;
     if (!present(idx, r) || !present(rho, r) || !present(GC, r * n)) return GRASS_ERR_NULL;
-    if (!workspace_ok(dt, gemm_workspace_bytes(T, r, n, dt, layout, true), ws, ws_bytes))
+    if (!workspace_ok(dt, gemm_workspace_bytes(T, r, n, dt, layout, true, m), ws, ws_bytes))
         return GRASS_ERR_WORKSPACE;
     return launch_tn_gemm(dY, layout, ldy, X, ldx, dt, T, r, n, idx, rho, GC, GRASS_F32, ldgc, ws,
                           ws_bytes, as_stream(stream), m, static_cast<hipEvent_t>(ev_gemm_start),

@@ -265,6 +265,16 @@ NarrowPlan narrow_plan(int64_t T, int64_t n, int tiles_m, int64_t panel_rows, in
 
 // ---- fp32 inputs (gemm_f32_split.hpp, gemm_f32.hpp, gemm_f32_short.hpp)
 enum class F32Kernel { kSplit, kMfma, kShort };
+enum class F32Tail { kNone, kRows, kCols };  // the rest of a regular step in the same call
+struct F32Shape {
+    int64_t T, n;
+    int count;
+    const int64_t* rows;  // of each set
+    const int64_t* src;   // values per token of each set's dY; nullptr: not known (some workspace queries)
+    grass_dy_layout layout;
+    F32Tail tail;
+    bool far;  // rows of T x m or T x n storage further apart than the kernels with split operands reach
+};
 struct F32Plan {
     F32Kernel kernel;
     int bm;  // tile edge
@@ -278,99 +288,169 @@ constexpr int64_t kF32SplitMinT = 1024;
 // (0.6e-7 / 1.4e-7 / 1.9e-7), T = 4: 4.0e-8 / 3.2e-8 / 4.1e-8 (1.7e-7 / 1.3e-7 / 1.7e-7), T = 8: 5.4e-8 / 3.1e-8 / 4.0e-8
 // (2.2e-7 / 1.0e-7 / 1.3e-7).  A step of 32 rows takes 13.5 us so, 11 with the short kernel.
 constexpr int64_t kF32PartsMinT = 8;
-// Which kernel: the one of short products where all sets are single row tiles and K is short enough for
-// one workgroup per tile (256 x 256, r = 16, T = 512: 9.0 us in one launch; 6.4 + 3.8 us and the gap between
-// them with the fp32 instruction; at T = 4096 47 us against 13); the fp32
-// instruction below 0.3 Gflop, where starting up is what costs (680 x 288, r = 42, T = 1856: 12.8 against
-// 16.7 us with split operands, 959 x 1928, r = 119, T = 448, 0.2 Gflop: 15.9 and 17.4, 1112 x 1056, r = 278,
-// T = 432, 0.25 Gflop: 16.5 both; 1800 x 1356, r = 450, T = 320, 0.39 Gflop: 22.5 and 20.9); split operands beyond.
-// `far`: rows of T x m or T x n storage further apart than the offsets of the kernels with split operands reach.
-F32Kernel f32_kernel(int64_t T, const int64_t* rows, int count, int64_t n, bool far) {
-    if (far) return F32Kernel::kMfma;
-    switch (test_option(GRASS_TEST_GEMM_TILE)) {
-        case 0: break;
-        case 16: return F32Kernel::kMfma;
-        case kShortTile: return F32Kernel::kShort;
-        default: return F32Kernel::kSplit;
-    }
-    if (T < kF32PartsMinT) return F32Kernel::kMfma;
-    int64_t total = 0, most = 0;
-    for (int i = 0; i < count; ++i) {
-        total += rows[i];
-        most = rows[i] > most ? rows[i] : most;
-    }
-    if (most <= kShortTile && T <= 512) return F32Kernel::kShort;
-    return 2.0 * static_cast<double>(T) * static_cast<double>(total) * static_cast<double>(n) < 0.3e9 ? F32Kernel::kMfma
-                                                                                                     : F32Kernel::kSplit;
-}
-// `rows`: the sets' row counts.  Tile and K slices are those of least estimated time.  Split operands: a
+
+// The K slices of a product with this kernel and tile, those of least estimated time.  Split operands: a
 // workgroup (one per compute unit) takes its slice in turns of two K tiles, and a turn takes so long.
 // Columns gathered one by one cost the 64 tile more than its arithmetic does.  Measured per step, 128 / 64
 // tile at the best slice count of each: 1024 x 1024, r = 256, T = 8192: 42 / 56 us (39 / 45 with dY stored
 // m x T); 2048 x 2048, r = 256, T = 1024: 26 / 29 (22 / 20); 2048 x 512, r = 512, T = 512: 19 / 16 (18 /
 // 15); 768 x 2000, r = 48, T = 8192: 40 / 44 (35 / 27).  The fp32 instruction: 150 TFLOP/s over the filled
 // share of the machine's rounds.  A slice of partial tiles costs 8 bytes per output element at 4 TB/s, and
-// every slice keeps at least four K tiles.  A call without a fused tail (`step` false) of fewer than 1024
-// tokens is not split, so that it needs no workspace: its K loop is short.
+// every slice keeps at least four K tiles.  A call without a fused tail of fewer than 1024 tokens is not
+// split, so that it needs no workspace: its K loop is short.
 constexpr double f32_turn_us(int bm, bool mxt) { return bm == 128 ? (mxt ? 1.2 : 1.4) : (mxt ? 1.1 : 1.6); }
-F32Plan f32_plan(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_layout layout, bool step,
-                 size_t cap_bytes, bool far = false) {
-    const F32Kernel kernel = f32_kernel(T, rows, count, n, far);
-    F32Plan best_plan{kernel, 64, 0, 0, 0, 0, 1, 1};  // an empty product
+F32Plan f32_slices(F32Kernel kernel, int bm, const F32Shape& q, size_t cap_bytes) {
+    int64_t total = 0, tm = 0;
+    for (int i = 0; i < q.count; ++i) {
+        total += (q.rows[i] + 7) / 8 * 8;
+        tm += (q.rows[i] + bm - 1) / bm;
+    }
+    const int64_t tn = (q.n + bm - 1) / bm, T = q.T;
+    F32Plan p;
+    p.kernel = kernel;
+    p.bm = bm;
+    p.tiles_m = static_cast<int>(tm);
+    p.tiles_n = static_cast<int>(tn);
+    p.Mp = total;
+    p.Np = (tn * bm + kF32Tile - 1) / kF32Tile * kF32Tile;  // a slice of any plan holds one of the fp32 instruction's
+    p.splits = p.ktiles_per_split = 1;
+    const int64_t bk = kernel == F32Kernel::kSplit ? f32_bk(bm) : kF32BK, ktiles = (T + bk - 1) / bk, tiles = tm * tn;
+    const int64_t slice_bytes = p.Mp * p.Np * 4;
+    const int64_t room = slice_bytes > 0 ? static_cast<int64_t>(cap_bytes) / slice_bytes : 1;
+    int64_t smax = ktiles / 4;
+    if (smax > 128) smax = 128;
+    if (smax < 1 || (q.tail == F32Tail::kNone && T < kF32SplitMinT) || kernel == F32Kernel::kShort) smax = 1;
+    if (const int cap = test_option(GRASS_TEST_MAX_K_SLICES)) smax = cap > 0 && cap < smax ? cap : smax;
+    const double slice_us = static_cast<double>(slice_bytes) * 2 / 4e6;
+    const double tile_us = 2.0 * static_cast<double>(T) * bm * bm / 150e6;  // on the whole machine
     double best = 1e300;
-    const int forced = test_option(GRASS_TEST_GEMM_TILE);
-    for (const int bm : {128, 64, kShortTile}) {
-        if (kernel == F32Kernel::kShort ? bm != kShortTile
-            : kernel == F32Kernel::kMfma ? bm != kF32Tile
-                                         : bm == kShortTile || (forced && bm != (forced == 64 ? 64 : 128)))
-            continue;
-        int64_t total = 0, tm = 0;
-        for (int i = 0; i < count; ++i) {
-            total += (rows[i] + 7) / 8 * 8;
-            tm += (rows[i] + bm - 1) / bm;
-        }
-        const int64_t tn = (n + bm - 1) / bm;
-        F32Plan p;
-        p.kernel = kernel;
-        p.bm = bm;
-        p.tiles_m = static_cast<int>(tm);
-        p.tiles_n = static_cast<int>(tn);
-        p.Mp = total;
-        p.Np = (tn * bm + kF32Tile - 1) / kF32Tile * kF32Tile;  // a slice of any plan holds one of the fp32 instruction's
-        const int64_t bk = kernel == F32Kernel::kSplit ? f32_bk(bm) : kF32BK, ktiles = (T + bk - 1) / bk, tiles = tm * tn;
-        const int64_t slice_bytes = p.Mp * p.Np * 4;
-        const int64_t room = slice_bytes > 0 ? static_cast<int64_t>(cap_bytes) / slice_bytes : 1;
-        int64_t smax = ktiles / 4;
-        if (smax > 128) smax = 128;
-        if (smax < 1 || (!step && T < kF32SplitMinT) || kernel == F32Kernel::kShort) smax = 1;
-        if (const int cap = test_option(GRASS_TEST_MAX_K_SLICES)) smax = cap > 0 && cap < smax ? cap : smax;
-        const double slice_us = static_cast<double>(slice_bytes) * 2 / 4e6;
-        const double tile_us = 2.0 * static_cast<double>(T) * bm * bm / 150e6;  // on the whole machine
-        for (int64_t c = 1; c <= smax && tiles > 0; ++c) {
-            // slices of whole K tiles: the room must hold those that remain (a workspace of the size that
-            // the unlimited plan asks for then gives that plan again)
-            const int64_t per = (ktiles + c - 1) / c > 0 ? (ktiles + c - 1) / c : 1, slices = (ktiles + per - 1) / per;
-            if (c > 1 && c > room && slices > room) break;
-            const double rounds = static_cast<double>((tiles * c + 255) / 256);
-            double cost = slice_us * static_cast<double>(c);
-            if (kernel == F32Kernel::kMfma) cost += tile_us * rounds * 256 / static_cast<double>(c);
-            else cost += rounds * static_cast<double>((per + 1) / 2) * f32_turn_us(bm, layout == GRASS_DY_MxT) + (bm == 128 ? 3 : 0);
-            if (cost < best * (1 - 1e-9)) {
-                best = cost;
-                p.ktiles_per_split = static_cast<int>(per);
-                p.splits = slices > 0 ? static_cast<int>(slices) : 1;
-                best_plan = p;
-            }
+    for (int64_t c = 1; c <= smax && tiles > 0; ++c) {
+        // slices of whole K tiles: the room must hold those that remain (a workspace of the size that
+        // the unlimited plan asks for then gives that plan again)
+        const int64_t per = (ktiles + c - 1) / c > 0 ? (ktiles + c - 1) / c : 1, slices = (ktiles + per - 1) / per;
+        if (c > 1 && c > room && slices > room) break;
+        const double rounds = static_cast<double>((tiles * c + 255) / 256);
+        double cost = slice_us * static_cast<double>(c);
+        if (kernel == F32Kernel::kMfma) cost += tile_us * rounds * 256 / static_cast<double>(c);
+        else cost += rounds * static_cast<double>((per + 1) / 2) * f32_turn_us(bm, q.layout == GRASS_DY_MxT) + (bm == 128 ? 3 : 0);
+        if (cost < best * (1 - 1e-9)) {
+            best = cost;
+            p.ktiles_per_split = static_cast<int>(per);
+            p.splits = slices > 0 ? static_cast<int>(slices) : 1;
         }
     }
-    return best_plan;
+    return p;
+}
+
+// Cache lines of 128 bytes that the gather of a set touches per token (T x m storage).
+int64_t f32_lines(int64_t rows, int64_t src) { return rows < (src + 31) / 32 ? rows : (src + 31) / 32; }
+
+// The kernel of short products: all sets single row tiles, one round of workgroups (each has a compute unit to
+// itself) or, with a fused tail, a second one that the longer product pays for; up to 512 tokens, the longest that
+// sixteen wavefronts take in two turns.  A workgroup fetches its selected columns of dY by itself, which bounds it on
+// inputs that no cache holds: steps of 0.60 times the time of the fp32 instruction's two launches below 2000 lines,
+// 0.7 - 1.08 around 5000, 1.2 - 1.8 beyond 6000 (600 layers of r <= 32, T <= 512; 418 x 3224 tokens, r = 13: 11.8
+// against 10.0 us, 343 x 142, r = 11: 7.1 and 10.4).  Column steps have their tail in launches of its own and gain
+// less: 0.90 below 2000 lines, 0.98 - 1.25 around 4000.  A call without a tail, which the other kernels do not split,
+// always gains (0.33 - 0.7 beyond 128 tokens).  Three sets of 8 rows, n = 8712, T = 4 (819 workgroups): 16 us against 9.
+bool f32_short_shape(const F32Shape& q) {
+    int64_t most = 0, sets = 0;
+    for (int i = 0; i < q.count; ++i) {
+        most = q.rows[i] > most ? q.rows[i] : most;
+        sets += q.rows[i] > 0;
+    }
+    const int64_t tiles = sets * ((q.n + kShortTile - 1) / kShortTile);
+    return most <= kShortTile && q.T <= 512 && (tiles <= 256 || (q.tail == F32Tail::kRows && q.T >= 64 && tiles <= 512));
+}
+bool f32_short_lines(const F32Shape& q) {
+    if (q.tail == F32Tail::kNone || q.layout == GRASS_DY_MxT) return true;
+    int64_t lines = 0;
+    for (int i = 0; i < q.count; ++i) {
+        const int64_t l = f32_lines(q.rows[i], q.src[i]);
+        lines = l > lines ? l : lines;
+    }
+    return q.T * lines <= (q.tail == F32Tail::kRows ? 5120 : 2048);
+}
+
+// Estimated time in us, apart from what is the same for the fp32 instruction and the two tiles with split operands: a
+// start, a time per K tile of a workgroup's slice (`alone`, and `shared` times the workgroups per compute unit), per
+// 128 MB of gathered lines, per 10^6 bytes of partial tiles and per round of workgroups.  Fitted to 900 random
+// layers between 0.1 and 30 Gflop (T 16 - 16384, r 1 - 4000, one to three sets, steps, separate calls, full gradients;
+// every input new to the caches), which it meets within 7 % (median, 4 % with dY stored m x T).
+double f32_us(const F32Plan& p, const F32Shape& q) {
+    struct Cost { double start, alone, shared, lines, slices, round; };
+    constexpr Cost kCosts[2][3] = {{{11.0, 0.19, 0.20, 0.024, 0.0, 0.0},     // T x m: the fp32 instruction
+                                    {8.2, 0.18, 0.34, 0.033, 0.12, 3.2},     // split operands, 64 tile
+                                    {8.8, 0.54, 0.067, 0.030, 0.34, 3.2}},   // 128 tile
+                                   {{11.0, 0.21, 0.17, 0.12, 0.0, 0.0},      // m x T
+                                    {7.7, 0.30, 0.23, 0.038, 0.43, 2.0},
+                                    {7.6, 0.63, 0.040, 0.038, 0.36, 2.8}}};
+    const bool mxt = q.layout == GRASS_DY_MxT;
+    const Cost& k = kCosts[mxt][p.kernel == F32Kernel::kMfma ? 0 : p.bm == 64 ? 1 : 2];
+    double lines = 0;
+    for (int i = 0; i < q.count; ++i)
+        lines += mxt ? static_cast<double>(q.rows[i]) * static_cast<double>((q.T + 31) / 32)
+                     : static_cast<double>(f32_lines(q.rows[i], q.src[i])) * static_cast<double>(q.T);
+    const double wgs = static_cast<double>(p.tiles_m) * p.tiles_n * p.splits, rounds = ceil(wgs / 256);
+    return k.start + p.ktiles_per_split * (k.alone * rounds + k.shared * wgs / 256) + k.lines * lines * p.tiles_n * 128e-6 +
+           k.slices * static_cast<double>(p.Mp * p.Np * 4) * p.splits * 1e-6 + k.round * rounds;
+}
+
+// The plans that this shape may get (one, or, where the source widths are not known, all that they decide
+// between); returns how many.
+int f32_candidates(const F32Shape& q, size_t cap_bytes, F32Plan (&c)[4]) {
+    const auto one = [&](F32Kernel kernel, int bm) {
+        c[0] = f32_slices(kernel, bm, q, cap_bytes);
+        return 1;
+    };
+    const int forced = test_option(GRASS_TEST_GEMM_TILE);
+    if (q.far || forced == 16) return one(F32Kernel::kMfma, kF32Tile);
+    if (forced == kShortTile) return one(F32Kernel::kShort, kShortTile);
+    if (forced) return one(F32Kernel::kSplit, forced == 64 ? 64 : 128);
+    if (q.T < kF32PartsMinT) return one(F32Kernel::kMfma, kF32Tile);
+    int found = 0;
+    if (f32_short_shape(q)) {
+        if (q.src && f32_short_lines(q)) return one(F32Kernel::kShort, kShortTile);
+        if (!q.src) c[found++] = f32_slices(F32Kernel::kShort, kShortTile, q, cap_bytes);
+    }
+    const int first = found;
+    c[found++] = f32_slices(F32Kernel::kMfma, kF32Tile, q, cap_bytes);
+    // below 0.3 Gflop starting up is what costs, and the fp32 instruction starts sooner (680 x 288, r = 42, T = 1856:
+    // 12.8 against 16.7 us with split operands, 959 x 1928, r = 119, T = 448, 0.2 Gflop: 15.9 and 17.4)
+    int64_t total = 0;
+    for (int i = 0; i < q.count; ++i) total += q.rows[i];
+    if (2.0 * static_cast<double>(q.T) * static_cast<double>(total) * static_cast<double>(q.n) < 0.3e9) return found;
+    c[found++] = f32_slices(F32Kernel::kSplit, 64, q, cap_bytes);
+    c[found++] = f32_slices(F32Kernel::kSplit, 128, q, cap_bytes);
+    if (!q.src) return found;
+    // half a microsecond in favour of the fp32 instruction: against it for everything beyond 0.3 Gflop, 1.5 times
+    // slower at 1706 x 3400 (full gradient, T = 70: 22.6 us, 30.0 with split operands) and at 304 columns of 28 rows,
+    // twice, T = 16234 (67.1, 100.5 with the 64 tile, 35.1 with the 128 tile that a cost without the gather passed over)
+    int best = first;
+    double least = f32_us(c[first], q) - 0.5;
+    for (int i = first + 1; i < found; ++i) {
+        const double us = f32_us(c[i], q);
+        if (us < least) { least = us; best = i; }
+    }
+    c[0] = c[best];
+    return 1;
+}
+F32Plan f32_plan(const F32Shape& q, size_t cap_bytes) {
+    F32Plan c[4];
+    f32_candidates(q, cap_bytes, c);
+    return c[0];
 }
 // Workspace for the partial tiles of a product that is planned without a limit: a single slice without a fused
 // tail has none (and is what the plan gives for no workspace too).
-size_t f32_partial_bytes(int64_t T, const int64_t* rows, int count, int64_t n, grass_dy_layout layout, bool step) {
-    const F32Plan p = f32_plan(T, rows, count, n, layout, step, ~size_t{0} >> 1);
-    if (p.splits == 1 && !step) return 0;
-    return static_cast<size_t>(p.splits) * p.Mp * p.Np * 4 + 256;
+size_t f32_partial_bytes(const F32Shape& q) {
+    F32Plan c[4];
+    size_t most = 0;
+    for (int i = f32_candidates(q, ~size_t{0} >> 1, c); i-- > 0;) {
+        if (c[i].splits == 1 && q.tail == F32Tail::kNone) continue;
+        const size_t bytes = static_cast<size_t>(c[i].splits) * c[i].Mp * c[i].Np * 4 + 256;
+        most = bytes > most ? bytes : most;
+    }
+    return most;
 }
 
 // More than 64 KB of dynamic LDS has to be asked for, per kernel and device; the attribute sticks for
@@ -518,8 +598,9 @@ size_t narrow_cap_bytes(int64_t T, int64_t rows, int64_t n) {
 }
 
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
-                            grass_dy_layout layout, bool gathered) {
-    if (dt == GRASS_F32) return f32_partial_bytes(T, &mrows, 1, n, layout, false);
+                            grass_dy_layout layout, bool gathered, int64_t src_rows) {
+    if (dt == GRASS_F32)
+        return f32_partial_bytes(F32Shape{T, n, 1, &mrows, gathered ? &src_rows : &mrows, layout, F32Tail::kNone, false});
     // The launcher may plan for the small tile where the large one cannot be used, and run either plan
     // with any tile: room for the larger number of slices and the widest padding.
     const KSplit k1 = split_k(kTile128, T, mrows, n), k2 = split_k(kTile256, T, mrows, n);
@@ -553,9 +634,12 @@ static KSplit paired(KSplit k, int64_t T) {
 void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n, grass_dtype dt,
                        grass_dy_layout layout, int* tile, int* k_slices) {
     if (dt == GRASS_F32) {
-        int64_t each[GRASS_MAX_GROUP];  // the sets taken to be of equal size
-        for (int i = 0; i < count; ++i) each[i] = rows / count;
-        const F32Plan p = f32_plan(T, each, count, n, layout, false, ~size_t{0} >> 1);
+        int64_t each[GRASS_MAX_GROUP], src[GRASS_MAX_GROUP];  // the sets taken to be of equal size
+        for (int i = 0; i < count; ++i) {
+            each[i] = rows / count;
+            src[i] = m > each[i] ? m : each[i];
+        }
+        const F32Plan p = f32_plan(F32Shape{T, n, count, each, src, layout, F32Tail::kNone, false}, ~size_t{0} >> 1);
         *tile = p.bm == 128 ? 128 : 64;
         *k_slices = p.splits;
         return;
@@ -579,7 +663,8 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
 
 size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int64_t n,
                                   grass_dtype dt, grass_dy_layout layout, bool step) {
-    if (dt == GRASS_F32) return f32_partial_bytes(T, rows, count, n, layout, step);
+    if (dt == GRASS_F32)
+        return f32_partial_bytes(F32Shape{T, n, count, rows, nullptr, layout, step ? F32Tail::kRows : F32Tail::kNone, false});
     int64_t total = 0;
     size_t need = 0;  // the sets may also be run one at a time
     for (int i = 0; i < count; ++i) {
@@ -688,18 +773,20 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     }
     if (total == 0 || n == 0) return GRASS_OK;
     if (dt == GRASS_F32) {
-        int64_t rows[GRASS_MAX_GROUP];
-        bool tails = false;
+        int64_t rows[GRASS_MAX_GROUP], src[GRASS_MAX_GROUP];
+        bool tails = false, cols = false, far = ldx >= kF32MaxStride;
         for (int i = 0; i < count; ++i) {
             rows[i] = seg[i].rows;
+            src[i] = seg[i].src_rows;
             tails = tails || seg[i].tail != nullptr;
+            cols = cols || (seg[i].tail && seg[i].tail->U);
+            far = far || (layout == GRASS_DY_TxM && seg[i].ldy >= kF32MaxStride);
         }
         char* base = static_cast<char*>(ws);
         const size_t skip = base ? (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256 : 0;
         const size_t cap = base && ws_bytes > skip ? ws_bytes - skip : 0;
-        bool far = ldx >= kF32MaxStride;
-        for (int i = 0; i < count; ++i) far = far || (layout == GRASS_DY_TxM && seg[i].ldy >= kF32MaxStride);
-        const F32Plan p = f32_plan(T, rows, count, n, layout, tails, cap, far);
+        const F32Tail tail = cols ? F32Tail::kCols : tails ? F32Tail::kRows : F32Tail::kNone;
+        const F32Plan p = f32_plan(F32Shape{T, n, count, rows, src, layout, tail, far}, cap);
         // partial tiles whenever something reads them: several slices, or a fused tail (which takes
         // the sums from there); a workspace that cannot hold even one slice leaves the direct form
         const bool partial = (p.splits > 1 || tails) &&

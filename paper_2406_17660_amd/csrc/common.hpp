@@ -111,8 +111,9 @@ grass_status launch_gather_rows(const void* G, grass_dtype gdt, int64_t n, int64
                                 int64_t ldo, hipStream_t s);
 // C[j, i] = scale_j * sum_t A[t, col_j] * B[t, i]  (cgrad: col_j = idx[j], scale_j = rho[j];
 // dense: idx = rho = nullptr).  Output dtype odt, leading dimension ldc.
+// src_rows: values per token of dY where rows are gathered (fp32 plans depend on it).
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
-                            grass_dy_layout layout, bool gathered);
+                            grass_dy_layout layout, bool gathered, int64_t src_rows = 0);
 // Tile edge and number of K slices the launcher plans for `count` gathered sets of `rows` rows in
 // all (m: row length of dY, 0 when not known; tile 0 = the kernel that gathers inside the GEMM).
 void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n, grass_dtype dt,

@@ -217,3 +217,36 @@ def test_row_strides_around_32_bit_offsets(kernel, ldy, ldx):
                              grass.DY_TxM, kernel)
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kernel,T,m,n,rs,layout", [
+    (32, 512, 256, 256, (16,), grass.DY_TxM),       # one round of short workgroups
+    (32, 500, 3000, 2048, (32,), grass.DY_MxT),     # nothing to gather
+    (32, 300, 128, 5000, (20, 3), grass.DY_TxM),    # two rounds, 64 tokens and more
+    (16, 63, 128, 5000, (20, 3), grass.DY_TxM),     # two rounds, fewer
+    (16, 512, 256, 5500, (32, 32, 32), grass.DY_TxM),  # more than two
+    (16, 503, 603, 64, (31, 31), grass.DY_TxM),     # more gathered lines than a short workgroup fetches in time
+    (16, 1344, 512, 352, (37,), grass.DY_TxM),      # below 0.3 Gflop
+    (128, 98, 2904, 9776, (55, 55, 55), grass.DY_TxM),  # the gather bounds it: fewest column tiles
+    (128, 1344, 5905, 6339, (37,), grass.DY_TxM),
+    (128, 8192, 1024, 1024, (256,), grass.DY_TxM),
+    (64, 1024, 1024, 4096, (40,), grass.DY_MxT),
+])
+def test_the_kernel_a_step_runs_with(kernel, T, m, n, rs, layout):
+    """Which kernel is chosen, told by the bits of the results: those of the one that is forced, and of no other."""
+    X, sets = torch.randn(T, n, device=DEV), []
+    for k, r in enumerate(rs):
+        dY, _, idx, rho = _inputs(T, m, n, r, layout, seed=k)
+        sets.append((dY, idx, rho))
+    results = {}
+    for forced in (0, *KERNELS):
+        if forced == 32 and max(rs) > 32:
+            continue
+        grass.set_test_option(grass.TEST_GEMM_TILE, forced)
+        Ms, Vs, GCs = ([torch.zeros(r, n, device=DEV) for r in rs] for _ in range(3))
+        Ws = [torch.zeros(m, n, device=DEV) for _ in rs]
+        dYs, idxs, rhos = (list(t) for t in zip(*sets))
+        grass.step_group(dYs, X, idxs, rhos, Ms, Vs, Ws, 1e-2, 0.9, 0.999, 1e-8, 1, 0.5,
+                         grass.workspace(grass.step_group_workspace(T, n, rs, grass.F32, layout)), layout, GCs=GCs)
+        results[forced] = torch.cat(GCs)
+    assert [k for k in KERNELS if k in results and torch.equal(results[k], results[0])] == [kernel]

@@ -56,6 +56,5 @@ def test_fp32_products_of_one_slice_ask_for_no_workspace(T, n, r, layout):
     """Partial tiles are written for several slices, or for the tail of a step; the sums of one slice go to the
     output."""
     _, slices = grass.cgrad_plan(T, n, r, grass.F32, layout)
-    sizes = [grass.cgrad_workspace(T, r, n, r, grass.F32, layout), grass.dense_workspace(T, r, n, grass.F32, layout),
-             grass.cgrad_group_workspace(T, n, [r], grass.F32, layout)]
+    sizes = [grass.cgrad_workspace(T, r, n, r, grass.F32, layout), grass.dense_workspace(T, r, n, grass.F32, layout)]
     assert all((size == 0) == (slices == 1) for size in sizes), (slices, sizes)
