@@ -605,11 +605,12 @@ __global__ __launch_bounds__(kThreads) void select_norepl_kernel(
 //
 // While the total weight is below 2^53 (always for fewer than 8192 rows, and for more unless most
 // weigh as much as the heaviest) every prefix and difference is an integer that a double holds
-// exactly, and 64-bit integer steps (two instructions and a carry each, fifteen for the high
-// product) become single double ones.  Only the target x S / 2^64 is rounded: the double product
+// exactly, and the fifteen instructions of the high product become a single double one.  Only the target x S / 2^64 is rounded: the double product
 // is within 2 of it, so unless a prefix lies within 4 (checked against every prefix compared) each
 // comparison falls as with the exact target floor(x S / 2^64); otherwise that is computed and used.
-// The rows drawn are those of the sequential integer definition in every case.
+// The rows drawn are those of the sequential integer definition in every case.  From 2^53 on (uniform weights of 8192
+// rows and more) the same draw runs in 64-bit integers: 220 us for 1100 of 8801 rows, 402 for 2048 of 13720; in a
+// loop of its own, with selects instead of masks and one draw a turn, 321 and 591.
 // E, R = 1, 1 up to 4096 rows, 1, 2 up to 8192 and 2, 2 up to 16384.  1024 draws take 128 us of 4096 rows,
 // 153 of 8192 and 177 of 13824; before the masks went into EXEC, four draws into a turn of the loop, the
 // weight ahead of the updates and two rows into a lane: 166, 188 and 264 (E, R = 1, 1; 2, 1; 4, 1), with the
@@ -629,6 +630,7 @@ __device__ __forceinline__ unsigned long long from_lane_below(unsigned long long
 __device__ __forceinline__ double from_lane_below(double v) {
     return __longlong_as_double(static_cast<long long>(from_lane_below(static_cast<unsigned long long>(__double_as_longlong(v)))));
 }
+__device__ __forceinline__ unsigned long long read_lane(unsigned long long v, int l) { return read_lane64(v, l); }
 __device__ __forceinline__ double read_lane(double v, int l) {
     return __longlong_as_double(static_cast<long long>(read_lane64(static_cast<unsigned long long>(__double_as_longlong(v)), l)));
 }
@@ -638,45 +640,47 @@ __device__ __forceinline__ void write_lane(int& v, int x, int l) {
     asm("s_mov_b32 m0, %2\n\tv_writelane_b32 %0, %1, m0" : "+v"(v) : "s"(x), "s"(l) : "m0");
 }
 
-// A draw in doubles.  pex[e]: the weight before group E * lane + e (infinite for groups that do not exist).
-// near: some boundary of the group lies within 4 of the target, the only ones a target off by 2 could be on
-// the wrong side of (a target put into the wrong group is next to that group's edge).
-template <int E, int R>
+// A draw, in doubles or in 64-bit integers.  pex[e]: the weight before group E * lane + e (more than any target for
+// groups that do not exist).  near (doubles): some boundary of the group lies within 4 of the target, the only
+// ones a target off by 2 could be on the wrong side of (a target put into the wrong group is next to that group's edge).
+template <typename V, int E, int R>
 struct Draw {
     int n, f;  // group n - 1, row f of it
-    double cur[R], w;
+    V cur[R], w;
     unsigned long long upto[E], below[R];  // the lanes outside these masks lose the drawn weight
     bool near;
 };
-template <int E, int R>
-__device__ __forceinline__ Draw<E, R> locate(const double (&pex)[E], const double* leaf, double target, int lane) {
-    Draw<E, R> q;
+template <typename V, int E, int R>
+__device__ __forceinline__ Draw<V, E, R> locate(const V (&pex)[E], const V* leaf, V target, int lane) {
+    constexpr bool kRounded = static_cast<V>(0.5) != static_cast<V>(0);
+    Draw<V, E, R> q;
     q.n = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         q.upto[e] = __ballot(pex[e] <= target);
         q.n += __popcll(q.upto[e]);  // at least 1: the first group's prefix is 0
     }
-    const double* src = leaf + (lane - kWave) * R + q.n * (kWave * R);
+    const V* src = leaf + (lane - kWave) * R + q.n * (kWave * R);
 #pragma unroll
     for (int i = 0; i < R; ++i) q.cur[i] = src[i];
-    double before = pex[0];  // of the last of this lane's groups that starts at or before the target
+    V before = pex[0];  // of the last of this lane's groups that starts at or before the target
 #pragma unroll
     for (int e = 1; e < E; ++e) before = pex[e] <= target ? pex[e] : before;
     before = read_lane(before, (__popcll(q.upto[0]) - 1) & (kWave - 1));
     __builtin_amdgcn_sched_barrier(0);  // while the read is under way: nothing that waits for it moves up
-    double own = q.cur[0] - from_lane_below(q.cur[R - 1]);
-    const double t = target - before;
-    double least = t;
+    V own = q.cur[0] - from_lane_below(q.cur[R - 1]);
+    const V t = target - before;
+    V least = t;
     q.f = 0;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         q.below[i] = __ballot(q.cur[i] <= t);
         q.f += __popcll(q.below[i]);
         if (i > 0) own = q.cur[i - 1] <= t ? q.cur[i] - q.cur[i - 1] : own;
-        least = fmin(fabs(q.cur[i] - t), least);
+        if constexpr (kRounded) least = fmin(fabs(q.cur[i] - t), least);
     }
-    q.near = __ballot(least < 4.0) != 0;
+    if constexpr (kRounded) q.near = __ballot(least < 4.0) != 0;
+    else q.near = false;
     q.w = read_lane(own, __popcll(q.below[R - 1]) & (kWave - 1));  // the first lane with a row past the target
     return q;
 }
@@ -684,65 +688,39 @@ __device__ __forceinline__ Draw<E, R> locate(const double (&pex)[E], const doubl
 // 64 lanes are active before and after: with a mask in EXEC a subtraction is one vector instruction
 // instead of three (two selects and an addition).  The s_nop: w may come from the instruction just before,
 // a v_readlane, and a vector instruction may read a scalar register two wait states after one wrote it.
-template <int E, int R>
-__device__ __forceinline__ void take_out(Draw<E, R>& q, double (&pex)[E], double* leaf, int lane) {
-    static_assert(E <= R && R <= 2, "the forms below");
-    if constexpr (R == 1)
-        asm("s_not_b64 exec, %3\n\ts_nop 0\n\tv_add_f64 %0, %0, -%2\n\ts_not_b64 exec, %4\n\tv_add_f64 %1, %1, -%2\n\t"
-            "s_mov_b64 exec, -1"
-            : "+v"(pex[0]), "+v"(q.cur[0]) : "s"(q.w), "s"(q.upto[0]), "s"(q.below[0]) : "scc");
-    else if constexpr (E == 1)
-        asm("s_not_b64 exec, %4\n\ts_nop 0\n\tv_add_f64 %0, %0, -%3\n\ts_not_b64 exec, %5\n\tv_add_f64 %1, %1, -%3\n\t"
-            "s_not_b64 exec, %6\n\tv_add_f64 %2, %2, -%3\n\ts_mov_b64 exec, -1"
-            : "+v"(pex[0]), "+v"(q.cur[0]), "+v"(q.cur[1])
-            : "s"(q.w), "s"(q.upto[0]), "s"(q.below[0]), "s"(q.below[1]) : "scc");
-    else
-        asm("s_not_b64 exec, %5\n\ts_nop 0\n\tv_add_f64 %0, %0, -%4\n\ts_not_b64 exec, %6\n\tv_add_f64 %1, %1, -%4\n\t"
-            "s_not_b64 exec, %7\n\tv_add_f64 %2, %2, -%4\n\ts_not_b64 exec, %8\n\tv_add_f64 %3, %3, -%4\n\t"
-            "s_mov_b64 exec, -1"
-            : "+v"(pex[0]), "+v"(pex[1]), "+v"(q.cur[0]), "+v"(q.cur[1])
-            : "s"(q.w), "s"(q.upto[0]), "s"(q.upto[1]), "s"(q.below[0]), "s"(q.below[1]) : "scc");
-    double* dst = leaf + (lane - kWave) * R + q.n * (kWave * R);
+#define GRASS_SUB_F64(d, w) "v_add_f64 " d ", " d ", -" w "\n\t"
+#define GRASS_SUB_U64(d, w) "v_lshl_add_u64 " d ", " d ", 0, " w "\n\t"  // w: its negative
+#define GRASS_TAKE_OUT(SUB, W)                                                                                       \
+    if constexpr (R == 1)                                                                                            \
+        asm("s_not_b64 exec, %3\n\ts_nop 0\n\t" SUB("%0", "%2") "s_not_b64 exec, %4\n\t" SUB("%1", "%2")             \
+            "s_mov_b64 exec, -1"                                                                                     \
+            : "+v"(pex[0]), "+v"(q.cur[0]) : "s"(W), "s"(q.upto[0]), "s"(q.below[0]) : "scc");                       \
+    else if constexpr (E == 1)                                                                                       \
+        asm("s_not_b64 exec, %4\n\ts_nop 0\n\t" SUB("%0", "%3") "s_not_b64 exec, %5\n\t" SUB("%1", "%3")             \
+            "s_not_b64 exec, %6\n\t" SUB("%2", "%3") "s_mov_b64 exec, -1"                                            \
+            : "+v"(pex[0]), "+v"(q.cur[0]), "+v"(q.cur[1])                                                           \
+            : "s"(W), "s"(q.upto[0]), "s"(q.below[0]), "s"(q.below[1]) : "scc");                                     \
+    else                                                                                                             \
+        asm("s_not_b64 exec, %5\n\ts_nop 0\n\t" SUB("%0", "%4") "s_not_b64 exec, %6\n\t" SUB("%1", "%4")             \
+            "s_not_b64 exec, %7\n\t" SUB("%2", "%4") "s_not_b64 exec, %8\n\t" SUB("%3", "%4") "s_mov_b64 exec, -1"   \
+            : "+v"(pex[0]), "+v"(pex[E - 1]), "+v"(q.cur[0]), "+v"(q.cur[R - 1])                                     \
+            : "s"(W), "s"(q.upto[0]), "s"(q.upto[E - 1]), "s"(q.below[0]), "s"(q.below[R - 1]) : "scc")
+template <typename V, int E, int R>
+__device__ __forceinline__ void take_out(Draw<V, E, R>& q, V (&pex)[E], V* leaf, int lane) {
+    static_assert(E <= R && R <= 2, "the forms above");
+    if constexpr (static_cast<V>(0.5) != static_cast<V>(0)) {
+        GRASS_TAKE_OUT(GRASS_SUB_F64, q.w);
+    } else {
+        const V minus = 0 - q.w;
+        GRASS_TAKE_OUT(GRASS_SUB_U64, minus);
+    }
+    V* dst = leaf + (lane - kWave) * R + q.n * (kWave * R);
 #pragma unroll
     for (int i = 0; i < R; ++i) dst[i] = q.cur[i];
 }
-
-// The same draw in 64-bit integers; returns the row.
-template <int E, int R>
-__device__ __forceinline__ int draw_in_integers(unsigned long long (&pex)[E], unsigned long long* leaf,
-                                                unsigned long long& left, unsigned long long word, int groups, int lane) {
-    unsigned long long target = __umul64hi(word, left);
-    int n = 0, f = 0;
-    unsigned long long before = 0, cur[R];
-    bool upto[E], below[R];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        upto[e] = pex[e] <= target;
-        n += __popcll(__ballot(upto[e]));
-    }
-    const int g = n < groups ? n - 1 : groups - 1;  // groups that do not exist have the total as their prefix
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-        if (g % E == e) before = read_lane64(pex[e], g / E);
-    target -= before;
-    unsigned long long* at = leaf + (g * kWave + lane) * R;
-#pragma unroll
-    for (int i = 0; i < R; ++i) cur[i] = at[i];
-    unsigned long long own = cur[0] - from_lane_below(cur[R - 1]);
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-        below[i] = cur[i] <= target;
-        f += __popcll(__ballot(below[i]));
-        if (i > 0) own = below[i - 1] ? cur[i] - cur[i - 1] : own;
-    }
-    const unsigned long long w = read_lane64(own, __popcll(__ballot(below[R - 1])));
-#pragma unroll
-    for (int i = 0; i < R; ++i) at[i] = cur[i] - (below[i] ? 0ull : w);
-#pragma unroll
-    for (int e = 0; e < E; ++e) pex[e] -= upto[e] ? 0ull : w;
-    left -= w;
-    return g * kWave * R + f;
-}
+#undef GRASS_TAKE_OUT
+#undef GRASS_SUB_U64
+#undef GRASS_SUB_F64
 
 template <int E, int R>
 __global__ __launch_bounds__(kThreads) void select_norepl_flat_kernel(
@@ -831,40 +809,52 @@ __global__ __launch_bounds__(kThreads) void select_norepl_flat_kernel(
         double* dleaf = reinterpret_cast<double*>(leaf);
         double dpex[E], dleft = static_cast<double>(total_w);
 #pragma unroll
-        for (int e = 0; e < E; ++e) dpex[e] = E * lane + e < groups ? static_cast<double>(pex[e]) : __builtin_inf();
+        for (int e = 0; e < E; ++e) {
+            dpex[e] = E * lane + e < groups ? static_cast<double>(pex[e]) : __builtin_inf();
+            if (E * lane + e >= groups) pex[e] = ~0ull;  // (stays above every target: it loses at most the total)
+        }
         unsigned long long left = total_w;
         for (int j0 = 0; j0 < r; j0 += kWave) {
             const unsigned long long words = draw_word(seed, refresh, j0 + lane);
             const double unit = static_cast<double>(words) * 0x1p-64;
             const int count = __builtin_amdgcn_readfirstlane(r - j0 < kWave ? r - j0 : kWave);
             int rows = 0;  // lane jj: the row of draw j0 + jj
-            if (in_doubles) {
-                double target = dleft * read_lane(unit, 0);
-                auto draw = [&](int jj) {
-                    const double next_unit = read_lane(unit, (jj + 1) & (kWave - 1));
-                    auto q = locate<E, R>(dpex, dleaf, target, lane);
-                    if (__builtin_expect(q.near, 0)) {  // too close to a boundary to call: the exact target
-                        const unsigned long long exact =
-                            __umul64hi(read_lane64(words, jj), static_cast<unsigned long long>(dleft));
-                        q = locate<E, R>(dpex, dleaf, static_cast<double>(exact), lane);
-                    }
-                    // the next draw's target first: it is what the next draw begins with
-                    dleft -= q.w;
-                    target = dleft * next_unit;
-                    take_out<E, R>(q, dpex, dleaf, lane);
-                    write_lane(rows, (q.n - 1) * (kWave * R) + q.f, jj);
-                };
+            auto four_a_turn = [&](auto draw) {  // a taken branch costs a lone wavefront tens of clocks
                 int jj = 0;
-                for (; jj + 4 <= count; jj += 4) {  // a taken branch costs a lone wavefront tens of clocks
+                for (; jj + 4 <= count; jj += 4) {
                     draw(jj);
                     draw(jj + 1);
                     draw(jj + 2);
                     draw(jj + 3);
                 }
                 for (; jj < count; ++jj) draw(jj);
+            };
+            if (in_doubles) {
+                double target = dleft * read_lane(unit, 0);
+                four_a_turn([&](int jj) {
+                    const double next_unit = read_lane(unit, (jj + 1) & (kWave - 1));
+                    auto q = locate<double, E, R>(dpex, dleaf, target, lane);
+                    if (__builtin_expect(q.near, 0)) {  // too close to a boundary to call: the exact target
+                        const unsigned long long exact =
+                            __umul64hi(read_lane64(words, jj), static_cast<unsigned long long>(dleft));
+                        q = locate<double, E, R>(dpex, dleaf, static_cast<double>(exact), lane);
+                    }
+                    // the next draw's target first: it is what the next draw begins with
+                    dleft -= q.w;
+                    target = dleft * next_unit;
+                    take_out<double, E, R>(q, dpex, dleaf, lane);
+                    write_lane(rows, (q.n - 1) * (kWave * R) + q.f, jj);
+                });
             } else {
-                for (int jj = 0; jj < count; ++jj)
-                    write_lane(rows, draw_in_integers<E, R>(pex, leaf, left, read_lane64(words, jj), groups, lane), jj);
+                unsigned long long target = __umul64hi(read_lane64(words, 0), left);
+                four_a_turn([&](int jj) {
+                    const unsigned long long next_word = read_lane64(words, (jj + 1) & (kWave - 1));
+                    auto q = locate<unsigned long long, E, R>(pex, leaf, target, lane);
+                    left -= q.w;
+                    target = __umul64hi(next_word, left);
+                    take_out<unsigned long long, E, R>(q, pex, leaf, lane);
+                    write_lane(rows, (q.n - 1) * (kWave * R) + q.f, jj);
+                });
             }
             if (lane < count) atomicOr(&chosen[rows >> 5], 1u << (rows & 31));
         }

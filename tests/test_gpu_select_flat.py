@@ -61,3 +61,15 @@ def test_every_row_of_groups_of_128_is_drawn():
     for m in (4500, 8400):
         idx, _, _ = gpu_select(torch.from_numpy(_statistic(m, "zeros", 2)).to(DEV), m, grass.SEL_MULTI_NORM2, False)
         assert np.array_equal(to_np(idx), np.arange(m))
+
+
+@pytest.mark.parametrize("m,r", [(8192, 1), (8192, 67), (8192, 8192), (9001, 2), (9001, 131), (12345, 3000), (16384, 259)])
+def test_totals_past_53_bits_are_drawn_in_integers(m, r):
+    """Uniform draws, and draws of equal norms but for the last row's, from 8192 rows on: every remainder of four
+    draws a turn, and all rows of the smallest such size."""
+    s = _statistic(m, "equal", m)
+    s[-1] *= 0.25
+    for method, oracle in ((grass.SEL_UNIFORM, ref.UNIFORM), (grass.SEL_MULTI_NORM, ref.MULTI_NORM)):
+        idx, _, status = gpu_select(torch.from_numpy(s).to(DEV), r, method, False, grass.SCALE_PAPER, seed=m + r)
+        want, _, _ = ref.select_rows(s, r, oracle, False, grass.SCALE_PAPER, m + r, 0)
+        assert status == grass.OK and np.array_equal(to_np(idx), want)
