@@ -463,6 +463,9 @@ grass_status grass_adam_scatter_replayable(const float* GC, int64_t ldgc, void* 
  *   GRASS_TEST_MAX_K_SLICES  k > 0: the token dimension is split into at most k slices
  *   GRASS_TEST_NO_NARROW_GATHER  1: narrow layers take the packed route like all others (forcing
  *                            the tile with GRASS_TEST_GEMM_TILE does the same)
+ *   GRASS_TEST_RUN_TILE      128, 192 or 256 (bf16): the tile that runs, on the K slices of the plan (which
+ *                            GRASS_TEST_GEMM_TILE forces together with the tile); left to the
+ *                            library where the operands' alignment rules that tile out
  * Errors: DTYPE for an unknown option. */
 typedef enum {
     GRASS_TEST_GEMM_TILE = 0,
@@ -470,9 +473,29 @@ typedef enum {
     GRASS_TEST_PACK_MXT = 2,
     GRASS_TEST_NO_PAIRS = 3,
     GRASS_TEST_MAX_K_SLICES = 4,
-    GRASS_TEST_NO_NARROW_GATHER = 5
+    GRASS_TEST_NO_NARROW_GATHER = 5,
+    GRASS_TEST_RUN_TILE = 6
 } grass_test_option;
 grass_status grass_set_test_option(grass_test_option option, int value);
+
+/* The matrix-multiply kernel that the last product of the calling thread ran with (of several launches, the
+ * last; GRASS_KERNEL_NONE before the first). */
+typedef enum {
+    GRASS_KERNEL_NONE = 0,
+    GRASS_KERNEL_128_STAGED = 1,       /* bf16, 128 x 128, operands through registers */
+    GRASS_KERNEL_128 = 2,              /* bf16, load-to-LDS */
+    GRASS_KERNEL_128_256 = 3,
+    GRASS_KERNEL_256 = 4,
+    GRASS_KERNEL_256_ROWS = 5,         /* rows of a dY stored m x T gathered by the tile loads */
+    GRASS_KERNEL_256_UNALIGNED = 6,    /* both operands in any position */
+    GRASS_KERNEL_256_UNALIGNED_X = 7,  /* X in any position */
+    GRASS_KERNEL_NARROW = 8,           /* gather inside the product */
+    GRASS_KERNEL_F32 = 9,              /* fp32 matrix instruction */
+    GRASS_KERNEL_F32_SPLIT_64 = 10,    /* operands split into bf16 parts */
+    GRASS_KERNEL_F32_SPLIT_128 = 11,
+    GRASS_KERNEL_F32_SHORT = 12
+} grass_test_kernel;
+int grass_test_last_kernel(void);
 
 #ifdef __cplusplus
 }

@@ -10,8 +10,9 @@ using namespace grass;
 
 namespace {
 
-constexpr int kNumTestOptions = 6;
+constexpr int kNumTestOptions = 7;
 std::atomic<int> g_test_options[kNumTestOptions];  // zero-initialised: the library decides
+thread_local grass_test_kernel t_last_kernel = GRASS_KERNEL_NONE;
 
 constexpr int64_t kMaxGridRows = 65535;  // rows are carried in blockIdx.y
 
@@ -64,6 +65,7 @@ namespace grass {
 int test_option(grass_test_option which) {
     return g_test_options[which].load(std::memory_order_relaxed);
 }
+void note_kernel(grass_test_kernel which) { t_last_kernel = which; }
 }  // namespace grass
 
 extern "C" {
@@ -480,5 +482,7 @@ grass_status grass_set_test_option(grass_test_option option, int value) {
     g_test_options[which].store(value, std::memory_order_relaxed);
     return GRASS_OK;
 }
+
+int grass_test_last_kernel(void) { return t_last_kernel; }
 
 }  // extern "C"

@@ -160,6 +160,13 @@ Copies choose_copies(TileId tile, int64_t T, int64_t rows, int64_t n, grass_dy_l
     const double copied = (a_odd ? 4.0 * t * rows / 5.2e12 + 3e-6 : 0.0) + (b_odd ? 4.0 * t * n / 5.2e12 + 3e-6 : 0.0);
     return copied < in_place ? Copies{a_odd, b_odd} : Copies{false, false};
 }
+// What the launcher knows about the operands' positions: whole aligned 16-byte chunks (the left operand's after
+// packing), and whether the copy kernel, which reads pairs of values, can read X.
+struct Positions { bool a_chunks, x_chunks, x_pairs; };
+Copies copies_at(TileId tile, int64_t T, int64_t rows, int64_t n, grass_dy_layout layout, bool gathered, const Positions& at) {
+    const Copies c = choose_copies(tile, T, rows, n, layout, gathered);
+    return c.b && !at.x_pairs ? Copies{false, false} : c;
+}
 size_t aligned_x_bytes(int64_t T, int64_t n) {
     return round_up(static_cast<size_t>(T) * ((n + 7) / 8 * 8) * 2, 256);
 }
@@ -170,17 +177,20 @@ size_t aligned_x_bytes(int64_t T, int64_t n) {
 // the range, all three tiles each):
 //   256 x 256   10 us, 0.45 + 0.3 u up to one per unit (the clock falls as the chip fills), then 0.78 a round
 //   128 x 256    8.3, 0.33 + 0.17 u up to one, 0.95 with two, then 0.5 u
-//   128 x 128    6 or, beyond one, 8; 0.345 with one, 0.69 with two, 1.0 with three, then 0.35 u
+//   128 x 128    6 + 2 u up to one, then 8; 0.345 with one, 0.69 with two, 1.0 with three, then 0.35 u
 // Measured products, 256 / 128 x 256 / 128 tile: 4096 x 4096, r = 1024, T = 2047: 30.7 / 24.8 / 26.8 us; 10016 x 3864,
 // r = 1024, T = 640: 19.4 / 15.0 / 12.9; 2176 x 480, r = 272, T = 4461: 18.8 / 13.8 / 11.2; 1408 x 608, r = 352,
 // T = 109824: 89 / 101 / 79; 512 x 1376, r = 128, T = 65536: 90 / 68 / 50; 10860 x 3616, r = 1024, T = 9280: 65 / 77 / 94;
 // 1024 x 2048, r = 128, T = 131072: 123 / 103 / 118.
-// Operands in any position: 1.2 and 0.5 PFLOP/s with full tiles on all compute units, and the register route of
-// the 256 tile takes 7 us longer to fill and drain.
+// Operands in any position: 1.2 and 0.5 PFLOP/s with full tiles on all compute units, and 11 and 4 us to start.
 // Slices of partial tiles cost 3e-12 s per output element (written, then read by the reduction), 2.2e-12
 // while they stay in the caches; dY stored m x T has to be packed (transposed) for all but the large tile, which
-// gathers its rows itself: one more launch, 8 us with its gap (1888 x 1072, r = 472, T = 2944: 25.5 us so, 26.3 with
-// the pack and 128 tiles).
+// gathers its rows itself: one more launch of 5 us with its gap, and the panel read and written at 2 TB/s (1888 x 1072,
+// r = 472, T = 2944: 25.5 us without, 26.3 with the pack and 128 tiles; 235 x 64, r = 58, T = 864: 22.6 and 16.0).  An
+// odd-width operand may first be copied into aligned rows, which the tile decides about (choose_copies) and which counts
+// with it: 680 x 4109, r = 42, T = 41408: 212 us with a copied X and the large tile, 124 with the pack and 128 tiles.
+// Over 810 random layers stored m x T the tile chosen takes 1.1 % longer than the best of the three (2.3 % with 8 us
+// for the pack and the copies left out).
 // Whole steps against a rule that knew full-chip rates only (1.4, 0.9 and 0.6 PFLOP/s): 400 x 744, r = 50, T = 1280:
 // 19.5 -> 17.2 us; 776 x 456, r = 97, T = 3136: 20.2 -> 18.1; 1648 x 1896, r = 474 (columns), T = 448: 34.5 -> 32.5; 4640 x
 // 1064, r = 1024, T = 896: 28.7 -> 26.5; 1672 x 288, r = 209, T = 12404: 32.0 -> 29.8; long products unchanged.
@@ -188,30 +198,42 @@ double direct_us(TileId id, double wgs, double ktiles) {
     const double u = wgs / 256.0;
     if (id == kTile256) return 10.0 + ktiles * (u <= 1 ? 0.45 + 0.3 * u : 0.78 * ceil(u));
     if (id == kTileMid) return 8.3 + ktiles * (u <= 1 ? 0.33 + 0.17 * u : u <= 2 ? 0.95 : 0.5 * u);
-    return (u <= 1 ? 6.0 : 8.0) + ktiles * (u <= 1 ? 0.345 : u <= 2 ? 0.69 : u <= 3 ? 1.0 : 0.35 * u);
+    return (u <= 1 ? 6.0 + 2.0 * u : 8.0) + ktiles * (u <= 1 ? 0.345 : u <= 2 ? 0.69 : u <= 3 ? 1.0 : 0.35 * u);
 }
 TileId choose_tile(TileId planned, const KSplit& k, int64_t T, int64_t rows, int64_t n, bool rows_form,
-                   grass_dy_layout layout, bool aligned) {
+                   grass_dy_layout layout, bool gathered, const Positions& at) {
+    const bool aligned = at.a_chunks && at.x_chunks;
     if (const int forced = test_option(GRASS_TEST_GEMM_TILE))
         return forced == 192 && aligned ? kTileMid : planned;
+    const int run = test_option(GRASS_TEST_RUN_TILE);
     TileId best = planned;
     double least = 1e300;
     for (const TileId id : {kTile256, kTileMid, kTile128}) {
         if (id == kTileMid && !aligned) continue;
-        if (id == kTile128 && planned == kTile256 && !aligned) continue;  // its K tiles are twice as long
+        const Copies copy = aligned ? Copies{false, false} : copies_at(id, T, rows, n, layout, gathered, at);
+        const bool chunks = (at.a_chunks || copy.a) && (at.x_chunks || copy.b);
+        if (id == kTile128 && planned == kTile256 && !chunks) continue;  // its K tiles are twice as long
+        if (run == (id == kTile256 ? 256 : id == kTileMid ? 192 : 128)) return id;
         const Plan p = make_plan(id, k, T, rows, n, false);
         const double outputs = static_cast<double>(p.Mp) * static_cast<double>(p.Np);
         const double wgs = static_cast<double>(p.tiles_m) * p.tiles_n * k.splits;
         double t;
-        if (aligned) {
+        if (chunks) {
             t = 1e-6 * direct_us(id, wgs, static_cast<double>(k.tokens) / kFastBK);
         } else {
             const double slots = id == kTile128 ? 512.0 : 256.0;
             t = 2.0 * static_cast<double>(T) * outputs / (id == kTile256 ? 1.22e15 : 0.52e15) * (ceil(wgs / slots) * slots / wgs);
-            if (id == kTile256) t += 7e-6;
+            t += id == kTile256 ? 11e-6 : 4e-6;
+        }
+        if (copy.a) t += 4.0 * static_cast<double>(T) * static_cast<double>(rows) / 5.2e12 + 3e-6;
+        if (copy.b) {  // (one workgroup per row and 2048 columns)
+            const double moved = 4.0 * static_cast<double>(T) * static_cast<double>(n) / 5.2e12;
+            const double groups = 2.8e-10 * static_cast<double>(T) * static_cast<double>((n + 2047) / 2048);
+            t += (moved > groups ? moved : groups) + 3e-6;
         }
         t += (outputs * 4 <= kCachedSliceBytes ? 2.2e-12 : 3e-12) * outputs * k.slices();
-        if (layout == GRASS_DY_MxT && !(rows_form && id == kTile256)) t += 4.0 * static_cast<double>(T) * p.Mp / 4e12 + 8e-6;
+        if (layout == GRASS_DY_MxT && !(rows_form && id == kTile256 && chunks))
+            t += 2.0 * static_cast<double>(T) * static_cast<double>(p.Mp + rows) / 2e12 + 5e-6;
         if (t < least) { least = t; best = id; }
     }
     return best;
@@ -811,6 +833,8 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         a.c_bf16 = odt == GRASS_BF16;
         a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
         a.splits = p.splits; a.ktiles_per_split = p.ktiles_per_split;
+        note_kernel(p.kernel == F32Kernel::kShort ? GRASS_KERNEL_F32_SHORT : p.kernel == F32Kernel::kMfma ? GRASS_KERNEL_F32
+                    : p.bm == 64 ? GRASS_KERNEL_F32_SPLIT_64 : GRASS_KERNEL_F32_SPLIT_128);
         if (p.kernel == F32Kernel::kShort) {
             F32StepArgs q{};
             // one row tile per set, and nobody asks for the product's and the tail's own times
@@ -930,6 +954,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
                 if (dev >= 0 && dev < 64) raised[dev].store(true, std::memory_order_release);
             }
         }
+        note_kernel(GRASS_KERNEL_NARROW);
         launch_stamped(tn_gemm_gather_narrow_kernel, dim3(grid), dim3(256), kNarrowLdsBytes, s, ev_start,
                        ev_stop, a);
         return finish_segments(seg, count, a.P, np.splits, np.Mp, np.Np, n, odt, s, ev_tail_start,
@@ -959,17 +984,15 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     // whole cache lines per row (64 values of k per load) when the K tiles pair up
     const bool pairs_ok = rows_ok && T % (2 * kFastBK) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0;
     if (pairs_ok && planned == kTile256) ks = paired(ks, T);
-    const bool chunks = aligned_to(X, 16) && ldx % 8 == 0 && n % 8 == 0 &&
-                        (pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0));
-    const TileId tile = sizes ? choose_tile(planned, ks, T, total, n, rows_ok, layout, chunks) : kTile128;
-    Copies copy = choose_copies(tile, T, total, n, layout, gathered);
-    if (copy.b && !aligned_to(X, 4)) copy = Copies{false, false};  // what the copy kernel asks for
+    const Positions at{pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0),
+                       aligned_to(X, 16) && ldx % 8 == 0 && n % 8 == 0, aligned_to(X, 4)};
+    const TileId tile = sizes ? choose_tile(planned, ks, T, total, n, rows_ok, layout, gathered, at) : kTile128;
+    const Copies copy = copies_at(tile, T, total, n, layout, gathered, at);
     pack = pack || copy.a;
     const int64_t nb = copy.b ? (n + 7) / 8 * 8 : n;  // columns the GEMM sees
     // whole aligned 16-byte chunks: what the load-to-LDS kernels and the aligned small tile move
-    const bool a_chunks = pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0);
-    const bool aligned = a_chunks &&
-                         (copy.b || (aligned_to(X, 16) && ldx % 8 == 0 && n % 8 == 0));
+    const bool a_chunks = pack || at.a_chunks;
+    const bool aligned = a_chunks && (copy.b || at.x_chunks);
     const bool a_rows_form = rows_ok && tile == kTile256 && aligned;
     const bool a_pairs = a_rows_form && pairs_ok;
     if (a_rows_form) pack = false;
@@ -1105,6 +1128,11 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
 
     const unsigned grid = static_cast<unsigned>(blocks);
     hipError_t le;
+    note_kernel(tile == kTileMid ? GRASS_KERNEL_128_256
+                : tile == kTile128 ? (small_direct ? GRASS_KERNEL_128 : GRASS_KERNEL_128_STAGED)
+                : a_rows_form ? GRASS_KERNEL_256_ROWS
+                : aligned ? GRASS_KERNEL_256
+                : a_direct ? GRASS_KERNEL_256_UNALIGNED_X : GRASS_KERNEL_256_UNALIGNED);
     if (tile == kTile256) {  // the events are stamped with this dispatch's own start and end
         if (a_pairs)
             launch_stamped(tn_gemm_bf16_direct_kernel<false, false, true, true>, dim3(grid), dim3(256), 0, s,

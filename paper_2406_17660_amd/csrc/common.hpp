@@ -72,6 +72,7 @@ inline bool aligned_to(const void* p, size_t a) { return (reinterpret_cast<uintp
 
 // Value of a test hook (grass_set_test_option): 0 unless a test has forced a code path.
 int test_option(grass_test_option which);
+void note_kernel(grass_test_kernel which);  // for grass_test_last_kernel
 
 // Kernel launchers, one per translation unit.  All pointers are device pointers; shapes
 // have been validated by the C entry points in api.hip before these are called.

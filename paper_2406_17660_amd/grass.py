@@ -20,7 +20,10 @@ SEL_TOPR, SEL_UNIFORM, SEL_MULTI_NORM, SEL_MULTI_NORM2 = 0, 1, 2, 3
 SCALE_PAPER, SCALE_ONE, SCALE_INV_SQRT_RQ = 0, 1, 2
 DY_TxM, DY_MxT = 0, 1
 TEST_GEMM_TILE, TEST_FUSED_STATS, TEST_PACK_MXT, TEST_NO_PAIRS, TEST_MAX_K_SLICES = 0, 1, 2, 3, 4
-TEST_NO_NARROW_GATHER = 5
+TEST_NO_NARROW_GATHER, TEST_RUN_TILE = 5, 6
+(KERNEL_NONE, KERNEL_128_STAGED, KERNEL_128, KERNEL_128_256, KERNEL_256, KERNEL_256_ROWS, KERNEL_256_UNALIGNED,
+ KERNEL_256_UNALIGNED_X, KERNEL_NARROW, KERNEL_F32, KERNEL_F32_SPLIT_64, KERNEL_F32_SPLIT_128,
+ KERNEL_F32_SHORT) = range(13)
 
 EXPORTS = [
     "grass_status_string", "grass_row_stats", "grass_select_workspace", "grass_select_rows",
@@ -30,7 +33,7 @@ EXPORTS = [
     "grass_grad_row_stats_workspace", "grass_grad_row_stats", "grass_scatter_update_cols",
     "grass_cgrad_group_workspace", "grass_compressed_grad_group",
     "grass_adam_rows_state", "grass_adam_scatter_state", "grass_cgrad_plan",
-    "grass_set_test_option", "grass_select_static_capacity", "grass_select_rows_static",
+    "grass_set_test_option", "grass_test_last_kernel", "grass_select_static_capacity", "grass_select_rows_static",
     "grass_adam_step_scalars", "grass_adam_scatter_replayable",
     "grass_step_group_workspace", "grass_step_group", "grass_step_group_timed",
     "grass_step_cols_workspace", "grass_step_cols",
@@ -239,6 +242,11 @@ def cgrad_plan(T, n, rows, dtype, layout=DY_TxM, m=0, count=1):
 def set_test_option(option: int, value: int):
     """Test hook: force one of the launcher's choices (0 gives it back to the library)."""
     _check(lib().grass_set_test_option(option, value), "grass_set_test_option")
+
+
+def last_kernel() -> int:
+    """Test hook: the matrix-multiply kernel (KERNEL_*) of this thread's last product."""
+    return lib().grass_test_last_kernel()
 
 
 def compressed_grad(dY, X, idx, rho, GC, ws, layout=DY_TxM, gemm_events=None):
