@@ -466,6 +466,8 @@ grass_status grass_adam_scatter_replayable(const float* GC, int64_t ldgc, void* 
  *   GRASS_TEST_RUN_TILE      128, 192 or 256 (bf16): the tile that runs, on the K slices of the plan (which
  *                            GRASS_TEST_GEMM_TILE forces together with the tile); left to the
  *                            library where the operands' alignment rules that tile out
+ *   GRASS_TEST_UNALIGNED_X   1: an X in any position beside an aligned left operand takes the 256 tile's kernel
+ *                            for it from the first K tile and row tile on
  * Errors: DTYPE for an unknown option. */
 typedef enum {
     GRASS_TEST_GEMM_TILE = 0,
@@ -474,7 +476,8 @@ typedef enum {
     GRASS_TEST_NO_PAIRS = 3,
     GRASS_TEST_MAX_K_SLICES = 4,
     GRASS_TEST_NO_NARROW_GATHER = 5,
-    GRASS_TEST_RUN_TILE = 6
+    GRASS_TEST_RUN_TILE = 6,
+    GRASS_TEST_UNALIGNED_X = 7
 } grass_test_option;
 grass_status grass_set_test_option(grass_test_option option, int value);
 

@@ -10,7 +10,7 @@ using namespace grass;
 
 namespace {
 
-constexpr int kNumTestOptions = 7;
+constexpr int kNumTestOptions = 8;
 std::atomic<int> g_test_options[kNumTestOptions];  // zero-initialised: the library decides
 thread_local grass_test_kernel t_last_kernel = GRASS_KERNEL_NONE;
 

@@ -1124,7 +1124,8 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     const bool small_direct = tile == kTile128 && aligned && sizes;
     g.ktiles_per_split = static_cast<int>(ks.tokens / (small_direct ? kMidBK : tile_k(tile)));
 
-    const bool a_direct = a_chunks && p.tiles_m > 1 && g.ktiles_per_split >= kUnalignedXMin;
+    const bool a_direct = a_chunks && (test_option(GRASS_TEST_UNALIGNED_X) == 1 ||
+                                       (p.tiles_m > 1 && g.ktiles_per_split >= kUnalignedXMin));
 
     const unsigned grid = static_cast<unsigned>(blocks);
     hipError_t le;

@@ -20,7 +20,7 @@ SEL_TOPR, SEL_UNIFORM, SEL_MULTI_NORM, SEL_MULTI_NORM2 = 0, 1, 2, 3
 SCALE_PAPER, SCALE_ONE, SCALE_INV_SQRT_RQ = 0, 1, 2
 DY_TxM, DY_MxT = 0, 1
 TEST_GEMM_TILE, TEST_FUSED_STATS, TEST_PACK_MXT, TEST_NO_PAIRS, TEST_MAX_K_SLICES = 0, 1, 2, 3, 4
-TEST_NO_NARROW_GATHER, TEST_RUN_TILE = 5, 6
+TEST_NO_NARROW_GATHER, TEST_RUN_TILE, TEST_UNALIGNED_X = 5, 6, 7
 (KERNEL_NONE, KERNEL_128_STAGED, KERNEL_128, KERNEL_128_256, KERNEL_256, KERNEL_256_ROWS, KERNEL_256_UNALIGNED,
  KERNEL_256_UNALIGNED_X, KERNEL_NARROW, KERNEL_F32, KERNEL_F32_SPLIT_64, KERNEL_F32_SPLIT_128,
  KERNEL_F32_SHORT) = range(13)

@@ -33,5 +33,5 @@ def _library_decides_again_after_each_test():
     if grass._lib is not None:
         for option in (grass.TEST_GEMM_TILE, grass.TEST_FUSED_STATS, grass.TEST_PACK_MXT,
                        grass.TEST_NO_PAIRS, grass.TEST_MAX_K_SLICES, grass.TEST_NO_NARROW_GATHER,
-                       grass.TEST_RUN_TILE):
+                       grass.TEST_RUN_TILE, grass.TEST_UNALIGNED_X):
             grass.set_test_option(option, 0)

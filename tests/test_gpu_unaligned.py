@@ -26,7 +26,7 @@ def _framed(rows, cols, ld, first, gen):
     return view
 
 
-def _check(T, m, n, r, layout, ldy_pad, ldx_pad, first, seed=0):
+def _check(T, m, n, r, layout, ldy_pad, ldx_pad, first, seed=0, kernel=None):
     gen = torch.Generator(device=DEV)
     gen.manual_seed(seed)
     X = _framed(T, n, n + ldx_pad, first, gen)
@@ -40,6 +40,7 @@ def _check(T, m, n, r, layout, ldy_pad, ldx_pad, first, seed=0):
     GC = torch.full((r, n), float("nan"), device=DEV)
     grass.compressed_grad(dY, X, idx, rho, GC,
                           grass.workspace(grass.cgrad_workspace(T, m, n, r, grass.BF16, layout)), layout)
+    assert kernel is None or grass.last_kernel() == kernel
     assert rel_fro(to_np(GC), want) <= TOL_F32
     G = torch.full((m, n), float("nan"), device=DEV)
     grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(T, m, n, grass.BF16, layout)), layout)
@@ -54,6 +55,18 @@ def _check(T, m, n, r, layout, ldy_pad, ldx_pad, first, seed=0):
 def test_any_position(tile, T, m, n, first, pad):
     grass.set_test_option(grass.TEST_GEMM_TILE, tile)
     _check(T, m, n, min(m, 140), grass.DY_TxM, pad, pad, first)
+
+
+# the same on the large tile's kernel for both operands in any position (X on a 2-byte boundary, which no copy reads),
+# on slices of 64 tokens
+@pytest.mark.parametrize("slices", [1, 3])
+@pytest.mark.parametrize("T", [32, 33, 63, 64, 95, 129, 192, 200, 257, 1000])
+@pytest.mark.parametrize("m,n,first,pad", [(9, 9, 9, 0), (257, 135, 9, 0), (263, 250, 11, 3), (120, 391, 15, 2)])
+def test_any_position_on_the_large_tile(T, m, n, first, pad, slices):
+    grass.set_test_option(grass.TEST_RUN_TILE, 256)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, slices)
+    _check(T, m, n, min(m, 140), grass.DY_TxM, pad, pad, first, kernel=grass.KERNEL_256_UNALIGNED)
+    assert grass.last_kernel() == grass.KERNEL_256_UNALIGNED  # the full gradient too
 
 
 @pytest.mark.parametrize("tile", [128, 256])
@@ -83,11 +96,35 @@ def test_full_gradient_whose_odd_operand_is_copied(T, m, n):
     _check(T, m, n, 8, grass.DY_TxM, 0, 0, 8)
 
 
-# aligned left operand, odd X: every length of the ring's start (nine whole tiles), of its steady loop
-# (four tiles a turn) and of its end
+# Aligned left operand, X in any position: every length of the ring's start (nine whole tiles), of its steady loop
+# (four tiles a turn) and of its end, one and two row and column tiles, a last slice of one to nine tiles.  X starts on
+# a 2-byte boundary, which no copy reads.
+def _left_operand_by_load_to_lds(T, r, n, slices):
+    grass.set_test_option(grass.TEST_RUN_TILE, 256)
+    grass.set_test_option(grass.TEST_UNALIGNED_X, 1)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, slices)
+    _check(T, 264, n, r, grass.DY_TxM, 0, 0, 9, kernel=grass.KERNEL_256_UNALIGNED_X)
+
+
 @pytest.mark.parametrize("rest", [0, 5])
 @pytest.mark.parametrize("tiles", [*range(1, 19), 21, 22])
 def test_left_operand_by_load_to_lds(tiles, rest):
-    grass.set_test_option(grass.TEST_GEMM_TILE, 256)
-    grass.set_test_option(grass.TEST_MAX_K_SLICES, 1)
-    _check(32 * tiles + rest, 264, 261, 140, grass.DY_TxM, 0, 0, 8)
+    _left_operand_by_load_to_lds(32 * tiles + rest, 140, 261, 1)
+    _left_operand_by_load_to_lds(32 * tiles + rest, 262, 250, 1)
+
+
+@pytest.mark.parametrize("last", range(1, 10))
+def test_left_operand_by_load_to_lds_in_slices(last):
+    """Slices of 20 K tiles (10 of the plan's 64 tokens) and a shorter one."""
+    T = 32 * (20 * 19 + last) - (3 if last % 2 else 0)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 20)
+    assert grass.cgrad_plan(T, 261, 260, grass.BF16) in ((128, 20), (256, 20))
+    _left_operand_by_load_to_lds(T, 260, 261, 20)
+
+
+def test_left_operand_by_load_to_lds_is_chosen():
+    """Odd width, more than one row tile and 64 K tiles per slice."""
+    dY, X = torch.zeros(65536, 512, dtype=BF, device=DEV), torch.zeros(65536, 2045, dtype=BF, device=DEV)
+    G = torch.empty(512, 2045, device=DEV)
+    grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(65536, 512, 2045, grass.BF16)))
+    assert grass.last_kernel() == grass.KERNEL_256_UNALIGNED_X
