@@ -243,7 +243,8 @@ void tn_gemm_bf16_unaligned_kernel(GemmArgs g) {
     }
 
     // Stores.  Only the tiles that hold a crossing chunk look at it: shift says how far the chunk was
-    // moved to the left; its first `shift` columns repeat the chunk before it and are skipped.
+    // moved to the left; its first `shift` columns repeat the chunk before it and are skipped.  (store_unaligned
+    // below does the same; called here it costs this kernel 5 %: 300 x 1111, T = 65536: 116 us as it is, 121 so.)
     float* P = g.P + (static_cast<int64_t>(split) * g.Mp + m0 + wr * 128) * g.Np + n0 + wc * 128;
     const int shiftN = static_cast<int>(-g.Ncols & 7), shiftM = static_cast<int>(-g.Mcols & 7);
     const int edgeN = static_cast<int>((g.Ncols & ~int64_t{7}) - n0 - wc * 128);  // crossing chunk,
