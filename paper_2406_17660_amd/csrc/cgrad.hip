@@ -445,11 +445,12 @@ int f32_candidates(const F32Shape& q, size_t cap_bytes, F32Plan (&c)[4]) {
     c[found++] = f32_slices(F32Kernel::kSplit, 64, q, cap_bytes);
     c[found++] = f32_slices(F32Kernel::kSplit, 128, q, cap_bytes);
     if (!q.src) return found;
-    // half a microsecond in favour of the fp32 instruction: against it for everything beyond 0.3 Gflop, 1.5 times
-    // slower at 1706 x 3400 (full gradient, T = 70: 22.6 us, 30.0 with split operands) and at 304 columns of 28 rows,
-    // twice, T = 16234 (67.1, 100.5 with the 64 tile, 35.1 with the 128 tile that a cost without the gather passed over)
+    // a fifth of a microsecond in favour of the fp32 instruction (90 other layers: 0.36 % above the best of the three,
+    // 0.58 and 0.74 with nothing and with half a microsecond).  With split operands for everything beyond 0.3 Gflop
+    // 1706 x 3400 (full gradient, T = 70) took 30.0 us, 22.6 with the fp32 instruction, and two sets of 28 of 304
+    // columns, T = 16234, 100.5 with the 64 tile that a cost without the gather preferred, 35.1 with the 128 tile.
     int best = first;
-    double least = f32_us(c[first], q) - 0.5;
+    double least = f32_us(c[first], q) - 0.2;
     for (int i = first + 1; i < found; ++i) {
         const double us = f32_us(c[i], q);
         if (us < least) { least = us; best = i; }
