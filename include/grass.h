@@ -20,8 +20,8 @@
  *     scratch memory is sized by the *_workspace queries and passed in by the caller.
  *     It keeps no state that a result depends on.  What it does keep, per process: one
  *     flag per device and kernel recording that the kernel's LDS limit has been raised
- *     (set once, atomically), and the test hooks of grass_set_test_option (initially
- *     off).
+ *     (set once, atomically), the test hooks of grass_set_test_option (initially
+ *     off) and, per thread, which kernel its last product ran (grass_test_last_kernel).
  *   - Matrices are row-major with an explicit leading dimension counted in
  *     ELEMENTS (ld >= number of columns).
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  All
@@ -185,8 +185,8 @@ grass_status grass_compressed_grad(const void* dY, grass_dy_layout layout, int64
  * one matrix), `rows` rows in all (r for one matrix; for a group call the sum of its r[i], each
  * rounded up to a multiple of 8; the sets are taken to be of equal size), m the row length of
  * dY (0: not given; fp32 plans, which it decides about, then take the rows of a set for it).  `*tile` receives the edge of the output tile that the slices are
- * planned for (256 or 128; for fp32 inputs 128 or 64, or 64 for the smaller tile of short products; the kernel may run with another tile where
- * that is faster, with the same sums), or 0 for narrow layers (bf16, T x m storage, m <= 512,
+ * planned for (256 or 128; for fp32 inputs 128 or 64, 64 also for the 32-wide tile of short products; the kernel
+ * may run with another tile where that is faster, with the same sums), or 0 for narrow layers (bf16, T x m storage, m <= 512,
  * r <= 128 per set, n <= 512, T a multiple of 16), whose gather runs inside the matrix-multiply kernel (128 x 256 tiles, no
  * packed panel); `*k_slices` the number of slices the token dimension is split into (their
  * partial products are what the split-K reduction, or the fused tail of grass_step_group /
@@ -394,7 +394,9 @@ grass_status grass_step_group(int count, const grass_step_layer* layers, grass_d
  * serves them together, or two launches where the rows of some layers start on 16-byte boundaries
  * and those of others do not; the last layer's when the layers run one after the other), stamped
  * with the dispatches' own times.  For a benchmark that wants the step's tail as it runs inside
- * the step sequence.  Everything else is grass_step_group. */
+ * the step sequence.  fp32 steps that otherwise run as one kernel (sets of at most 32 rows, at most 512
+ * tokens) run as two when any event is given, with the same bits: the events time those two.  Everything else
+ * is grass_step_group. */
 grass_status grass_step_group_timed(int count, const grass_step_layer* layers,
                                     grass_dy_layout layout, const void* X, int64_t ldx,
                                     grass_dtype dt, int64_t T, int64_t n, grass_dtype sdt,
