@@ -273,7 +273,7 @@ __global__ __launch_bounds__(kManyWaves * 64) void reduce_adam_scatter_kernel(
     float* __restrict__ GC = q.GC;
     float* __restrict__ U = q.U;
     const AdamParams p = resolve(p_in);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int32_t row = kToU ? 0 : idx[j];
     if (!kToU && j > 0 && idx[j - 1] == row) return;  // whole workgroup: no barrier is skipped by part of it
     // summing phase: this lane's four columns of the partial tiles, whose rows are whole tiles (where
@@ -292,16 +292,11 @@ __global__ __launch_bounds__(kManyWaves * 64) void reduce_adam_scatter_kernel(
     if (!kToU && live1) wv.load_once(W + static_cast<int64_t>(row) * ldw + c1);
     float acc = 0.f;
     for (int64_t jj = j; kToU ? jj == j : (jj < r && idx[jj] == row); ++jj) {
-        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (live4) {
-            const float* src = part + (static_cast<int64_t>(k0) * Mp + jj) * Np + c4;
-#pragma unroll 8
-            for (int k = k0; k < k1; ++k, src += slice_stride) {
-                const float4 v = *reinterpret_cast<const float4*>(src);
-                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-            }
-        }
-        share[w][lane] = s;
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
+        if (live4)
+            add_slices(part + (static_cast<int64_t>(k0) * Mp + jj) * Np + static_cast<int64_t>(blockIdx.x) * 256, lane * 16,
+                       slice_stride, k1 - k0, s);
+        share[w][lane] = make_float4(s[0], s[1], s[2], s[3]);
         __syncthreads();
         if (live1) {
             const float sc = rho[jj];
@@ -359,15 +354,11 @@ __global__ __launch_bounds__(kThreads) void reduce_adam_scatter_few_kernel(
         WVec<ST, 4> mv, vv;
         mv.load_once(M + jj * n + c);
         vv.load_once(V + jj * n + c);
-        const float* src = part + jj * Np + c;
+        const float* src = part + jj * Np + static_cast<int64_t>(blockIdx.x) * kThreads * 4;
         F32Vec<4> g;
 #pragma unroll
         for (int e = 0; e < 4; ++e) g.x[e] = 0.f;
-#pragma unroll 8
-        for (int k = 0; k < slices; ++k, src += slice_stride) {
-            const float4 v = *reinterpret_cast<const float4*>(src);
-            g.x[0] += v.x; g.x[1] += v.y; g.x[2] += v.z; g.x[3] += v.w;
-        }
+        add_slices(src, threadIdx.x * 16, slice_stride, slices, g.x);
         const float sc = rho[jj];
 #pragma unroll
         for (int e = 0; e < 4; ++e) g.x[e] *= sc;
@@ -418,11 +409,13 @@ __global__ __launch_bounds__(kThreads) void reduce_adam_scatter_strided_kernel(
     if (c0 >= n) return;
     WT* __restrict__ wrow = static_cast<WT*>(q.W) + (kToU ? 0 : static_cast<int64_t>(row) * q.ldw);
     int64_t c[kStrided];
+    uint32_t lane[kStrided];
     bool live[kStrided];
 #pragma unroll
     for (int u = 0; u < kStrided; ++u) {
         live[u] = c0 + u * kThreads < n;
         c[u] = live[u] ? c0 + u * kThreads : c0;  // past the edge: this thread's first column again
+        lane[u] = (threadIdx.x + (live[u] ? u * kThreads : 0)) * 4;
     }
     const int64_t slice_stride = Mp * Np;
     WVec<WT, 1> wv[kStrided];
@@ -438,11 +431,8 @@ __global__ __launch_bounds__(kThreads) void reduce_adam_scatter_strided_kernel(
             mv[u].load_once(M + jj * n + c[u]);
             vv[u].load_once(V + jj * n + c[u]);
         }
-        const float* src = part + jj * Np;
-#pragma unroll 4
-        for (int k = 0; k < slices; ++k, src += slice_stride)
-#pragma unroll
-            for (int u = 0; u < kStrided; ++u) g[u] += src[c[u]];
+        const float* src = part + jj * Np + static_cast<int64_t>(blockIdx.x) * kThreads * kStrided;
+        add_columns(src, lane, slice_stride, slices, g);
         const float sc = rho[jj];
 #pragma unroll
         for (int u = 0; u < kStrided; ++u) {

@@ -30,18 +30,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
                                                             const float* __restrict__ scale,
                                                             OT* __restrict__ out, int64_t ldo) {
     const int64_t j = blockIdx.y;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 * kReduceCols + threadIdx.x;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * 256 * kReduceCols, i = first + threadIdx.x;
     if (i >= cols) return;
     float s[kReduceCols] = {0.f, 0.f, 0.f, 0.f};
-    const float* src = P + j * Np;
+    const float* src = P + j * Np + first;
     const int64_t step = Mp * Np;
-    int64_t c[kReduceCols];
+    uint32_t lane[kReduceCols];  // past the edge: the thread's first column again
 #pragma unroll
-    for (int u = 0; u < kReduceCols; ++u) c[u] = i + u * 256 < cols ? i + u * 256 : i;
-#pragma unroll 4
-    for (int k = 0; k < splits; ++k, src += step)
-#pragma unroll
-        for (int u = 0; u < kReduceCols; ++u) s[u] += src[c[u]];
+    for (int u = 0; u < kReduceCols; ++u) lane[u] = (threadIdx.x + (i + u * 256 < cols ? u * 256 : 0)) * 4;
+    add_columns(src, lane, step, splits, s);
     const float sc = scale ? scale[j] : 1.0f;
 #pragma unroll
     for (int u = 0; u < kReduceCols; ++u)
@@ -57,22 +54,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_many_kernel(
     const float* __restrict__ P, int splits, int64_t Mp, int64_t Np, int64_t rows, int64_t cols,
     const float* __restrict__ scale, OT* __restrict__ out, int64_t ldo) {
     __shared__ float4 part[4][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t j = blockIdx.y;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + lane * 4;  // < Np: Np % 128 == 0
     const int per = (splits + 3) / 4;
     const int k0 = w * per, k1 = k0 + per < splits ? k0 + per : splits;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i < Np) {
-        const float* p = P + (static_cast<int64_t>(k0) * Mp + j) * Np + i;
-        const int64_t step = Mp * Np;
-#pragma unroll 4
-        for (int k = k0; k < k1; ++k, p += step) {
-            const float4 v = *reinterpret_cast<const float4*>(p);
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-        }
-    }
-    part[w][lane] = s;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    if (i < Np)
+        add_slices(P + (static_cast<int64_t>(k0) * Mp + j) * Np + static_cast<int64_t>(blockIdx.x) * 256, lane * 16, Mp * Np, k1 - k0, s);
+    part[w][lane] = make_float4(s[0], s[1], s[2], s[3]);
     __syncthreads();
     if (w != 0 || i >= cols) return;
     float r[4] = {0.f, 0.f, 0.f, 0.f};
