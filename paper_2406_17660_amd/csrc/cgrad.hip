@@ -51,13 +51,11 @@ constexpr int tile_rows(TileId id) { return 1 << rows_log2(id); }
 constexpr int tile_k(TileId id) { return id == kTile128 ? Cfg128::BK : kFastBK; }
 static_assert(kFastBM == 256 && kFastBN == 256 && kMidBM == 128 && kMidBK == kFastBK, "tile shapes");
 
-// How the token dimension is divided: `splits` slices of `tokens` tokens (the last one shorter), and,
-// with `tail`, the tokens past the last whole K tile of 32 as one more slice.
+// How the token dimension is divided: `splits` slices of `tokens` tokens, the last one shorter (it may end in a ragged
+// K tile, whose missing tokens the kernels clear in LDS).
 struct KSplit {
     int splits;
     int64_t tokens;
-    bool tail;
-    int slices() const { return splits + (tail ? 1 : 0); }
 };
 struct Plan {
     int64_t Mp, Np, rp;  // padded rows / cols of the partial buffer; packed panel width
@@ -84,7 +82,7 @@ KSplit split_k(TileId planned, int64_t T, int64_t rows, int64_t n) {
     const int edge = tile_rows(planned), bk = tile_k(planned);
     const int64_t tm = (rows + edge - 1) >> rows_log2(planned), tn = (n + edge - 1) >> rows_log2(planned);
     const int64_t tiles = tm * tn;
-    const int64_t ktiles = planned == kTile256 ? T / kFastBK : (T + Cfg128::BK - 1) / Cfg128::BK;
+    const int64_t ktiles = (T + bk - 1) / bk;
     // Split K so that the workgroups fill whole rounds of the machine (256 CUs x workgroups
     // per CU) without paying too much for the partial tiles every slice adds.  In units of
     // the GEMM's time at full occupancy, c slices cost about 1 / fill(c) + c * k / T.  For
@@ -115,7 +113,6 @@ KSplit split_k(TileId planned, int64_t T, int64_t rows, int64_t n) {
     q.tokens = per * bk;
     q.splits = static_cast<int>((ktiles + per - 1) / per);
     if (q.splits < 1) q.splits = 1;
-    q.tail = planned == kTile256 && T % bk != 0;
     return q;
 }
 
@@ -127,7 +124,7 @@ Plan make_plan(TileId id, const KSplit& k, int64_t T, int64_t rows, int64_t n, b
     p.Np = static_cast<int64_t>(p.tiles_n) << cols_log2(id);
     p.rp = p.Mp;
     p.pack_bytes = pack ? round_up(static_cast<size_t>(T) * p.rp * 2, 256) : 0;
-    p.partial_bytes = static_cast<size_t>(k.slices()) * p.Mp * p.Np * 4;
+    p.partial_bytes = static_cast<size_t>(k.splits) * p.Mp * p.Np * 4;
     return p;
 }
 
@@ -231,7 +228,7 @@ TileId choose_tile(TileId planned, const KSplit& k, int64_t T, int64_t rows, int
             const double groups = 2.8e-10 * static_cast<double>(T) * static_cast<double>((n + 2047) / 2048);
             t += (moved > groups ? moved : groups) + 3e-6;
         }
-        t += (outputs * 4 <= kCachedSliceBytes ? 2.2e-12 : 3e-12) * outputs * k.slices();
+        t += (outputs * 4 <= kCachedSliceBytes ? 2.2e-12 : 3e-12) * outputs * k.splits;
         if (layout == GRASS_DY_MxT && !(rows_form && id == kTile256 && chunks))
             t += 2.0 * static_cast<double>(T) * static_cast<double>(p.Mp + rows) / 2e12 + 5e-6;
         if (t < least) { least = t; best = id; }
@@ -583,7 +580,6 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
         g.Mp = static_cast<int64_t>(g.tiles_m) * kFastBM;
         g.Np = static_cast<int64_t>(g.tiles_n) * kFastBN;
         g.splits = 1;
-        g.tail = 0;
         g.ktiles_per_split = static_cast<int>(T / kFastBK);
         g.a_rows = nullptr;
         const int64_t items = static_cast<int64_t>(g.tiles_m) * g.tiles_n;
@@ -627,7 +623,7 @@ size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
     // The launcher may plan for the small tile where the large one cannot be used, and run either plan
     // with any tile: room for the larger number of slices and the widest padding.
     const KSplit k1 = split_k(kTile128, T, mrows, n), k2 = split_k(kTile256, T, mrows, n);
-    const int64_t slices = k1.slices() > k2.slices() ? k1.slices() : k2.slices();
+    const int64_t slices = k1.splits > k2.splits ? k1.splits : k2.splits;
     const int64_t Mp = (mrows + 255) / 256 * 256, Np = (n + 255) / 256 * 256;
     bool pack = needs_pack(layout, gathered), copy_x = false;
     if (n % 8 != 0 || (!pack && mrows % 8 != 0)) {
@@ -681,7 +677,7 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
         test_option(GRASS_TEST_PACK_MXT) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0)
         k = paired(k, T);
     *tile = tile_rows(id);
-    *k_slices = k.slices();
+    *k_slices = k.splits;
 }
 
 size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int64_t n,
@@ -1005,7 +1001,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     // launch sizes are checked before the first launch: a refused call has done nothing
     const int64_t tiles = static_cast<int64_t>(p.tiles_m) * p.tiles_n;
     const int64_t chunk = (tiles * ks.splits + kNumXcd - 1) / kNumXcd;
-    const int64_t blocks = chunk * kNumXcd + (ks.tail ? tiles : 0);
+    const int64_t blocks = chunk * kNumXcd;
     const int x_chunks = static_cast<int>((nb / 8 + 255) / 256);  // workgroups per row of the aligning copy
     if (blocks > 0x7FFFFFFF || (copy.b && T * x_chunks > 0x7FFFFFFF)) return GRASS_ERR_SHAPE;
 
@@ -1119,8 +1115,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     g.Np = p.Np;
     g.tiles_m = p.tiles_m;
     g.tiles_n = p.tiles_n;
-    g.splits = ks.slices();
-    g.tail = ks.tail ? 1 : 0;
+    g.splits = ks.splits;
     // the 128 tile by load-to-LDS where that can fetch the operands (its K tiles are shorter, its sums the same)
     const bool small_direct = tile == kTile128 && aligned && sizes;
     g.ktiles_per_split = static_cast<int>(ks.tokens / (small_direct ? kMidBK : tile_k(tile)));
@@ -1186,7 +1181,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
         if (le == hipSuccess && ev_stop) (void)hipEventRecord(ev_stop, s);
     }
     if (le != hipSuccess) return GRASS_ERR_DEVICE;
-    return finish_segments(seg, count, partial, ks.slices(), p.Mp, p.Np, n, odt, s, ev_tail_start, ev_tail_stop);
+    return finish_segments(seg, count, partial, ks.splits, p.Mp, p.Np, n, odt, s, ev_tail_start, ev_tail_stop);
 }
 
 grass_status launch_tn_gemm(const void* dY, grass_dy_layout layout, int64_t ldy, const void* X,

@@ -30,9 +30,10 @@ namespace {
 // Edges.  Columns past the matrix edge are redirected to column 0 of the same row: they
 // only feed output rows / columns that are never read back.  A ragged last K tile (T x m form) is
 // loaded during the drain with the tokens past T redirected to the last one, and their LDS rows
-// are cleared once it has landed.  Where the ragged tile is a K slice of its own, that slice's
-// workgroups are part of the same launch (4096 x 4096, r = 1024, T = 2047: a separate launch cost
-// 7.4 us of a 63 us step).
+// are cleared once it has landed.  It ends the last slice; as a K slice of its own it cost one more slice
+// of partial tiles, written and read again (whole steps: 4096 x 4096, r = 1024, T = 2047: 53.0 -> 48.8 us,
+// T = 1001: 46.3 -> 41.2, T = 17001: 172.3 -> 164.2; 11008 x 4096, r = 1024, T = 3001: 70.1 -> 64.7;
+// 2048 x 5461, r = 512, T = 4099: 70.3 -> 67.0).
 // Requirements (checked by the launcher): bases 16-byte aligned, leading dimensions and
 // column counts multiples of 8.
 constexpr int kFastBM = 256, kFastBN = 256, kFastBK = 32, kFastStages = 4;

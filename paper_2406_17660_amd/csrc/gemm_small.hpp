@@ -73,9 +73,6 @@ struct GemmArgs {
     float* P;           // partials [S][Mp][Np]
     int64_t lda, ldb, K, Mcols, Ncols, Mp, Np;
     int tiles_m, tiles_n, splits, ktiles_per_split;
-    // 1: the last slice is the ragged K tile alone (the 256-wide kernels): its workgroups come after
-    // all others, one per tile, and the slices before it end with the last whole K tile
-    int tail;
     // row form of the left operand (large-tile kernel only): A is [rows of length K], row j of
     // the product is A + a_rows[j] * lda (a_rows == nullptr: row j itself)
     const int32_t* a_rows;
@@ -83,29 +80,21 @@ struct GemmArgs {
 
 // The item (K slice and tile) of a workgroup of the 256-wide kernels; negative: none.  Consecutive
 // items share a K slice and neighbouring tiles, and XCD x (workgroup b lands on XCD b % 8) is handed
-// a contiguous range of them; the items of a ragged tail come last, spread over the XCDs.
+// a contiguous range of them.
 __device__ __forceinline__ int64_t work_item(const GemmArgs& g) {
-    const int64_t tiles = static_cast<int64_t>(g.tiles_m) * g.tiles_n;
-    const int64_t main_items = tiles * (g.splits - g.tail);
-    const int64_t chunk = (main_items + kNumXcd - 1) / kNumXcd;
-    if (blockIdx.x >= chunk * kNumXcd) return main_items + (blockIdx.x - chunk * kNumXcd);
+    const int64_t items = static_cast<int64_t>(g.tiles_m) * g.tiles_n * g.splits;
+    const int64_t chunk = (items + kNumXcd - 1) / kNumXcd;
     const int64_t item = static_cast<int64_t>(blockIdx.x % kNumXcd) * chunk + blockIdx.x / kNumXcd;
-    return item < main_items ? item : -1;
+    return item < items ? item : -1;
 }
 // K tiles [begin, end) of slice `split`; `rows`: rows of the last of them (the others are whole).
 struct KRange { int64_t begin, end; int rows; };
 template <int BK>
 __device__ __forceinline__ KRange k_range(const GemmArgs& g, int split) {
-    const int64_t whole = g.K / BK, all = (g.K + BK - 1) / BK;
+    const int64_t all = (g.K + BK - 1) / BK;
     KRange q;
-    if (g.tail && split == g.splits - 1) {
-        q.begin = whole;
-        q.end = all;
-    } else {
-        const int64_t limit = g.tail ? whole : all;
-        q.begin = static_cast<int64_t>(split) * g.ktiles_per_split;
-        q.end = q.begin + g.ktiles_per_split < limit ? q.begin + g.ktiles_per_split : limit;
-    }
+    q.begin = static_cast<int64_t>(split) * g.ktiles_per_split;
+    q.end = q.begin + g.ktiles_per_split < all ? q.begin + g.ktiles_per_split : all;
     q.rows = q.end > q.begin && q.end * BK > g.K ? static_cast<int>(g.K - (q.end - 1) * BK) : BK;
     return q;
 }

@@ -302,7 +302,7 @@ def test_adam_scatter_empty():
 # ------------------------------------------------------------------------------ large-tile GEMM path
 @pytest.mark.parametrize("layout", [grass.DY_TxM, grass.DY_MxT])
 @pytest.mark.parametrize("T,m,n,r,dup", [
-    (1000, 700, 1376, 300, True),    # ragged T (tail slice), n = 5*256 + 96, panel padded 300 -> 512
+    (1000, 700, 1376, 300, True),    # ragged T, n = 5*256 + 96, panel padded 300 -> 512
     (2048, 512, 512, 512, False),    # exact tiles, r = m
     (4100, 600, 264, 257, False),    # one row past a tile boundary, narrow n, T tail of 4 rows
     (96, 300, 512, 256, False),      # fewer K tiles than ring stages
@@ -824,7 +824,7 @@ def test_step_group_equals_the_separate_calls_and_the_oracle(dtype, wdtype, sdty
     (8192, 1280, (24,), (40,), False, None),                 # every row drawn repeatedly; five column blocks
     (8192, 264, (300, 90), (40, 9), True, None),             # the last column block is mostly empty
     (8192, 1024, (400,), (256,), True, "256"),               # large tile: 32 slices
-    (8200, 512, (300,), (200,), False, "256"),               # ... with a ragged tail of T as one more slice
+    (8200, 512, (300,), (200,), False, "256"),               # ... with a ragged last K tile
     (4608, 256, (64,), (9,), False, None),                   # the fewest slices that take this kernel (9)
     (6656, 128, (64,), (5,), True, None),                    # 13 slices: quarters of 4, 4, 4 and 1
     (5120, 128, (40,), (8,), False, None),                   # 10 slices: quarters of 3, 3, 3 and 1

@@ -28,7 +28,7 @@ def test_tile_of_products_stored_mxt(kernel, T, m, n, r):
 @pytest.mark.parametrize("layout", [grass.DY_TxM, grass.DY_MxT])
 @pytest.mark.parametrize("T", [32, 33, 63, 64, 96, 127, 1001, 1056, 2080, 2112, 2477])
 def test_every_tile_on_slices_planned_for_the_large_one(T, layout):
-    """Slices in units of 32 tokens (pairs of them for gathered rows), the ragged rest a slice of its own: the tiles
+    """Slices in units of 32 tokens (pairs of them for gathered rows), a ragged last one: the tiles
     give the same bits, those of a sum of all tokens.  Inf lies behind the last token and the last column."""
     m, n, r = 520, 504, 500
     gen = torch.Generator(device=DEV)
