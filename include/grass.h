@@ -164,6 +164,9 @@ grass_status grass_select_rows_static(const float* sumsq, int64_t m, int64_t r,
  * device: idx comes from grass_select_rows); duplicates are allowed.
  * T = 0 writes zeros.  `ws` must hold grass_cgrad_workspace(...) bytes.
  *
+ * bf16 inputs, up to 8192 tokens: the query counts the tiles and slices that the library prefers where there is room.  A
+ * smaller workspace, down to what the slices planned by themselves need, is accepted too.
+ *
  * fp32 inputs: the partial tiles of the product are an aid, and a workspace that is smaller than
  * the query says is accepted as follows.  grass_compressed_grad, grass_compressed_grad_group
  * and grass_dense_grad: any size, or NULL.  grass_grad_row_stats: from m*n*4 + 256 bytes on.

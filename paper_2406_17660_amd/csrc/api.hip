@@ -172,7 +172,7 @@ grass_status grass_compressed_grad_timed(const void* dY, grass_dy_layout layout,
     if (st != GRASS_OK) return st;
     if (r < 0 || r > kMaxGridRows || ldgc < n || (r > 0 && m == 0)) return GRASS_ERR_SHAPE;
     if (!present(idx, r) || !present(rho, r) || !present(GC, r * n)) return GRASS_ERR_NULL;
-    if (!workspace_ok(dt, gemm_workspace_bytes(T, r, n, dt, layout, true, m), ws, ws_bytes))
+    if (!workspace_ok(dt, gemm_workspace_bytes(T, r, n, dt, layout, true, m, true), ws, ws_bytes))
         return GRASS_ERR_WORKSPACE;
     return launch_tn_gemm(dY, layout, ldy, X, ldx, dt, T, r, n, idx, rho, GC, GRASS_F32, ldgc, ws,
                           ws_bytes, as_stream(stream), m, static_cast<hipEvent_t>(ev_gemm_start),
@@ -207,7 +207,7 @@ grass_status grass_compressed_grad_group(int count, const void* const* dY, grass
             return GRASS_ERR_NULL;
         seg[i] = GemmSegment{dY[i], ldy[i], idx[i], rho[i], GC[i], ldgc[i], r[i], m[i]};
     }
-    if (!workspace_ok(dt, gemm_group_workspace_bytes(T, r, count, n, dt, layout, false), ws, ws_bytes))
+    if (!workspace_ok(dt, gemm_group_workspace_bytes(T, r, count, n, dt, layout, false, true), ws, ws_bytes))
         return GRASS_ERR_WORKSPACE;
     return launch_tn_gemm_segments(seg, count, layout, X, ldx, dt, T, n, GRASS_F32, ws, ws_bytes,
                                    as_stream(stream));
@@ -327,12 +327,13 @@ grass_status grass_step_group_timed(int count, const grass_step_layer* layers,
         if (st != GRASS_OK) return st;
         rows[i] = L.r;
     }
-    size_t gemm_bytes = gemm_group_workspace_bytes(T, rows, count, n, dt, layout, true);
+    size_t gemm_bytes = gemm_group_workspace_bytes(T, rows, count, n, dt, layout, true, true);
     size_t gc_bytes = 256;
     for (int i = 0; i < count; ++i) gc_bytes += scratch_gc_bytes(rows[i], n);
     if (!ws || ws_bytes < gc_bytes) return GRASS_ERR_WORKSPACE;
     if (!workspace_ok(dt, gemm_bytes, ws, ws_bytes - gc_bytes)) return GRASS_ERR_WORKSPACE;
-    if (gemm_bytes > ws_bytes - gc_bytes) gemm_bytes = (ws_bytes - gc_bytes) / 256 * 256;
+    // bf16: all the room there is, which more plans fit into
+    if (dt != GRASS_F32 || gemm_bytes > ws_bytes - gc_bytes) gemm_bytes = (ws_bytes - gc_bytes) / 256 * 256;
     char* scratch = static_cast<char*>(ws) + gemm_bytes;
     scratch += (256 - reinterpret_cast<uintptr_t>(scratch) % 256) % 256;
     for (int i = 0; i < count; ++i) {
@@ -350,9 +351,9 @@ grass_status grass_step_group_timed(int count, const grass_step_layer* layers,
                                    static_cast<hipEvent_t>(ev_tail_stop));
 }
 
-static size_t cols_gemm_bytes(int64_t T, int64_t m, int64_t r, grass_dtype dt) {
+static size_t cols_gemm_bytes(int64_t T, int64_t m, int64_t r, grass_dtype dt, bool least = false) {
     return dt == GRASS_F32 ? gemm_group_workspace_bytes(T, &r, 1, m, dt, GRASS_DY_TxM, true)
-                           : gemm_workspace_bytes(T, r, m, dt, GRASS_DY_TxM, true);
+                           : gemm_workspace_bytes(T, r, m, dt, GRASS_DY_TxM, true, 0, least);
 }
 
 size_t grass_step_cols_workspace(int64_t T, int64_t m, int64_t n, int64_t r, grass_dtype dt) {
@@ -380,11 +381,11 @@ grass_status grass_step_cols(const void* dY, int64_t ldy, const void* X, int64_t
         return GRASS_ERR_NULL;
     if (!dtype_ok(wdt)) return GRASS_ERR_DTYPE;
     if (!aligned_to(U, 16)) return GRASS_ERR_SHAPE;
-    size_t gemm_bytes = cols_gemm_bytes(T, m, r, dt);
+    size_t gemm_bytes = cols_gemm_bytes(T, m, r, dt, true);
     const size_t gc_bytes = 256 + scratch_gc_bytes(r, m);
     if (!ws || ws_bytes < gc_bytes) return GRASS_ERR_WORKSPACE;
     if (!workspace_ok(dt, gemm_bytes, ws, ws_bytes - gc_bytes)) return GRASS_ERR_WORKSPACE;
-    if (gemm_bytes > ws_bytes - gc_bytes) gemm_bytes = (ws_bytes - gc_bytes) / 256 * 256;
+    if (dt != GRASS_F32 || gemm_bytes > ws_bytes - gc_bytes) gemm_bytes = (ws_bytes - gc_bytes) / 256 * 256;
     char* scratch = static_cast<char*>(ws) + gemm_bytes;
     scratch += (256 - reinterpret_cast<uintptr_t>(scratch) % 256) % 256;
     StepTail tail{M, V, sdt, lr, beta1, beta2, eps, t, nullptr, W, wdt, ldw, alpha};
@@ -438,7 +439,7 @@ grass_status grass_dense_grad(const void* dY, grass_dy_layout layout, int64_t ld
     if (ldg < n || m > kMaxGridRows) return GRASS_ERR_SHAPE;
     if (!present(G, m * n)) return GRASS_ERR_NULL;
     if (!dtype_ok(gdt)) return GRASS_ERR_DTYPE;
-    if (!workspace_ok(dt, gemm_workspace_bytes(T, m, n, dt, layout, false), ws, ws_bytes))
+    if (!workspace_ok(dt, gemm_workspace_bytes(T, m, n, dt, layout, false, 0, true), ws, ws_bytes))
         return GRASS_ERR_WORKSPACE;
     return launch_tn_gemm(dY, layout, ldy, X, ldx, dt, T, m, n, nullptr, nullptr, G, gdt, ldg, ws,
                           ws_bytes, as_stream(stream), m);

@@ -69,7 +69,7 @@ size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 constexpr int64_t kCachedSliceBytes = int64_t{16} << 20;
 
 // The square tile that a product's K slices are planned for: 256 x 256 unless it wastes much of
-// itself on padding.  (The kernel that runs may use another tile, see choose_tile: a slice's sums are
+// itself on padding.  (The kernel that runs may use another tile, see choose_plan: a slice's sums are
 // taken in the same order whatever the tile, so results depend on the slices alone.)
 TileId planned_tile(int64_t rows, int64_t n) {
     if (const int forced = test_option(GRASS_TEST_GEMM_TILE)) return forced == 256 ? kTile256 : kTile128;
@@ -168,70 +168,116 @@ size_t aligned_x_bytes(int64_t T, int64_t n) {
     return round_up(static_cast<size_t>(T) * ((n + 7) / 8 * 8) * 2, 256);
 }
 
-// The tile a product with these K slices runs with: the one whose estimated time is smallest.
-// Load-to-LDS kernels (aligned operands): a workgroup takes `start` us and, per K tile of 32, a time that
-// depends on how many share a compute unit, u = workgroups / 256 (fitted to the kernel times of 44 layers over
-// the range, all three tiles each):
-//   256 x 256   10 us, 0.45 + 0.3 u up to one per unit (the clock falls as the chip fills), then 0.78 a round
-//   128 x 256    8.3, 0.33 + 0.17 u up to one, 0.95 with two, then 0.5 u
-//   128 x 128    6 + 2 u up to one, then 8; 0.345 with one, 0.69 with two, 1.0 with three, then 0.35 u
-// Measured products, 256 / 128 x 256 / 128 tile: 4096 x 4096, r = 1024, T = 2047: 30.7 / 24.8 / 26.8 us; 10016 x 3864,
-// r = 1024, T = 640: 19.4 / 15.0 / 12.9; 2176 x 480, r = 272, T = 4461: 18.8 / 13.8 / 11.2; 1408 x 608, r = 352,
-// T = 109824: 89 / 101 / 79; 512 x 1376, r = 128, T = 65536: 90 / 68 / 50; 10860 x 3616, r = 1024, T = 9280: 65 / 77 / 94;
-// 1024 x 2048, r = 128, T = 131072: 123 / 103 / 118.
-// Operands in any position: 1.2 and 0.5 PFLOP/s with full tiles on all compute units, and 11 and 4 us to start.
-// Slices of partial tiles cost 3e-12 s per output element (written, then read by the reduction), 2.2e-12
-// while they stay in the caches; dY stored m x T has to be packed (transposed) for all but the large tile, which
-// gathers its rows itself: one more launch of 5 us with its gap, and the panel read and written at 2 TB/s (1888 x 1072,
-// r = 472, T = 2944: 25.5 us without, 26.3 with the pack and 128 tiles; 235 x 64, r = 58, T = 864: 22.6 and 16.0).  An
-// odd-width operand may first be copied into aligned rows, which the tile decides about (choose_copies) and which counts
-// with it: 680 x 4109, r = 42, T = 41408: 212 us with a copied X and the large tile, 124 with the pack and 128 tiles.
-// Over 810 random layers stored m x T the tile chosen takes 1.1 % longer than the best of the three (2.3 % with 8 us
-// for the pack and the copies left out).
-// Whole steps against a rule that knew full-chip rates only (1.4, 0.9 and 0.6 PFLOP/s): 400 x 744, r = 50, T = 1280:
-// 19.5 -> 17.2 us; 776 x 456, r = 97, T = 3136: 20.2 -> 18.1; 1648 x 1896, r = 474 (columns), T = 448: 34.5 -> 32.5; 4640 x
-// 1064, r = 1024, T = 896: 28.7 -> 26.5; 1672 x 288, r = 209, T = 12404: 32.0 -> 29.8; long products unchanged.
-double direct_us(TileId id, double wgs, double ktiles) {
+// Estimated time of a product's kernel in us.  A workgroup takes a time to start and to store its tile and, per K
+// tile of 32 tokens, one that depends on how many workgroups a compute unit has, u = workgroups / 256.  `chunks`:
+// load-to-LDS kernels (aligned operands), otherwise operands in any position through registers.
+double product_us(TileId id, bool chunks, bool row_form, double wgs, double ktiles) {
     const double u = wgs / 256.0;
-    if (id == kTile256) return 10.0 + ktiles * (u <= 1 ? 0.45 + 0.3 * u : 0.78 * ceil(u));
-    if (id == kTileMid) return 8.3 + ktiles * (u <= 1 ? 0.33 + 0.17 * u : u <= 2 ? 0.95 : 0.5 * u);
-    return (u <= 1 ? 6.0 + 2.0 * u : 8.0) + ktiles * (u <= 1 ? 0.345 : u <= 2 ? 0.69 : u <= 3 ? 1.0 : 0.35 * u);
+    if (id == kTile256 && chunks) return (row_form ? 12.0 : 13.0) + ktiles * (u <= 1 ? 0.538 + 0.161 * u : 0.86 * ceil(u));
+    if (id == kTile256) return 7.26 + ktiles * (u <= 1 ? 0.715 + 0.161 * u : 0.799 * ceil(u));
+    if (id == kTileMid) return 9.06 + ktiles * (u <= 1 ? 0.338 + 0.2 * u : u <= 2 ? 0.967 : 0.581 * u);
+    if (chunks) return (u <= 1 ? 5.9 + 3.0 * u : 5.6) + ktiles * (u <= 1 ? 0.376 : u <= 2 ? 0.676 : u <= 3 ? 1.28 : 0.41 * u);
+    return 1.45 + ktiles * (u <= 2 ? 1.02 + 0.0872 * u : 0.586 * 2 * ceil(u / 2));
 }
-TileId choose_tile(TileId planned, const KSplit& k, int64_t T, int64_t rows, int64_t n, bool rows_form,
-                   grass_dy_layout layout, bool gathered, const Positions& at) {
-    const bool aligned = at.a_chunks && at.x_chunks;
+// A bf16 product as the launcher sees it.
+struct Shape {
+    int64_t T, rows, n;
+    grass_dy_layout layout;
+    bool gathered;
+    bool row_form, pairs;  // the 256 tile gathers the rows of an m x T dY itself, 64 tokens per load
+    Positions at;
+};
+struct Choice { TileId tile; KSplit k; };
+bool chunks_at(TileId id, const Shape& q, Copies* copy) {
+    *copy = q.at.a_chunks && q.at.x_chunks ? Copies{false, false} : copies_at(id, q.T, q.rows, q.n, q.layout, q.gathered, q.at);
+    return (q.at.a_chunks || copy->a) && (q.at.x_chunks || copy->b);
+}
+// The parts of a step's time that the tile and the slices decide, in us: the product, its partial tiles (written, then
+// read by the reduction), and the passes that the tile needs ahead of it: dY stored m x T is packed (transposed) for all
+// but the large tile, which gathers its rows itself, and an odd-width operand may be copied into aligned rows
+// (choose_copies).
+struct TileTime {
+    TileId id;
+    bool chunks, row_form;
+    double tiles, outputs, passes;
+    double us(double slices, double tokens) const {
+        return passes + product_us(id, chunks, row_form, tiles * slices, tokens * (1.0 / kFastBK)) + 1.45e-6 * outputs * slices;
+    }
+};
+TileTime tile_time(TileId id, const Shape& q) {
+    Copies copy;
+    TileTime r;
+    r.id = id;
+    r.chunks = chunks_at(id, q, &copy);
+    r.row_form = q.row_form && id == kTile256 && r.chunks;
+    const Plan p = make_plan(id, KSplit{1, 0}, q.T, q.rows, q.n, false);
+    const double T = static_cast<double>(q.T);
+    r.tiles = static_cast<double>(p.tiles_m) * p.tiles_n;
+    r.outputs = static_cast<double>(p.Mp) * static_cast<double>(p.Np);
+    r.passes = 0;
+    if (copy.a) r.passes += 4.0 * T * static_cast<double>(q.rows) / 5.2e6 + 3;
+    if (copy.b) {  // (one workgroup per row and 2048 columns)
+        const double moved = 4.0 * T * static_cast<double>(q.n) / 5.2e6, groups = 2.8e-4 * T * static_cast<double>((q.n + 2047) / 2048);
+        r.passes += (moved > groups ? moved : groups) + 3;
+    }
+    if (q.layout == GRASS_DY_MxT && !r.row_form) r.passes += 2.0 * T * static_cast<double>(p.Mp + q.rows) / 1.5e6 + 6;
+    return r;
+}
+// What a plan needs of the workspace: packed panel, partial tiles and the aligned copy of X.
+size_t choice_bytes(const Choice& c, const Shape& q) {
+    Copies copy;
+    const bool chunks = chunks_at(c.tile, q, &copy), row_form = q.row_form && c.tile == kTile256 && chunks;
+    const Plan p = make_plan(c.tile, c.k, q.T, q.rows, q.n, !row_form && (needs_pack(q.layout, q.gathered) || copy.a));
+    return p.pack_bytes + round_up(p.partial_bytes, 256) + (copy.b ? aligned_x_bytes(q.T, q.n) : 0);
+}
+// The tile and the K slices of a product, by estimated time.
+//
+// `k` are the slices planned for the square tile `planned`; of the tiles that run on them the quickest is taken.  Up
+// to kJointMaxT tokens every tile is also tried with slices of its own, down to two K tiles each, and taken if
+// that is at least 5 % quicker: slices planned by how they fill the machine (split_k) know nothing of what starting a
+// workgroup costs, nor which tile runs, and keep at least eight K tiles of the square one.  The slices of split_k are
+// fitted to longer products, whose sums also move more with another order.
+// The estimates' constants are fitted to the times of 740 random layers of up to 20000 tokens (all three tiles, up to
+// 16 numbers of slices; steps, column steps and full gradients, both layouts, odd widths) and 150 longer ones (tiles only).
+// The plan taken is 1.0 % from the best of all tried and 4.0 % quicker than the tile alone (7 % between 512 and 1024
+// tokens, 2 - 4 % elsewhere); none is more than 6.7 % slower.  Whole steps: 352 x 8667, r = 88, T = 563: 29.7 -> 22.0 us;
+// 302 x 1745, r = 37, T = 7341: 31.3 -> 25.3; 688 x 327, r = 172, T = 1924: 23.6 -> 19.3; 5848 x 744, r = 1024, T = 1523:
+// 28.0 -> 25.0.  Tiles of the longer ones: 0.3 % from the best (1.1 % with constants fitted to the kernels alone).
+constexpr int64_t kJointMaxT = 8192;
+Choice choose_plan(TileId planned, const KSplit& k, const Shape& q, size_t room) {
     if (const int forced = test_option(GRASS_TEST_GEMM_TILE))
-        return forced == 192 && aligned ? kTileMid : planned;
+        return Choice{forced == 192 && q.at.a_chunks && q.at.x_chunks ? kTileMid : planned, k};
     const int run = test_option(GRASS_TEST_RUN_TILE);
-    TileId best = planned;
+    const bool aligned = q.at.a_chunks && q.at.x_chunks;
+    Choice best{planned, k};
+    TileTime times[3];
+    int found = 0;
     double least = 1e300;
     for (const TileId id : {kTile256, kTileMid, kTile128}) {
         if (id == kTileMid && !aligned) continue;
-        const Copies copy = aligned ? Copies{false, false} : copies_at(id, T, rows, n, layout, gathered, at);
-        const bool chunks = (at.a_chunks || copy.a) && (at.x_chunks || copy.b);
-        if (id == kTile128 && planned == kTile256 && !chunks) continue;  // its K tiles are twice as long
-        if (run == (id == kTile256 ? 256 : id == kTileMid ? 192 : 128)) return id;
-        const Plan p = make_plan(id, k, T, rows, n, false);
-        const double outputs = static_cast<double>(p.Mp) * static_cast<double>(p.Np);
-        const double wgs = static_cast<double>(p.tiles_m) * p.tiles_n * k.splits;
-        double t;
-        if (chunks) {
-            t = 1e-6 * direct_us(id, wgs, static_cast<double>(k.tokens) / kFastBK);
-        } else {
-            const double slots = id == kTile128 ? 512.0 : 256.0;
-            t = 2.0 * static_cast<double>(T) * outputs / (id == kTile256 ? 1.22e15 : 0.52e15) * (ceil(wgs / slots) * slots / wgs);
-            t += id == kTile256 ? 11e-6 : 4e-6;
+        const TileTime& time = times[found++] = tile_time(id, q);
+        if (id == kTile128 && planned == kTile256 && !time.chunks) continue;  // its K tiles are twice as long
+        if (run == (id == kTile256 ? 256 : id == kTileMid ? 192 : 128)) return Choice{id, k};
+        const double t = time.us(k.splits, static_cast<double>(k.tokens));
+        if (t < least) { least = t; best.tile = id; }
+    }
+    if (run || q.T > kJointMaxT || test_option(GRASS_TEST_MAX_K_SLICES)) return best;
+    least *= 0.95;
+    for (int i = 0; i < found; ++i) {
+        const TileTime& time = times[i];
+        const uint32_t unit = (time.id == kTile128 && !time.chunks) || (time.row_form && q.pairs) ? 64 : 32;
+        const uint32_t units = (static_cast<uint32_t>(q.T) + unit - 1) / unit, most = (static_cast<uint32_t>(q.T) + kFastBK - 1) / kFastBK / 2;
+        uint32_t before = 0;
+        for (const uint32_t c : {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 20, 24, 32, 42, 64}) {
+            if (c > 1 && c > most) break;
+            const uint32_t per = (units + c - 1) / c, slices = (units + per - 1) / per;
+            if (slices == before) continue;
+            before = slices;
+            const double t = time.us(slices, per * unit);
+            if (!(t < least)) continue;
+            const Choice other{time.id, KSplit{static_cast<int>(slices), static_cast<int64_t>(per) * unit}};
+            if (choice_bytes(other, q) <= room) { least = t; best = other; }
         }
-        if (copy.a) t += 4.0 * static_cast<double>(T) * static_cast<double>(rows) / 5.2e12 + 3e-6;
-        if (copy.b) {  // (one workgroup per row and 2048 columns)
-            const double moved = 4.0 * static_cast<double>(T) * static_cast<double>(n) / 5.2e12;
-            const double groups = 2.8e-10 * static_cast<double>(T) * static_cast<double>((n + 2047) / 2048);
-            t += (moved > groups ? moved : groups) + 3e-6;
-        }
-        t += (outputs * 4 <= kCachedSliceBytes ? 2.2e-12 : 3e-12) * outputs * k.splits;
-        if (layout == GRASS_DY_MxT && !(rows_form && id == kTile256 && chunks))
-            t += 2.0 * static_cast<double>(T) * static_cast<double>(p.Mp + rows) / 2e12 + 5e-6;
-        if (t < least) { least = t; best = id; }
     }
     return best;
 }
@@ -555,8 +601,9 @@ size_t grad_row_stats_workspace_bytes(int64_t T, int64_t m, int64_t n, grass_dty
 
 size_t grad_row_stats_least_bytes(int64_t T, int64_t m, int64_t n, grass_dtype dt,
                                   grass_dy_layout layout, int64_t ldy, int64_t ldx) {
-    return dt == GRASS_F32 ? static_cast<size_t>(m) * n * 4 + 256
-                           : grad_row_stats_workspace_bytes(T, m, n, dt, layout, ldy, ldx);
+    if (dt != GRASS_F32 && fused_stats_shape_ok(T, m, n, dt, layout, ldy, ldx)) return fused_stats_bytes(m, n);
+    return static_cast<size_t>(m) * n * 4 + 256 +
+           (dt == GRASS_F32 ? 0 : gemm_workspace_bytes(T, m, n, dt, layout, false, 0, true));
 }
 
 grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64_t ldy,
@@ -592,7 +639,7 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
     }
     // G, then the product's own workspace (which starts at the next multiple of 256 bytes)
     const size_t g_bytes = static_cast<size_t>(m) * n * 4;
-    if (ws_bytes < g_bytes + 256 + (dt == GRASS_F32 ? 0 : gemm_workspace_bytes(T, m, n, dt, layout, false)))
+    if (ws_bytes < g_bytes + 256 + (dt == GRASS_F32 ? 0 : gemm_workspace_bytes(T, m, n, dt, layout, false, 0, true)))
         return GRASS_ERR_WORKSPACE;
     if (m > 65535) return GRASS_ERR_SHAPE;
     float* G = reinterpret_cast<float*>(base);
@@ -617,7 +664,7 @@ size_t narrow_cap_bytes(int64_t T, int64_t rows, int64_t n) {
 }
 
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
-                            grass_dy_layout layout, bool gathered, int64_t src_rows) {
+                            grass_dy_layout layout, bool gathered, int64_t src_rows, bool least) {
     if (dt == GRASS_F32)
         return f32_partial_bytes(F32Shape{T, n, 1, &mrows, gathered ? &src_rows : &mrows, layout, F32Tail::kNone, false});
     // The launcher may plan for the small tile where the large one cannot be used, and run either plan
@@ -633,8 +680,22 @@ size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
             copy_x = copy_x || copy.b;
         }
     }
-    const size_t tiled = (pack ? round_up(static_cast<size_t>(T) * Mp * 2, 256) : 0) +
+    size_t tiled = (pack ? round_up(static_cast<size_t>(T) * Mp * 2, 256) : 0) +
                          static_cast<size_t>(slices) * Mp * Np * 4 + (copy_x ? aligned_x_bytes(T, n) : 0);
+    // what the launcher may choose instead wherever the operands lie (it keeps to the above without the room)
+    if (!least && T >= kFastBK && T <= kJointMaxT && mrows >= 8 && n >= 8) {
+        const bool packed = needs_pack(layout, gathered), rows_form = layout == GRASS_DY_MxT && T % kFastBK == 0;
+        for (const bool chunks : {true, false})
+            for (const bool row_form : {false, true}) {
+                if (row_form && !rows_form) continue;
+                const Shape q{T, mrows, n, layout, gathered, row_form, row_form && T % (2 * kFastBK) == 0,
+                              Positions{packed || (chunks && mrows % 8 == 0), chunks && n % 8 == 0, chunks}};
+                for (const TileId planned : {kTile128, kTile256}) {
+                    const size_t bytes = choice_bytes(choose_plan(planned, planned == kTile128 ? k1 : k2, q, ~size_t{0}), q);
+                    tiled = bytes > tiled ? bytes : tiled;
+                }
+            }
+    }
     // the narrow kernel's slices are bounded by a cap of their own
     const bool narrow = gathered && narrow_shape_ok(T, n, dt, layout) && mrows <= GRASS_MAX_GROUP * kNarrowBM;
     const size_t cap = narrow ? narrow_cap_bytes(T, mrows, n) : 0;
@@ -676,22 +737,28 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
     if (id == kTile256 && layout == GRASS_DY_MxT && T % (2 * kFastBK) == 0 &&
         test_option(GRASS_TEST_PACK_MXT) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0)
         k = paired(k, T);
+    if (T >= kFastBK && rows >= 8 && n >= 8) {  // gathered rows, aligned operands
+        const bool row_form = layout == GRASS_DY_MxT && T % kFastBK == 0 && test_option(GRASS_TEST_PACK_MXT) == 0;
+        const Shape q{T, rows, n, layout, true, row_form, row_form && T % (2 * kFastBK) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0,
+                      Positions{true, n % 8 == 0, true}};
+        k = choose_plan(id, k, q, ~size_t{0}).k;
+    }
     *tile = tile_rows(id);
     *k_slices = k.splits;
 }
 
 size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int64_t n,
-                                  grass_dtype dt, grass_dy_layout layout, bool step) {
+                                  grass_dtype dt, grass_dy_layout layout, bool step, bool least) {
     if (dt == GRASS_F32)
         return f32_partial_bytes(F32Shape{T, n, count, rows, nullptr, layout, step ? F32Tail::kRows : F32Tail::kNone, false});
     int64_t total = 0;
     size_t need = 0;  // the sets may also be run one at a time
     for (int i = 0; i < count; ++i) {
         total += (rows[i] + 7) / 8 * 8;
-        const size_t one = gemm_workspace_bytes(T, rows[i], n, dt, layout, true);
+        const size_t one = gemm_workspace_bytes(T, rows[i], n, dt, layout, true, 0, least);
         need = one > need ? one : need;
     }
-    const size_t joint = gemm_workspace_bytes(T, total, n, dt, layout, true);
+    const size_t joint = gemm_workspace_bytes(T, total, n, dt, layout, true, 0, least);
     return joint > need ? joint : need;
 }
 
@@ -983,7 +1050,16 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     if (pairs_ok && planned == kTile256) ks = paired(ks, T);
     const Positions at{pack || (aligned_to(dY0, 16) && ldy0 % 8 == 0 && total % 8 == 0),
                        aligned_to(X, 16) && ldx % 8 == 0 && n % 8 == 0, aligned_to(X, 4)};
-    const TileId tile = sizes ? choose_tile(planned, ks, T, total, n, rows_ok, layout, gathered, at) : kTile128;
+    char* base = static_cast<char*>(ws);
+    const size_t skip = (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256;
+    base += skip;
+    TileId tile = kTile128;
+    if (sizes) {
+        const Choice c = choose_plan(planned, ks, Shape{T, total, n, layout, gathered, rows_ok, pairs_ok, at},
+                                     ws_bytes > skip ? ws_bytes - skip : 0);
+        tile = c.tile;
+        ks = c.k;
+    }
     const Copies copy = copies_at(tile, T, total, n, layout, gathered, at);
     pack = pack || copy.a;
     const int64_t nb = copy.b ? (n + 7) / 8 * 8 : n;  // columns the GEMM sees
@@ -994,8 +1070,6 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     const bool a_pairs = a_rows_form && pairs_ok;
     if (a_rows_form) pack = false;
     const Plan p = make_plan(tile, ks, T, total, n, pack);
-    char* base = static_cast<char*>(ws);
-    base += (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256;
     uint16_t* panel = reinterpret_cast<uint16_t*>(base);
     float* partial = reinterpret_cast<float*>(base + p.pack_bytes);
     // launch sizes are checked before the first launch: a refused call has done nothing

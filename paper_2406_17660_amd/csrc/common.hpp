@@ -112,9 +112,10 @@ grass_status launch_gather_rows(const void* G, grass_dtype gdt, int64_t n, int64
                                 int64_t ldo, hipStream_t s);
 // C[j, i] = scale_j * sum_t A[t, col_j] * B[t, i]  (cgrad: col_j = idx[j], scale_j = rho[j];
 // dense: idx = rho = nullptr).  Output dtype odt, leading dimension ldc.
-// src_rows: values per token of dY where rows are gathered (fp32 plans depend on it).
+// src_rows: values per token of dY where rows are gathered (fp32 plans depend on it).  least: what a call cannot do
+// without (bf16; the query counts the plans that the launcher may prefer where there is room, too).
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
-                            grass_dy_layout layout, bool gathered, int64_t src_rows = 0);
+                            grass_dy_layout layout, bool gathered, int64_t src_rows = 0, bool least = false);
 // Tile edge and number of K slices the launcher plans for `count` gathered sets of `rows` rows in
 // all (m: row length of dY, 0 when not known; tile 0 = the kernel that gathers inside the GEMM).
 void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n, grass_dtype dt,
@@ -265,7 +266,7 @@ struct GemmSegment {
     bool c_wanted = true;
 };
 size_t gemm_group_workspace_bytes(int64_t T, const int64_t* rows, int count, int64_t n,
-                                  grass_dtype dt, grass_dy_layout layout, bool step);
+                                  grass_dtype dt, grass_dy_layout layout, bool step, bool least = false);
 // ev_start / ev_stop: stamped with the start and the end of the matrix-multiply kernel (the
 // large-tile kernel's own dispatch; for the other kernels, recorded before and after the
 // launches); ev_tail_start / ev_tail_stop: the same for the fused tail of a regular step.

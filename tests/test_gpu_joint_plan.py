@@ -1,0 +1,70 @@
+"""Tile and K slices chosen together (products of up to 8192 tokens): random layers on both sides of the choice, in
+both layouts, odd widths and columns, against 64-bit products, with the workspace the query asks for and with the least
+one that a call accepts.  The workspace holds NaN before each call, so a slice that nobody writes shows.  Bound: products
+of bf16 values are exact in fp32, sums of T of them off by about sqrt(T) * 2^-24 = 5e-6; TOL_F32 (1e-5) covers it."""
+import random
+
+import pytest
+import torch
+
+from paper_2406_17660_amd import grass
+from gpu_util import DEV, TOL_F32
+
+pytestmark = pytest.mark.gpu
+BF = torch.bfloat16
+
+
+def _rel(got, want):
+    return float((got.double() - want).norm() / want.norm())
+
+
+def _case(seed):
+    rng = random.Random(seed)
+    T = rng.choice([32, 63, 257, 640, 1001, 2080, 4099, 8192, 8193])
+    m, n = (rng.choice([8, 128, 261, 488, 1030, 2376]) + 8 * rng.randrange(4) for _ in range(2))
+    return T, m, n, max(1, m // rng.choice([1, 4, 8])), rng.choice([grass.DY_TxM, grass.DY_MxT])
+
+
+@pytest.mark.parametrize("seed", range(60))
+def test_products_and_steps(seed):
+    T, m, n, r, layout = _case(seed)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    dY = torch.randn((T, m) if layout == grass.DY_TxM else (m, T), generator=gen, device=DEV).to(BF)
+    X = torch.randn(T, n, generator=gen, device=DEV).to(BF)
+    W = torch.randn(m, n, generator=gen, device=DEV).to(BF)
+    idx = torch.randperm(m, generator=gen, device=DEV)[:r].sort()[0].to(torch.int32)
+    rho = torch.rand(r, generator=gen, device=DEV) + 0.5
+    full = (dY.double().t() if layout == grass.DY_TxM else dY.double()) @ X.double()
+    want = rho.double()[:, None] * full[idx.long()]
+
+    def check(nbytes_cgrad, nbytes_dense, nbytes_step):
+        GC, G = torch.full((r, n), float("nan"), device=DEV), torch.full((m, n), float("nan"), device=DEV)
+        grass.compressed_grad(dY, X, idx, rho, GC, grass.workspace(nbytes_cgrad).fill_(255), layout)
+        assert _rel(GC, want) <= TOL_F32
+        grass.dense_grad(dY, X, G, grass.workspace(nbytes_dense).fill_(255), layout)
+        assert _rel(G, full) <= TOL_F32
+        M, V = torch.zeros(r, n, device=DEV), torch.zeros(r, n, device=DEV)
+        grass.step_group([dY], X, [idx], [rho], [M], [V], [W], 1e-3, 0.9, 0.999, 1e-8, 1, 0.25,
+                         grass.workspace(nbytes_step).fill_(255), layout=layout)
+        assert _rel(M, 0.1 * want) <= TOL_F32
+
+    def queries():
+        return (grass.cgrad_workspace(T, m, n, r, grass.BF16, layout), grass.dense_workspace(T, m, n, grass.BF16, layout),
+                grass.step_group_workspace(T, n, [r], grass.BF16, layout))
+
+    check(*queries())
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 128)  # the slices planned by themselves: their room is the least
+    least = queries()
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 0)
+    assert all(a <= b for a, b in zip(least, queries()))
+    check(*least)
+
+
+def test_slices_of_a_short_product_and_of_a_long_one():
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 128)
+    alone = grass.cgrad_plan(4270, 488, 166, grass.BF16)
+    long = grass.cgrad_plan(65536, 2048, 512, grass.BF16)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 0)
+    assert grass.cgrad_plan(4270, 488, 166, grass.BF16)[1] > alone[1]
+    assert grass.cgrad_plan(65536, 2048, 512, grass.BF16) == long
