@@ -471,8 +471,9 @@ grass_status grass_adam_scatter_replayable(const float* GC, int64_t ldgc, void* 
  *   GRASS_TEST_RUN_TILE      128, 192 or 256 (bf16): the tile that runs, on the K slices of the plan (which
  *                            GRASS_TEST_GEMM_TILE forces together with the tile); left to the
  *                            library where the operands' alignment rules that tile out
- *   GRASS_TEST_UNALIGNED_X   1: an X in any position beside an aligned left operand takes the 256 tile's kernel
- *                            for it from the first K tile and row tile on
+ *   GRASS_TEST_UNALIGNED_X   1: an X in any position beside an aligned left operand (or the other way round)
+ *                            takes the 256 tile's kernel for it from the first K tile and row tile on, and nothing
+ *                            is copied into aligned rows
  * Errors: DTYPE for an unknown option. */
 typedef enum {
     GRASS_TEST_GEMM_TILE = 0,
@@ -501,7 +502,8 @@ typedef enum {
     GRASS_KERNEL_F32 = 9,              /* fp32 matrix instruction */
     GRASS_KERNEL_F32_SPLIT_64 = 10,    /* operands split into bf16 parts */
     GRASS_KERNEL_F32_SPLIT_128 = 11,
-    GRASS_KERNEL_F32_SHORT = 12
+    GRASS_KERNEL_F32_SHORT = 12,
+    GRASS_KERNEL_256_UNALIGNED_DY = 13 /* dY of a full gradient in any position */
 } grass_test_kernel;
 int grass_test_last_kernel(void);
 

@@ -149,7 +149,7 @@ struct Copies { bool a, b; };
 // any pack, which the copy keeps possible.
 Copies choose_copies(TileId tile, int64_t T, int64_t rows, int64_t n, grass_dy_layout layout, bool gathered) {
     const bool b_odd = n % 8 != 0, a_odd = !needs_pack(layout, gathered) && rows % 8 != 0;
-    if (T < 1 || !(a_odd || b_odd)) return Copies{false, false};
+    if (T < 1 || !(a_odd || b_odd) || test_option(GRASS_TEST_UNALIGNED_X) == 1) return Copies{false, false};
     if (layout == GRASS_DY_MxT && tile == kTile256 && T % kFastBK == 0) return Copies{false, b_odd};
     const double t = static_cast<double>(T);
     const double in_place = tile == kTile256 ? 7e-6 + 0.15 * 2.0 * t * rows * n / 1.3e15
@@ -1196,6 +1196,8 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
 
     const bool a_direct = a_chunks && (test_option(GRASS_TEST_UNALIGNED_X) == 1 ||
                                        (p.tiles_m > 1 && g.ktiles_per_split >= kUnalignedXMin));
+    const bool x_direct = !a_chunks && at.x_chunks && !gathered &&
+                          (test_option(GRASS_TEST_UNALIGNED_X) == 1 || (p.tiles_n > 1 && g.ktiles_per_split >= kUnalignedXMin));
 
     const unsigned grid = static_cast<unsigned>(blocks);
     hipError_t le;
@@ -1203,7 +1205,8 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
                 : tile == kTile128 ? (small_direct ? GRASS_KERNEL_128 : GRASS_KERNEL_128_STAGED)
                 : a_rows_form ? GRASS_KERNEL_256_ROWS
                 : aligned ? GRASS_KERNEL_256
-                : a_direct ? GRASS_KERNEL_256_UNALIGNED_X : GRASS_KERNEL_256_UNALIGNED);
+                : a_direct ? GRASS_KERNEL_256_UNALIGNED_X
+                : x_direct ? GRASS_KERNEL_256_UNALIGNED_DY : GRASS_KERNEL_256_UNALIGNED);
     if (tile == kTile256) {  // the events are stamped with this dispatch's own start and end
         if (a_pairs)
             launch_stamped(tn_gemm_bf16_direct_kernel<false, false, true, true>, dim3(grid), dim3(256), 0, s,
@@ -1215,6 +1218,8 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
             launch_stamped(tn_gemm_bf16_unaligned_x_kernel<false>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else if (!aligned && a_direct)
             launch_stamped(tn_gemm_bf16_unaligned_x_kernel<true>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
+        else if (!aligned && x_direct)
+            launch_stamped(tn_gemm_bf16_unaligned_x_kernel<true, true>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else if (!aligned && gathered)
             launch_stamped(tn_gemm_bf16_unaligned_kernel<false>, dim3(grid), dim3(256), 0, s, ev_start, ev_stop, g);
         else if (!aligned)

@@ -347,12 +347,18 @@ __device__ __forceinline__ void store_unaligned(const GemmArgs& g, const f32x16 
 // 70 with this); a single, mostly padded row tile is bound by the memory's time for X (4738 x 561, r = 70 columns,
 // T = 112447: 289 and 296).  6288 x 9370, r = 786, T = 66176: 1224 us above, 1172 here.
 constexpr int kUnalignedXMin = 64;
-template <bool kDense>
+// kLeft: the left operand in any position and X in aligned chunks (a full gradient of odd height): the same with the
+// operands' ways exchanged.  5461 x 2048, T = 65536: whole refresh steps 1351 -> 1274 us (with both
+// operands through registers the product took 1290).
+template <bool kDense, bool kLeft = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void tn_gemm_bf16_unaligned_x_kernel(GemmArgs g) {
     constexpr int kStagesA = 4, kAheadA = 3;
     __shared__ __attribute__((aligned(1024))) uint16_t ringA[kStagesA * kFastOperandElems];
     __shared__ __attribute__((aligned(1024))) uint16_t ringB[2 * kFastOperandElems];
+    // A and B below: the operand that goes to LDS directly and the one that passes through registers
+    const int64_t lda = kLeft ? g.ldb : g.lda, ldb = kLeft ? g.lda : g.ldb;
+    const int64_t colsA = kLeft ? g.Ncols : g.Mcols, colsB = kLeft ? g.Mcols : g.Ncols;
 
     const int64_t item = work_item(g);
     if (item < 0) return;
@@ -375,17 +381,17 @@ void tn_gemm_bf16_unaligned_x_kernel(GemmArgs g) {
     const int lrow = wave * 2 + (lane >> 5);
     const int slot = lane & 31;
     const int lchunk_g = slot ^ (4 * (lrow & 3));
-    int64_t colA = m0 + lchunk_g * 8, colB = n0 + lchunk_g * 8;
-    colA = colA >= g.Mcols ? 0 : colA;
-    colB = colB >= g.Ncols ? 0 : (colB + 8 > g.Ncols ? g.Ncols - 8 : colB);
-    const uint16_t* gA = g.A + kt_begin * kFastBK * g.lda;
-    const uint16_t* gB = g.B + kt_begin * kFastBK * g.ldb;
-    const int64_t tileA = kFastBK * g.lda, tileB = kFastBK * g.ldb;
+    int64_t colA = (kLeft ? n0 : m0) + lchunk_g * 8, colB = (kLeft ? m0 : n0) + lchunk_g * 8;
+    colA = colA >= colsA ? 0 : colA;
+    colB = colB >= colsB ? 0 : (colB + 8 > colsB ? colsB - 8 : colB);
+    const uint16_t* gA = (kLeft ? g.B : g.A) + kt_begin * kFastBK * lda;
+    const uint16_t* gB = (kLeft ? g.A : g.B) + kt_begin * kFastBK * ldb;
+    const int64_t tileA = kFastBK * lda, tileB = kFastBK * ldb;
     uint32_t laneA[4], laneB[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        laneA[p] = static_cast<uint32_t>(((p * 8 + lrow) * g.lda + colA) * 2);
-        laneB[p] = static_cast<uint32_t>(((p * 8 + lrow) * g.ldb + colB) * 2);
+        laneA[p] = static_cast<uint32_t>(((p * 8 + lrow) * lda + colA) * 2);
+        laneB[p] = static_cast<uint32_t>(((p * 8 + lrow) * ldb + colB) * 2);
     }
     const uint32_t ring_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)ringA)) + wave * 2 * 256 * 2;
     uint16_t* const lds_lane = ringB + lrow * 256 + slot * 8;
@@ -395,7 +401,7 @@ void tn_gemm_bf16_unaligned_x_kernel(GemmArgs g) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
             const int row = p * 8 + lrow, src = row < last_rows ? row : last_rows - 1;
-            load16_to_lds(gA, full ? laneA[p] : static_cast<uint32_t>((src * g.lda + colA) * 2), stage_a(i) + p * 8 * 256 * 2);
+            load16_to_lds(gA, full ? laneA[p] : static_cast<uint32_t>((src * lda + colA) * 2), stage_a(i) + p * 8 * 256 * 2);
         }
         gA += tileA;
     };
@@ -407,7 +413,7 @@ void tn_gemm_bf16_unaligned_x_kernel(GemmArgs g) {
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
                 const int row = p * 8 + lrow, src = row < last_rows ? row : last_rows - 1;
-                const u32x4_t v = load16_any(gB, static_cast<uint32_t>((src * g.ldb + colB) * 2));
+                const u32x4_t v = load16_any(gB, static_cast<uint32_t>((src * ldb + colB) * 2));
                 const u32x4_t zero = {0u, 0u, 0u, 0u};
                 r[p] = row < last_rows ? v : zero;
             }
@@ -417,7 +423,7 @@ void tn_gemm_bf16_unaligned_x_kernel(GemmArgs g) {
     auto write_b = [&](const u32x4_t& r, int i, int p) {
         *reinterpret_cast<u32x4_t*>(lds_lane + (i & 1) * kFastOperandElems + p * 8 * 256) = r;
     };
-    // clears the left operand's rows of the ragged last tile that lie past K (after it has landed)
+    // clears the direct operand's rows of the ragged last tile that lie past K (after it has landed)
     auto clear_rows = [&](int i) {
         if (last_rows < kFastBK && i == ntiles - 1) {
             uint16_t* st = ringA + (i % kStagesA) * kFastOperandElems;
@@ -450,8 +456,9 @@ void tn_gemm_bf16_unaligned_x_kernel(GemmArgs g) {
 
     struct Frags { bf16x8 a[4], b[4]; };
     auto read_quarter = [&](Frags& f, int i, int k16, int part) {
-        const uint16_t* sa = ringA + (i % kStagesA) * kFastOperandElems + k16 * 256;
-        const uint16_t* sb = ringB + (i & 1) * kFastOperandElems + k16 * 256;
+        const uint16_t* direct = ringA + (i % kStagesA) * kFastOperandElems + k16 * 256;
+        const uint16_t* staged = ringB + (i & 1) * kFastOperandElems + k16 * 256;
+        const uint16_t *sa = kLeft ? staged : direct, *sb = kLeft ? direct : staged;  // left operand, X
         if (part == 0) { f.a[0] = read_frag_swz(sa + offA[0]); f.b[0] = read_frag_swz(sb + offB[0]); }
         else if (part == 1) { f.b[1] = read_frag_swz(sb + offB[1]); f.b[2] = read_frag_swz(sb + offB[2]); }
         else if (part == 2) { f.b[3] = read_frag_swz(sb + offB[3]); f.a[1] = read_frag_swz(sa + offA[1]); }

@@ -23,7 +23,7 @@ TEST_GEMM_TILE, TEST_FUSED_STATS, TEST_PACK_MXT, TEST_NO_PAIRS, TEST_MAX_K_SLICE
 TEST_NO_NARROW_GATHER, TEST_RUN_TILE, TEST_UNALIGNED_X = 5, 6, 7
 (KERNEL_NONE, KERNEL_128_STAGED, KERNEL_128, KERNEL_128_256, KERNEL_256, KERNEL_256_ROWS, KERNEL_256_UNALIGNED,
  KERNEL_256_UNALIGNED_X, KERNEL_NARROW, KERNEL_F32, KERNEL_F32_SPLIT_64, KERNEL_F32_SPLIT_128,
- KERNEL_F32_SHORT) = range(13)
+ KERNEL_F32_SHORT, KERNEL_256_UNALIGNED_DY) = range(14)
 
 EXPORTS = [
     "grass_status_string", "grass_row_stats", "grass_select_workspace", "grass_select_rows",

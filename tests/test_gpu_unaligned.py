@@ -128,3 +128,36 @@ def test_left_operand_by_load_to_lds_is_chosen():
     G = torch.empty(512, 2045, device=DEV)
     grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(65536, 512, 2045, grass.BF16)))
     assert grass.last_kernel() == grass.KERNEL_256_UNALIGNED_X
+
+
+# The operands' ways exchanged: X in aligned chunks, dY of a full gradient in any position.
+def _x_by_load_to_lds(T, m, n, slices):
+    grass.set_test_option(grass.TEST_RUN_TILE, 256)
+    grass.set_test_option(grass.TEST_UNALIGNED_X, 1)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, slices)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T)
+    dY, X = _framed(T, m, m, 9, gen), _framed(T, n, n + 8, 8, gen)
+    G = torch.full((m, n), float("nan"), device=DEV)
+    grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(T, m, n, grass.BF16)))
+    assert grass.last_kernel() == grass.KERNEL_256_UNALIGNED_DY
+    assert rel_fro(to_np(G), to_f64(dY).T @ to_f64(X)) <= TOL_F32
+
+
+@pytest.mark.parametrize("rest", [0, 5])
+@pytest.mark.parametrize("tiles", [*range(1, 19), 21, 22])
+def test_x_by_load_to_lds(tiles, rest):
+    _x_by_load_to_lds(32 * tiles + rest, 261, 136, 1)
+    _x_by_load_to_lds(32 * tiles + rest, 141, 264, 1)
+
+
+@pytest.mark.parametrize("last", range(1, 10))
+def test_x_by_load_to_lds_in_slices(last):
+    _x_by_load_to_lds(32 * (20 * 19 + last) - (3 if last % 2 else 0), 261, 264, 20)
+
+
+def test_x_by_load_to_lds_is_chosen():
+    dY, X = torch.zeros(65536, 2045, dtype=BF, device=DEV), torch.zeros(65536, 512, dtype=BF, device=DEV)
+    G = torch.empty(2045, 512, device=DEV)
+    grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(65536, 2045, 512, grass.BF16)))
+    assert grass.last_kernel() == grass.KERNEL_256_UNALIGNED_DY
