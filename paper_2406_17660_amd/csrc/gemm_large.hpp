@@ -479,16 +479,7 @@ __device__ __forceinline__ void direct_gemm(const GemmArgs& g) {
             }
         return;
     }
-    float* P = g.P + (static_cast<int64_t>(split) * g.Mp + m0 + wr * 128) * g.Np + n0 + wc * 128;
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = a * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-                P[static_cast<int64_t>(row) * g.Np + b * 32 + (lane & 31)] = acc[a][b][v];
-            }
+    store_block<4, 4>(g, acc, split, m0 + wr * 128, n0 + wc * 128, lane);
 }
 
 template <bool kDense, bool kRowStats = false, bool kARows = false, bool kAPairs = false>

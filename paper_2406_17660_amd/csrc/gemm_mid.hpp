@@ -258,16 +258,7 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void tn_gemm_bf16_mid_kerne
         mfma_row(G, 1);
     }
 
-    float* P = g.P + (static_cast<int64_t>(split) * g.Mp + m0 + wr * 64) * g.Np + n0 + wc * (BN / 2);
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = a * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-                P[static_cast<int64_t>(row) * g.Np + b * 32 + (lane & 31)] = acc[a][b][v];
-            }
+    store_block<2, NB>(g, acc, split, m0 + wr * 64, n0 + wc * (BN / 2), lane);
 }
 
 }  // namespace

@@ -70,8 +70,9 @@ __device__ __forceinline__ bf16x8 read_frag(const uint16_t* tile, int ld, int k1
 struct GemmArgs {
     const uint16_t* A;  // [K x Mcols], leading dimension lda
     const uint16_t* B;  // [K x Ncols], leading dimension ldb
-    float* P;           // partials [S][Mp][Np]
+    float* P;           // partials [S][Mp][Np], or the output itself (one slice, Np its leading dimension)
     int64_t lda, ldb, K, Mcols, Ncols, Mp, Np;
+    int64_t out_rows, out_cols;  // of P: whole tiles, or the output's (not looked at by the staged 128 tile)
     int tiles_m, tiles_n, splits, ktiles_per_split;
     // row form of the left operand (large-tile kernel only): A is [rows of length K], row j of
     // the product is A + a_rows[j] * lda (a_rows == nullptr: row j itself)
@@ -97,6 +98,37 @@ __device__ __forceinline__ KRange k_range(const GemmArgs& g, int split) {
     q.end = q.begin + g.ktiles_per_split < all ? q.begin + g.ktiles_per_split : all;
     q.rows = q.end > q.begin && q.end * BK > g.K ? static_cast<int>(g.K - (q.end - 1) * BK) : BK;
     return q;
+}
+
+// Stores a wavefront's block of FA x FB 32 x 32 accumulators at (m, n) of slice `split`.
+template <int FA, int FB>
+__device__ __forceinline__ void store_block(const GemmArgs& g, const f32x16 (&acc)[FA][FB], int split, int64_t m, int64_t n, int lane) {
+    const int h = lane >> 5;
+    float* P = g.P + (static_cast<int64_t>(split) * g.Mp + m) * g.Np + n;
+    if (m + FA * 32 <= g.out_rows && n + FB * 32 <= g.out_cols) {
+#pragma unroll
+        for (int a = 0; a < FA; ++a)
+#pragma unroll
+            for (int b = 0; b < FB; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = a * 32 + 8 * (v / 4) + 4 * h + (v % 4);
+                    P[static_cast<int64_t>(row) * g.Np + b * 32 + (lane & 31)] = acc[a][b][v];
+                }
+        return;
+    }
+    const int64_t rows = g.out_rows - m, cols = g.out_cols - n - (lane & 31);  // an output of its own: its edge
+#pragma unroll
+    for (int a = 0; a < FA; ++a)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = a * 32 + 8 * (v / 4) + 4 * h + (v % 4);
+            if (row >= rows) continue;
+            float* dst = P + static_cast<int64_t>(row) * g.Np + (lane & 31);
+#pragma unroll
+            for (int b = 0; b < FB; ++b)
+                if (b * 32 < cols) dst[b * 32] = acc[a][b][v];
+        }
 }
 
 // kDense only tags the instantiation (dense full gradient vs compressed gradient) so that a

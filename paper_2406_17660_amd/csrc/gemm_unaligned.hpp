@@ -250,15 +250,7 @@ void tn_gemm_bf16_unaligned_kernel(GemmArgs g) {
     const int edgeN = static_cast<int>((g.Ncols & ~int64_t{7}) - n0 - wc * 128);  // crossing chunk,
     const int edgeM = static_cast<int>((g.Mcols & ~int64_t{7}) - m0 - wr * 128);  // in this block
     if ((shiftN == 0 || edgeN >= 128 || edgeN <= -8) && (shiftM == 0 || edgeM >= 128 || edgeM <= -8)) {
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = a * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-                    P[static_cast<int64_t>(row) * g.Np + b * 32 + (lane & 31)] = acc[a][b][v];
-                }
+        store_block<4, 4>(g, acc, split, m0 + wr * 128, n0 + wc * 128, lane);
         return;
     }
     int col[4];  // where fragment column b goes, -1: nowhere
@@ -267,6 +259,7 @@ void tn_gemm_bf16_unaligned_kernel(GemmArgs g) {
         col[b] = b * 32 + (lane & 31);
         const int e = col[b] - edgeN;
         if (shiftN != 0 && e >= 0) col[b] = e < shiftN || e >= 8 ? -1 : col[b] - shiftN;
+        if (n0 + wc * 128 + col[b] >= g.out_cols) col[b] = -1;
     }
 #pragma unroll
     for (int a = 0; a < 4; ++a)
@@ -276,6 +269,7 @@ void tn_gemm_bf16_unaligned_kernel(GemmArgs g) {
             const int e = row - edgeM;
             bool ok = true;
             if (shiftM != 0 && e >= 0) { ok = e >= shiftM && e < 8; row -= shiftM; }
+            ok = ok && m0 + wr * 128 + row < g.out_rows;
             float* dst = P + static_cast<int64_t>(row) * g.Np;
 #pragma unroll
             for (int b = 0; b < 4; ++b)
@@ -294,15 +288,7 @@ __device__ __forceinline__ void store_unaligned(const GemmArgs& g, const f32x16 
     const int edgeN = static_cast<int>((g.Ncols & ~int64_t{7}) - n);  // crossing chunk,
     const int edgeM = static_cast<int>((g.Mcols & ~int64_t{7}) - m);  // in this block
     if ((shiftN == 0 || edgeN >= 128 || edgeN <= -8) && (shiftM == 0 || edgeM >= 128 || edgeM <= -8)) {
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = a * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-                    P[static_cast<int64_t>(row) * g.Np + b * 32 + (lane & 31)] = acc[a][b][v];
-                }
+        store_block<4, 4>(g, acc, split, m, n, lane);
         return;
     }
     int col[4];  // where fragment column b goes, -1: nowhere
@@ -311,6 +297,7 @@ __device__ __forceinline__ void store_unaligned(const GemmArgs& g, const f32x16 
         col[b] = b * 32 + (lane & 31);
         const int e = col[b] - edgeN;
         if (shiftN != 0 && e >= 0) col[b] = e < shiftN || e >= 8 ? -1 : col[b] - shiftN;
+        if (n + col[b] >= g.out_cols) col[b] = -1;
     }
 #pragma unroll
     for (int a = 0; a < 4; ++a)
@@ -320,6 +307,7 @@ __device__ __forceinline__ void store_unaligned(const GemmArgs& g, const f32x16 
             const int e = row - edgeM;
             bool ok = true;
             if (shiftM != 0 && e >= 0) { ok = e >= shiftM && e < 8; row -= shiftM; }
+            ok = ok && m + row < g.out_rows;
             float* dst = P + static_cast<int64_t>(row) * g.Np;
 #pragma unroll
             for (int b = 0; b < 4; ++b)
