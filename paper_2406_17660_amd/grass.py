@@ -139,43 +139,51 @@ def _check(code, where):
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+# The small layers' steps are bound by this module: a kernel of 8.6 us behind 10.9 us of calls (9.2 so).  Addresses
+# therefore stay plain integers (every argument's type is declared), and sizes and strides are read once per tensor.
 def _stream():
     """Handle of torch's current stream on the current device (every call is issued there)."""
-    if _raw_stream is not None:  # the same handle without building a Stream object per call
-        return C.c_void_p(_raw_stream(torch.cuda.current_device()))
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is not None and _device is not None:  # the same handle without building a Stream object per call
+        return _raw_stream(_device())
+    return torch.cuda.current_stream().cuda_stream
+
+
+_DTYPES = {torch.float32: F32, torch.bfloat16: BF16}
 
 
 def _dtype(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    code = _DTYPES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _mat(t: torch.Tensor):
-    """(pointer, rows, cols, leading dimension) of a row-major 2-D device tensor."""
-    assert t.is_cuda and t.dim() == 2, "2-D CUDA tensor expected"
-    rows, cols = t.shape
+    """(address, rows, cols, leading dimension) of a row-major 2-D device tensor."""
+    shape = t.shape
+    assert t.is_cuda and len(shape) == 2, "2-D CUDA tensor expected"
+    rows, cols = shape
+    ld, step = t.stride()
     if rows > 1 and cols > 0:
-        assert cols == 1 or t.stride(1) == 1, "rows must be contiguous"
-        ld = t.stride(0)
-    else:
-        ld = max(cols, 1) if t.stride(0) < cols else t.stride(0)
-    return C.c_void_p(t.data_ptr()), rows, cols, ld
+        assert cols == 1 or step == 1, "rows must be contiguous"
+    elif ld < cols:
+        ld = max(cols, 1)
+    return t.data_ptr(), rows, cols, ld
 
 
 def _vec(t: torch.Tensor, dtype):
     assert t.is_cuda and t.dim() == 1 and t.dtype == dtype and t.is_contiguous()
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _ws(ws):
     if ws is None:
         return None, 0
     assert ws.is_cuda and ws.is_contiguous()
-    return C.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size()
+    return ws.data_ptr(), ws.nbytes
 
 
 def row_stats(G: torch.Tensor, sumsq: torch.Tensor):
@@ -310,11 +318,24 @@ def _moments(M, V, r, n):
     """Pointers and dtype code of the Adam moments (fp32, or bf16 for the 2-byte state)."""
     for a in (M, V):
         assert a.shape == (r, n) and a.is_contiguous() and a.is_cuda and a.dtype == M.dtype
-    return C.c_void_p(M.data_ptr()), C.c_void_p(V.data_ptr()), _dtype(M)
+    return M.data_ptr(), V.data_ptr(), _dtype(M)
 
 
 def step_group_workspace(T, n, rs, dtype, layout=DY_TxM) -> int:
     return int(lib().grass_step_group_workspace(T, n, len(rs), _i64_array(rs), dtype, layout))
+
+
+_WORDS = {}
+
+
+def _words(n):
+    """The type of an array of n 8-byte words."""
+    if n not in _WORDS:
+        _WORDS[n] = C.c_int64 * n
+    return _WORDS[n]
+
+
+assert C.sizeof(StepLayer) == 8 * len(StepLayer._fields_)
 
 
 def step_group(dYs, X, idxs, rhos, Ms, Vs, Ws, lr, beta1, beta2, eps, t, alpha, ws, layout=DY_TxM,
@@ -325,25 +346,28 @@ def step_group(dYs, X, idxs, rhos, Ms, Vs, Ws, lr, beta1, beta2, eps, t, alpha, 
     that their handles exist) for the matrix-multiply kernel and for the fused tail."""
     count = len(dYs)
     pX, T, n, ldx = _mat(X)
-    arr = (StepLayer * count)()
+    fields = []  # of the grass_step_layer array, 8 bytes each
     sdt = wdt = None
+    dtype = X.dtype
     for i in range(count):
-        pY, ry, cy, ldy = _mat(dYs[i])
-        assert (ry if layout == DY_TxM else cy) == T and dYs[i].dtype == X.dtype
+        dY = dYs[i]
+        pY, ry, cy, ldy = _mat(dY)
+        assert (ry if layout == DY_TxM else cy) == T and dY.dtype == dtype
         m = cy if layout == DY_TxM else ry
         r = idxs[i].shape[0]
         pW, mw, nw, ldw = _mat(Ws[i])
         assert (mw, nw) == (m, n)
         pM, pV, sd = _moments(Ms[i], Vs[i], r, n)
-        assert sdt in (None, sd) and wdt in (None, _dtype(Ws[i]))
-        sdt, wdt = sd, _dtype(Ws[i])
+        wd = _dtype(Ws[i])
+        assert sdt in (None, sd) and wdt in (None, wd)
+        sdt, wdt = sd, wd
         gc = GCs[i] if GCs is not None else None
+        pG, ldgc = 0, 0
         if gc is not None:
             pG, gr, gcols, ldgc = _mat(gc)
             assert (gr, gcols) == (r, n) and gc.dtype == torch.float32
-        arr[i] = StepLayer(pY.value, ldy, m, r, _vec(idxs[i], torch.int32).value,
-                           _vec(rhos[i], torch.float32).value, pG.value if gc is not None else None,
-                           ldgc if gc is not None else 0, pM.value, pV.value, pW.value, ldw)
+        fields += (pY, ldy, m, r, _vec(idxs[i], torch.int32), _vec(rhos[i], torch.float32), pG, ldgc, pM, pV, pW, ldw)
+    arr = _words(len(fields))(*fields)
     wp, wb = _ws(ws)
     sc = C.c_void_p(step_scalars.data_ptr()) if step_scalars is not None else None
     e0, e1 = ((C.c_void_p(e.cuda_event) for e in gemm_events) if gemm_events is not None
