@@ -305,15 +305,44 @@ struct NarrowPlan {
 // per compute unit (what the kernel's LDS use allows), as long as the partial tiles stay under a
 // quarter of the input bytes (measured at the 60M shapes, T = 65536: 512 x 512 at r = 128 takes
 // 26 us with 128 slices, 30 - 33 with 96, 170 or 256; the q/k/v group 66 us with 85 slices, 82
-// with 42), every slice keeps at least four K tiles, and the workspace holds them.
+// with 42), every slice keeps at least four K tiles, and cap_bytes hold them.
+// Up to kNarrowFitT tokens: the slices of least estimated time that fit `room`.  A round of workgroups (two per compute
+// unit) takes 1.4 us and, per K tile of 16 tokens, 0.42 us and 0.34 times the workgroups per unit; a slice of partial
+// tiles 0.27 us per MB.  Fitted to the steps of 110 random layers (one and three sets, 14 numbers of slices each), of
+// which it is 1.1 % from the best; a quarter of the inputs' bytes allows a short product so few slices that
+// most of the chip is idle.  512 x 512, r = 128, T = 1280: 29.7 -> 13.6 us, three of them, T = 2176: 51 -> 21; 256 x 256,
+// r = 64, T = 256: 16.9 -> 11.1; 448 x 320, r = 56, T = 15552: 21.4 -> 17.7.
+constexpr int64_t kNarrowFitT = 32768;
 NarrowPlan narrow_plan(int64_t T, int64_t n, int tiles_m, int64_t panel_rows, int64_t in_cols,
-                       size_t cap_bytes) {
+                       size_t cap_bytes, size_t room) {
     NarrowPlan p;
     p.tiles_n = static_cast<int>((n + kNarrowBN - 1) / kNarrowBN);
     p.Np = static_cast<int64_t>(p.tiles_n) * kNarrowBN;
     p.Mp = (panel_rows + 7) / 8 * 8;
     const int64_t ktiles = T / kNarrowBK, tiles = static_cast<int64_t>(tiles_m) * p.tiles_n;
     const int64_t slice_bytes = p.Mp * p.Np * 4;
+    if (T <= kNarrowFitT) {
+        const int limit = test_option(GRASS_TEST_MAX_K_SLICES);
+        const int64_t fit = room / static_cast<size_t>(slice_bytes > 0 ? slice_bytes : 1) < 128
+                                ? static_cast<int64_t>(room / static_cast<size_t>(slice_bytes > 0 ? slice_bytes : 1)) : 128;
+        p.splits = 1;
+        p.ktiles_per_split = static_cast<int>(ktiles > 0 ? ktiles : 1);
+        double least = 1e300;
+        for (const int c : {1, 2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64, 72, 85, 96, 112, 128}) {
+            if (c > 1 && (2 * c > ktiles || (limit > 0 && c > limit))) break;
+            const int64_t per = (ktiles + c - 1) / c, slices = (ktiles + per - 1) / per, wgs = tiles * slices;
+            if (slices > 1 && slices > fit) break;
+            const double u = static_cast<double>(wgs < 512 ? wgs : 512) / 256.0;
+            const double us = static_cast<double>((wgs + 511) / 512) * (1.4 + static_cast<double>(per) * (0.42 + 0.34 * u)) +
+                              0.27e-6 * static_cast<double>(slices * slice_bytes);
+            if (us < least) {
+                least = us;
+                p.splits = static_cast<int>(slices);
+                p.ktiles_per_split = static_cast<int>(per);
+            }
+        }
+        return p;
+    }
     int64_t s = tiles > 0 ? (512 + tiles - 1) / tiles : 1;
     const int64_t by_traffic = T * in_cols * 2 / 4 / (slice_bytes > 0 ? slice_bytes : 1);
     const int64_t by_space = static_cast<int64_t>(cap_bytes) / (slice_bytes > 0 ? slice_bytes : 1);
@@ -700,7 +729,15 @@ size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
     }
     // the narrow kernel's slices are bounded by a cap of their own
     const bool narrow = gathered && narrow_shape_ok(T, n, dt, layout) && mrows <= GRASS_MAX_GROUP * kNarrowBM;
-    const size_t cap = narrow ? narrow_cap_bytes(T, mrows, n) : 0;
+    size_t cap = narrow ? narrow_cap_bytes(T, mrows, n) : 0;
+    if (narrow && !least && T <= kNarrowFitT) {
+        // (the number of sets, one row tile each, is not known here)
+        for (int sets = static_cast<int>((mrows + kNarrowBM - 1) / kNarrowBM); sets <= GRASS_MAX_GROUP; ++sets) {
+            const NarrowPlan p = narrow_plan(T, n, sets, mrows, 0, cap, ~size_t{0});
+            const size_t bytes = static_cast<size_t>(p.splits) * p.Mp * p.Np * 4;
+            cap = bytes > cap ? bytes : cap;
+        }
+    }
     return (cap > tiled ? cap : tiled) + 256;
 }
 
@@ -729,7 +766,7 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
     if (m > 0 && count >= 1 && narrow_shape_ok(T, n, dt, layout) &&
         narrow_set_ok((rows / count + 7) / 8 * 8, m)) {  // the sets taken to be of equal size
         const size_t cap = narrow_cap_bytes(T, rows, n);
-        const NarrowPlan p = narrow_plan(T, n, count, rows, m * count + n, cap);
+        const NarrowPlan p = narrow_plan(T, n, count, rows, m * count + n, cap, ~size_t{0});
         *tile = 0;
         *k_slices = p.splits;
         return;
@@ -992,7 +1029,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
             in_cols += seg[i].src_rows;
         }
         const size_t cap = narrow_cap_bytes(T, total, n);
-        const NarrowPlan np = narrow_plan(T, n, count, off, in_cols, cap);
+        const NarrowPlan np = narrow_plan(T, n, count, off, in_cols, cap, room);
         if (static_cast<size_t>(np.splits) * np.Mp * np.Np * 4 > room) return GRASS_ERR_WORKSPACE;
         a.count = count;
         a.X = static_cast<const uint16_t*>(X);

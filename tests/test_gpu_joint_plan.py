@@ -68,3 +68,32 @@ def test_slices_of_a_short_product_and_of_a_long_one():
     grass.set_test_option(grass.TEST_MAX_K_SLICES, 0)
     assert grass.cgrad_plan(4270, 488, 166, grass.BF16)[1] > alone[1]
     assert grass.cgrad_plan(65536, 2048, 512, grass.BF16) == long
+
+
+@pytest.mark.parametrize("T", [256, 272, 1280, 8192, 32768, 32784])
+@pytest.mark.parametrize("m,n,r,count", [(512, 512, 128, 1), (264, 200, 40, 3), (512, 264, 7, 1)])
+def test_slices_of_narrow_layers(T, m, n, r, count):
+    """The gather inside the product: slices for the workspace of the query, and for the least one, alone and grouped."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T)
+    dYs = [torch.randn(T, m, generator=gen, device=DEV).to(BF) for _ in range(count)]
+    X = torch.randn(T, n, generator=gen, device=DEV).to(BF)
+    idx = torch.randperm(m, generator=gen, device=DEV)[:r].sort()[0].to(torch.int32)
+    rho = torch.rand(r, generator=gen, device=DEV) + 0.5
+    query = grass.step_group_workspace(T, n, [r] * count, grass.BF16)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 1)
+    least = grass.step_group_workspace(T, n, [r] * count, grass.BF16)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 0)
+    for nbytes in (query, least):
+        Ms, Vs = ([torch.zeros(r, n, device=DEV) for _ in range(count)] for _ in range(2))
+        Ws = [torch.zeros(m, n, dtype=BF, device=DEV) for _ in range(count)]
+        try:
+            grass.step_group(dYs, X, [idx] * count, [rho] * count, Ms, Vs, Ws, 1e-3, 0.9, 0.999, 1e-8, 1, 0.25,
+                             grass.workspace(nbytes).fill_(255))
+        except grass.GrassError as e:  # what one slice asks for is below what a call accepts
+            assert nbytes == least < query and e.code == grass.ERR_WORKSPACE
+            continue
+        assert grass.last_kernel() == grass.KERNEL_NARROW
+        for dY, M in zip(dYs, Ms):
+            want = 0.1 * rho.double()[:, None] * (dY.double()[:, idx.long()].t() @ X.double())
+            assert _rel(M, want) <= TOL_F32
