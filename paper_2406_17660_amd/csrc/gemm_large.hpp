@@ -28,7 +28,7 @@ namespace {
 // banks exactly once.
 //
 // Edges.  Columns past the matrix edge are redirected to column 0 of the same row: they
-// only feed output rows / columns that are never read back.  A ragged last K tile (T x m form) is
+// only feed output rows / columns that are never read back (or not stored, see store_block).  A ragged last K tile (T x m form) is
 // loaded during the drain with the tokens past T redirected to the last one, and their LDS rows
 // are cleared once it has landed.  It ends the last slice; as a K slice of its own it cost one more slice
 // of partial tiles, written and read again (whole steps: 4096 x 4096, r = 1024, T = 2047: 53.0 -> 48.8 us,
