@@ -283,8 +283,7 @@ def _i64_array(values):
 
 
 def _ptr_array(pointers):
-    return (C.c_void_p * len(pointers))(*[p.value if isinstance(p, C.c_void_p) else p
-                                          for p in pointers])
+    return (C.c_void_p * len(pointers))(*pointers)
 
 
 def cgrad_group_workspace(T, n, rs, dtype, layout=DY_TxM) -> int:
