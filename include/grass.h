@@ -507,6 +507,15 @@ typedef enum {
 } grass_test_kernel;
 int grass_test_last_kernel(void);
 
+/* The bytes of workspace from which a call with bf16 inputs is accepted (the queries count faster plans, too). */
+typedef enum {
+    GRASS_TEST_CALL_CGRAD = 0, /* grass_compressed_grad (count = 1) or grass_compressed_grad_group */
+    GRASS_TEST_CALL_STEP = 1,  /* grass_step_group */
+    GRASS_TEST_CALL_DENSE = 2  /* grass_dense_grad, r[0] = m */
+} grass_test_call;
+size_t grass_test_least_workspace(grass_test_call call, int64_t T, int64_t n, int count, const int64_t* r,
+                                  grass_dy_layout layout);
+
 #ifdef __cplusplus
 }
 #endif

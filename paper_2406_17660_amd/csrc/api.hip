@@ -486,4 +486,17 @@ grass_status grass_set_test_option(grass_test_option option, int value) {
 
 int grass_test_last_kernel(void) { return t_last_kernel; }
 
+size_t grass_test_least_workspace(grass_test_call call, int64_t T, int64_t n, int count, const int64_t* r,
+                                  grass_dy_layout layout) {
+    if (T < 0 || n < 0 || !small(T) || !small(n) || count < 1 || count > GRASS_MAX_GROUP || !r) return 0;
+    size_t extra = call == GRASS_TEST_CALL_STEP ? 256 : 0;
+    for (int i = 0; i < count; ++i) {
+        if (r[i] < 0 || r[i] > kMaxGridRows) return 0;
+        if (call == GRASS_TEST_CALL_STEP) extra += scratch_gc_bytes(r[i], n);
+    }
+    if (call == GRASS_TEST_CALL_DENSE) return gemm_workspace_bytes(T, r[0], n, GRASS_BF16, layout, false, 0, true);
+    if (count == 1 && call == GRASS_TEST_CALL_CGRAD) return gemm_workspace_bytes(T, r[0], n, GRASS_BF16, layout, true, 0, true);
+    return gemm_group_workspace_bytes(T, r, count, n, GRASS_BF16, layout, call == GRASS_TEST_CALL_STEP, true) + extra;
+}
+
 }  // extern "C"

@@ -78,11 +78,22 @@ TileId planned_tile(int64_t rows, int64_t n) {
     return padded <= 1.35 * static_cast<double>(rows) * static_cast<double>(n) ? kTile256 : kTile128;
 }
 
-KSplit split_k(TileId planned, int64_t T, int64_t rows, int64_t n) {
-    const int edge = tile_rows(planned), bk = tile_k(planned);
+// The K tiles that slices are counted in: the large tile's whole ones (a ragged one ends the last slice), the small tile's all.
+int64_t slice_tiles(TileId planned, int64_t T) {
+    return planned == kTile256 ? T / kFastBK : (T + Cfg128::BK - 1) / Cfg128::BK;
+}
+KSplit in_slices(int64_t ktiles, int64_t slices, int bk) {
+    int64_t per = (ktiles + slices - 1) / slices;
+    if (per < 1) per = 1;
+    const int splits = static_cast<int>((ktiles + per - 1) / per);
+    return KSplit{splits < 1 ? 1 : splits, per * bk};
+}
+
+int64_t slice_count(TileId planned, int64_t T, int64_t rows, int64_t n) {
+    const int edge = tile_rows(planned);
     const int64_t tm = (rows + edge - 1) >> rows_log2(planned), tn = (n + edge - 1) >> rows_log2(planned);
     const int64_t tiles = tm * tn;
-    const int64_t ktiles = (T + bk - 1) / bk;
+    const int64_t ktiles = slice_tiles(planned, T);
     // Split K so that the workgroups fill whole rounds of the machine (256 CUs x workgroups
     // per CU) without paying too much for the partial tiles every slice adds.  In units of
     // the GEMM's time at full occupancy, c slices cost about 1 / fill(c) + c * k / T.  For
@@ -107,13 +118,12 @@ KSplit split_k(TileId planned, int64_t T, int64_t rows, int64_t n) {
         const double cost = static_cast<double>(filled << slots_log2) / static_cast<double>(wgs) + per_slice * c;
         if (cost < best - 1e-12) { best = cost; s = c; }
     }
-    int64_t per = (ktiles + s - 1) / s;
-    if (per < 1) per = 1;
-    KSplit q;
-    q.tokens = per * bk;
-    q.splits = static_cast<int>((ktiles + per - 1) / per);
-    if (q.splits < 1) q.splits = 1;
-    return q;
+    return s;
+}
+
+KSplit split_k(TileId planned, int64_t T, int64_t rows, int64_t n) {
+    const int bk = tile_k(planned);
+    return in_slices((T + bk - 1) / bk, slice_count(planned, T, rows, n), bk);
 }
 
 Plan make_plan(TileId id, const KSplit& k, int64_t T, int64_t rows, int64_t n, bool pack) {
@@ -686,7 +696,7 @@ grass_status launch_grad_row_stats(const void* dY, grass_dy_layout layout, int64
 size_t narrow_cap_bytes(int64_t T, int64_t rows, int64_t n) {
     size_t cap = 0;
     for (const TileId id : {kTile128, kTile256}) {
-        const KSplit k = split_k(id, T, rows, n);
+        const KSplit k = in_slices(slice_tiles(id, T), slice_count(id, T, rows, n), tile_k(id));
         const Plan p = make_plan(id, k, T, rows, n, true);
         const size_t bytes = p.pack_bytes + static_cast<size_t>(k.splits + 1) * p.Mp * p.Np * 4;
         cap = bytes > cap ? bytes : cap;

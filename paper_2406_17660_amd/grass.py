@@ -21,6 +21,7 @@ SCALE_PAPER, SCALE_ONE, SCALE_INV_SQRT_RQ = 0, 1, 2
 DY_TxM, DY_MxT = 0, 1
 TEST_GEMM_TILE, TEST_FUSED_STATS, TEST_PACK_MXT, TEST_NO_PAIRS, TEST_MAX_K_SLICES = 0, 1, 2, 3, 4
 TEST_NO_NARROW_GATHER, TEST_RUN_TILE, TEST_UNALIGNED_X = 5, 6, 7
+CALL_CGRAD, CALL_STEP, CALL_DENSE = range(3)
 (KERNEL_NONE, KERNEL_128_STAGED, KERNEL_128, KERNEL_128_256, KERNEL_256, KERNEL_256_ROWS, KERNEL_256_UNALIGNED,
  KERNEL_256_UNALIGNED_X, KERNEL_NARROW, KERNEL_F32, KERNEL_F32_SPLIT_64, KERNEL_F32_SPLIT_128,
  KERNEL_F32_SHORT, KERNEL_256_UNALIGNED_DY) = range(14)
@@ -33,7 +34,7 @@ EXPORTS = [
     "grass_grad_row_stats_workspace", "grass_grad_row_stats", "grass_scatter_update_cols",
     "grass_cgrad_group_workspace", "grass_compressed_grad_group",
     "grass_adam_rows_state", "grass_adam_scatter_state", "grass_cgrad_plan",
-    "grass_set_test_option", "grass_test_last_kernel", "grass_select_static_capacity", "grass_select_rows_static",
+    "grass_set_test_option", "grass_test_last_kernel", "grass_test_least_workspace", "grass_select_static_capacity", "grass_select_rows_static",
     "grass_adam_step_scalars", "grass_adam_scatter_replayable",
     "grass_step_group_workspace", "grass_step_group", "grass_step_group_timed",
     "grass_step_cols_workspace", "grass_step_cols",
@@ -112,6 +113,8 @@ def lib():
     L.grass_grad_row_stats.argtypes = [vp, i32, i64, vp, i64, i32, i64, i64, i64, vp, vp, sz, vp]
     L.grass_cgrad_plan.argtypes = [i64, i64, i64, i64, i32, i32, i32, C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.grass_set_test_option.argtypes = [i32, i32]
+    L.grass_test_least_workspace.argtypes = [i32, i64, i64, i32, vp, i32]
+    L.grass_test_least_workspace.restype = sz
     L.grass_cgrad_group_workspace.argtypes = [i64, i64, i32, vp, i32, i32]
     L.grass_cgrad_group_workspace.restype = sz
     L.grass_compressed_grad_group.argtypes = [i32, vp, i32, vp, vp, i64, i32, i64, vp, i64, vp,
@@ -121,7 +124,7 @@ def lib():
                         "grass_select_static_capacity",
                         "grass_dense_workspace", "grass_grad_row_stats_workspace",
                         "grass_cgrad_group_workspace", "grass_step_group_workspace",
-                        "grass_step_cols_workspace"):
+                        "grass_step_cols_workspace", "grass_test_least_workspace"):
             getattr(L, name).restype = i32
     _lib = L
     return L
@@ -255,6 +258,11 @@ def set_test_option(option: int, value: int):
 def last_kernel() -> int:
     """Test hook: the matrix-multiply kernel (KERNEL_*) of this thread's last product."""
     return lib().grass_test_last_kernel()
+
+
+def least_workspace(call: int, T, n, rs, layout=DY_TxM) -> int:
+    """Bytes of workspace from which a bf16 call (CALL_CGRAD, CALL_STEP, CALL_DENSE) is accepted (see grass.h)."""
+    return int(lib().grass_test_least_workspace(call, T, n, len(rs), _i64_array(rs), layout))
 
 
 def compressed_grad(dY, X, idx, rho, GC, ws, layout=DY_TxM, gemm_events=None):

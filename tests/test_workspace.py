@@ -58,3 +58,27 @@ def test_fp32_products_of_one_slice_ask_for_no_workspace(T, n, r, layout):
     _, slices = grass.cgrad_plan(T, n, r, grass.F32, layout)
     sizes = [grass.cgrad_workspace(T, r, n, r, grass.F32, layout), grass.dense_workspace(T, r, n, grass.F32, layout)]
     assert all((size == 0) == (slices == 1) for size in sizes), (slices, sizes)
+
+
+# Ragged token counts: bytes that the queries once asked for, with the tokens past the last whole K tile as a slice of
+# their own.  A program that keeps the size of its workspace is still served.
+@pytest.mark.parametrize("call,T,rows,n,layout,size", [
+    (grass.CALL_CGRAD, 496, 8, 72, grass.DY_TxM, 778496), (grass.CALL_CGRAD, 4338, 8, 128, grass.DY_TxM, 6415616),
+    (grass.CALL_CGRAD, 4578, 16, 160, grass.DY_MxT, 6800640), (grass.CALL_CGRAD, 4600, 4, 3, grass.DY_TxM, 6885632),
+    (grass.CALL_DENSE, 5105, 11, 61, grass.DY_MxT, 8248320), (grass.CALL_DENSE, 5358, 8, 160, grass.DY_TxM, 5243136),
+    (grass.CALL_CGRAD, 6378, 48, 180, grass.DY_TxM, 11904512), (grass.CALL_CGRAD, 6884, 115, 11, grass.DY_MxT, 10298880),
+    (grass.CALL_DENSE, 6910, 71, 10, grass.DY_TxM, 10312960),
+    (grass.CALL_STEP, 496, 8, 72, grass.DY_TxM, 778496 + 256 + 8 * 72 * 4)])
+def test_sizes_once_asked_for_are_accepted(call, T, rows, n, layout, size):
+    assert grass.least_workspace(call, T, n, [rows], layout) <= size
+
+
+@pytest.mark.parametrize("layout", [grass.DY_TxM, grass.DY_MxT])
+def test_the_least_workspace_is_part_of_the_query(layout):
+    rng = np.random.default_rng(3)
+    for _ in range(300):
+        T, n = int(2 ** rng.uniform(0, 16)), int(2 ** rng.uniform(0, 12))
+        rs = [int(2 ** rng.uniform(0, 10)) for _ in range(rng.integers(1, 5))]
+        assert grass.least_workspace(grass.CALL_CGRAD, T, n, rs[:1], layout) <= grass.cgrad_workspace(T, rs[0], n, rs[0], grass.BF16, layout)
+        assert grass.least_workspace(grass.CALL_DENSE, T, n, rs[:1], layout) <= grass.dense_workspace(T, rs[0], n, grass.BF16, layout)
+        assert grass.least_workspace(grass.CALL_STEP, T, n, rs, layout) <= grass.step_group_workspace(T, n, rs, grass.BF16, layout)
