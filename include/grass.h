@@ -316,7 +316,8 @@ grass_status grass_adam_scatter_state(const float* GC, int64_t ldgc, void* M, vo
  * methods compute every step ("mbn" FLOPs, Appendix F) and what GRASS needs on a
  * refresh step to obtain row norms; it also serves as the naive comparator
  * (full G followed by a row gather).  G has dtype gdt (fp32 accumulation, one
- * rounding), leading dimension ldg.
+ * rounding), leading dimension ldg.  G must not lie over ws, nor, for fp32 inputs, over dY or X;
+ * over bf16 inputs it may, at the cost of one pass more (it is then written once both are used up).
  * Errors: NULL, SHAPE, DTYPE, WORKSPACE. */
 size_t grass_dense_workspace(int64_t T, int64_t m, int64_t n, grass_dtype dt,
                              grass_dy_layout layout);

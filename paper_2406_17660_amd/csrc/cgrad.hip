@@ -292,6 +292,14 @@ Choice choose_plan(TileId planned, const KSplit& k, const Shape& q, size_t room)
     return best;
 }
 
+// The addresses that a matrix of `rows` rows (at least one) takes up.
+struct Span { uintptr_t begin, end; };
+Span span_of(const void* p, int64_t rows, int64_t cols, int64_t ld, size_t elem) {
+    const uintptr_t begin = reinterpret_cast<uintptr_t>(p);
+    return Span{begin, begin + (static_cast<size_t>(rows - 1) * ld + cols) * elem};
+}
+bool overlap(const Span& a, const Span& b) { return a.begin < b.end && b.begin < a.end; }
+
 // ---- narrow layers: the gather inside the GEMM (gemm_gather_narrow.hpp)
 // Shapes the kernel takes, apart from what is asked of every set and of the addresses: at most two
 // column tiles (beyond that each tile re-reads and re-gathers the rows of dY once more and the
@@ -1235,7 +1243,12 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     // a full gradient of one slice is stored where it is wanted: no partial tiles, no pass over them (refresh steps: 6144 x
     // 4096, T = 300: 148 -> 83 us; 5461 x 2048, T = 1000: 108 -> 74, T = 4096: 149 -> 133; 6144 x 6144, T = 4096: 371 -> 335)
     const bool small_staged = tile == kTile128 && !(aligned && sizes);
-    const bool straight = ks.splits == 1 && count == 1 && !seg[0].tail && !seg[0].rho && odt == GRASS_F32 && !small_staged;
+    bool straight = ks.splits == 1 && count == 1 && !seg[0].tail && !seg[0].rho && odt == GRASS_F32 && !small_staged;
+    if (straight) {  // (not over anything that other workgroups still read: the reduction starts when all inputs are used up)
+        const Span out = span_of(seg[0].C, total, n, seg[0].ldc, 4);
+        straight = !overlap(out, layout == GRASS_DY_MxT ? span_of(dY0, total, T, ldy0, 2) : span_of(dY0, T, total, ldy0, 2)) &&
+                   !overlap(out, span_of(X, T, n, ldx, 2)) && !overlap(out, span_of(ws, 1, static_cast<int64_t>(ws_bytes), 0, 1));
+    }
     g.P = straight ? static_cast<float*>(seg[0].C) : partial;
     g.K = T;
     g.Mp = p.Mp;

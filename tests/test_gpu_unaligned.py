@@ -179,3 +179,21 @@ def test_full_gradient_of_one_slice(tile, T, m, n):
     grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(T, m, n, grass.BF16)))
     assert rel_fro(to_np(G), to_f64(dY).T @ to_f64(X)) <= TOL_F32
     assert bool((out[m] == 7).all()) and bool((out[:m, n:] == 7).all())
+
+
+@pytest.mark.parametrize("over", ["dY", "X"])
+@pytest.mark.parametrize("tile", [128, 192, 256])
+@pytest.mark.parametrize("m,n", [(512, 512), (520, 264), (257, 264), (264, 261)])
+def test_full_gradient_over_an_input(over, tile, m, n):
+    """G may lie over a bf16 input: no workgroup stores while another still reads (dY and X have room for it)."""
+    T = 2048
+    grass.set_test_option(grass.TEST_RUN_TILE, tile)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 1)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(m)
+    dY, X = (torch.randn(T, w, generator=gen, device=DEV).to(BF) for w in (m, n))
+    want = to_f64(dY).T @ to_f64(X)
+    under = dY if over == "dY" else X
+    G = under.view(-1)[:2 * m * n].view(torch.float32).view(m, n)
+    grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(T, m, n, grass.BF16)))
+    assert G.data_ptr() == under.data_ptr() and rel_fro(to_np(G), want) <= TOL_F32
