@@ -243,9 +243,10 @@ size_t choice_bytes(const Choice& c, const Shape& q) {
 // The tile and the K slices of a product, by estimated time.
 //
 // `k` are the slices planned for the square tile `planned`; of the tiles that run on them the quickest is taken.  Up
-// to kJointMaxT tokens every tile is also tried with slices of its own, down to two K tiles each, and taken if
+// to kJointMaxT tokens every tile is also tried with shorter slices of its own, down to two K tiles each, and taken if
 // that is at least 5 % quicker: slices planned by how they fill the machine (split_k) know nothing of what starting a
-// workgroup costs, nor which tile runs, and keep at least eight K tiles of the square one.  The slices of split_k are
+// workgroup costs, nor which tile runs, and keep at least eight K tiles of the square one.  Longer slices are left out: the
+// longer a sum in fp32 accumulators, the less exact (7833 x 2072, r = 334, T = 7833: 5 slices against 10).  The slices of split_k are
 // fitted to longer products, whose sums also move more with another order.
 // The estimates' constants are fitted to the times of 740 random layers of up to 20000 tokens (all three tiles, up to
 // 16 numbers of slices; steps, column steps and full gradients, both layouts, odd widths) and 150 longer ones (tiles only).
@@ -283,9 +284,11 @@ Choice choose_plan(TileId planned, const KSplit& k, const Shape& q, size_t room)
             const uint32_t per = (units + c - 1) / c, slices = (units + per - 1) / per;
             if (slices == before) continue;
             before = slices;
-            const double t = time.us(slices, per * unit);
+            const int64_t tokens = static_cast<int64_t>(per) * unit;
+            if ((tokens < q.T ? tokens : q.T) > k.tokens) continue;
+            const double t = time.us(slices, static_cast<double>(tokens));
             if (!(t < least)) continue;
-            const Choice other{time.id, KSplit{static_cast<int>(slices), static_cast<int64_t>(per) * unit}};
+            const Choice other{time.id, KSplit{static_cast<int>(slices), tokens}};
             if (choice_bytes(other, q) <= room) { least = t; best = other; }
         }
     }

@@ -82,3 +82,15 @@ def test_the_least_workspace_is_part_of_the_query(layout):
         assert grass.least_workspace(grass.CALL_CGRAD, T, n, rs[:1], layout) <= grass.cgrad_workspace(T, rs[0], n, rs[0], grass.BF16, layout)
         assert grass.least_workspace(grass.CALL_DENSE, T, n, rs[:1], layout) <= grass.dense_workspace(T, rs[0], n, grass.BF16, layout)
         assert grass.least_workspace(grass.CALL_STEP, T, n, rs, layout) <= grass.step_group_workspace(T, n, rs, grass.BF16, layout)
+
+
+@pytest.mark.parametrize("T,n,rows,layout", [(5018, 8288, 785, grass.DY_MxT), (5647, 9336, 889, grass.DY_TxM),
+                                             (7833, 2072, 334, grass.DY_TxM), (6637, 2745, 3371, grass.DY_TxM)])
+def test_slices_are_not_longer_than_those_planned_by_themselves(T, n, rows, layout):
+    rng = np.random.default_rng(T)
+    shapes = [(T, n, rows)] + [(int(2 ** rng.uniform(5, 13)), int(2 ** rng.uniform(3, 13.4)), int(2 ** rng.uniform(3, 12)))
+                               for _ in range(2000)]
+    found = [grass.cgrad_plan(T, n, rows, grass.BF16, layout)[1] for T, n, rows in shapes]
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 128)  # the slices planned by themselves
+    alone = [grass.cgrad_plan(T, n, rows, grass.BF16, layout)[1] for T, n, rows in shapes]
+    assert [s for s, f, a in zip(shapes, found, alone) if f < a] == []
