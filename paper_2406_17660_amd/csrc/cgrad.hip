@@ -330,7 +330,7 @@ struct NarrowPlan {
 // Up to kNarrowFitT tokens: the slices of least estimated time that fit `room`.  A round of workgroups (two per compute
 // unit) takes 1.4 us and, per K tile of 16 tokens, 0.42 us and 0.34 times the workgroups per unit; a slice of partial
 // tiles 0.27 us per MB.  Fitted to the steps of 110 random layers (one and three sets, 14 numbers of slices each), of
-// which it is 1.1 % from the best; a quarter of the inputs' bytes allows a short product so few slices that
+// which it is 1.1 % from the best, but none longer than by the rule above (a longer sum is less exact); a quarter of the inputs' bytes allows a short product so few slices that
 // most of the chip is idle.  512 x 512, r = 128, T = 1280: 29.7 -> 13.6 us, three of them, T = 2176: 51 -> 21; 256 x 256,
 // r = 64, T = 256: 16.9 -> 11.1; 448 x 320, r = 56, T = 15552: 21.4 -> 17.7.
 constexpr int64_t kNarrowFitT = 32768;
@@ -342,28 +342,6 @@ NarrowPlan narrow_plan(int64_t T, int64_t n, int tiles_m, int64_t panel_rows, in
     p.Mp = (panel_rows + 7) / 8 * 8;
     const int64_t ktiles = T / kNarrowBK, tiles = static_cast<int64_t>(tiles_m) * p.tiles_n;
     const int64_t slice_bytes = p.Mp * p.Np * 4;
-    if (T <= kNarrowFitT) {
-        const int limit = test_option(GRASS_TEST_MAX_K_SLICES);
-        const int64_t fit = room / static_cast<size_t>(slice_bytes > 0 ? slice_bytes : 1) < 128
-                                ? static_cast<int64_t>(room / static_cast<size_t>(slice_bytes > 0 ? slice_bytes : 1)) : 128;
-        p.splits = 1;
-        p.ktiles_per_split = static_cast<int>(ktiles > 0 ? ktiles : 1);
-        double least = 1e300;
-        for (const int c : {1, 2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64, 72, 85, 96, 112, 128}) {
-            if (c > 1 && (2 * c > ktiles || (limit > 0 && c > limit))) break;
-            const int64_t per = (ktiles + c - 1) / c, slices = (ktiles + per - 1) / per, wgs = tiles * slices;
-            if (slices > 1 && slices > fit) break;
-            const double u = static_cast<double>(wgs < 512 ? wgs : 512) / 256.0;
-            const double us = static_cast<double>((wgs + 511) / 512) * (1.4 + static_cast<double>(per) * (0.42 + 0.34 * u)) +
-                              0.27e-6 * static_cast<double>(slices * slice_bytes);
-            if (us < least) {
-                least = us;
-                p.splits = static_cast<int>(slices);
-                p.ktiles_per_split = static_cast<int>(per);
-            }
-        }
-        return p;
-    }
     int64_t s = tiles > 0 ? (512 + tiles - 1) / tiles : 1;
     const int64_t by_traffic = T * in_cols * 2 / 4 / (slice_bytes > 0 ? slice_bytes : 1);
     const int64_t by_space = static_cast<int64_t>(cap_bytes) / (slice_bytes > 0 ? slice_bytes : 1);
@@ -375,6 +353,30 @@ NarrowPlan narrow_plan(int64_t T, int64_t n, int tiles_m, int64_t panel_rows, in
     s = s < 1 ? 1 : s;
     p.ktiles_per_split = static_cast<int>((ktiles + s - 1) / s);
     p.splits = static_cast<int>((ktiles + p.ktiles_per_split - 1) / p.ktiles_per_split);
+    if (T > kNarrowFitT) return p;
+    // the quickest that fit, unless they are longer than the above (which every accepted workspace holds)
+    const int limit = test_option(GRASS_TEST_MAX_K_SLICES), longest = p.ktiles_per_split;
+    int64_t quick_slices = 1, quick_per = ktiles;
+    const size_t one = static_cast<size_t>(slice_bytes > 0 ? slice_bytes : 1);
+    const int64_t fit = room / one < 128 ? static_cast<int64_t>(room / one) : 128;
+    double least = 1e300;
+    for (const int c : {1, 2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64, 72, 85, 96, 112, 128}) {
+        if (c > 1 && (2 * c > ktiles || (limit > 0 && c > limit))) break;
+        const int64_t per = (ktiles + c - 1) / c, slices = (ktiles + per - 1) / per, wgs = tiles * slices;
+        if (slices > 1 && slices > fit) break;
+        const double u = static_cast<double>(wgs < 512 ? wgs : 512) / 256.0;
+        const double us = static_cast<double>((wgs + 511) / 512) * (1.4 + static_cast<double>(per) * (0.42 + 0.34 * u)) +
+                          0.27e-6 * static_cast<double>(slices * slice_bytes);
+        if (us < least) {
+            least = us;
+            quick_slices = slices;
+            quick_per = per;
+        }
+    }
+    if (quick_per <= longest) {
+        p.splits = static_cast<int>(quick_slices);
+        p.ktiles_per_split = static_cast<int>(quick_per);
+    }
     return p;
 }
 

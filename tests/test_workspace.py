@@ -94,3 +94,13 @@ def test_slices_are_not_longer_than_those_planned_by_themselves(T, n, rows, layo
     grass.set_test_option(grass.TEST_MAX_K_SLICES, 128)  # the slices planned by themselves
     alone = [grass.cgrad_plan(T, n, rows, grass.BF16, layout)[1] for T, n, rows in shapes]
     assert [s for s, f, a in zip(shapes, found, alone) if f < a] == []
+
+
+@pytest.mark.parametrize("T,n,m,r,count", [(21936, 448, 248, 3, 3), (12960, 16, 488, 41, 8), (31392, 416, 160, 1, 3),
+                                           (19792, 8, 504, 38, 4), (16368, 368, 440, 1, 3), (12320, 24, 480, 36, 8)])
+def test_slices_of_narrow_layers_are_not_longer_than_by_the_traffic_rule(T, n, m, r, count):
+    """Two workgroups per compute unit, a quarter of the inputs' bytes, four K tiles of 16 tokens at least, 128 slices."""
+    tile, slices = grass.cgrad_plan(T, n, (r + 7) // 8 * 8 * count, grass.BF16, m=m, count=count)
+    ktiles, tiles, slice_bytes = T // 16, count * ((n + 255) // 256), (r + 7) // 8 * 8 * count * ((n + 255) // 256) * 1024
+    rule = max(1, min(-(-512 // tiles), T * (m * count + n) // 2 // slice_bytes, ktiles // 4, 128))
+    assert tile == 0 and -(-ktiles // slices) <= -(-ktiles // rule)
