@@ -188,8 +188,8 @@ grass_status grass_compressed_grad(const void* dY, grass_dy_layout layout, int64
  * one matrix), `rows` rows in all (r for one matrix; for a group call the sum of its r[i], each
  * rounded up to a multiple of 8; the sets are taken to be of equal size), m the row length of
  * dY (0: not given; fp32 plans, which it decides about, then take the rows of a set for it).  `*tile` receives the edge of the output tile that the slices are
- * planned for (256 or 128; for fp32 inputs 128 or 64, 64 also for the 32-wide tile of short products; the kernel
- * may run with another tile where that is faster, with the same sums), or 0 for narrow layers (bf16, T x m storage, m <= 512,
+ * planned for (256 or 128; 128 also for the tile of 128 x 256; for fp32 inputs 128 or 64, 64 also for the 32-wide tile of short
+ * products; the kernel may run with another tile where that is faster, with the same sums), or 0 for narrow layers (bf16, T x m storage, m <= 512,
  * r <= 128 per set, n <= 512, T a multiple of 16), whose gather runs inside the matrix-multiply kernel (128 x 256 tiles, no
  * packed panel); `*k_slices` the number of slices the token dimension is split into (their
  * partial products are what the split-K reduction, or the fused tail of grass_step_group /

@@ -794,16 +794,16 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
         *k_slices = p.splits;
         return;
     }
-    const TileId id = T >= kFastBK && rows >= 8 && n >= 8 ? planned_tile(rows, n) : kTile128;
+    TileId id = T >= kFastBK && rows >= 8 && n >= 8 ? planned_tile(rows, n) : kTile128;
     KSplit k = split_k(id, T, rows, n);
-    if (id == kTile256 && layout == GRASS_DY_MxT && T % (2 * kFastBK) == 0 &&
-        test_option(GRASS_TEST_PACK_MXT) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0)
-        k = paired(k, T);
-    if (T >= kFastBK && rows >= 8 && n >= 8) {  // gathered rows, aligned operands
-        const bool row_form = layout == GRASS_DY_MxT && T % kFastBK == 0 && test_option(GRASS_TEST_PACK_MXT) == 0;
-        const Shape q{T, rows, n, layout, true, row_form, row_form && T % (2 * kFastBK) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0,
-                      Positions{true, n % 8 == 0, true}};
-        k = choose_plan(id, k, q, ~size_t{0}).k;
+    // gathered rows, aligned operands; the rows of one set only are gathered by the product itself
+    const bool row_form = layout == GRASS_DY_MxT && count == 1 && T % kFastBK == 0 && test_option(GRASS_TEST_PACK_MXT) == 0;
+    const bool pairs = row_form && T % (2 * kFastBK) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0;
+    if (id == kTile256 && pairs) k = paired(k, T);
+    if (T >= kFastBK && rows >= 8 && n >= 8) {
+        const Choice c = choose_plan(id, k, Shape{T, rows, n, layout, true, row_form, pairs, Positions{true, n % 8 == 0, true}}, ~size_t{0});
+        if (c.k.splits != k.splits || c.k.tokens != k.tokens) id = c.tile;  // slices of that tile's own
+        k = c.k;
     }
     *tile = tile_rows(id);
     *k_slices = k.splits;

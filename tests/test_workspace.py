@@ -104,3 +104,21 @@ def test_slices_of_narrow_layers_are_not_longer_than_by_the_traffic_rule(T, n, m
     ktiles, tiles, slice_bytes = T // 16, count * ((n + 255) // 256), (r + 7) // 8 * 8 * count * ((n + 255) // 256) * 1024
     rule = max(1, min(-(-512 // tiles), T * (m * count + n) // 2 // slice_bytes, ktiles // 4, 128))
     assert tile == 0 and -(-ktiles // slices) <= -(-ktiles // rule)
+
+
+@pytest.mark.parametrize("T,n,rows", [(5365, 608, 1472), (271, 416, 512), (137, 216, 512), (2119, 256, 208)])
+def test_plan_names_the_tile_whose_slices_it_names(T, n, rows):
+    """Planned by themselves these slices are the large tile's; the quicker ones are a smaller tile's own."""
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 128)
+    alone = grass.cgrad_plan(T, n, rows, grass.BF16)
+    grass.set_test_option(grass.TEST_MAX_K_SLICES, 0)
+    tile, slices = grass.cgrad_plan(T, n, rows, grass.BF16)
+    assert alone[0] == 256 and slices > alone[1] and tile == 128
+
+
+@pytest.mark.parametrize("T,n,rows", [(1600, 136, 1232), (6848, 5048, 448), (4928, 392, 312), (704, 512, 760)])
+def test_plan_of_a_group_stored_mxt_packs(T, n, rows):
+    """The rows of several sets are packed; only those of a single one are gathered by the product itself."""
+    group = grass.cgrad_plan(T, n, rows, grass.BF16, grass.DY_MxT, count=2)
+    grass.set_test_option(grass.TEST_PACK_MXT, 1)
+    assert grass.cgrad_plan(T, n, rows, grass.BF16, grass.DY_MxT, count=2) == group
