@@ -164,8 +164,10 @@ grass_status grass_select_rows_static(const float* sumsq, int64_t m, int64_t r,
  * device: idx comes from grass_select_rows); duplicates are allowed.
  * T = 0 writes zeros.  `ws` must hold grass_cgrad_workspace(...) bytes.
  *
- * bf16 inputs, up to 8192 tokens (narrow layers 32768): the query counts the tiles and slices that the library prefers where there is room.  A
- * smaller workspace, down to what the slices planned by themselves need, is accepted too.
+ * bf16 inputs, up to 8192 tokens (narrow layers 32768): the query counts the tiles and slices that the
+ * library prefers where there is room, wherever the operands lie.  Every size from the query on gives the
+ * same sums.  A smaller workspace, down to what the slices planned by themselves need, is accepted too: the
+ * sums over T are then split into other slices, which changes them within fp32 rounding and takes longer.
  *
  * fp32 inputs: the partial tiles of the product are an aid, and a workspace that is smaller than
  * the query says is accepted as follows.  grass_compressed_grad, grass_compressed_grad_group

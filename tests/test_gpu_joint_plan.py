@@ -97,3 +97,22 @@ def test_slices_of_narrow_layers(T, m, n, r, count):
         for dY, M in zip(dYs, Ms):
             want = 0.1 * rho.double()[:, None] * (dY.double()[:, idx.long()].t() @ X.double())
             assert _rel(M, want) <= TOL_F32
+
+
+@pytest.mark.parametrize("T,m,n", [(192, 40, 3522), (192, 24, 1851), (960, 16, 1227), (536, 232, 702), (1001, 520, 264), (640, 264, 1030)])
+@pytest.mark.parametrize("a_off,x_off", [(0, 0), (1, 0), (0, 1), (1, 1)])
+def test_a_workspace_beyond_the_query_changes_no_sum(T, m, n, a_off, x_off):
+    """The query holds the plan that is taken with any amount of room, wherever the operands lie: the sums are the same."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T)
+
+    def operand(width, off):
+        return torch.randn(T * width + 8, generator=gen, device=DEV).to(BF)[off:off + T * width].view(T, width)
+
+    dY, X = operand(m, a_off), operand(n, x_off)
+    query = grass.dense_workspace(T, m, n, grass.BF16)
+    G, H = torch.empty(m, n, device=DEV), torch.empty(m, n, device=DEV)
+    grass.dense_grad(dY, X, G, grass.workspace(query))
+    grass.dense_grad(dY, X, H, grass.workspace(4 * query))
+    assert torch.equal(G, H)
+    assert _rel(G, dY.double().t() @ X.double()) <= TOL_F32
