@@ -519,6 +519,10 @@ typedef enum {
 size_t grass_test_least_workspace(grass_test_call call, int64_t T, int64_t n, int count, const int64_t* r,
                                   grass_dy_layout layout);
 
+/* The time in us that the planner estimates for the bf16 product of so many workgroups of `ktiles` K tiles of 32 tokens
+ * each: tile 128, 192 or 256 as in GRASS_TEST_RUN_TILE, direct: operands in aligned chunks (load-to-LDS). */
+double grass_test_product_us(int tile, int direct, int64_t workgroups, int64_t ktiles);
+
 #ifdef __cplusplus
 }
 #endif

@@ -486,6 +486,10 @@ grass_status grass_set_test_option(grass_test_option option, int value) {
 
 int grass_test_last_kernel(void) { return t_last_kernel; }
 
+double grass_test_product_us(int tile, int direct, int64_t workgroups, int64_t ktiles) {
+    return product_estimate_us(tile, direct != 0, workgroups, ktiles);
+}
+
 size_t grass_test_least_workspace(grass_test_call call, int64_t T, int64_t n, int count, const int64_t* r,
                                   grass_dy_layout layout) {
     if (T < 0 || n < 0 || !small(T) || !small(n) || count < 1 || count > GRASS_MAX_GROUP || !r) return 0;

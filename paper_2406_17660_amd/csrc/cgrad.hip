@@ -180,13 +180,18 @@ size_t aligned_x_bytes(int64_t T, int64_t n) {
 
 // Estimated time of a product's kernel in us.  A workgroup takes a time to start and to store its tile and, per K
 // tile of 32 tokens, one that depends on how many workgroups a compute unit has, u = workgroups / 256.  `chunks`:
-// load-to-LDS kernels (aligned operands), otherwise operands in any position through registers.
+// load-to-LDS kernels (aligned operands), otherwise operands in any position through registers (one line for all three of
+// the large tile's, which differ by 1 - 8 %).  No form falls when workgroups are added: slices are chosen by the least
+// of these, and would be pushed past a fall for nothing.
 double product_us(TileId id, bool chunks, bool row_form, double wgs, double ktiles) {
     const double u = wgs / 256.0;
     if (id == kTile256 && chunks) return (row_form ? 12.0 : 13.0) + ktiles * (u <= 1 ? 0.538 + 0.161 * u : 0.86 * ceil(u));
     if (id == kTile256) return 7.26 + ktiles * (u <= 1 ? 0.715 + 0.161 * u : 0.799 * ceil(u));
     if (id == kTileMid) return 9.06 + ktiles * (u <= 1 ? 0.338 + 0.2 * u : u <= 2 ? 0.967 : 0.581 * u);
-    if (chunks) return (u <= 1 ? 5.9 + 3.0 * u : 5.6) + ktiles * (u <= 1 ? 0.376 : u <= 2 ? 0.676 : u <= 3 ? 1.28 : 0.41 * u);
+    if (chunks) {
+        const double many = 0.384 * u;
+        return 4.64 + 0.958 * (u <= 1 ? u : 1) + ktiles * (u <= 1 ? 0.308 : u <= 2 ? 0.677 : many > 1.05 ? many : 1.05);
+    }
     return 1.45 + ktiles * (u <= 2 ? 1.02 + 0.0872 * u : 0.586 * 2 * ceil(u / 2));
 }
 // A bf16 product as the launcher sees it.
@@ -711,6 +716,11 @@ static KSplit paired(KSplit k, int64_t T) {
         k.splits = static_cast<int>((T + k.tokens - 1) / k.tokens);
     }
     return k;
+}
+
+double product_estimate_us(int tile, bool direct, int64_t workgroups, int64_t ktiles) {
+    return product_us(tile == 256 ? kTile256 : tile == 192 ? kTileMid : kTile128, direct, false, static_cast<double>(workgroups),
+                      static_cast<double>(ktiles));
 }
 
 // Bytes the narrow kernel's partial tiles may take: what a packed product with either square tile

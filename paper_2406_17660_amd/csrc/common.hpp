@@ -116,6 +116,7 @@ grass_status launch_gather_rows(const void* G, grass_dtype gdt, int64_t n, int64
 // without (bf16; the query counts the plans that the launcher may prefer where there is room, too).
 size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
                             grass_dy_layout layout, bool gathered, int64_t src_rows = 0, bool least = false);
+double product_estimate_us(int tile, bool direct, int64_t workgroups, int64_t ktiles);  // for grass_test_product_us
 // Tile edge and number of K slices the launcher plans for `count` gathered sets of `rows` rows in
 // all (m: row length of dY, 0 when not known; tile 0 = the kernel that gathers inside the GEMM).
 void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n, grass_dtype dt,

@@ -34,7 +34,8 @@ EXPORTS = [
     "grass_grad_row_stats_workspace", "grass_grad_row_stats", "grass_scatter_update_cols",
     "grass_cgrad_group_workspace", "grass_compressed_grad_group",
     "grass_adam_rows_state", "grass_adam_scatter_state", "grass_cgrad_plan",
-    "grass_set_test_option", "grass_test_last_kernel", "grass_test_least_workspace", "grass_select_static_capacity", "grass_select_rows_static",
+    "grass_set_test_option", "grass_test_last_kernel", "grass_test_least_workspace", "grass_test_product_us",
+    "grass_select_static_capacity", "grass_select_rows_static",
     "grass_adam_step_scalars", "grass_adam_scatter_replayable",
     "grass_step_group_workspace", "grass_step_group", "grass_step_group_timed",
     "grass_step_cols_workspace", "grass_step_cols",
@@ -126,6 +127,8 @@ def lib():
                         "grass_cgrad_group_workspace", "grass_step_group_workspace",
                         "grass_step_cols_workspace", "grass_test_least_workspace"):
             getattr(L, name).restype = i32
+    L.grass_test_product_us.argtypes = [i32, i32, i64, i64]
+    L.grass_test_product_us.restype = C.c_double
     _lib = L
     return L
 

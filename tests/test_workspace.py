@@ -122,3 +122,14 @@ def test_plan_of_a_group_stored_mxt_packs(T, n, rows):
     group = grass.cgrad_plan(T, n, rows, grass.BF16, grass.DY_MxT, count=2)
     grass.set_test_option(grass.TEST_PACK_MXT, 1)
     assert grass.cgrad_plan(T, n, rows, grass.BF16, grass.DY_MxT, count=2) == group
+
+
+@pytest.mark.parametrize("tile,direct", [(128, 1), (128, 0), (192, 1), (256, 1), (256, 0)])
+def test_estimate_does_not_fall_when_work_is_added(tile, direct):
+    f = grass.lib().grass_test_product_us
+    for ktiles in (1, 2, 4, 8, 10, 11, 16, 32, 100, 1000):
+        times = [f(tile, direct, wgs, ktiles) for wgs in range(1, 2600)]
+        assert times == sorted(times), (ktiles, [w for w in range(1, 2599) if times[w] < times[w - 1]][:4])
+    for wgs in (1, 100, 256, 257, 512, 768, 769, 3000):
+        times = [f(tile, direct, wgs, k) for k in range(1, 300)]
+        assert times == sorted(times)
