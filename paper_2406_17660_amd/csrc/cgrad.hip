@@ -201,6 +201,7 @@ struct Shape {
     bool gathered;
     bool row_form, pairs;  // the 256 tile gathers the rows of an m x T dY itself, 64 tokens per load
     Positions at;
+    bool full_f32;  // a full gradient in fp32, which the product of one slice stores itself (but the staged 128 tile)
 };
 struct Choice { TileId tile; KSplit k; };
 bool chunks_at(TileId id, const Shape& q, Copies* copy) {
@@ -210,13 +211,17 @@ bool chunks_at(TileId id, const Shape& q, Copies* copy) {
 // The parts of a step's time that the tile and the slices decide, in us: the product, its partial tiles (written, then
 // read by the reduction), and the passes that the tile needs ahead of it: dY stored m x T is packed (transposed) for all
 // but the large tile, which gathers its rows itself, and an odd-width operand may be copied into aligned rows
-// (choose_copies).
+// (choose_copies).  A full gradient's reduction is a launch and a pass more (2.76 us and 1.78 us per million outputs); stored
+// by the product it takes the large tile 4.5 us where the output ends inside of it, next to nothing otherwise.
 struct TileTime {
     TileId id;
     bool chunks, row_form;
     double tiles, outputs, passes;
+    bool stores;             // the product of one slice stores the full gradient itself
+    double stored, reduced;  // us for that, and for the pass that it saves
     double us(double slices, double tokens) const {
-        return passes + product_us(id, chunks, row_form, tiles * slices, tokens * (1.0 / kFastBK)) + 1.45e-6 * outputs * slices;
+        const double out = stores && slices == 1 ? stored : 1.45e-6 * outputs * slices + reduced;
+        return passes + product_us(id, chunks, row_form, tiles * slices, tokens * (1.0 / kFastBK)) + out;
     }
 };
 TileTime tile_time(TileId id, const Shape& q) {
@@ -235,7 +240,10 @@ TileTime tile_time(TileId id, const Shape& q) {
         const double moved = 4.0 * T * static_cast<double>(q.n) / 5.2e6, groups = 2.8e-4 * T * static_cast<double>((q.n + 2047) / 2048);
         r.passes += (moved > groups ? moved : groups) + 3;
     }
-    if (q.layout == GRASS_DY_MxT && !r.row_form) r.passes += 2.0 * T * static_cast<double>(p.Mp + q.rows) / 1.5e6 + 6;
+    if (q.layout == GRASS_DY_MxT && !r.row_form) r.passes += 2.0 * T * static_cast<double>(p.Mp + q.rows) / 2.31e6 + 9.63;
+    r.stores = q.full_f32 && (id != kTile128 || r.chunks);
+    r.stored = 0.08e-6 * r.outputs + (id == kTile256 && (q.rows % 128 != 0 || q.n % 128 != 0) ? 4.5 : 0.0);
+    r.reduced = q.full_f32 ? 2.76 + 1.78e-6 * r.outputs : 0.0;
     return r;
 }
 // What a plan needs of the workspace: packed panel, partial tiles and the aligned copy of X.
@@ -253,12 +261,14 @@ size_t choice_bytes(const Choice& c, const Shape& q) {
 // workgroup costs, nor which tile runs, and keep at least eight K tiles of the square one.  Longer slices are left out: the
 // longer a sum in fp32 accumulators, the less exact (7833 x 2072, r = 334, T = 7833: 5 slices against 10).  The slices of split_k are
 // fitted to longer products, whose sums also move more with another order.
-// The estimates' constants are fitted to the times of 740 random layers of up to 20000 tokens (all three tiles, up to
-// 16 numbers of slices; steps, column steps and full gradients, both layouts, odd widths) and 150 longer ones (tiles only).
-// The plan taken is 1.0 % from the best of all tried and 4.0 % quicker than the tile alone (7 % between 512 and 1024
-// tokens, 2 - 4 % elsewhere); none is more than 6.7 % slower.  Whole steps: 352 x 8667, r = 88, T = 563: 29.7 -> 22.0 us;
-// 302 x 1745, r = 37, T = 7341: 31.3 -> 25.3; 688 x 327, r = 172, T = 1924: 23.6 -> 19.3; 5848 x 744, r = 1024, T = 1523:
-// 28.0 -> 25.0.  Tiles of the longer ones: 0.3 % from the best (1.1 % with constants fitted to the kernels alone).
+// The estimates' constants are fitted to the steps of 590 random layers of up to 20000 tokens (all three tiles, up to
+// 16 numbers of slices; both layouts, odd widths, rows and columns), 150 longer ones (tiles only) and 4200 full gradients
+// of up to 9000 tokens.  The plan taken is 1.1 % from the best that is not left out, for steps and for full gradients (2.2 % for
+// those of odd widths); full gradients 3.9 % before the estimate knew that one slice saves a pass (256 x 256, T = 256: 6.6 ->
+// 4.6 us; 2064 x 608, m x T, T = 192: 14.6 -> 11.3; 3128 x 2736, T = 467: 23.1 -> 18.9; 512 x 512, T = 512: 8.0 -> 8.9).  Whole steps
+// against the tile alone: 352 x 8667, r = 88, T = 563: 29.7 -> 22.0 us; 302 x 1745, r = 37, T = 7341: 31.3 -> 25.3; 688 x 327,
+// r = 172, T = 1924: 23.6 -> 19.3; 5848 x 744, r = 1024, T = 1523: 28.0 -> 25.0.  Longer slices left out cost full gradients most:
+// 3608 x 1064, T = 960: 18 us in one slice, 30 in two.  Tiles of the longer layers: 0.3 % from the best.
 constexpr int64_t kJointMaxT = 8192;
 Choice choose_plan(TileId planned, const KSplit& k, const Shape& q, size_t room) {
     if (const int forced = test_option(GRASS_TEST_GEMM_TILE))
@@ -763,11 +773,15 @@ size_t gemm_workspace_bytes(int64_t T, int64_t mrows, int64_t n, grass_dtype dt,
         for (int where = 0; where < 8; ++where) {
             const bool a_off = where & 1, x_off = where & 2, row_form = where & 4, pairs = row_form && T % (2 * kFastBK) == 0;
             if ((a_off && !a_matters) || (row_form && !rows_form)) continue;
-            const Shape q{T, mrows, n, layout, gathered, row_form, pairs, Positions{packed || (a_matters && !a_off), !x_off && n % 8 == 0, !x_off}};
-            for (const TileId planned : {kTile128, kTile256}) {
-                const KSplit k = planned == kTile128 ? k1 : pairs ? paired(k2, T) : k2;
-                const size_t bytes = choice_bytes(choose_plan(planned, k, q, ~size_t{0}), q);
-                tiled = bytes > tiled ? bytes : tiled;
+            for (const bool full_f32 : {false, true}) {
+                if (full_f32 && gathered) continue;
+                const Shape q{T, mrows, n, layout, gathered, row_form, pairs,
+                              Positions{packed || (a_matters && !a_off), !x_off && n % 8 == 0, !x_off}, full_f32};
+                for (const TileId planned : {kTile128, kTile256}) {
+                    const KSplit k = planned == kTile128 ? k1 : pairs ? paired(k2, T) : k2;
+                    const size_t bytes = choice_bytes(choose_plan(planned, k, q, ~size_t{0}), q);
+                    tiled = bytes > tiled ? bytes : tiled;
+                }
             }
         }
     }
@@ -813,7 +827,8 @@ void gemm_plan_summary(int64_t T, int64_t m, int64_t rows, int count, int64_t n,
     const bool pairs = row_form && T % (2 * kFastBK) == 0 && test_option(GRASS_TEST_NO_PAIRS) == 0;
     if (id == kTile256 && pairs) k = paired(k, T);
     if (T >= kFastBK && rows >= 8 && n >= 8) {
-        const Choice c = choose_plan(id, k, Shape{T, rows, n, layout, true, row_form, pairs, Positions{true, n % 8 == 0, true}}, ~size_t{0});
+        const Choice c = choose_plan(id, k, Shape{T, rows, n, layout, true, row_form, pairs, Positions{true, n % 8 == 0, true}, false},
+                                     ~size_t{0});
         if (c.k.splits != k.splits || c.k.tokens != k.tokens) id = c.tile;  // slices of that tile's own
         k = c.k;
     }
@@ -1128,8 +1143,9 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     const size_t skip = (256 - reinterpret_cast<uintptr_t>(base) % 256) % 256;
     base += skip;
     TileId tile = kTile128;
+    const bool full_f32 = count == 1 && !seg[0].tail && !seg[0].rho && odt == GRASS_F32;
     if (sizes) {
-        const Choice c = choose_plan(planned, ks, Shape{T, total, n, layout, gathered, rows_ok, pairs_ok, at},
+        const Choice c = choose_plan(planned, ks, Shape{T, total, n, layout, gathered, rows_ok, pairs_ok, at, full_f32},
                                      ws_bytes > skip ? ws_bytes - skip : 0);
         tile = c.tile;
         ks = c.k;
@@ -1260,7 +1276,7 @@ grass_status launch_tn_gemm_segments(const GemmSegment* seg, int count, grass_dy
     // a full gradient of one slice is stored where it is wanted: no partial tiles, no pass over them (refresh steps: 6144 x
     // 4096, T = 300: 148 -> 83 us; 5461 x 2048, T = 1000: 108 -> 74, T = 4096: 149 -> 133; 6144 x 6144, T = 4096: 371 -> 335)
     const bool small_staged = tile == kTile128 && !(aligned && sizes);
-    bool straight = ks.splits == 1 && count == 1 && !seg[0].tail && !seg[0].rho && odt == GRASS_F32 && !small_staged;
+    bool straight = ks.splits == 1 && full_f32 && !small_staged;
     if (straight) {  // (not over anything that other workgroups still read: the reduction starts when all inputs are used up)
         const Span out = span_of(seg[0].C, total, n, seg[0].ldc, 4);
         straight = !overlap(out, layout == GRASS_DY_MxT ? span_of(dY0, total, T, ldy0, 2) : span_of(dY0, T, total, ldy0, 2)) &&

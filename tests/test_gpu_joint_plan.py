@@ -116,3 +116,17 @@ def test_a_workspace_beyond_the_query_changes_no_sum(T, m, n, a_off, x_off):
     grass.dense_grad(dY, X, H, grass.workspace(4 * query))
     assert torch.equal(G, H)
     assert _rel(G, dY.double().t() @ X.double()) <= TOL_F32
+
+
+@pytest.mark.parametrize("T,m,n", [(256, 256, 256), (467, 3128, 2736), (128, 720, 128), (384, 2704, 3024)])
+def test_full_gradients_of_one_planned_slice_stay_in_one(T, m, n):
+    """The product of one slice stores a full gradient itself, which saves more than slices would: nothing is written to
+    the workspace."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T)
+    dY, X = (torch.randn(T, w, generator=gen, device=DEV).to(BF) for w in (m, n))
+    G = torch.full((m, n), float("nan"), device=DEV)
+    ws = grass.workspace(grass.dense_workspace(T, m, n, grass.BF16)).fill_(165)
+    grass.dense_grad(dY, X, G, ws)
+    assert bool((ws == 165).all())
+    assert _rel(G, dY.double().t() @ X.double()) <= TOL_F32
