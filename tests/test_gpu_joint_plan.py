@@ -38,7 +38,11 @@ def test_products_and_steps(seed):
     full = (dY.double().t() if layout == grass.DY_TxM else dY.double()) @ X.double()
     want = rho.double()[:, None] * full[idx.long()]
 
-    def check(nbytes_cgrad, nbytes_dense, nbytes_step):
+    c = min(r, n)  # columns of W: the transposed problem
+    cols = torch.randperm(n, generator=gen, device=DEV)[:c].sort()[0].to(torch.int32)
+    want_cols = rho.double()[:c, None] * full.t()[cols.long()]
+
+    def check(nbytes_cgrad, nbytes_dense, nbytes_step, nbytes_cols):
         GC, G = torch.full((r, n), float("nan"), device=DEV), torch.full((m, n), float("nan"), device=DEV)
         grass.compressed_grad(dY, X, idx, rho, GC, grass.workspace(nbytes_cgrad).fill_(255), layout)
         assert _rel(GC, want) <= TOL_F32
@@ -48,17 +52,39 @@ def test_products_and_steps(seed):
         grass.step_group([dY], X, [idx], [rho], [M], [V], [W], 1e-3, 0.9, 0.999, 1e-8, 1, 0.25,
                          grass.workspace(nbytes_step).fill_(255), layout=layout)
         assert _rel(M, 0.1 * want) <= TOL_F32
+        if layout == grass.DY_TxM:
+            M, V, U = (torch.zeros(c, m, device=DEV) for _ in range(3))
+            grass.step_cols(dY, X, cols, rho[:c], M, V, U, W, 1e-3, 0.9, 0.999, 1e-8, 1, 0.25,
+                            grass.workspace(nbytes_cols).fill_(255))
+            assert _rel(M, 0.1 * want_cols) <= TOL_F32
 
-    def queries():
-        return (grass.cgrad_workspace(T, m, n, r, grass.BF16, layout), grass.dense_workspace(T, m, n, grass.BF16, layout),
-                grass.step_group_workspace(T, n, [r], grass.BF16, layout))
-
-    check(*queries())
-    grass.set_test_option(grass.TEST_MAX_K_SLICES, 128)  # the slices planned by themselves: their room is the least
-    least = queries()
-    grass.set_test_option(grass.TEST_MAX_K_SLICES, 0)
-    assert all(a <= b for a, b in zip(least, queries()))
+    query = (grass.cgrad_workspace(T, m, n, r, grass.BF16, layout), grass.dense_workspace(T, m, n, grass.BF16, layout),
+             grass.step_group_workspace(T, n, [r], grass.BF16, layout), grass.step_cols_workspace(T, m, n, c, grass.BF16))
+    least = (grass.least_workspace(grass.CALL_CGRAD, T, n, [r], layout), grass.least_workspace(grass.CALL_DENSE, T, n, [m], layout),
+             grass.least_workspace(grass.CALL_STEP, T, n, [r], layout), grass.least_workspace(grass.CALL_STEP, T, m, [c]))
+    assert all(a <= b for a, b in zip(least, query))
+    check(*query)
     check(*least)
+
+
+@pytest.mark.parametrize("layout", [grass.DY_TxM, grass.DY_MxT])
+@pytest.mark.parametrize("T,m,n,rs", [(257, 1030, 264, (60, 9)), (640, 600, 1032, (128, 40, 40)), (1001, 261, 517, (30, 31)),
+                                      (2080, 1024, 600, (256, 256)), (8192, 544, 264, (50, 7, 120))])
+def test_sets_in_one_panel(T, m, n, rs, layout):
+    """Several sets that share X in one step, with the workspace of the query and with the least one."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T)
+    dYs = [torch.randn((T, m) if layout == grass.DY_TxM else (m, T), generator=gen, device=DEV).to(BF) for _ in rs]
+    X = torch.randn(T, n, generator=gen, device=DEV).to(BF)
+    idxs = [torch.randperm(m, generator=gen, device=DEV)[:r].sort()[0].to(torch.int32) for r in rs]
+    rhos = [torch.rand(r, generator=gen, device=DEV) + 0.5 for r in rs]
+    for nbytes in (grass.step_group_workspace(T, n, rs, grass.BF16, layout), grass.least_workspace(grass.CALL_STEP, T, n, rs, layout)):
+        Ms, Vs = ([torch.zeros(r, n, device=DEV) for r in rs] for _ in range(2))
+        Ws = [torch.zeros(m, n, dtype=BF, device=DEV) for _ in rs]
+        grass.step_group(dYs, X, idxs, rhos, Ms, Vs, Ws, 1e-3, 0.9, 0.999, 1e-8, 1, 0.25, grass.workspace(nbytes).fill_(255), layout=layout)
+        for dY, idx, rho, M in zip(dYs, idxs, rhos, Ms):
+            d = dY.double() if layout == grass.DY_TxM else dY.double().t()
+            assert _rel(M, 0.1 * rho.double()[:, None] * (d[:, idx.long()].t().contiguous() @ X.double())) <= TOL_F32
 
 
 def test_slices_of_a_short_product_and_of_a_long_one():
@@ -73,7 +99,8 @@ def test_slices_of_a_short_product_and_of_a_long_one():
 @pytest.mark.parametrize("T", [256, 272, 1280, 8192, 32768, 32784])
 @pytest.mark.parametrize("m,n,r,count", [(512, 512, 128, 1), (264, 200, 40, 3), (512, 264, 7, 1)])
 def test_slices_of_narrow_layers(T, m, n, r, count):
-    """The gather inside the product: slices for the workspace of the query, and for the least one, alone and grouped."""
+    """The gather inside the product, alone and grouped: slices for the workspace of the query, and for the least one
+    that is accepted, into which fewer of them fit where it is the smaller one by a slice or more."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(T)
     dYs = [torch.randn(T, m, generator=gen, device=DEV).to(BF) for _ in range(count)]
@@ -81,22 +108,36 @@ def test_slices_of_narrow_layers(T, m, n, r, count):
     idx = torch.randperm(m, generator=gen, device=DEV)[:r].sort()[0].to(torch.int32)
     rho = torch.rand(r, generator=gen, device=DEV) + 0.5
     query = grass.step_group_workspace(T, n, [r] * count, grass.BF16)
-    grass.set_test_option(grass.TEST_MAX_K_SLICES, 1)
-    least = grass.step_group_workspace(T, n, [r] * count, grass.BF16)
-    grass.set_test_option(grass.TEST_MAX_K_SLICES, 0)
-    for nbytes in (query, least):
+    least = grass.least_workspace(grass.CALL_STEP, T, n, [r] * count)
+    rows = (r + 7) // 8 * 8 * count
+    tile, slices = grass.cgrad_plan(T, n, rows if count > 1 else r, grass.BF16, m=m, count=count)
+    slice_bytes = rows * ((n + 255) // 256 * 256) * 4
+    assert tile == 0 and least <= query
+
+    def step(nbytes):
         Ms, Vs = ([torch.zeros(r, n, device=DEV) for _ in range(count)] for _ in range(2))
         Ws = [torch.zeros(m, n, dtype=BF, device=DEV) for _ in range(count)]
-        try:
-            grass.step_group(dYs, X, [idx] * count, [rho] * count, Ms, Vs, Ws, 1e-3, 0.9, 0.999, 1e-8, 1, 0.25,
-                             grass.workspace(nbytes).fill_(255))
-        except grass.GrassError as e:  # what one slice asks for is below what a call accepts
-            assert nbytes == least < query and e.code == grass.ERR_WORKSPACE
-            continue
+        ws = grass.workspace(nbytes).fill_(255)
+        grass.step_group(dYs, X, [idx] * count, [rho] * count, Ms, Vs, Ws, 1e-3, 0.9, 0.999, 1e-8, 1, 0.25, ws)
         assert grass.last_kernel() == grass.KERNEL_NARROW
         for dY, M in zip(dYs, Ms):
-            want = 0.1 * rho.double()[:, None] * (dY.double()[:, idx.long()].t() @ X.double())
+            want = 0.1 * rho.double()[:, None] * (dY.double()[:, idx.long()].t().contiguous() @ X.double())
             assert _rel(M, want) <= TOL_F32
+        return -(-(int((ws != 255).nonzero().max()) + 1) // slice_bytes)  # the slices that were written
+
+    assert step(query) == slices
+    room = (least - 256 - 256 - sum((r * n * 4 + 255) // 256 * 256 for _ in range(count))) // slice_bytes
+    used = step(least)
+    assert used <= room and (used < slices or slices <= room)
+    with pytest.raises(grass.GrassError) as e:
+        step(least - 256)
+    assert e.value.code == grass.ERR_WORKSPACE
+
+
+def test_least_workspace_holds_fewer_slices_of_a_narrow_layer():
+    """(so that the above runs a plan that the room bounds)"""
+    least = grass.least_workspace(grass.CALL_CGRAD, 1280, 512, [128])
+    assert grass.cgrad_plan(1280, 512, 128, grass.BF16, m=512)[1] * 128 * 512 * 4 > least
 
 
 @pytest.mark.parametrize("T,m,n", [(192, 40, 3522), (192, 24, 1851), (960, 16, 1227), (536, 232, 702), (1001, 520, 264), (640, 264, 1030)])

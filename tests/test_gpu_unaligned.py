@@ -163,8 +163,8 @@ def test_x_by_load_to_lds_is_chosen():
     assert grass.last_kernel() == grass.KERNEL_256_UNALIGNED_DY
 
 
-# A full gradient of one slice is stored by the product itself: edges of every tile, an output with padded rows, whose
-# padding stays as it is.
+# A full gradient of one slice is stored by the product itself (by the staged 128 tile through partial tiles): edges of
+# every tile, an output with padded rows, whose padding stays as it is.
 @pytest.mark.parametrize("tile", [128, 192, 256])
 @pytest.mark.parametrize("T", [32, 333])
 @pytest.mark.parametrize("m,n", [(8, 8), (128, 256), (136, 264), (264, 248), (512, 128), (257, 264), (264, 261), (131, 517)])
@@ -176,9 +176,14 @@ def test_full_gradient_of_one_slice(tile, T, m, n):
     dY, X = _framed(T, m, m, 9 if m % 8 else 8, gen), _framed(T, n, n, 9 if n % 8 else 8, gen)
     out = torch.full((m + 1, n + 3), 7.0, device=DEV)
     G = out[:m, :n]
-    grass.dense_grad(dY, X, G, grass.workspace(grass.dense_workspace(T, m, n, grass.BF16)))
+    ws = grass.workspace(grass.dense_workspace(T, m, n, grass.BF16)).fill_(165)
+    grass.dense_grad(dY, X, G, ws)
     assert rel_fro(to_np(G), to_f64(dY).T @ to_f64(X)) <= TOL_F32
     assert bool((out[m] == 7).all()) and bool((out[:m, n:] == 7).all())
+    if m % 8 == 0 and n % 8 == 0:  # nothing is copied ahead of the product: a workspace as it was shows that G went past it
+        assert grass.last_kernel() != grass.KERNEL_128_STAGED and bool((ws == 165).all())
+    elif grass.last_kernel() == grass.KERNEL_128_STAGED:  # (stores partial tiles)
+        assert tile != 256 and not bool((ws == 165).all())
 
 
 @pytest.mark.parametrize("over", ["dY", "X"])
