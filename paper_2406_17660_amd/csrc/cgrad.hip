@@ -259,8 +259,10 @@ size_t choice_bytes(const Choice& c, const Shape& q) {
 // to kJointMaxT tokens every tile is also tried with shorter slices of its own, down to two K tiles each, and taken if
 // that is at least 5 % quicker: slices planned by how they fill the machine (split_k) know nothing of what starting a
 // workgroup costs, nor which tile runs, and keep at least eight K tiles of the square one.  Longer slices are left out: the
-// longer a sum in fp32 accumulators, the less exact (7833 x 2072, r = 334, T = 7833: 5 slices against 10).  The slices of split_k are
-// fitted to longer products, whose sums also move more with another order.
+// longer a sum in fp32 accumulators, the less exact (7833 x 2072, r = 334, T = 7833: 5 slices against 10).  Products of more
+// tokens keep the slices of split_k and with them the order of their sums, in which one to ten of four million bf16 weights are rounded the
+// other way: that is why the line lies there, and not for want of gain (1456 x 1800, r = 364, T = 128866: 335 us with split_k's, 292
+// with slices of its own; 1200 x 9524, r = 300, T = 14720: 175 and 148).
 // The estimates' constants are fitted to the steps of 590 random layers of up to 20000 tokens (all three tiles, up to
 // 16 numbers of slices; both layouts, odd widths, rows and columns), 150 longer ones (tiles only) and 4200 full gradients
 // of up to 9000 tokens.  The plan taken is 1.1 % from the best that is not left out, for steps and for full gradients (2.2 % for
@@ -347,7 +349,8 @@ struct NarrowPlan {
 // tiles 0.27 us per MB.  Fitted to the steps of 110 random layers (one and three sets, 14 numbers of slices each), of
 // which it is 1.1 % from the best, but none longer than by the rule above (a longer sum is less exact); a quarter of the inputs' bytes allows a short product so few slices that
 // most of the chip is idle.  512 x 512, r = 128, T = 1280: 29.7 -> 13.6 us, three of them, T = 2176: 51 -> 21; 256 x 256,
-// r = 64, T = 256: 16.9 -> 11.1; 448 x 320, r = 56, T = 15552: 21.4 -> 17.7.
+// r = 64, T = 256: 16.9 -> 11.1; 448 x 320, r = 56, T = 15552: 21.4 -> 17.7.  Longer layers keep their order of sums; the
+// gain does not end at the line (512 x 512, r = 128: 108 slices and 25.7 us at T = 32768, 63 and 31.7 at T = 32784).
 constexpr int64_t kNarrowFitT = 32768;
 NarrowPlan narrow_plan(int64_t T, int64_t n, int tiles_m, int64_t panel_rows, int64_t in_cols,
                        size_t cap_bytes, size_t room) {

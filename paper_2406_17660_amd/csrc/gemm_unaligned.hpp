@@ -336,8 +336,11 @@ __device__ __forceinline__ void store_unaligned(const GemmArgs& g, const f32x16 
 // T = 112447: 289 and 296).  6288 x 9370, r = 786, T = 66176: 1224 us above, 1172 here.
 constexpr int kUnalignedXMin = 64;
 // kLeft: the left operand in any position and X in aligned chunks (a full gradient of odd height): the same with the
-// operands' ways exchanged.  5461 x 2048, T = 65536: whole refresh steps 1351 -> 1274 us (with both
-// operands through registers the product took 1290).
+// operands' ways exchanged, taken by the same rule with columns for rows.  5461 x 2048, T = 65536: whole refresh steps
+// 1351 -> 1274 us (with both operands through registers the product took 1290).  Full gradients in one slice, with both through
+// registers / with this: 5461 x 2048 of 32 K tiles 33.0 / 34.2 us, 64: 52.9 / 53.0, 96: 73.0 / 72.1, 128: 92.9 / 91.1,
+// 256: 182 / 168; 1021 x 4096 of 64: 52.6 / 53.6, 96: 70.9 / 70.1, 256: 164 / 154.  (Outputs of a few tiles gain from 4 K tiles on, but
+// run on smaller tiles.)  A single column tile in many slices: 5461 x 256 in 12 of 128 K tiles 228 / 231.
 template <bool kDense, bool kLeft = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void tn_gemm_bf16_unaligned_x_kernel(GemmArgs g) {
