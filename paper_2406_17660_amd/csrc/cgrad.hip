@@ -347,8 +347,9 @@ struct NarrowPlan {
 // Up to kNarrowFitT tokens: the slices of least estimated time that fit `room`.  A round of workgroups (two per compute
 // unit) takes 1.4 us and, per K tile of 16 tokens, 0.42 us and 0.34 times the workgroups per unit; a slice of partial
 // tiles 0.27 us per MB.  Fitted to the steps of 110 random layers (one and three sets, 14 numbers of slices each), of
-// which it is 1.1 % from the best, but none longer than by the rule above (a longer sum is less exact); a quarter of the inputs' bytes allows a short product so few slices that
-// most of the chip is idle.  512 x 512, r = 128, T = 1280: 29.7 -> 13.6 us, three of them, T = 2176: 51 -> 21; 256 x 256,
+// which it is 1.1 % from the best.  Where those are longer than by the rule above (in 1 of 2000 random calls), the rule's are
+// taken: a longer sum is less exact.  A quarter of the inputs' bytes allows a short product so few slices that most of
+// the chip is idle.  512 x 512, r = 128, T = 1280: 29.7 -> 13.6 us, three of them, T = 2176: 51 -> 21; 256 x 256,
 // r = 64, T = 256: 16.9 -> 11.1; 448 x 320, r = 56, T = 15552: 21.4 -> 17.7.  Longer layers keep their order of sums; the
 // gain does not end at the line (512 x 512, r = 128: 108 slices and 25.7 us at T = 32768, 63 and 31.7 at T = 32784).
 constexpr int64_t kNarrowFitT = 32768;
