@@ -189,8 +189,8 @@ double product_us(TileId id, bool chunks, bool row_form, double wgs, double ktil
     if (id == kTile256) return 7.26 + ktiles * (u <= 1 ? 0.715 + 0.161 * u : 0.799 * ceil(u));
     if (id == kTileMid) return 9.06 + ktiles * (u <= 1 ? 0.338 + 0.2 * u : u <= 2 ? 0.967 : 0.581 * u);
     if (chunks) {
-        const double many = 0.384 * u;
-        return 4.64 + 0.958 * (u <= 1 ? u : 1) + ktiles * (u <= 1 ? 0.308 : u <= 2 ? 0.677 : many > 1.05 ? many : 1.05);
+        const double many = 0.375 * u;
+        return 2.83 + 3.17 * (u <= 1 ? u : 1) + ktiles * (u <= 1 ? 0.391 : u <= 2 ? 0.667 : many > 1.03 ? many : 1.03);
     }
     return 1.45 + ktiles * (u <= 2 ? 1.02 + 0.0872 * u : 0.586 * 2 * ceil(u / 2));
 }
@@ -211,8 +211,9 @@ bool chunks_at(TileId id, const Shape& q, Copies* copy) {
 // The parts of a step's time that the tile and the slices decide, in us: the product, its partial tiles (written, then
 // read by the reduction), and the passes that the tile needs ahead of it: dY stored m x T is packed (transposed) for all
 // but the large tile, which gathers its rows itself, and an odd-width operand may be copied into aligned rows
-// (choose_copies).  A full gradient's reduction is a launch and a pass more (2.76 us and 1.78 us per million outputs); stored
-// by the product it takes the large tile 4.5 us where the output ends inside of it, next to nothing otherwise.
+// (choose_copies).  A full gradient's reduction is a launch more (3 us); stored by the product it takes the large tile
+// 4.5 us where the output ends inside of it, next to nothing otherwise.  (The pack's terms are fitted with the others: they hold
+// what else tells the packed products from the large tile's.)
 struct TileTime {
     TileId id;
     bool chunks, row_form;
@@ -240,10 +241,13 @@ TileTime tile_time(TileId id, const Shape& q) {
         const double moved = 4.0 * T * static_cast<double>(q.n) / 5.2e6, groups = 2.8e-4 * T * static_cast<double>((q.n + 2047) / 2048);
         r.passes += (moved > groups ? moved : groups) + 3;
     }
-    if (q.layout == GRASS_DY_MxT && !r.row_form) r.passes += 2.0 * T * static_cast<double>(p.Mp + q.rows) / 2.31e6 + 9.63;
+    if (q.layout == GRASS_DY_MxT && !r.row_form) {
+        const double moved = 2.0 * T * static_cast<double>(p.Mp + q.rows);
+        r.passes += q.gathered ? moved / 1.13e6 + 9.04 : moved / 8.62e6 + 9.52;
+    }
     r.stores = q.full_f32 && (id != kTile128 || r.chunks);
-    r.stored = 0.08e-6 * r.outputs + (id == kTile256 && (q.rows % 128 != 0 || q.n % 128 != 0) ? 4.5 : 0.0);
-    r.reduced = q.full_f32 ? 2.76 + 1.78e-6 * r.outputs : 0.0;
+    r.stored = id == kTile256 && (q.rows % 128 != 0 || q.n % 128 != 0) ? 4.55 : 0.0;
+    r.reduced = q.full_f32 ? 2.96 : 0.0;
     return r;
 }
 // What a plan needs of the workspace: packed panel, partial tiles and the aligned copy of X.
@@ -265,9 +269,9 @@ size_t choice_bytes(const Choice& c, const Shape& q) {
 // with slices of its own; 1200 x 9524, r = 300, T = 14720: 175 and 148).
 // The estimates' constants are fitted to the steps of 590 random layers of up to 20000 tokens (all three tiles, up to
 // 16 numbers of slices; both layouts, odd widths, rows and columns), 150 longer ones (tiles only) and 4200 full gradients
-// of up to 9000 tokens.  The plan taken is 1.1 % from the best that is not left out, for steps and for full gradients (2.2 % for
-// those of odd widths); full gradients 3.9 % before the estimate knew that one slice saves a pass (256 x 256, T = 256: 6.6 ->
-// 4.6 us; 2064 x 608, m x T, T = 192: 14.6 -> 11.3; 3128 x 2736, T = 467: 23.1 -> 18.9; 512 x 512, T = 512: 8.0 -> 8.9).  Whole steps
+// of up to 9000 tokens.  The plan taken is 1.1 % from the best that is not left out for steps and 1.2 % for full gradients,
+// 3.7 % before the estimate knew that one slice saves a pass (256 x 256, T = 256: 7.4 -> 4.9 us; 2064 x 608, m x T, T = 192:
+// 14.6 -> 11.3; 3128 x 2736, T = 467: 22.9 -> 18.6; 1 % of them are slower by a tenth or more).  Whole steps
 // against the tile alone: 352 x 8667, r = 88, T = 563: 29.7 -> 22.0 us; 302 x 1745, r = 37, T = 7341: 31.3 -> 25.3; 688 x 327,
 // r = 172, T = 1924: 23.6 -> 19.3; 5848 x 744, r = 1024, T = 1523: 28.0 -> 25.0.  Longer slices left out cost full gradients most:
 // 3608 x 1064, T = 960: 18 us in one slice, 30 in two.  Tiles of the longer layers: 0.3 % from the best.

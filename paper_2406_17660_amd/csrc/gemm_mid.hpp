@@ -22,8 +22,8 @@ namespace {
 // BN = 128 is the same kernel on 128 x 128 tiles (wavefronts of 64 x 64, stages of 16 KB, three workgroups per
 // compute unit).  It reads twice as much of the dense operand from L2 per flop as 128 x 256, so a filled chip
 // prefers that one; a product that leaves compute units idle is bound by the time one workgroup takes per K
-// tile, 0.31 us here, 0.34 + 0.2 u and 0.54 + 0.16 u us on the larger tiles at u workgroups per unit, and by
-// starting up (5, 9 and 13 us).  (More stages for a workgroup that has a unit to itself change nothing: 48.8 us
+// tile, 0.39 us here, 0.34 + 0.2 u and 0.54 + 0.16 u us on the larger tiles at u workgroups per unit, and by
+// starting up (3 - 6, 9 and 13 us).  (More stages for a workgroup that has a unit to itself change nothing: 48.8 us
 // for 4096 x 4096, r = 1024, T = 2047 with three and with six.)  The register-staged kernel takes 0.5 - 0.7 us: 2360 x 416, r = 295, T = 674: 21.0 us
 // per step with it, 18.5 with this; 440 x 272, r = 110, T = 9282: 22.2 and 20.2.
 constexpr int kMidBM = 128, kMidBK = 32, kMidStages = 3;
